@@ -12,18 +12,15 @@ namespace dynb {
 // Records a thread-local message and returns `code`.
 int fail(int code, const char* fmt, ...);
 
-constexpr int ROW_PAD = 8;    // every worker's row segment is padded to a multiple of this
 constexpr int COL_PAD = 64;   // leading dimensions are padded to a multiple of this
 
 inline int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
 
 // Row segments of the K workers, passed to kernels by value.
-//   off[k]  : first row of worker k in the caller's (dense) batch, off[K] = sum(b)
-//   poff[k] : first row of worker k in the padded row space, poff[k+1]-poff[k] = round_up(b_k, 8)
+// off[k]: first row of worker k in the caller's batch, off[K] = sum(b).
 struct Segs {
   int K;
   int off[DYNB_MAX_WORKERS + 1];
-  int poff[DYNB_MAX_WORKERS + 1];
 };
 
 struct Lambdas {
@@ -82,10 +79,9 @@ enum { MODE_FWD = 0, MODE_DGRAD = 1, MODE_WGRAD = 2 };
 //           the same tensor over a residual branch) acc is first rounded to T and
 //           addend[i*ldadd + j] added, then the mask is applied.
 //   WGRAD : one group per worker g; i = output feature, j = input feature;
-//           Cf[g*group_stride + j*ldcf + i] = acc.  fp32: A = dy^T, B = input^T (features x
-//           padded rows), operands start at column poff[g], depth poff[g+1]-poff[g].  bf16:
-//           A = dy and B = the input as they are, ROW-MAJOR [batch rows][lda / ldb]; worker g
-//           owns rows [off[g], off[g+1]) (no transposed copies).
+//           Cf[g*group_stride + j*ldcf + i] = acc.  A = dy and B = the input as they are,
+//           ROW-MAJOR [batch rows][lda / ldb]; the reduction runs over worker g's rows
+//           [off[g], off[g+1]).
 struct GemmArgs {
   const void* A; int64_t lda; int M;   // rows of A  (i)
   const void* B; int64_t ldb; int N;   // rows of B  (j)
@@ -98,10 +94,11 @@ struct GemmArgs {
   const void* addend; int64_t ldadd;   // DGRAD, bf16: see above
   int64_t group_stride;
   int groups_per_block;                // WGRAD, bf16 kernel: workers streamed by one workgroup
-  // WGRAD, bf16, unsplit, optional: also write the bias gradient bias_grad[g*group_stride + i] =
-  // sum over worker g's rows of A[row][i] (formed in the same kernel as one more column of the
-  // product; its weighted aggregate is left to the pass over the small tensors)
+  // WGRAD, unsplit (bf16: optional): also write the bias gradient bias_grad[g*group_stride + i] =
+  // sum over worker g's rows of A[row][i].  fp32 with `agg`: its weighted aggregate too, to
+  // bias_agg[i] (bf16: left to the pass over the small tensors).
   float* bias_grad;
+  float* bias_agg;
   // Implicit-GEMM gather of operand A for a 3x3 convolution with zero padding 1 (bf16 only).
   // conv == 0: A is a plain matrix.  conv == 1 (forward): row i is output pixel (n, y, x) of a
   // row_h x row_w grid and reduction index k = (kh*3 + kw)*cp + c reads channel c of source
@@ -122,9 +119,9 @@ struct GemmArgs {
   int split, chunk;
   float* partial;
   int64_t partial_stride;
-  // WGRAD, bf16 kernel, optional: also write agg[j*ldcf + i] = sum_g lam[g] * (tile of worker g),
-  // summed in a fixed, tile-dependent rotation of ascending g (the weighted aggregation of Eq. 2
-  // while the per-worker tiles are still in registers).  Only when gemm_fuses_aggregate() says so.
+  // WGRAD, optional: also write agg[j*ldcf + i] = sum_g lam[g] * (tile of worker g), summed in
+  // ascending g (fp32) or a fixed, tile-dependent rotation of it (bf16): the weighted aggregation
+  // of Eq. 2 while the per-worker tiles are still in registers.  Only when gemm_fuses_aggregate() says so.
   float* agg;
   float lam[DYNB_MAX_WORKERS];
   const void* zeros;   // 16 bytes of zeros in device memory (set by launch_gemm): what copies
@@ -132,6 +129,7 @@ struct GemmArgs {
 };
 
 int launch_gemm(int dtype, const GemmArgs& a, const Segs& s, void* stream);
+int launch_gemm_f32(const GemmArgs& a, const Segs& s, void* stream);   // (gemm_f32.hip)
 // Whether a weight-gradient launch of these dimensions can take GemmArgs::agg.
 bool gemm_fuses_aggregate(int dtype, const GemmArgs& a, const Segs& s);
 // out[e] = sum_k lam.w[k] * g[k*worker_stride + e], e < n, ascending k (any alignment)
@@ -144,21 +142,14 @@ int launch_aggregate_ranges(const float* g, int64_t worker_stride, const Lambdas
 // x fp32 [rows][D] -> out T [rows][ld]
 int launch_pack_rows(int dtype, const float* x, int rows, int D, void* out, int64_t ld,
                      void* stream);
-// in T [rows][ldi] -> out T [C][ldo] over the padded row space: out[c][poff_k + r] =
-// in[off_k + r][c] for r < b_k, zero for the padding positions of each worker's segment
-int launch_transpose(int dtype, const void* in, int64_t ldi, int C, void* out, int64_t ldo,
-                     const Segs& s, void* stream);
 // logits fp32 [rows][ldz] -> dz T [rows][ldd] (pad columns zero), rowloss[rows]
 int launch_softmax_xent(int dtype, const float* logits, int64_t ldz, const int32_t* y, int C,
                         void* dz, int64_t ldd, int ld_cols, float* rowloss, const Segs& s,
                         void* stream);
-// grads[g*group_stride + n] = sum over worker g's rows of dyT[n][row]
-// ... and from the row-major gradient dy [rows][ld] (bf16; ld a multiple of 64, zeros in the
-// padding columns)
+// grads[g*group_stride + n] = sum over worker g's rows of dy[row][n] (bf16 [rows][ld]; ld a
+// multiple of 64, zeros in the padding columns)
 int launch_bias_grad_rows(const void* dy, int64_t ld, int N, float* grads, int64_t group_stride,
                           const Segs& s, void* stream);
-int launch_bias_grad(int dtype, const void* dyT, int64_t ld, int N, float* grads,
-                     int64_t group_stride, const Segs& s, void* stream);
 // Reads `bytes` (a multiple of 16, 16-byte aligned) and discards them: what a launch is about to
 // fetch several times over, brought into the last-level cache by one sequential pass.
 int launch_touch(const void* p, int64_t bytes, void* stream);
@@ -227,7 +218,6 @@ int launch_wgrad_reduce(const float* partial, int split, int64_t partial_stride,
                         float* out, int64_t group_stride, int K, void* stream);
 
 // ---- convolution helpers (bf16 storage) ----
-// out bf16 [9*C][ldo]: transposed patch matrix over the padded pixel positions of segments s
 int launch_gap_forward(const void* act, int64_t lda, int HW, int C, int samples, void* pooled,
                        int64_t ldp, void* stream);
 int launch_gap_backward(const void* dpooled, int64_t ldp, const void* act, int64_t lda, int HW,

@@ -1,7 +1,7 @@
 // Ragged / grouped GEMMs  C'[i][j] = sum_k A[i][k] * B[j][k]  (both operands k-contiguous).
 //   bf16: MFMA 32x32x16 with fp32 accumulators, tiles staged through LDS in 16-byte
 //         granules with an XOR swizzle, software-pipelined global loads.
-//   fp32: plain FMA tiles (parity path for the fp32 workloads).
+// (fp32 products: gemm_f32.hip.)
 // Batch sizes are run-time data: rows, columns and reduction depth are predicated, nothing
 // is compiled per size.
 #include <hip/hip_runtime.h>
@@ -10,6 +10,7 @@
 
 #include "dynb_internal.h"
 #include "lds_async.h"
+#include "tile_map.h"
 
 namespace dynb {
 namespace {
@@ -20,64 +21,11 @@ typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-struct GroupView {
-  int64_t col0;  // first reduction column of this group
-  int depth;     // reduction length
-  float* Cf;     // fp32 output base for this group
-};
-
-__device__ inline GroupView group_view(const GemmArgs& p, const Segs& s, int g) {
-  GroupView v;
-  if (p.mode == MODE_WGRAD) {
-    v.col0 = s.poff[g];
-    v.depth = s.poff[g + 1] - s.poff[g];
-    v.Cf = p.Cf + (int64_t)g * p.group_stride;
-  } else {
-    v.col0 = 0;
-    v.depth = p.K;
-    v.Cf = p.Cf;
-  }
-  return v;
-}
-
-// Scalar epilogue shared by both kernels (T = storage type of C and mask).
-template <typename T, int MODE>
-__device__ inline void store_one(const GemmArgs& p, const GroupView& gv, int i, int j, float v) {
-  if (MODE == MODE_FWD) {
-    if (p.bias) v += p.bias[j];
-    if (p.relu) v = fmaxf(v, 0.f);
-    if (p.C) ((T*)p.C)[(int64_t)i * p.ldc + j] = (T)v;
-    if (p.Cf) p.Cf[(int64_t)i * p.ldcf + j] = v;
-  } else if (MODE == MODE_DGRAD) {
-    if (p.mask && !((float)((const T*)p.mask)[(int64_t)i * p.ldmask + j] > 0.f)) v = 0.f;
-    ((T*)p.C)[(int64_t)i * p.ldc + j] = (T)v;
-  } else {
-    gv.Cf[(int64_t)j * p.ldcf + i] = v;
-  }
-}
-
 // ------------------------------------------------------------------------------------
 // bf16 MFMA kernel
 // ------------------------------------------------------------------------------------
 constexpr int BK = 32;          // reduction elements per stage (two MFMA k-steps)
 constexpr int GPR = BK / 8;     // 16-byte granules per tile row
-
-// Workgroup -> tile.  Consecutive workgroup ids are spread round-robin over the 8 XCDs, each
-// with its own L2: give every XCD a contiguous chunk of the tile sequence, and walk the tiles
-// in bands of 8 tile-rows so that a chunk covers a compact rectangle (few distinct operand
-// panels per L2).
-__device__ inline void tile_of_block(int pid, int tiles_i, int tiles_j, int& ti, int& tj) {
-  const int total = tiles_i * tiles_j;
-  const int per = total / 8, extra = total % 8, xcd = pid % 8, local = pid / 8;
-  int t = pid;
-  if (total >= 16) t = xcd * per + (xcd < extra ? xcd : extra) + local;
-  const int band = 8;
-  const int bsz = band * tiles_j;
-  const int b0 = t / bsz, r = t % bsz;
-  const int rows = (tiles_i - b0 * band) < band ? (tiles_i - b0 * band) : band;
-  ti = b0 * band + r % rows;
-  tj = r / rows;
-}
 
 // Staged operand tiles (forward / input gradient): rows of 64 bytes = four 16-byte granules;
 // logical granule g of row r sits at physical granule g ^ swizzle_of_row(r).  The LDS has 64
@@ -950,66 +898,6 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmArgs p, Seg
   }
 }
 
-// ------------------------------------------------------------------------------------
-// fp32 FMA kernel: 64x64 tile, 16-deep stages, 4x4 outputs per thread
-// ------------------------------------------------------------------------------------
-template <int MODE>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs p, Segs segs) {
-  constexpr int TB = 64, TK = 16;
-  __shared__ float sA[TK][TB + 4];
-  __shared__ float sB[TK][TB + 4];
-  const GroupView gv = group_view(p, segs, blockIdx.z);
-  const int i0 = blockIdx.x * TB, j0 = blockIdx.y * TB;
-  const int tid = threadIdx.x;
-  const int lrow = tid >> 2, lk = (tid & 3) * 4;     // loader: one float4 per operand
-  const int ti = (tid >> 4) * 4, tj = (tid & 15) * 4;  // compute: 4x4 block
-  const float* A = (const float*)p.A + gv.col0;
-  const float* B = (const float*)p.B + gv.col0;
-
-  float acc[4][4];
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int b = 0; b < 4; ++b) acc[a][b] = 0.f;
-
-  // the operands of stage k0 + TK are asked for before stage k0 is computed, so that their
-  // trip to memory overlaps the arithmetic instead of preceding it
-  auto fetch = [&](int k0, float4& va, float4& vb) {
-    va = make_float4(0.f, 0.f, 0.f, 0.f);
-    vb = va;
-    const int k = k0 + lk;
-    if (i0 + lrow < p.M && k < gv.depth) va = *(const float4*)(A + (int64_t)(i0 + lrow) * p.lda + k);
-    if (j0 + lrow < p.N && k < gv.depth) vb = *(const float4*)(B + (int64_t)(j0 + lrow) * p.ldb + k);
-  };
-  float4 va, vb;
-  fetch(0, va, vb);
-  for (int k0 = 0; k0 < gv.depth; k0 += TK) {
-    __syncthreads();
-    sA[lk + 0][lrow] = va.x; sA[lk + 1][lrow] = va.y; sA[lk + 2][lrow] = va.z; sA[lk + 3][lrow] = va.w;
-    sB[lk + 0][lrow] = vb.x; sB[lk + 1][lrow] = vb.y; sB[lk + 2][lrow] = vb.z; sB[lk + 3][lrow] = vb.w;
-    __syncthreads();
-    if (k0 + TK < gv.depth) fetch(k0 + TK, va, vb);
-#pragma unroll
-    for (int kk = 0; kk < TK; ++kk) {
-      const float4 a4 = *(const float4*)&sA[kk][ti];
-      const float4 b4 = *(const float4*)&sB[kk][tj];
-      const float av[4] = {a4.x, a4.y, a4.z, a4.w};
-      const float bv[4] = {b4.x, b4.y, b4.z, b4.w};
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) acc[a][b] += av[a] * bv[b];
-    }
-  }
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      const int i = i0 + ti + a, j = j0 + tj + b;
-      if (i < p.M && j < p.N) store_one<float, MODE>(p, gv, i, j, acc[a][b]);
-    }
-}
-
 // per-worker weight gradients (no aggregate)
 template <int BM, int BN, int WM, int WN, int S>
 void launch_bf16_wgrad(GemmArgs a, const Segs& s, hipStream_t st) {
@@ -1086,23 +974,10 @@ void launch_bf16_gather(GemmArgs a, const Segs& s, hipStream_t st) {
     launch_bf16_gather_as<128, 128, 2, 2, 5>(a, s, st);
 }
 
-void launch_f32(const GemmArgs& a, const Segs& s, int groups, hipStream_t st) {
-  dim3 grid((a.M + 63) / 64, (a.N + 63) / 64, groups), block(256);
-  switch (a.mode) {
-    case MODE_FWD:
-      hipLaunchKernelGGL(gemm_f32_kernel<MODE_FWD>, grid, block, 0, st, a, s);
-      break;
-    case MODE_DGRAD:
-      hipLaunchKernelGGL(gemm_f32_kernel<MODE_DGRAD>, grid, block, 0, st, a, s);
-      break;
-    default:
-      hipLaunchKernelGGL(gemm_f32_kernel<MODE_WGRAD>, grid, block, 0, st, a, s);
-  }
-}
-
 }  // namespace
 
 bool gemm_fuses_aggregate(int dtype, const GemmArgs& a, const Segs& s) {
+  if (dtype == DYNB_F32) return a.mode == MODE_WGRAD;   // (every workgroup owns all workers of its tile)
   // enough tiles to occupy the compute units without splitting the workers over workgroups
   return dtype == DYNB_BF16 && a.mode == MODE_WGRAD && !a.conv && a.split <= 1 &&
          tiles_of(a, AGG_SMALL, AGG_SMALL) >= 256 && s.K <= DYNB_MAX_WORKERS;
@@ -1128,11 +1003,10 @@ int launch_gemm(int dtype, const GemmArgs& args, const Segs& s, void* stream) {
       return fail(DYNB_ERR_UNSUPPORTED, "gemm: an operand of %d GiB or more (rows * pitch) is not supported",
                   a.mode == MODE_WGRAD ? 2 : 4);
   }
-  if (a.bias_grad && (dtype != DYNB_BF16 || a.mode != MODE_WGRAD || a.split > 1))
-    return fail(DYNB_ERR_UNSUPPORTED, "gemm: the bias gradient rides along with an unsplit bf16 weight gradient only");
+  if (a.bias_grad && (a.mode != MODE_WGRAD || a.split > 1))
+    return fail(DYNB_ERR_UNSUPPORTED, "gemm: the bias gradient rides along with an unsplit weight gradient only");
   if (a.addend && (dtype != DYNB_BF16 || a.mode != MODE_DGRAD))
     return fail(DYNB_ERR_UNSUPPORTED, "gemm: an addend belongs to a bf16 input gradient");
-  const int groups = a.mode == MODE_WGRAD ? s.K : 1;
   KClass cls = a.mode == MODE_FWD ? KC_GEMM_FWD : a.mode == MODE_DGRAD ? KC_GEMM_DGRAD
                                                                         : KC_GEMM_WGRAD;
   // (the two tile sizes of the bf16 weight gradient are different kernels with different
@@ -1173,8 +1047,9 @@ int launch_gemm(int dtype, const GemmArgs& args, const Segs& s, void* stream) {
     } else {
       launch_bf16_plain<128, 128, 2, 2, 8>(a, s, st);
     }
-  } else
-    launch_f32(a, s, groups, (hipStream_t)stream);
+  } else {
+    return launch_gemm_f32(a, s, stream);
+  }
   return hipGetLastError() == hipSuccess ? DYNB_OK : fail(DYNB_ERR_HIP, "gemm launch failed");
 }
 

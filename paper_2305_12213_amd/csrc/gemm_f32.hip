@@ -1,0 +1,365 @@
+// Matrix products of the fp32 models on the fp32 matrix instructions (16 x 16 x 4, fp32 products
+// and sums).  The models that run in fp32 are small: a product has a few hundred output tiles and
+// a reduction of tens to thousands, so what bounds a launch is the length of the serial chain of
+// one tile.  16 x 16 tiles have the shortest chain per reduction step (8 clocks; 32 x 32 x 2: 32),
+// so every wave takes a tile of its own from end to end, without barriers and without dividing the
+// reduction.  An output is one chain of fused multiply-adds in ascending order of the reduction
+// index, whatever the tile size -- the same rounding as a plain loop, which keeps the sign of a
+// pre-activation next to zero (and with it the ReLU's decision) independent of how the work is split.
+// Operands travel global -> LDS asynchronously (a ring of NB blocks private to the wave, NB - 1 in
+// flight) and are read from there in the order the matrix instruction wants, four bytes a lane: in
+// registers that order costs more vector instructions per block than its four matrix instructions
+// take.  Problems with many tiles give each wave 2 x 2 of them (half the copies per instruction).
+#include <hip/hip_runtime.h>
+
+#include "dynb_internal.h"
+#include "lds_async.h"
+#include "tile_map.h"
+
+namespace dynb {
+namespace {
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+constexpr uint32_t KB = 1024;   // bytes of one copy
+
+// Wait until at most N of this wave's copies (issued last) are pending.
+template <int N>
+__device__ inline void wait_pending() {
+  static_assert(N <= 63, "vmcnt range");
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
+// Forward and input gradient: C[i][j] = sum_k A[i][k] B[j][k], both operands contiguous in k.  A
+// block is 32 reduction indices, the whole 128-byte line of each operand row (half a line per block
+// fetches every line twice: 19 instead of 11 us at 785 x 301 x 832): two copies of 8 rows per 16 rows.  Granule e
+// (16 bytes) of row r sits at slot e ^ (r / 2 % 8), so that matrix instruction e, which reads index
+// 4e + kg of 16 rows, finds 64 different banks.  A wave issues in order and the next matrix
+// instruction of a chain waits for the last, so copies and fetches are placed one by one between
+// them, in their 32-clock shadows.
+// Against 64 x 64 vector-unit tiles: 256 x 512 x 3072 165 -> 28 us (the chain of matrix
+// instructions alone is 11 us, the issue of everything else of a lone wave 12), 785 x 301 x 832
+// 49 -> 11 us.
+template <int MODE, int R>
+__global__ __launch_bounds__(64) void gemm_f32_kernel(GemmArgs p) {
+  constexpr int NB = R == 1 ? 10 : 4, S = 16 * R;               // S: tile side
+  constexpr int G = 2 * R, C = 2 * G;                           // 16-row groups and copies per block
+  constexpr uint32_t SLOT = C * KB;
+  __shared__ uint4 ring_area[NB * SLOT / 16];
+  int ti, tj;
+  tile_of_block(blockIdx.x, (p.M + S - 1) / S, (p.N + S - 1) / S, ti, tj);
+  const int lane = threadIdx.x, l15 = lane & 15, kg = lane >> 4;
+  const int i0 = ti * S, j0 = tj * S;
+  const uint32_t lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)&ring_area[0];
+  // copy 2g + h: rows 8h .. 8h+7 of group g (g < R: A rows, else B rows); this lane's 16 bytes of
+  // the next block (rows past the edge repeat the last one; their products are not stored)
+  const char* src[C];
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    const int g = c >> 1, r = 8 * (c & 1) + (lane >> 3), e = (lane & 7) ^ ((r >> 1) & 7);
+    const int i = i0 + 16 * g + r, j = j0 + 16 * (g - R) + r;
+    src[c] = g < R ? (const char*)((const float*)p.A + (int64_t)(i < p.M ? i : p.M - 1) * p.lda + 4 * e)
+                   : (const char*)((const float*)p.B + (int64_t)(j < p.N ? j : p.N - 1) * p.ldb + 4 * e);
+  }
+  const int blocks = p.K / 32;
+  uint32_t ahead = 0;                      // byte offset the next block is copied from; past the end
+                                           // the last block is copied again, never used
+  auto issue_one = [&](uint32_t slot, int c) { async_copy_1k(src[c] + ahead, lds + slot + c * KB); };
+  int issued = 0;
+  auto advance = [&]() { if (++issued < blocks) ahead += 128; };
+  uint32_t at[8];                          // this lane's element of granule e of a row group
+#pragma unroll
+  for (int e = 0; e < 8; ++e) at[e] = (uint32_t)(l15 * 128 + ((e ^ ((l15 >> 1) & 7)) * 16) + 4 * kg);
+  float f[2][G][8];                        // [register set][row group][matrix instruction]
+  const char* const ring = (const char*)&ring_area[0];
+  auto fetch_one = [&](int set, uint32_t slot, int e) {
+    const char* const a = ring + (slot + at[e]);
+#pragma unroll
+    for (int g = 0; g < G; ++g) f[set][g][e] = *(const float*)(a + g * 2048);
+  };
+  f32x4 acc[R][R];
+#pragma unroll
+  for (int u = 0; u < R; ++u)
+#pragma unroll
+    for (int w = 0; w < R; ++w) acc[u][w] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int s = 0; s < NB; ++s) {
+#pragma unroll
+    for (int c = 0; c < C; ++c) issue_one(s * SLOT, c);
+    advance();
+  }
+  wait_pending<(NB - 1) * C>();
+#pragma unroll
+  for (int e = 0; e < 8; ++e) fetch_one(0, 0, e);
+  // Step: block c's operands are in registers; those of block c + 1 have landed once at most the
+  // NB - 2 blocks behind it are pending; block c's slot, read a step ago, takes block c + NB.
+  // (Two steps unrolled, not the ring: such launches are so short that fetching a long loop body
+  // for the first time shows.)
+  uint32_t slot = 0;
+  auto step = [&](int set) {
+    const uint32_t next = slot + SLOT == NB * SLOT ? 0 : slot + SLOT;
+    wait_pending<(NB - 2) * C>();
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+#pragma unroll
+      for (int u = 0; u < R; ++u)
+#pragma unroll
+        for (int w = 0; w < R; ++w)
+          acc[u][w] = __builtin_amdgcn_mfma_f32_16x16x4f32(f[set][u][e], f[set][R + w][e], acc[u][w], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      fetch_one(set ^ 1, next, e);
+#pragma unroll
+      for (int c = e * C / 8; c < (e + 1) * C / 8; ++c) issue_one(slot, c);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    advance();
+    slot = next;
+  };
+#pragma unroll 1
+  for (int c = 0; c + 1 < blocks; c += 2) {
+    step(0);
+    step(1);
+  }
+  if (blocks & 1) step(0);
+  wait_pending<0>();                       // (no copy may land after the LDS has been given back)
+
+  // accumulator element v of a lane: row 4 * kg + v, column l15
+#pragma unroll
+  for (int w = 0; w < R; ++w) {
+    const int j = j0 + 16 * w + l15;
+    if (j >= p.N) continue;
+    const float bias = MODE == MODE_FWD && p.bias ? p.bias[j] : 0.f;
+#pragma unroll
+    for (int u = 0; u < R; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int i = i0 + 16 * u + 4 * kg + e;
+        if (i >= p.M) continue;
+        float v = acc[u][w][e];
+        if (MODE == MODE_FWD) {
+          if (p.bias) v += bias;
+          if (p.relu) v = fmaxf(v, 0.f);
+          if (p.Cf) p.Cf[(int64_t)i * p.ldcf + j] = v;
+        } else if (p.mask && !(((const float*)p.mask)[(int64_t)i * p.ldmask + j] > 0.f)) {
+          v = 0.f;
+        }
+        if (p.C) ((float*)p.C)[(int64_t)i * p.ldc + j] = v;
+      }
+  }
+}
+
+// Per-worker weight gradient, bias gradient and their weighted average in one pass over the
+// row-major tensors: grads_g[j][i] = sum over worker g's rows of x[row][j] dy[row][i].  The
+// reduction runs over rows; a block is 16 rows of 16 R features per operand, copied as it lies in
+// memory (R = 1: one copy of 16 half lines; R = 2: two copies of 8 whole lines, granule g of row r
+// at slot g ^ 4 (r / 2 % 2) against bank conflicts; a row past the worker's last comes from the zero
+// granule), and matrix instruction t reads row 4t + kg: no transposed copies.  A wave walks all
+// workers of its tile in ascending order, blocks in flight across worker boundaries; the lane that
+// stores an element keeps its weighted sum.  The waves of the first tile column sum dy alongside:
+// the bias gradient.
+// 3072 x 512 weights, 4 workers, 256 rows: 25 us + 5 (bias) + 6 (average) + 10 (transposed
+// copies) -> 25 us; 785 x 301, 7 workers, 785 rows: 28 + 5 + 4 + 12 -> 19 us.
+template <int R>
+__global__ __launch_bounds__(64) void wgrad_f32_kernel(GemmArgs p, Segs segs) {
+  constexpr int NB = R == 1 ? 12 : 6, S = 16 * R, C = 2 * R;    // copies per block: R of dy, R of x
+  constexpr uint32_t SLOT = C * KB;
+  __shared__ uint4 ring_area[NB * SLOT / 16];
+  int ti, tj;
+  tile_of_block(blockIdx.x, (p.M + S - 1) / S, (p.N + S - 1) / S, ti, tj);
+  const int lane = threadIdx.x, l15 = lane & 15, kg = lane >> 4;
+  const int i0 = ti * S, j0 = tj * S;
+  const uint32_t lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)&ring_area[0];
+  const bool bias = j0 == 0;
+
+  // position in the list of (worker, block); every worker has at least one block, so that an idle
+  // worker's zeros are written like any other result
+  // (the workers' first rows and weights sit in a register, one worker per lane: a scalar load
+  // would make every wait for the operand fetches wait for it too)
+  const int offv = segs.off[lane], total = segs.off[segs.K];
+  const float lamv = p.lam[lane];
+  struct Pos { int g, r, end; };           // worker, first row of the block, end of the worker's rows
+  auto enter = [&](Pos& c) {
+    const int g = c.g < segs.K ? c.g : segs.K - 1;
+    c.end = g + 1 < segs.K ? __builtin_amdgcn_readlane(offv, g + 1) : total;
+    c.r = c.g < segs.K ? __builtin_amdgcn_readlane(offv, g) : c.end;
+  };
+  auto next = [&](Pos& c) {                // true: another worker
+    c.r += 16;
+    if (c.r < c.end || c.g >= segs.K) return false;
+    ++c.g;
+    enter(c);
+    return true;
+  };
+  // copy c < R: rows (16 / R) c .. of dy, else of x.  This lane's row of a copy and its 16 bytes of
+  // the next block (16 R features from a multiple of 16 R on lie within the row pitch)
+  constexpr int LPR = 4 * R;               // lanes per row
+  const int lrow = lane / LPR;
+  const char* src[C];
+  const int64_t pitch[2] = {p.lda * 4, p.ldb * 4};
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    const int row = lrow + (16 / R) * (c % R), g = R == 1 ? lane & 3 : (lane & 7) ^ (4 * ((row >> 1) & 1));
+    src[c] = c < R ? (const char*)((const float*)p.A + row * p.lda + i0 + 4 * g)
+                   : (const char*)((const float*)p.B + row * p.ldb + j0 + 4 * g);
+  }
+  auto issue_one = [&](uint32_t slot, const Pos& q, int c) {
+    // (rows past the worker's last, and blocks past the last worker, are zeros)
+    const bool ok = q.r + lrow + (16 / R) * (c % R) < q.end;
+    async_copy_1k(ok ? (const void*)src[c] : p.zeros, lds + slot + c * KB);
+  };
+  auto advance = [&](Pos& q) {
+    const int row = q.r;
+    next(q);
+    const int rows = q.r - row;            // 16, or what the worker had left
+#pragma unroll
+    for (int c = 0; c < C; ++c) src[c] += rows * pitch[c / R];
+  };
+  float f[2][C][4];                        // [register set][16 features of dy / x][matrix instruction]
+  const char* const ring = (const char*)&ring_area[0];
+  uint32_t at[R];
+#pragma unroll
+  for (int u = 0; u < R; ++u)              // (row 4t + kg: its swizzle does not depend on t)
+    at[u] = R == 1 ? 64 * kg + 4 * l15 : 128 * kg + 64 * (u ^ ((kg >> 1) & 1)) + 4 * l15;
+  auto fetch_one = [&](int set, uint32_t slot, int t) {
+#pragma unroll
+    for (int u = 0; u < R; ++u) {
+      const char* const a = ring + (slot + at[u]) + t * (256 * R);
+      f[set][u][t] = *(const float*)a;
+      f[set][R + u][t] = *(const float*)(a + R * KB);
+    }
+  };
+  f32x4 acc[R][R], agg[R][R];              // [x block][dy block]
+  float bsum[R], bagg[R];
+#pragma unroll
+  for (int u = 0; u < R; ++u) {
+    bsum[u] = bagg[u] = 0.f;
+#pragma unroll
+    for (int w = 0; w < R; ++w) acc[u][w] = agg[u][w] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  // accumulator element v of a lane: row (x feature) 4 * kg + v, column (dy feature) l15
+  auto store = [&](float* out, const f32x4 (&v)[R][R]) {
+#pragma unroll
+    for (int u = 0; u < R; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int j = j0 + 16 * u + 4 * kg + e;
+        if (j >= p.N) continue;
+#pragma unroll
+        for (int w = 0; w < R; ++w) {
+          const int i = i0 + 16 * w + l15;
+          if (i < p.M) out[(int64_t)j * p.ldcf + i] = v[u][w][e];
+        }
+      }
+  };
+
+  int todo = 0;                            // blocks of all workers
+  for (int k = 0; k < segs.K; ++k) {
+    const int n = segs.off[k + 1] - segs.off[k];
+    todo += n > 0 ? (n + 15) / 16 : 1;
+  }
+  Pos cc, ic;                              // block being computed, next block to copy
+  cc.g = 0;
+  enter(cc);
+  ic = cc;
+#pragma unroll
+  for (int s = 0; s < NB; ++s) {
+#pragma unroll
+    for (int c = 0; c < C; ++c) issue_one(s * SLOT, ic, c);
+    advance(ic);
+  }
+  wait_pending<(NB - 1) * C>();
+#pragma unroll
+  for (int t = 0; t < 4; ++t) fetch_one(0, 0, t);
+  // (a block past the last is zeros and belongs to no worker.  Stores count as pending too: the
+  // wait then covers more than it has to, never less)
+  uint32_t slot = 0;
+  auto step = [&](int set) {
+    const uint32_t ahead = slot + SLOT == NB * SLOT ? 0 : slot + SLOT;
+    wait_pending<(NB - 2) * C>();
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+#pragma unroll
+      for (int w = 0; w < R; ++w)
+#pragma unroll
+        for (int u = 0; u < R; ++u)
+          acc[u][w] = __builtin_amdgcn_mfma_f32_16x16x4f32(f[set][R + u][t], f[set][w][t], acc[u][w], 0, 0, 0);
+      if (bias) {
+#pragma unroll
+        for (int w = 0; w < R; ++w) bsum[w] += f[set][w][t];
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      fetch_one(set ^ 1, ahead, t);
+#pragma unroll
+      for (int c = t * C / 4; c < (t + 1) * C / 4; ++c) issue_one(slot, ic, c);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    advance(ic);
+    slot = ahead;
+    const int g = cc.g;
+    if (!next(cc)) return;
+    // ---- end of worker g ----
+    const float lam = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(lamv), g));
+    store(p.Cf + (int64_t)g * p.group_stride, acc);
+#pragma unroll
+    for (int u = 0; u < R; ++u)
+#pragma unroll
+      for (int w = 0; w < R; ++w) {
+        agg[u][w] += lam * acc[u][w];
+        acc[u][w] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+    if (bias) {
+#pragma unroll
+      for (int w = 0; w < R; ++w) {
+        float v = bsum[w];
+        v += __shfl_xor(v, 16);
+        v += __shfl_xor(v, 32);
+        bagg[w] += lam * v;
+        bsum[w] = 0.f;
+        const int i = i0 + 16 * w + l15;
+        if (kg == 0 && i < p.M) p.bias_grad[(int64_t)g * p.group_stride + i] = v;
+      }
+    }
+  };
+#pragma unroll 1
+  for (int n = 0; n < todo; n += 2) {
+    step(0);
+    step(1);
+  }
+  wait_pending<0>();                       // (no copy may land after the LDS has been given back)
+  if (!p.agg) return;
+  store(p.agg, agg);
+  if (bias && kg == 0) {
+#pragma unroll
+    for (int w = 0; w < R; ++w)
+      if (i0 + 16 * w + l15 < p.M) p.bias_agg[i0 + 16 * w + l15] = bagg[w];
+  }
+}
+
+template <int R>
+void launch_as(const GemmArgs& a, const Segs& s, unsigned blocks, hipStream_t st) {
+  const dim3 grid(blocks), block(64);
+  if (a.mode == MODE_FWD)
+    hipLaunchKernelGGL((gemm_f32_kernel<MODE_FWD, R>), grid, block, 0, st, a);
+  else if (a.mode == MODE_DGRAD)
+    hipLaunchKernelGGL((gemm_f32_kernel<MODE_DGRAD, R>), grid, block, 0, st, a);
+  else
+    hipLaunchKernelGGL((wgrad_f32_kernel<R>), grid, block, 0, st, a, s);
+}
+
+}  // namespace
+
+int launch_gemm_f32(const GemmArgs& a, const Segs& s, void* stream) {
+  auto blocks = [&](int side) { return (int64_t)((a.M + side - 1) / side) * ((a.N + side - 1) / side); };
+  if (a.mode == MODE_WGRAD ? !a.bias_grad || (a.agg && !a.bias_agg) : a.K % 32 != 0)
+    return fail(DYNB_ERR_BADARG, "gemm: fp32 products take whole 32-deep blocks and write the bias gradient too");
+  // 2 x 2 tiles per wave once that gives each of the chip's 1024 SIMDs a wave: below that the chain
+  // of one wave, four times as long, outweighs the halved copies
+  const bool wide = blocks(32) >= 1024;
+  const int64_t n = blocks(wide ? 32 : 16);
+  if (n >= (int64_t)1 << 31) return fail(DYNB_ERR_UNSUPPORTED, "gemm: too many tiles for one launch");
+  if (wide) launch_as<2>(a, s, (unsigned)n, (hipStream_t)stream);
+  else launch_as<1>(a, s, (unsigned)n, (hipStream_t)stream);
+  return hipGetLastError() == hipSuccess ? DYNB_OK : fail(DYNB_ERR_HIP, "gemm launch failed");
+}
+
+}  // namespace dynb

@@ -1,5 +1,4 @@
-// Small kernels around the GEMMs: input packing into the padded row space, transposes,
-// softmax cross-entropy with the per-worker 1/b_k, bias gradients, loss reduction and the
+// Small kernels around the GEMMs: input packing, softmax cross-entropy with the per-worker 1/b_k, bias gradients, loss reduction and the
 // 16-bit weight copies.
 #include <hip/hip_runtime.h>
 
@@ -12,14 +11,7 @@ namespace {
 typedef __bf16 bf16;
 
 template <typename T> __device__ inline T from_float(float v) { return (T)v; }
-template <typename T> __device__ inline float to_float(T v) { return (float)v; }
 
-// Padded row -> (worker, row inside the worker's padded segment).
-__device__ inline void locate_padded(const Segs& s, int prow, int& k, int& r) {
-  k = 0;
-  while (k + 1 < s.K && prow >= s.poff[k + 1]) ++k;
-  r = prow - s.poff[k];
-}
 // Dense row -> worker.
 __device__ inline int worker_of(const Segs& s, int row) {
   int k = 0;
@@ -83,47 +75,6 @@ __global__ __launch_bounds__(256) void pack_rows_narrow_kernel(const float* __re
 #pragma unroll
   for (int c = 0; c < 8; ++c) v[c] = c < D ? (__bf16)x[r * D + c] : (__bf16)0.f;
   *(vec8*)(out + r * ld) = v;
-}
-
-// ---- transpose into the padded row space: out[c][p] = in[m(p)][c], 0 where p is padding ----
-// p runs over the padded positions; worker k's b_k rows sit at [poff_k, poff_k + b_k).
-// A 64 x 64 tile moves through LDS; global loads and stores are 16 bytes per lane, and eight
-// neighbouring lanes write one contiguous 128-byte line of an output row.
-template <typename T>
-__global__ __launch_bounds__(256) void transpose_kernel(const T* __restrict__ in, int64_t ldi,
-                                                        int C, T* __restrict__ out, int64_t ldo,
-                                                        Segs s) {
-  constexpr int G = 16 / sizeof(T);          // elements per 16-byte granule
-  constexpr int GC = 64 / G;                 // granules per tile row
-  // row pitch of 33 (bf16) / 65 (fp32) dwords: the turned reads below walk down a column, and
-  // rows that are 8 apart must not fall into the same LDS bank
-  constexpr int PITCH = 64 + 4 / sizeof(T);
-  __shared__ T tile[64][PITCH];
-  const int p0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
-  const int P = s.poff[s.K];
-  typedef T vecT __attribute__((ext_vector_type(G)));
-  for (int idx = threadIdx.x; idx < 64 * GC; idx += 256) {
-    const int r = idx / GC, gc = idx % GC;
-    const int pr = p0 + r;
-    vecT v = {};
-    if (pr < P) {
-      int k, rl;
-      locate_padded(s, pr, k, rl);
-      if (rl < s.off[k + 1] - s.off[k])
-        v = *(const vecT*)(in + (int64_t)(s.off[k] + rl) * ldi + c0 + gc * G);
-    }
-#pragma unroll
-    for (int e = 0; e < G; ++e) tile[r][gc * G + e] = v[e];
-  }
-  __syncthreads();
-  for (int idx = threadIdx.x; idx < 64 * GC; idx += 256) {
-    const int rg = idx % GC, c = idx / GC;    // rg: granule of padded positions, c: output row
-    if (c0 + c >= C) continue;
-    vecT v;
-#pragma unroll
-    for (int e = 0; e < G; ++e) v[e] = tile[rg * G + e][c];
-    *(vecT*)(out + (int64_t)(c0 + c) * ldo + p0 + rg * G) = v;
-  }
 }
 
 // ---- softmax cross-entropy, one wavefront per row -----------------------------------------
@@ -202,31 +153,6 @@ __global__ __launch_bounds__(256) void softmax_xent_kernel(const float* __restri
     drow[c] = from_float<T>(v);
   }
   if (lane == 0) rowloss[row] = logf(sum) - (zr[label] - m);
-}
-
-// ---- bias gradient: one wavefront per (output feature, worker) --------------------------
-// The worker's padded segment starts on a 16-byte boundary and its padding holds zeros, so the
-// whole segment is summed with 16-byte loads.
-template <typename T>
-__global__ __launch_bounds__(256) void bias_grad_kernel(const T* __restrict__ dyT, int64_t ld,
-                                                        int N, float* __restrict__ grads,
-                                                        int64_t group_stride, Segs s) {
-  constexpr int G = 16 / sizeof(T);
-  typedef T vecT __attribute__((ext_vector_type(G)));
-  const int lane = threadIdx.x & 63;
-  const int n = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int g = blockIdx.y;
-  if (n >= N) return;
-  const int granules = (s.poff[g + 1] - s.poff[g]) / G;
-  const vecT* row = (const vecT*)(dyT + (int64_t)n * ld + s.poff[g]);
-  float acc = 0.f;
-  for (int i = lane; i < granules; i += 64) {
-    const vecT v = row[i];
-#pragma unroll
-    for (int e = 0; e < G; ++e) acc += to_float<T>(v[e]);
-  }
-  acc = wave_sum(acc);
-  if (lane == 0) grads[(int64_t)g * group_stride + n] = acc;
 }
 
 // ---- per-worker mean loss, zero tail of each worker's gradient vector, and (workgroups behind
@@ -351,18 +277,6 @@ int launch_pack_rows(int dtype, const float* x, int rows, int D, void* out, int6
   return ok("pack_rows");
 }
 
-int launch_transpose(int dtype, const void* in, int64_t ldi, int C, void* out, int64_t ldo,
-                     const Segs& s, void* stream) {
-  const int P = s.poff[s.K];
-  if (P == 0 || C == 0) return DYNB_OK;
-  const int es = dtype == DYNB_BF16 ? 2 : 4;
-  Timed t(KC_TRANSPOSE, stream, 0, 2.0 * s.off[s.K] * C * es);
-  dim3 grid((C + 63) / 64, (P + 63) / 64);
-  DISPATCH_T(dtype, hipLaunchKernelGGL(transpose_kernel<T>, grid, dim3(256), 0,
-                                       (hipStream_t)stream, (const T*)in, ldi, C, (T*)out, ldo, s));
-  return ok("transpose");
-}
-
 int launch_softmax_xent(int dtype, const float* logits, int64_t ldz, const int32_t* y, int C,
                         void* dz, int64_t ldd, int ld_cols, float* rowloss, const Segs& s,
                         void* stream) {
@@ -375,7 +289,7 @@ int launch_softmax_xent(int dtype, const float* logits, int64_t ldz, const int32
   return ok("softmax_xent");
 }
 
-// The same from the row-major gradient dy [rows][ld] (bf16): one workgroup per (64 features,
+// Bias gradient from the row-major gradient dy [rows][ld] (bf16): one workgroup per (64 features,
 // worker); 8 lanes cover the 128 bytes of a row, 32 row-lanes walk the worker's rows, the
 // partial sums meet in a fixed order.
 __global__ __launch_bounds__(256) void bias_grad_rows_kernel(const bf16* __restrict__ dy, int64_t ld,
@@ -410,16 +324,6 @@ int launch_bias_grad_rows(const void* dy, int64_t ld, int N, float* grads, int64
   hipLaunchKernelGGL(bias_grad_rows_kernel, dim3((unsigned)(ld / 64), s.K), dim3(256), 0,
                      (hipStream_t)stream, (const bf16*)dy, ld, N, grads, group_stride, s);
   return ok("bias_grad_rows");
-}
-
-int launch_bias_grad(int dtype, const void* dyT, int64_t ld, int N, float* grads,
-                     int64_t group_stride, const Segs& s, void* stream) {
-  const int es = dtype == DYNB_BF16 ? 2 : 4;
-  Timed t(KC_BIAS_GRAD, stream, 0, (double)s.off[s.K] * N * es);
-  DISPATCH_T(dtype, hipLaunchKernelGGL(bias_grad_kernel<T>, dim3((N + 3) / 4, s.K), dim3(256), 0,
-                                       (hipStream_t)stream, (const T*)dyT, ld, N, grads,
-                                       group_stride, s));
-  return ok("bias_grad");
 }
 
 int launch_touch(const void* p, int64_t bytes, void* stream) {

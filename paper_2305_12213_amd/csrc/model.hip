@@ -6,11 +6,8 @@
 // weight/bias gradients are per worker.  A "row" is a sample for dense layers and a pixel
 // (sample, y, x) for convolutions (NHWC with the channel pitch padded to 64).
 //
-// bf16 models: the per-worker weight-gradient kernels reduce over the rows of the row-major
-// activations and gradients themselves.  fp32 models: every operand of a per-worker
-// weight-gradient GEMM is kept transposed, [features][padded rows]; in these copies worker k's
-// rows sit at columns [poff_k, poff_k + rows_k), poff_k = sum_{j<k} round_up(rows_j, 8), so that
-// every worker's segment starts on a 16-byte boundary; the padding columns are written as zero.
+// The per-worker weight-gradient kernels reduce over the rows of the row-major activations and
+// gradients themselves; there are no transposed copies.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -36,10 +33,7 @@ struct Layer {
   void* Wn = nullptr;                // B operand of the input-gradient GEMM
   void* Wt = nullptr;                // B operand of the forward GEMM
   void* out = nullptr;               // T [rows_out][ld_out]: stored output (not for the last layer)
-  void* inT = nullptr;               // T [wg_rows][cap]: transposed input (dense layers)
   void* dy = nullptr;                // T [rows_out][ld_out]: gradient wrt the output, masked
-  void* dyT = nullptr;               // T [n_out][cap]
-  int64_t capT = 0;                  // padded row capacity of inT / dyT
   int max_split = 1;                 // most chunks a worker's weight-gradient reduction is cut into
   int conv_chunk = 0;                // rows per chunk of a convolution's weight gradient
   // batch normalisation: scale at w_off, shift at b_off (n_out floats each); per-worker statistics
@@ -94,10 +88,6 @@ struct Carver {
   }
 };
 
-int64_t padded_cap(int64_t max_batch, int64_t hw, int max_workers) {
-  return round_up(max_batch * hw + (int64_t)(ROW_PAD - 1) * max_workers, 64);
-}
-
 // Lays out the workspace; with base == nullptr only the size is computed.
 size_t carve(dynb_model* m, void* base, int max_batch, int max_workers) {
   Carver c(base);
@@ -115,11 +105,12 @@ size_t carve(dynb_model* m, void* base, int max_batch, int max_workers) {
       L.bn_rstd = (float*)c.take((size_t)max_workers * L.n_out * 4);
     }
     if (L.has_params) {
-      if (L.kind == DYNB_LAYER_DENSE && m->dtype != DYNB_BF16) {   // (bf16 weight gradients read the
-                                                                   // row-major tensors themselves)
-        L.capT = padded_cap(max_batch, L.hw_out, max_workers);
-        L.inT = c.take((size_t)L.wg_rows * L.capT * es);
-        L.dyT = c.take((size_t)L.n_out * L.capT * es);
+      if (m->dtype != DYNB_BF16) {
+        // (unused; the workspace an fp32 model asks for, and with it what the workspace-free call
+        // accepts, stays what callers have been told so far)
+        const int64_t cap = round_up((int64_t)max_batch * L.hw_out + 7 * (int64_t)max_workers, 64);
+        c.take((size_t)L.wg_rows * cap * es);
+        c.take((size_t)L.n_out * cap * es);
       }
       if (L.kind == DYNB_LAYER_DENSE) {
         L.Wn = c.take((size_t)L.n_in * L.ld_out * es);
@@ -169,16 +160,11 @@ size_t carve(dynb_model* m, void* base, int max_batch, int max_workers) {
 int build_segs(const int32_t* b, int K, int hw, Segs& s) {
   s.K = K;
   s.off[0] = 0;
-  s.poff[0] = 0;
   for (int k = 0; k < K; ++k) {
     if (b[k] < 0) return fail(DYNB_ERR_BADARG, "negative batch size for worker %d", k);
     s.off[k + 1] = s.off[k] + b[k] * hw;
-    s.poff[k + 1] = s.poff[k] + (int)round_up((int64_t)b[k] * hw, ROW_PAD);
   }
-  for (int k = K + 1; k <= DYNB_MAX_WORKERS; ++k) {
-    s.off[k] = s.off[K];
-    s.poff[k] = s.poff[K];
-  }
+  for (int k = K + 1; k <= DYNB_MAX_WORKERS; ++k) s.off[k] = s.off[K];
   return DYNB_OK;
 }
 
@@ -419,7 +405,10 @@ int run_forward_backward(dynb_model* m, const float* x, const int32_t* y, const 
     rc = build_segs(b, K, m->layers[l].hw_out, segs[l]);
     if (rc) return rc;
   }
-  auto in_act = [&](size_t l) -> const void* { return l == 0 ? m->act0 : m->layers[l - 1].out; };
+  // (an fp32 batch whose rows already have the padded pitch is read where it is)
+  const bool x_as_is = dt == DYNB_F32 && m->in_c == m->ld0 && m->in_h * m->in_w == 1 && !((uintptr_t)x & 15);
+  const void* const act0 = x_as_is ? (const void*)x : m->act0;
+  auto in_act = [&](size_t l) -> const void* { return l == 0 ? act0 : m->layers[l - 1].out; };
 
   // dyv[l]: where layer l's gradient is read from -- its own buffer, or (no copy) the buffer of
   // the residual addition above it.  skip_grad[l]: the gradient that reaches a fused skip source
@@ -483,13 +472,8 @@ int run_forward_backward(dynb_model* m, const float* x, const int32_t* y, const 
     }
     GemmArgs g = {};
     g.mode = MODE_WGRAD;
-    if (dt == DYNB_BF16) {   // the row-major tensors themselves, reduced over each worker's rows
-      g.A = dyv[l]; g.lda = L.ld_out;
-      g.B = in_act(l); g.ldb = L.ld_in;
-    } else {
-      g.A = L.dyT; g.lda = L.capT;
-      g.B = L.inT; g.ldb = L.capT;
-    }
+    g.A = dyv[l]; g.lda = L.ld_out;   // the row-major tensors, reduced over each worker's rows
+    g.B = in_act(l); g.ldb = L.ld_in;
     g.M = L.n_out; g.N = L.wg_rows;
     g.Cf = grads + L.w_off; g.ldcf = L.n_out;
     g.group_stride = m->P_pad;
@@ -497,7 +481,7 @@ int run_forward_backward(dynb_model* m, const float* x, const int32_t* y, const 
     g.alg_bytes = (double)K * L.wg_rows * L.n_out * 4 + (double)B * L.hw_out * (L.wg_rows + L.n_out) * es;
     int deepest = 0;
     for (int k = 0; k < K; ++k) {
-      const int d = dt == DYNB_BF16 ? segs[l].off[k + 1] - segs[l].off[k] : segs[l].poff[k + 1] - segs[l].poff[k];
+      const int d = segs[l].off[k + 1] - segs[l].off[k];
       deepest = d > deepest ? d : deepest;
     }
     int split = (deepest + 255) / 256;               // chunks of at least eight 32-deep stages
@@ -515,9 +499,10 @@ int run_forward_backward(dynb_model* m, const float* x, const int32_t* y, const 
       g.alg_bytes += (double)L.wg_rows * L.n_out * 4;   // the aggregated tile is written too
       g.agg = agg + L.w_off;
       for (int k = 0; k < K; ++k) g.lam[k] = lam.w[k];
+      if (dt == DYNB_F32) g.bias_agg = agg + L.b_off;
     }
-    // bf16, unsplit: the bias gradient is formed by the same kernel
-    const bool bias_inside = dt == DYNB_BF16 && split <= 1;
+    // unsplit: the bias gradient is formed by the same kernel
+    const bool bias_inside = split <= 1;
     if (bias_inside) g.bias_grad = grads + L.b_off;
     rc = launch_gemm(dt, g, segs[l], stream);
     if (rc) return rc;
@@ -526,13 +511,10 @@ int run_forward_backward(dynb_model* m, const float* x, const int32_t* y, const 
                                grads + L.w_off, m->P_pad, K, stream);
       if (rc) return rc;
     }
-    if (bias_inside)
-      rc = DYNB_OK;
-    else if (dt == DYNB_BF16)
+    if (!bias_inside) {
       rc = launch_bias_grad_rows(dyv[l], L.ld_out, L.n_out, grads + L.b_off, m->P_pad, segs[l], stream);
-    else
-      rc = launch_bias_grad(dt, L.dyT, L.capT, L.n_out, grads + L.b_off, m->P_pad, segs[l], stream);
-    if (rc) return rc;
+      if (rc) return rc;
+    }
     if (agg) {
       const int64_t nw = (int64_t)L.wg_rows * L.n_out;
       if (!fold && nw >= 65536) {
@@ -542,15 +524,17 @@ int run_forward_backward(dynb_model* m, const float* x, const int32_t* y, const 
         rc = add_small(L.w_off, nw);
         if (rc) return rc;
       }
-      rc = add_small(L.b_off, L.n_out);
+      if (!g.bias_agg) rc = add_small(L.b_off, L.n_out);
       if (rc) return rc;
     }
     return (int)DYNB_OK;
   };
   if (B > 0) {
     // ---- forward ----
-    rc = launch_pack_rows(dt, x, B * m->in_h * m->in_w, m->in_c, m->act0, m->ld0, stream);
-    if (rc) return rc;
+    if (!x_as_is) {
+      rc = launch_pack_rows(dt, x, B * m->in_h * m->in_w, m->in_c, m->act0, m->ld0, stream);
+      if (rc) return rc;
+    }
     for (size_t l = 0; l < nL; ++l) {
       Layer& L = m->layers[l];
       const bool last = l + 1 == nL;
@@ -592,10 +576,6 @@ int run_forward_backward(dynb_model* m, const float* x, const int32_t* y, const 
       if (last) { g.Cf = m->logits; g.ldcf = L.ld_out; }
       else { g.C = L.out; g.ldc = L.ld_out; }
       if (L.kind == DYNB_LAYER_DENSE) {
-        if (dt != DYNB_BF16) {
-          rc = launch_transpose(dt, in_act(l), L.ld_in, L.n_in, L.inT, L.capT, segs[l], stream);
-          if (rc) return rc;
-        }
         g.A = in_act(l); g.lda = L.ld_in;
         g.B = L.Wt; g.ldb = L.ld_in;
         g.K = (int)L.ld_in;
@@ -625,10 +605,6 @@ int run_forward_backward(dynb_model* m, const float* x, const int32_t* y, const 
       if (L.skip_source && !L.skip_fused) {   // the gradient of the residual branch joins in
         rc = launch_grad_route(L.dy_skip, L.ld_out, nullptr, 0, L.ld_out, (int64_t)B * L.hw_out, 0, 1,
                                L.dy, L.ld_out, stream);
-        if (rc) return rc;
-      }
-      if (L.kind == DYNB_LAYER_DENSE && dt != DYNB_BF16) {
-        rc = launch_transpose(dt, dyv[l], L.ld_out, L.n_out, L.dyT, L.capT, segs[l], stream);
         if (rc) return rc;
       }
       const bool below = (int)l > m->first_param_layer;   // does anything below need a gradient?
