@@ -162,10 +162,6 @@ int launch_aggregate(const float* grads, const Lambdas& lam, int64_t n, float* o
 int launch_sgd(float* params, const float* g, int64_t n, float lr, void* stream);
 int launch_momentum(float* params, float* v, const float* g, int64_t n, float lr, float mu,
                     void* stream);
-// W fp32 [R][C] (dense) -> Wn T [R][ldn] and Wt T [C][ldt]
-int launch_weight_cast(int dtype, const float* W, int R, int C, void* Wn, int64_t ldn, void* Wt,
-                       int64_t ldt, void* stream);
-
 // One optimizer step per parameter.  kind: DYNB_OPT_*.  s1 = velocity (momentum) or first
 // moment (Adam), s2 = second moment (Adam).  Adam's bias corrections are passed as
 // inv_c1 = 1/(1 - beta1^t), inv_c2 = 1/(1 - beta2^t), and omb = 1 - beta, all formed in double.
@@ -185,28 +181,28 @@ struct GradSource {
   Lambdas lam;
 };
 
-// Dense weights W fp32 [R][C] at parameter offset `off`, each with its copies Wn T [R][ldn] and
-// Wt T [C][ldt] (T = the model's storage type), passed to the kernel by value.
+// Weights W fp32 [taps][R][C] at parameter offset `off` (a dense layer: one tap), each tap with its
+// copies Wn T [R][ldn] and Wt T [C][ldt] (T = the model's storage type), tap_n / tap_t elements
+// apart.  Passed to the kernel by value.
 constexpr int MAX_CAST_MATS = 8;
 struct CastMats {
   int n;
   int64_t off[MAX_CAST_MATS];
-  int R[MAX_CAST_MATS], C[MAX_CAST_MATS];
+  int R[MAX_CAST_MATS], C[MAX_CAST_MATS], taps[MAX_CAST_MATS];
   void* Wn[MAX_CAST_MATS];
-  int64_t ldn[MAX_CAST_MATS];
+  int64_t ldn[MAX_CAST_MATS], tap_n[MAX_CAST_MATS];
   void* Wt[MAX_CAST_MATS];
-  int64_t ldt[MAX_CAST_MATS];
+  int64_t ldt[MAX_CAST_MATS], tap_t[MAX_CAST_MATS];
   int first_block[MAX_CAST_MATS + 1];   // first workgroup of each matrix (set by the launcher)
 };
+// The copies alone, of the weights as they are.
+int launch_weight_casts(int dtype, const float* params, CastMats& mats, void* stream);
 // One launch: the optimizer step of every matrix of `mats` fused with the refresh of its two
 // copies, and the element-wise step of every range of `small`; s1/s2 point at the state of
 // parameter 0 (may be null when the rule has no such state)
 int launch_update_cast(int dtype, float* params, CastMats& mats, const Ranges& small,
                        const GradSource& src, const UpdateRule& rule, float* s1, float* s2,
                        void* stream);
-// element-wise step of parameters [off, off + n) (any alignment)
-int launch_update_range(float* params, int64_t off, const GradSource& src, const UpdateRule& rule,
-                        float* s1, float* s2, int64_t n, void* stream);
 // element-wise step of every range of r
 int launch_update_ranges(float* params, const Ranges& r, const GradSource& src, const UpdateRule& rule,
                          float* s1, float* s2, void* stream);
@@ -222,9 +218,6 @@ int launch_gap_forward(const void* act, int64_t lda, int HW, int C, int samples,
                        int64_t ldp, void* stream);
 int launch_gap_backward(const void* dpooled, int64_t ldp, const void* act, int64_t lda, int HW,
                         int C, int samples, int relu, void* dact, int64_t ldd, void* stream);
-int launch_conv_weight_cast(const float* W, int Cin, int Cout, int cin_p, int cout_p, void* Wf,
-                            int kf, void* Wd, int kd, void* stream);
-
 // Forward / input gradient of a 3x3 convolution from one halo tile in LDS (conv_direct.hip):
 // takes the same description as the gathered-operand GEMM where conv_direct_applies() says so.
 bool conv_direct_applies(int dtype, const GemmArgs& a);

@@ -1,5 +1,5 @@
 // Kernels around the implicit-GEMM convolutions (NHWC, 3x3, zero padding 1; bf16 storage):
-// global average pooling forward/backward and the two 16-bit weight layouts of a convolution.
+// global average pooling forward/backward.
 #include <hip/hip_runtime.h>
 
 #include "device_rows.h"
@@ -59,32 +59,6 @@ __global__ __launch_bounds__(256) void gap_backward_kernel(const bf16* __restric
   store8(dact + row * ldd + c0, pack8(v));
 }
 
-// W fp32 [3][3][Cin][Cout] ->
-//   Wf [Cout][kf] : Wf[co][(kh*3+kw)*cin_p + ci] = W[kh][kw][ci][co]   (forward B operand)
-//   Wd [Cin][kd]  : Wd[ci][(kh*3+kw)*cout_p + co] = W[kh][kw][ci][co]  (input-gradient B operand)
-// Positions that correspond to padded channels or padded reduction length are written as zero.
-__global__ __launch_bounds__(256) void conv_weight_cast_kernel(const float* __restrict__ W, int Cin,
-                                                               int Cout, int cin_p, int cout_p,
-                                                               bf16* __restrict__ Wf, int kf,
-                                                               bf16* __restrict__ Wd, int kd) {
-  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int64_t nf = (int64_t)Cout * kf, nd = (int64_t)Cin * kd;
-  if (t < nf) {
-    const int co = (int)(t / kf), k = (int)(t - (int64_t)co * kf);
-    const int tap = k / cin_p, ci = k - tap * cin_p;
-    float v = 0.f;
-    if (tap < 9 && ci < Cin) v = W[((int64_t)tap * Cin + ci) * Cout + co];
-    Wf[t] = (bf16)v;
-  } else if (t < nf + nd) {
-    const int64_t u = t - nf;
-    const int ci = (int)(u / kd), k = (int)(u - (int64_t)ci * kd);
-    const int tap = k / cout_p, co = k - tap * cout_p;
-    float v = 0.f;
-    if (tap < 9 && co < Cout) v = W[((int64_t)tap * Cin + ci) * Cout + co];
-    Wd[u] = (bf16)v;
-  }
-}
-
 inline int ok(const char* what) {
   return hipGetLastError() == hipSuccess ? DYNB_OK : fail(DYNB_ERR_HIP, "%s: launch failed", what);
 }
@@ -114,15 +88,6 @@ int launch_gap_backward(const void* dpooled, int64_t ldp, const void* act, int64
                      (hipStream_t)stream, (const bf16*)dpooled, ldp, (const bf16*)act, lda, HW, gpr,
                      total, relu, (bf16*)dact, ldd);
   return ok("gap_backward");
-}
-
-int launch_conv_weight_cast(const float* W, int Cin, int Cout, int cin_p, int cout_p, void* Wf,
-                            int kf, void* Wd, int kd, void* stream) {
-  const int64_t total = (int64_t)Cout * kf + (int64_t)Cin * kd;
-  Timed t(KC_WEIGHT_CAST, stream, 0, 9.0 * Cin * Cout * 4 + total * 2);
-  hipLaunchKernelGGL(conv_weight_cast_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0,
-                     (hipStream_t)stream, W, Cin, Cout, cin_p, cout_p, (bf16*)Wf, kf, (bf16*)Wd, kd);
-  return ok("conv_weight_cast");
 }
 
 }  // namespace dynb

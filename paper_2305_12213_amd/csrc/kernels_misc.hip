@@ -205,30 +205,6 @@ __global__ __launch_bounds__(256) void touch_kernel(const uint4* __restrict__ p,
   if (sink) *sink = acc;   // (sink is always null: the condition only keeps the loads alive)
 }
 
-// ---- weight copies: Wn[r][c] = T(W[r][c]),  Wt[c][r] = T(W[r][c]) ----------------------
-template <typename T>
-__global__ __launch_bounds__(256) void weight_cast_kernel(const float* __restrict__ W, int R, int C,
-                                                          T* __restrict__ Wn, int64_t ldn,
-                                                          T* __restrict__ Wt, int64_t ldt) {
-  __shared__ float tile[64][65];
-  const int r0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
-  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-  for (int i = ty; i < 64; i += 4) {
-    const int r = r0 + i, c = c0 + tx;
-    float v = 0.f;
-    if (r < R && c < C) {
-      v = W[(int64_t)r * C + c];
-      Wn[(int64_t)r * ldn + c] = from_float<T>(v);
-    }
-    tile[i][tx] = v;
-  }
-  __syncthreads();
-  for (int i = ty; i < 64; i += 4) {
-    const int c = c0 + i, r = r0 + tx;
-    if (c < C && r < R) Wt[(int64_t)c * ldt + r] = from_float<T>(tile[tx][i]);
-  }
-}
-
 // ---- sum of the split weight-gradient chunks, fixed order -------------------------------
 __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float* __restrict__ partial,
                                                            int split, int64_t pstride, int64_t n,
@@ -369,16 +345,6 @@ int launch_wgrad_reduce(const float* partial, int split, int64_t partial_stride,
   hipLaunchKernelGGL(wgrad_reduce_kernel, dim3((unsigned)bx, K), dim3(256), 0, (hipStream_t)stream,
                      partial, split, partial_stride, n, out, group_stride);
   return ok("wgrad_reduce");
-}
-
-int launch_weight_cast(int dtype, const float* W, int R, int C, void* Wn, int64_t ldn, void* Wt,
-                       int64_t ldt, void* stream) {
-  const int es = dtype == DYNB_BF16 ? 2 : 4;
-  Timed t(KC_WEIGHT_CAST, stream, 0, (double)R * C * (4 + 2 * es));
-  dim3 grid((C + 63) / 64, (R + 63) / 64);
-  DISPATCH_T(dtype, hipLaunchKernelGGL(weight_cast_kernel<T>, grid, dim3(256), 0,
-                                       (hipStream_t)stream, W, R, C, (T*)Wn, ldn, (T*)Wt, ldt));
-  return ok("weight_cast");
 }
 
 }  // namespace dynb

@@ -17,8 +17,10 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 template <typename T> __device__ inline T from_float(float v) { return (T)v; }
 
 // One parameter, one step.  s1/s2 are the optimizer's state for this parameter.
+constexpr int COPY_ONLY = -1;   // no step: only the copies of the weights as they are
 template <int KIND>
 __device__ inline float step_one(const UpdateRule& r, float w, float g, float& s1, float& s2) {
+  if (KIND == COPY_ONLY) return w;
   if (KIND == DYNB_OPT_SGD) return w - r.lr * g;
   if (KIND == DYNB_OPT_MOMENTUM) {
     s1 = r.mu * s1 + g;
@@ -57,8 +59,38 @@ __device__ inline float gradient1(const GradSource& src, int64_t o) {
   return acc;
 }
 
-// ---- dense weight matrices: step + both 16-bit copies in one pass ---------------------------
-// W[r][c] <- step(W[r][c]); Wn[r][c] = T(W), Wt[c][r] = T(W).  A workgroup owns a 64 x TC tile:
+// Gradients of U parameters at o[0..U): every load of a worker's U elements, and of four workers, is
+// in flight at once (ascending k per element, as above).
+template <bool AGG, int U>
+__device__ inline void gradients(const GradSource& src, const int64_t (&o)[U], float (&g)[U]) {
+  if (!AGG) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) g[u] = src.g[o[u]];
+    return;
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u) g[u] = 0.f;
+  const float* base = src.g;
+  int k = 0;
+  for (; k + 4 <= src.lam.K; k += 4, base += 4 * src.worker_stride) {
+    float v[4][U];
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+#pragma unroll
+      for (int u = 0; u < U; ++u) v[w][u] = base[w * src.worker_stride + o[u]];
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+#pragma unroll
+      for (int u = 0; u < U; ++u) g[u] += src.lam.w[k + w] * v[w][u];
+  }
+  for (; k < src.lam.K; ++k, base += src.worker_stride)
+#pragma unroll
+    for (int u = 0; u < U; ++u) g[u] += src.lam.w[k] * base[o[u]];
+}
+
+// ---- weight matrices: step + both 16-bit copies in one pass ----------------------------------
+// W[r][c] <- step(W[r][c]); Wn[r][c] = T(W), Wt[c][r] = T(W).  (A convolution is nine such matrices,
+// one per tap, whose copies lie side by side in the rows of its two operands.)  A workgroup owns a 64 x TC tile:
 // 16-byte accesses on the fp32 side, the transposed copy goes through an LDS tile so that its
 // stores are 16 bytes per lane and whole 128-byte lines per 8 (bf16) lanes.
 // One launch serves every matrix of `mats` (workgroups mats.first_block[i] ... belong to matrix
@@ -71,6 +103,7 @@ __global__ __launch_bounds__(256) void update_cast_kernel(float* __restrict__ pa
                                                           GradSource src, UpdateRule rule,
                                                           float* __restrict__ s1,
                                                           float* __restrict__ s2) {
+  constexpr bool HAS_S1 = KIND == DYNB_OPT_MOMENTUM || KIND == DYNB_OPT_ADAM;
   const int blk = blockIdx.x;
   if (blk >= mats.first_block[mats.n]) {   // the small tensors, element by element
     const int rb = blk - mats.first_block[mats.n];
@@ -78,10 +111,10 @@ __global__ __launch_bounds__(256) void update_cast_kernel(float* __restrict__ pa
       const int64_t off = small.off[q], n = small.len[q];
       for (int64_t i = (int64_t)rb * 256 + threadIdx.x; i < n; i += (int64_t)range_blocks * 256) {
         const int64_t o = off + i;
-        float a = KIND != DYNB_OPT_SGD ? s1[o] : 0.f;
+        float a = HAS_S1 ? s1[o] : 0.f;
         float b = KIND == DYNB_OPT_ADAM ? s2[o] : 0.f;
         params[o] = step_one<KIND>(rule, params[o], gradient1<AGG>(src, o), a, b);
-        if (KIND != DYNB_OPT_SGD) s1[o] = a;
+        if (HAS_S1) s1[o] = a;
         if (KIND == DYNB_OPT_ADAM) s2[o] = b;
       }
     }
@@ -89,32 +122,69 @@ __global__ __launch_bounds__(256) void update_cast_kernel(float* __restrict__ pa
   }
   int mi = 0;
   while (blk >= mats.first_block[mi + 1]) ++mi;
-  const int64_t off = mats.off[mi], ldn = mats.ldn[mi], ldt = mats.ldt[mi];
+  const int64_t ldn = mats.ldn[mi], ldt = mats.ldt[mi];
   const int R = mats.R[mi], C = mats.C[mi];
-  T* __restrict__ Wn = (T*)mats.Wn[mi];
-  T* __restrict__ Wt = (T*)mats.Wt[mi];
   const int tiles_x = (C + TC - 1) / TC, local = blk - mats.first_block[mi];
-  const int tile_x = local % tiles_x, tile_y = local / tiles_x;
+  const int per_tap = tiles_x * ((R + 63) / 64), tap = local / per_tap, in_tap = local - tap * per_tap;
+  const int tile_x = in_tap % tiles_x, tile_y = in_tap / tiles_x;
+  const int64_t off = mats.off[mi] + (int64_t)tap * R * C;
+  T* __restrict__ Wn = (T*)mats.Wn[mi] + tap * mats.tap_n[mi];
+  T* __restrict__ Wt = (T*)mats.Wt[mi] + tap * mats.tap_t[mi];
   constexpr int G = 16 / sizeof(T);
   typedef T vecT __attribute__((ext_vector_type(G)));
   typedef T vec4T __attribute__((ext_vector_type(4)));
   constexpr int QC = TC / 4;   // 16-byte granules per tile row
   __shared__ float tile[64][TC + 1];
   const int r0 = tile_y * 64, c0 = tile_x * TC;
-  // 16-byte accesses need aligned rows in every array (all start at a multiple of 4 floats)
+  // 16-byte accesses need aligned rows in every array (all start at a multiple of 4 floats);
+  // otherwise a lane takes single elements, 64 neighbouring ones of a row per wave, U rows or column
+  // halves at once.  (1001 x 2050 and 2050 x 777, 7 workers, Adam: 106 us with four elements in turn
+  // per lane -> 43 us, what its 210 MB take at the rate of a large copy.)
   const bool vec = (C & 3) == 0 && (off & 3) == 0;
+  if (!vec) {
+    constexpr int U = 4;
+    for (int idx = threadIdx.x; idx < 64 * TC; idx += 256 * U) {
+      int64_t o[U];
+      bool live[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int e = idx + 256 * u, gr = r0 + e / TC, gc = c0 + e % TC;
+        live[u] = gr < R && gc < C;
+        o[u] = live[u] ? off + (int64_t)gr * C + gc : off;   // (a dead lane reads the first element)
+      }
+      float g[U], w[U], a[U], b[U];
+      if (KIND != COPY_ONLY) gradients<AGG, U>(src, o, g);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        w[u] = params[o[u]];
+        a[u] = HAS_S1 ? s1[o[u]] : 0.f;
+        b[u] = KIND == DYNB_OPT_ADAM ? s2[o[u]] : 0.f;
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int e = idx + 256 * u, r = e / TC, c = e % TC;
+        w[u] = step_one<KIND>(rule, w[u], g[u], a[u], b[u]);
+        if (live[u]) {
+          if (KIND != COPY_ONLY) params[o[u]] = w[u];
+          if (HAS_S1) s1[o[u]] = a[u];
+          if (KIND == DYNB_OPT_ADAM) s2[o[u]] = b[u];
+          Wn[(int64_t)(r0 + r) * ldn + c0 + c] = from_float<T>(w[u]);
+        }
+        tile[r][c] = live[u] ? w[u] : 0.f;
+      }
+    }
+  } else {
 #pragma unroll 2
-  for (int idx = threadIdx.x; idx < 64 * QC; idx += 256) {
-    const int r = idx / QC, cq = (idx % QC) * 4;
-    const int gr = r0 + r, gc = c0 + cq;
-    f4 w = {0.f, 0.f, 0.f, 0.f};
-    if (gr < R && gc < C) {
-      const int64_t o = off + (int64_t)gr * C + gc;
-      if (vec) {
-        const f4 d = gradient4<AGG>(src, o);
+    for (int idx = threadIdx.x; idx < 64 * QC; idx += 256) {
+      const int r = idx / QC, cq = (idx % QC) * 4;
+      const int gr = r0 + r, gc = c0 + cq;
+      f4 w = {0.f, 0.f, 0.f, 0.f};
+      if (gr < R && gc < C) {
+        const int64_t o = off + (int64_t)gr * C + gc;
+        f4 a = {0.f, 0.f, 0.f, 0.f}, b = a, d = a;
+        if (KIND != COPY_ONLY) d = gradient4<AGG>(src, o);
         w = *(const f4*)(params + o);
-        f4 a = {0.f, 0.f, 0.f, 0.f}, b = a;
-        if (KIND != DYNB_OPT_SGD) a = *(const f4*)(s1 + o);
+        if (HAS_S1) a = *(const f4*)(s1 + o);
         if (KIND == DYNB_OPT_ADAM) b = *(const f4*)(s2 + o);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -123,25 +193,15 @@ __global__ __launch_bounds__(256) void update_cast_kernel(float* __restrict__ pa
           a[e] = ae;
           b[e] = be;
         }
-        *(f4*)(params + o) = w;
-        if (KIND != DYNB_OPT_SGD) *(f4*)(s1 + o) = a;
+        if (KIND != COPY_ONLY) *(f4*)(params + o) = w;
+        if (HAS_S1) *(f4*)(s1 + o) = a;
         if (KIND == DYNB_OPT_ADAM) *(f4*)(s2 + o) = b;
         const vec4T q = {from_float<T>(w[0]), from_float<T>(w[1]), from_float<T>(w[2]), from_float<T>(w[3])};
         *(vec4T*)(Wn + (int64_t)gr * ldn + gc) = q;
-      } else {
-        for (int e = 0; e < 4 && gc + e < C; ++e) {
-          float ae = KIND != DYNB_OPT_SGD ? s1[o + e] : 0.f;
-          float be = KIND == DYNB_OPT_ADAM ? s2[o + e] : 0.f;
-          w[e] = step_one<KIND>(rule, params[o + e], gradient1<AGG>(src, o + e), ae, be);
-          params[o + e] = w[e];
-          if (KIND != DYNB_OPT_SGD) s1[o + e] = ae;
-          if (KIND == DYNB_OPT_ADAM) s2[o + e] = be;
-          Wn[(int64_t)gr * ldn + gc + e] = from_float<T>(w[e]);
-        }
       }
-    }
 #pragma unroll
-    for (int e = 0; e < 4; ++e) tile[r][cq + e] = w[e];
+      for (int e = 0; e < 4; ++e) tile[r][cq + e] = w[e];
+    }
   }
   __syncthreads();
   constexpr int GR = 64 / G;   // granules of rows per tile column
@@ -160,23 +220,7 @@ __global__ __launch_bounds__(256) void update_cast_kernel(float* __restrict__ pa
   }
 }
 
-// ---- element-wise step of params[off, off + n) (biases, convolution weights) ---------------
-template <int KIND, bool AGG>
-__global__ __launch_bounds__(256) void update_range_kernel(float* __restrict__ params, int64_t off,
-                                                           GradSource src, UpdateRule rule,
-                                                           float* __restrict__ s1,
-                                                           float* __restrict__ s2, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
-    const int64_t o = off + i;
-    float a = KIND != DYNB_OPT_SGD ? s1[o] : 0.f;
-    float b = KIND == DYNB_OPT_ADAM ? s2[o] : 0.f;
-    params[o] = step_one<KIND>(rule, params[o], gradient1<AGG>(src, o), a, b);
-    if (KIND != DYNB_OPT_SGD) s1[o] = a;
-    if (KIND == DYNB_OPT_ADAM) s2[o] = b;
-  }
-}
-
-// the same over a list of ranges (blockIdx.y = range)
+// ---- element-wise step over a list of ranges (blockIdx.y = range) ---------------------------
 template <int KIND, bool AGG>
 __global__ __launch_bounds__(256) void update_ranges_kernel(float* __restrict__ params, Ranges r,
                                                             GradSource src, UpdateRule rule,
@@ -268,15 +312,21 @@ void launch_update_cast_d(float* params, const CastMats& mats, const Ranges& sma
   }
 }
 
-template <int KIND>
-void launch_update_range_k(float* params, int64_t off, const GradSource& src, const UpdateRule& rule,
-                           float* s1, float* s2, int64_t n, unsigned bx, hipStream_t st) {
-  if (src.lam.K > 0)
-    hipLaunchKernelGGL((update_range_kernel<KIND, true>), dim3(bx), dim3(256), 0, st, params, off, src,
-                       rule, s1, s2, n);
-  else
-    hipLaunchKernelGGL((update_range_kernel<KIND, false>), dim3(bx), dim3(256), 0, st, params, off, src,
-                       rule, s1, s2, n);
+// Fills first_block and counts the parameters of `mats`.
+int count_blocks(CastMats& mats, int tile_columns, double& params_counted) {
+  if (mats.n < 0 || mats.n > MAX_CAST_MATS) return fail(DYNB_ERR_BADARG, "update_cast: too many tensors for one launch");
+  int64_t blocks = 0;
+  params_counted = 0.0;
+  for (int i = 0; i < mats.n; ++i) {
+    if (mats.R[i] <= 0 || mats.C[i] <= 0) return fail(DYNB_ERR_BADARG, "update_cast: empty matrix");
+    mats.first_block[i] = (int)blocks;
+    blocks += (int64_t)((mats.C[i] + tile_columns - 1) / tile_columns) * ((mats.R[i] + 63) / 64) * mats.taps[i];
+    if (blocks >= ((int64_t)1 << 31) - 256)
+      return fail(DYNB_ERR_UNSUPPORTED, "update_cast: too many tiles for one launch");
+    params_counted += (double)mats.R[i] * mats.C[i] * mats.taps[i];
+  }
+  for (int i = mats.n; i <= MAX_CAST_MATS; ++i) mats.first_block[i] = (int)blocks;
+  return DYNB_OK;
 }
 
 }  // namespace
@@ -284,28 +334,19 @@ void launch_update_range_k(float* params, int64_t off, const GradSource& src, co
 int launch_update_cast(int dtype, float* params, CastMats& mats, const Ranges& small,
                        const GradSource& src, const UpdateRule& rule, float* s1, float* s2,
                        void* stream) {
-  if (mats.n < 0 || mats.n > MAX_CAST_MATS || small.n < 0 || small.n > MAX_RANGES)
+  if (small.n < 0 || small.n > MAX_RANGES)
     return fail(DYNB_ERR_BADARG, "update_cast: too many tensors for one launch");
   const int es = dtype == DYNB_BF16 ? 2 : 4;
-  const int TC = cast_tile_columns(src.lam.K > 0);
   double cast_n = 0.0, small_n = 0.0;
-  int64_t blocks = 0, longest = 0;
-  for (int i = 0; i < mats.n; ++i) {
-    if (mats.R[i] <= 0 || mats.C[i] <= 0) return fail(DYNB_ERR_BADARG, "update_cast: empty matrix");
-    mats.first_block[i] = (int)blocks;
-    blocks += (int64_t)((mats.C[i] + TC - 1) / TC) * ((mats.R[i] + 63) / 64);
-    cast_n += (double)mats.R[i] * mats.C[i];
-  }
+  int64_t longest = 0;
+  if (int rc = count_blocks(mats, cast_tile_columns(src.lam.K > 0), cast_n)) return rc;
   for (int i = 0; i < small.n; ++i) {
     longest = small.len[i] > longest ? small.len[i] : longest;
     small_n += (double)small.len[i];
   }
   int64_t range_blocks = (longest + 255) / 256;
   if (range_blocks > 256) range_blocks = 256;
-  if (blocks + range_blocks >= ((int64_t)1 << 31))
-    return fail(DYNB_ERR_UNSUPPORTED, "update_cast: too many tiles for one launch");
-  if (blocks + range_blocks == 0) return DYNB_OK;
-  for (int i = mats.n; i <= MAX_CAST_MATS; ++i) mats.first_block[i] = (int)blocks;
+  if (mats.first_block[mats.n] + range_blocks == 0) return DYNB_OK;
   Timed t(KC_UPDATE, stream, flops_per_param(rule, src) * (cast_n + small_n),
           (bytes_per_param(rule, src) + 2 * es) * cast_n + bytes_per_param(rule, src) * small_n);
   if (dtype == DYNB_BF16)
@@ -315,23 +356,23 @@ int launch_update_cast(int dtype, float* params, CastMats& mats, const Ranges& s
   return ok("update_cast");
 }
 
-int launch_update_range(float* params, int64_t off, const GradSource& src, const UpdateRule& rule,
-                        float* s1, float* s2, int64_t n, void* stream) {
-  if (n <= 0) return DYNB_OK;
-  Timed t(KC_UPDATE, stream, flops_per_param(rule, src) * n, bytes_per_param(rule, src) * n);
-  int64_t bx = (n + 255) / 256;
-  if (bx > 2048) bx = 2048;
-  switch (rule.kind) {
-    case DYNB_OPT_SGD:
-      launch_update_range_k<DYNB_OPT_SGD>(params, off, src, rule, s1, s2, n, (unsigned)bx, (hipStream_t)stream);
-      break;
-    case DYNB_OPT_MOMENTUM:
-      launch_update_range_k<DYNB_OPT_MOMENTUM>(params, off, src, rule, s1, s2, n, (unsigned)bx, (hipStream_t)stream);
-      break;
-    default:
-      launch_update_range_k<DYNB_OPT_ADAM>(params, off, src, rule, s1, s2, n, (unsigned)bx, (hipStream_t)stream);
-  }
-  return ok("update_range");
+int launch_weight_casts(int dtype, const float* params, CastMats& mats, void* stream) {
+  const int es = dtype == DYNB_BF16 ? 2 : 4;
+  double n = 0.0;
+  if (int rc = count_blocks(mats, cast_tile_columns(false), n)) return rc;
+  if (n == 0.0) return DYNB_OK;
+  Timed t(KC_WEIGHT_CAST, stream, 0, n * (4 + 2 * es));
+  Ranges none;
+  none.n = 0;
+  const GradSource src = {};
+  const UpdateRule rule = {};
+  if (dtype == DYNB_BF16)
+    launch_update_cast_t<bf16, COPY_ONLY, false>(const_cast<float*>(params), mats, none, 0, src, rule, nullptr,
+                                                 nullptr, (hipStream_t)stream);
+  else
+    launch_update_cast_t<float, COPY_ONLY, false>(const_cast<float*>(params), mats, none, 0, src, rule, nullptr,
+                                                  nullptr, (hipStream_t)stream);
+  return ok("weight_casts");
 }
 
 void set_adam(UpdateRule& r, double beta1, double beta2, float eps, int64_t t) {

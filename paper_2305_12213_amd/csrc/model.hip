@@ -168,6 +168,25 @@ int build_segs(const int32_t* b, int K, int hw, Segs& s) {
   return DYNB_OK;
 }
 
+// The weights of layer L and where their copies go.  Convolution: W [3][3][c_in][c_out]; the forward
+// operand Wt [c_out][kf] holds tap t's input channels from column t * cin_p on, the input-gradient
+// operand Wn [c_in][kd] its output channels from t * cout_p on.  Padding columns are never written
+// (zero since the workspace was cleared).
+void add_mat(CastMats& mats, const Layer& L) {
+  const bool conv = L.kind == DYNB_LAYER_CONV3X3;
+  const int i = mats.n++;
+  mats.off[i] = L.w_off;
+  mats.R[i] = L.n_in;
+  mats.C[i] = L.n_out;
+  mats.taps[i] = conv ? 9 : 1;
+  mats.Wn[i] = L.Wn;
+  mats.ldn[i] = conv ? L.kd : L.ld_out;
+  mats.tap_n[i] = conv ? L.cout_p : 0;
+  mats.Wt[i] = L.Wt;
+  mats.ldt[i] = conv ? L.kf : L.ld_in;
+  mats.tap_t[i] = conv ? L.cin_p : 0;
+}
+
 int bad_model(dynb_model* m, int code, const char* msg, int layer) {
   delete m;
   return fail(code, "model_create: layer %d: %s", layer, msg);
@@ -311,18 +330,17 @@ extern "C" size_t dynb_model_workspace_bytes(const dynb_model* m, int32_t max_ba
 extern "C" int dynb_model_sync_weights(dynb_model* m, void* stream) {
   if (!m) return fail(DYNB_ERR_BADARG, "sync_weights: null model");
   if (!m->bound) return fail(DYNB_ERR_STATE, "sync_weights: model not bound");
-  for (Layer& L : m->layers) {
+  CastMats mats;
+  mats.n = 0;
+  for (const Layer& L : m->layers) {
     if (!L.has_params) continue;
-    int rc;
-    if (L.kind == DYNB_LAYER_DENSE)
-      rc = launch_weight_cast(m->dtype, m->params + L.w_off, L.n_in, L.n_out, L.Wn, L.ld_out, L.Wt,
-                              L.ld_in, stream);
-    else
-      rc = launch_conv_weight_cast(m->params + L.w_off, L.n_in, L.n_out, L.cin_p, L.cout_p, L.Wt,
-                                   L.kf, L.Wn, L.kd, stream);
-    if (rc) return rc;
+    add_mat(mats, L);
+    if (mats.n == MAX_CAST_MATS) {
+      if (int rc = launch_weight_casts(m->dtype, m->params, mats, stream)) return rc;
+      mats.n = 0;
+    }
   }
-  return DYNB_OK;
+  return mats.n ? launch_weight_casts(m->dtype, m->params, mats, stream) : DYNB_OK;
 }
 
 extern "C" int dynb_model_bind(dynb_model* m, float* params, void* ws, size_t ws_bytes,
@@ -824,18 +842,16 @@ int make_rule(const dynb_optimizer* opt, const float* s1, const float* s2, Updat
   return DYNB_OK;
 }
 
-// One step over all layers.  Dense weight matrices: the step and both 16-bit copies in one
-// pass, MAX_CAST_MATS matrices per launch; the first such launch also steps the small tensors
-// (biases, convolution weights, normalisation parameters), whose 16-bit layouts follow.
+// One step over all layers: every weight tensor's step and both 16-bit copies in one pass,
+// MAX_CAST_MATS tensors per launch; the first launch also steps the small tensors (biases,
+// normalisation parameters).
 int update_layers(dynb_model* m, const GradSource& src, const UpdateRule& rule, float* s1,
                   float* s2, void* stream) {
   Ranges r;
   r.n = 0;
   CastMats mats;
   mats.n = 0;
-  bool any_dense = false;
-  for (Layer& L : m->layers) any_dense = any_dense || (L.has_params && L.kind == DYNB_LAYER_DENSE);
-  // without a dense layer, or with more small tensors than one launch takes: element-wise launches
+  // more small tensors than one launch takes: element-wise launches
   auto flush_small = [&]() {
     const int rc = r.n ? launch_update_ranges(m->params, r, src, rule, s1, s2, stream) : DYNB_OK;
     r.n = 0;
@@ -851,17 +867,11 @@ int update_layers(dynb_model* m, const GradSource& src, const UpdateRule& rule, 
     return (int)DYNB_OK;
   };
   for (Layer& L : m->layers) {
-    if (L.kind == DYNB_LAYER_BN) {
-      if (int rc = add(L.w_off, 2 * (int64_t)L.n_out)) return rc;
-      continue;
-    }
-    if (!L.has_params) continue;
-    int rc = add(L.b_off, L.n_out);
-    if (!rc && L.kind != DYNB_LAYER_DENSE) rc = add(L.w_off, (int64_t)9 * L.n_in * L.n_out);
+    int rc = DYNB_OK;
+    if (L.kind == DYNB_LAYER_BN) rc = add(L.w_off, 2 * (int64_t)L.n_out);
+    else if (L.has_params) rc = add(L.b_off, L.n_out);
     if (rc) return rc;
   }
-  if (!any_dense)
-    if (int rc = flush_small()) return rc;
   auto flush_mats = [&]() {
     const int rc = launch_update_cast(m->dtype, m->params, mats, r, src, rule, s1, s2, stream);
     mats.n = 0;
@@ -871,28 +881,13 @@ int update_layers(dynb_model* m, const GradSource& src, const UpdateRule& rule, 
   // (last layer first: the first layer's copies are then the most recently written when the next
   // step's forward pass starts with them -- measured 1.5 % of a step on the wide MLP)
   for (size_t li = m->layers.size(); li-- > 0;) {
-    Layer& L = m->layers[li];
-    if (!L.has_params || L.kind != DYNB_LAYER_DENSE) continue;
-    const int i = mats.n++;
-    mats.off[i] = L.w_off;
-    mats.R[i] = L.n_in;
-    mats.C[i] = L.n_out;
-    mats.Wn[i] = L.Wn;
-    mats.ldn[i] = L.ld_out;
-    mats.Wt[i] = L.Wt;
-    mats.ldt[i] = L.ld_in;
+    const Layer& L = m->layers[li];
+    if (!L.has_params) continue;
+    add_mat(mats, L);
     if (mats.n == MAX_CAST_MATS)
       if (int rc = flush_mats()) return rc;
   }
-  if (mats.n)
-    if (int rc = flush_mats()) return rc;
-  for (Layer& L : m->layers) {
-    if (!L.has_params || L.kind == DYNB_LAYER_DENSE) continue;
-    if (int rc = launch_conv_weight_cast(m->params + L.w_off, L.n_in, L.n_out, L.cin_p, L.cout_p, L.Wt,
-                                         L.kf, L.Wn, L.kd, stream))
-      return rc;
-  }
-  return DYNB_OK;
+  return mats.n ? flush_mats() : DYNB_OK;
 }
 
 }  // namespace
