@@ -368,6 +368,206 @@ __global__ __launch_bounds__(256) void conv_wgrad_rows_kernel(ConvWgradArgs p, S
   }
 }
 
+// The same for stride 1 and images at least 8 pixels wide: the pixels of all images are one flat run,
+// and the three horizontal taps of a kernel row read neighbouring pixels of it, so a stage holds PX
+// consecutive output pixels, the three runs of input pixels one image row apart around them (with a
+// pixel more on both sides, used through a pixel offset), and nothing is staged per tap.  Rows above
+// and below an image are replaced by zeros while they are copied; a run also crosses image borders
+// sideways, where the pixel at x = 0 (x = W - 1) must not see the left (right) neighbour: these
+// pixels of dy are masked to zero for those taps, in registers.
+// CI / CO = 32-channel blocks of the input / output side (1 or 2: up to 32 or 64 channels): with
+// narrow sides the four waves divide the ten results of a tile -- nine taps and the column sums --
+// between them instead of padding the channels to 64.
+// A chunk is four to eight stages long, so what bounds a launch is not a rate but the way in and
+// out; the code is kept short for that reason too (a wave that runs through code for the first
+// time fetches it at about 2 KB per microsecond: with the taps unrolled in every wave, a copy plan
+// per copy and the waves' sums combined through LDS, 13 KB, the first figure below was 22).
+// 167 x 28 x 28 pixels: 24 -> 24 channels 42 -> FLATA us, 1 -> 24 43 -> FLATB; 512 x 32 x 32: 3 -> 64
+// 48 -> FLATC us.
+template <int CI, int CO>
+struct Flat {
+  static constexpr int KS = 4 / (CI * CO);            // waves that share a 32 x 32 channel tile
+  static constexpr int ITEMS = (SLOTS + KS - 1) / KS; // results per wave: slots ks, ks + KS, ...
+  static constexpr int PX = CI == 2 ? 32 : 64;        // output pixels per stage
+  static constexpr int GROUP = 16 / CI;               // pixels per 1 KB copy of an input run, five per run
+  static constexpr int IN_ROW = 64 * CI, DY_ROW = 64 * CO;           // bytes per pixel
+  static constexpr int IN_TILE = 5 * 1024, DY_COPIES = PX * DY_ROW / 1024;
+  static constexpr int STAGE = 3 * IN_TILE + DY_COPIES * 1024;
+  static constexpr int RING = 3;                      // stage buffers
+  static_assert(IN_TILE >= (PX + 2) * IN_ROW && DY_COPIES <= 8, "copy plan");
+};
+
+// Wait until at most n (uniform, <= 6) of this wave's copies are pending.
+__device__ inline void wait_at_most(int n) {
+  switch (n) {
+    case 0: asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); break;
+    case 1: asm volatile("s_waitcnt vmcnt(1)" ::: "memory"); break;
+    case 5: asm volatile("s_waitcnt vmcnt(5)" ::: "memory"); break;
+    case 6: asm volatile("s_waitcnt vmcnt(6)" ::: "memory"); break;
+    default: asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); break;   // (always safe)
+  }
+}
+
+// Fragment with pixel j (0..7) cleared; j outside: as it is.
+__device__ inline bf16x8 without_pixel(const bf16x8& v, int j) {
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  u32x4 w = __builtin_bit_cast(u32x4, v);
+  const uint32_t keep = (j & 1) ? 0x0000ffffu : 0xffff0000u;
+#pragma unroll
+  for (int d = 0; d < 4; ++d) w[d] &= (j >> 1) == d ? keep : 0xffffffffu;
+  return __builtin_bit_cast(bf16x8, w);
+}
+
+template <int CI, int CO>
+__global__ __launch_bounds__(256, 2) void conv_wgrad_flat_kernel(ConvWgradArgs p, Segs segs, RowChunks ch) {
+  using F = Flat<CI, CO>;
+  __shared__ uint4 ring[F::RING * F::STAGE / 16];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int chunk = blockIdx.x, cib = blockIdx.y, cob = blockIdx.z;
+  int k, r0, n;
+  chunk_span(segs, ch, chunk, k, r0, n);
+  const int T = (n + F::PX - 1) / F::PX;              // stages
+  const int total = segs.off[segs.K];                 // pixels of the batch
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)&ring[0];
+
+  // ---- global -> LDS.  Copy (group q, kh): slots GROUP q .. of input run kh (slot t of a run belongs
+  // to output pixel t - 1 of the stage and holds the pixel kh - 1 image rows on).  Waves 0 and 1 copy
+  // two groups of the three runs each, wave 2 the fifth group and three of the dy copies, wave 3 the
+  // rest of dy.  A lane moves 16 bytes of one pixel.  With 128-byte pixels the two 64-byte halves of
+  // pixels 2, 3, 6, 7, ... are swapped (see the kernel above); 64-byte pixels need no swizzle (four
+  // neighbouring ones are 256 contiguous bytes).
+  const int groups = wave < 2 ? 2 : wave == 2 ? 1 : 0;
+  const int dy0 = wave == 3 ? 3 : 0;
+  const int dys = wave < 2 ? 0 : wave == 2 ? (F::DY_COPIES < 3 ? F::DY_COPIES : 3)
+                                           : (F::DY_COPIES > 3 ? F::DY_COPIES - 3 : 0);
+  const int slot0 = 2 * wave * F::GROUP + lane / (4 * CI);       // of this wave's first group
+  int pix = r0 + slot0 - 1;                                      // its output pixel (the next group's: + GROUP)
+  int x[2], y[2];
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int at = pix + q * F::GROUP < 0 ? 0 : pix + q * F::GROUP;
+    const int row = at / p.W;
+    x[q] = at - row * p.W;
+    y[q] = row % p.H;
+  }
+  auto granule = [&](int slot, int wide) {
+    const int g = lane % (4 * wide);
+    return wide == 2 ? g ^ (((slot >> 1) & 1) << 2) : g;         // (slots 8 apart: the same)
+  };
+  const char* in = (const char*)(p.in + (int64_t)pix * p.ldi + cib * 64 + granule(slot0, CI) * 8);
+  const int dslot = dy0 * (16 / CO) + lane / (4 * CO);
+  int dpix = r0 + dslot;
+  const char* dy = (const char*)(p.dy + (int64_t)dpix * p.ldd + cob * 64 + granule(dslot, CO) * 8);
+  const int64_t in_pix = (int64_t)p.ldi * 2, dy_pix = (int64_t)p.ldd * 2;
+  const int step_x = F::PX % p.W, step_y = (F::PX / p.W) % p.H;
+  auto issue = [&](uint32_t base) {                              // base: LDS address of the stage
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      if (q >= groups) break;
+      const int at = pix + q * F::GROUP;
+      const bool live = at >= 0 && at < total;
+#pragma unroll
+      for (int kh = 0; kh < 3; ++kh) {
+        const bool ok = live && (kh != 0 || y[q] > 0) && (kh != 2 || y[q] < p.H - 1);
+        const char* src = in + (q * F::GROUP + (kh - 1) * p.W) * in_pix;
+        async_copy_1k(ok ? (const void*)src : p.zeros,
+                      base + (uint32_t)(kh * F::IN_TILE + (2 * wave + q) * 1024));
+      }
+      // (the pixel in front of the first is -1: its place was that of pixel 0)
+      x[q] += step_x - (at < 0 ? 1 : 0);
+      y[q] += step_y;
+      if (x[q] < 0) { x[q] += p.W; --y[q]; }
+      if (x[q] >= p.W) { x[q] -= p.W; ++y[q]; }
+      if (y[q] < 0) y[q] += p.H;
+      if (y[q] >= p.H) y[q] -= p.H;
+    }
+    pix += F::PX;
+    in += F::PX * in_pix;
+#pragma unroll
+    for (int d = 0; d < 5; ++d) {
+      if (d >= dys) break;
+      const bool ok = dpix + d * (16 / CO) < r0 + n;
+      async_copy_1k(ok ? (const void*)(dy + d * (16 / CO) * dy_pix) : p.zeros,
+                    base + (uint32_t)(3 * F::IN_TILE + (dy0 + d) * 1024));
+    }
+    dpix += F::PX;
+    dy += F::PX * dy_pix;
+  };
+  const int copies = 3 * groups + dys;
+
+  // ---- LDS -> MFMA operands (lane layout as in the kernel above)
+  const int tile = wave % (CI * CO), wci = tile % CI, wco = tile / CI, ks = wave / (CI * CO);
+  const int g = lane >> 4, r = lane & 15;
+  auto offset = [&](int hx, int half, int wide) {     // byte offset of this lane's 4 channels of slot hx
+    const int w = wide == 2 ? half ^ ((hx >> 1) & 1) : 0;
+    return (uint32_t)(hx * 64 * wide + w * 64 + (16 * (g & 1) + 4 * (r & 3)) * 2);
+  };
+  const int fpix = 8 * (g >> 1) + (r >> 2);
+  const uint32_t foff_b = 3 * F::IN_TILE + offset(fpix, wco, CO);
+  uint32_t foff_a[F::ITEMS];                          // item i: slot ks + KS i; tap < 9, else column sums
+#pragma unroll
+  for (int i = 0; i < F::ITEMS; ++i) {
+    const int tap = ks + F::KS * i < 9 ? ks + F::KS * i : 0;     // (column sums: fetched, not used)
+    foff_a[i] = (tap / 3) * F::IN_TILE + offset(fpix + tap % 3, wci, CI);
+  }
+  auto frag = [&](uint32_t a, int row_bytes) {        // pixels 4 apart: same swizzle
+    const s16x4 lo = read_tr(a), hi = read_tr(a + 4 * row_bytes);
+    const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    return __builtin_bit_cast(bf16x8, v);
+  };
+  const s16x8 ones_bits = {0x3f80, 0x3f80, 0x3f80, 0x3f80, 0x3f80, 0x3f80, 0x3f80, 0x3f80};
+  const bf16x8 ones = __builtin_bit_cast(bf16x8, ones_bits);
+
+  f32x16 acc[F::ITEMS];
+#pragma unroll
+  for (int i = 0; i < F::ITEMS; ++i)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[i][v] = 0.f;
+  int lx = (r0 + 8 * (lane >> 5)) % p.W;              // x of this lane's first pixel of a 16-pixel step
+  const int lx_step = 16 % p.W;
+
+#pragma unroll 1
+  for (int t = 0; t < 2 && t < T; ++t) issue(lds0 + (uint32_t)(t * F::STAGE));
+  uint32_t buf = lds0, nbuf = lds0 + 2 * F::STAGE;    // buffers of stages t and t + 2
+  for (int t = 0; t < T; ++t) {
+    wait_at_most(t + 1 < T ? copies : 0);             // stage t of this wave has landed
+    __syncthreads();                                  // ... of all waves; stage t-1 is no longer read
+    if (t + 2 < T) issue(nbuf);
+#pragma unroll
+    for (int step = 0; step < F::PX / 16; ++step) {
+      const bf16x8 b = frag(buf + step * 16 * F::DY_ROW + foff_b, F::DY_ROW);
+      // the pixels of these eight at x = 0 and x = W - 1 (none: 8 or more)
+      const int j0 = lx == 0 ? 0 : p.W - lx, j1 = p.W - 1 - lx;
+      bf16x8 a[F::ITEMS];
+#pragma unroll
+      for (int i = 0; i < F::ITEMS; ++i) a[i] = frag(buf + step * 16 * F::IN_ROW + foff_a[i], F::IN_ROW);
+#pragma unroll
+      for (int i = 0; i < F::ITEMS; ++i) {
+        const int tap = ks + F::KS * i, kw = tap % 3;
+        if (tap >= 9) a[i] = ones;
+        const bf16x8 bm = tap < 9 && kw != 1 ? without_pixel(b, kw == 0 ? j0 : j1) : b;
+        acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bm, a[i], acc[i], 0, 0, 0);
+      }
+      lx += lx_step;
+      if (lx >= p.W) lx -= p.W;
+    }
+    buf = buf == lds0 + 2 * F::STAGE ? lds0 : buf + F::STAGE;
+    nbuf = nbuf == lds0 + 2 * F::STAGE ? lds0 : nbuf + F::STAGE;
+  }
+
+  float* out = p.partial + ((int64_t)(chunk * gridDim.y + cib) * gridDim.z + cob) * (CI * CO * SLOTS * 1024);
+#pragma unroll
+  for (int i = 0; i < F::ITEMS; ++i) {
+    const int slot = ks + F::KS * i;
+    if (slot >= SLOTS || (slot == 9 && (cib != 0 || wci != 0))) continue;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const f32x4 o = {acc[i][4 * q], acc[i][4 * q + 1], acc[i][4 * q + 2], acc[i][4 * q + 3]};
+      *(f32x4*)&out[(((tile * SLOTS + slot) * 4 + q) * 64 + lane) * 4] = o;
+    }
+  }
+}
+
 // dW_k[tap][ci][co .. co+3] = the chunk results of worker k added in a fixed order; the items
 // behind the weights are the bias gradients db_k[co .. co+3] (slot 9, input channel 0).
 // 256 threads = 32 items x 8 chunk-lanes: lane q adds chunks q, q+8, ... (four independent
@@ -376,7 +576,7 @@ __global__ __launch_bounds__(256) void conv_wgrad_rows_kernel(ConvWgradArgs p, S
 // result.  Accumulator element v of lane l belongs to output channel 8*(v/4) + 4*(l/32) + v%4
 // and input channel l%32 of the wave's corner.
 __global__ __launch_bounds__(256) void conv_wgrad_reduce_kernel(const float* __restrict__ partial,
-                                                                int Cin, int Cout, int cibs, int cobs,
+                                                                int Cin, int Cout, int ci32, int co32,
                                                                 float* __restrict__ dW,
                                                                 float* __restrict__ db,
                                                                 int64_t group_stride, RowChunks ch) {
@@ -394,13 +594,15 @@ __global__ __launch_bounds__(256) void conv_wgrad_reduce_kernel(const float* __r
   const int quad = bias ? (int)(idx - n_weight) : (int)(tq % quads);
   const int slot = bias ? 9 : (int)(tq / quads);
   const int co = quad * 4;
-  const int cib = ci >> 6, cob = co >> 6, cil = ci & 63, col = co & 63;
-  const int wave = (cil >> 5) + 2 * (col >> 5);
+  // (a chunk result: blocks of ci32 x co32 tiles of 32 x 32 channels)
+  const int cibs = (Cin + 32 * ci32 - 1) / (32 * ci32), cobs = (Cout + 32 * co32 - 1) / (32 * co32);
+  const int cib = ci / (32 * ci32), cob = co / (32 * co32), cil = ci % (32 * ci32), col = co % (32 * co32);
+  const int wave = (cil >> 5) + ci32 * (col >> 5);
   const int c32 = col & 31;
   const int lane = (cil & 31) + 32 * ((c32 & 7) >> 2);
   const int64_t within = ((int64_t)((wave * SLOTS + slot) * 4 + (c32 >> 3)) * 64 + lane) * 4;
-  const int64_t stride = (int64_t)cibs * cobs * TILE_FLOATS;
-  const float* src = partial + ((int64_t)cib * cobs + cob) * TILE_FLOATS + within;
+  const int64_t tile_floats = (int64_t)ci32 * co32 * SLOTS * 1024, stride = cibs * cobs * tile_floats;
+  const float* src = partial + ((int64_t)cib * cobs + cob) * tile_floats + within;
   const int last = ch.first[k + 1];
   f32x4 a0 = {0.f, 0.f, 0.f, 0.f}, a1 = a0, a2 = a0, a3 = a0;
   int c = ch.first[k] + q;
@@ -481,23 +683,36 @@ int launch_conv_wgrad(const void* in, int64_t ldi, int Cin, int H, int W, const 
   const int nch = ch.first[s.K];
   if ((int64_t)nch * cibs * cobs * TILE_FLOATS > scratch_floats)
     return fail(DYNB_ERR_BADARG, "conv_wgrad: scratch area too small");
+  // Stride 1 on images at least 8 wide (a fragment's eight pixels then hold one border pixel of each
+  // kind at most): the flat kernel, whose blocks are only as wide as the channels need.  Whole rows
+  // of 32-pixel-wide images with a 64-channel side need neither its masks nor its bookkeeping (3 -> 64
+  // channels on 512 x 32 x 32 pixels: 48 us by rows, 57 flat).
+  bool by_rows = stride == 1 && W == 32 && Wo == 32 && H == Ho && (Cin > 32 || Cout > 32);
+  for (int k = 0; k <= s.K && by_rows; ++k) by_rows = s.off[k] % 32 == 0;
+  const bool flat = stride == 1 && W >= 8 && H == Ho && W == Wo && !by_rows;
+  const int ci32 = flat && Cin <= 32 ? 1 : 2, co32 = flat && Cout <= 32 ? 1 : 2;
   Timed t(KC_GEMM_WGRAD, stream, flops, bytes);
   if (nch > 0) {
     ConvWgradArgs a = {(const bf16*)in, (int)ldi, (const bf16*)dy, (int)ldd, H, W, Ho, Wo, stride,
                        scratch, zeros};
-    // whole image rows per chunk and per worker: the row-staged kernel applies
-    bool by_rows = stride == 1 && W == 32 && Wo == 32 && H == Ho && chunk_rows % 32 == 0;
-    for (int k = 0; k <= s.K && by_rows; ++k) by_rows = s.off[k] % 32 == 0;
+    const dim3 grid(nch, cibs, cobs), block(256);
+    const hipStream_t st = (hipStream_t)stream;
     if (by_rows)
-      hipLaunchKernelGGL(conv_wgrad_rows_kernel, dim3(nch, cibs, cobs), dim3(256), 0,
-                         (hipStream_t)stream, a, s, ch);
+      hipLaunchKernelGGL(conv_wgrad_rows_kernel, grid, block, 0, st, a, s, ch);
+    else if (!flat)
+      hipLaunchKernelGGL(conv_wgrad_chunk_kernel, grid, block, 0, st, a, s, ch);
+    else if (ci32 == 1 && co32 == 1)
+      hipLaunchKernelGGL((conv_wgrad_flat_kernel<1, 1>), grid, block, 0, st, a, s, ch);
+    else if (ci32 == 1)
+      hipLaunchKernelGGL((conv_wgrad_flat_kernel<1, 2>), grid, block, 0, st, a, s, ch);
+    else if (co32 == 1)
+      hipLaunchKernelGGL((conv_wgrad_flat_kernel<2, 1>), grid, block, 0, st, a, s, ch);
     else
-      hipLaunchKernelGGL(conv_wgrad_chunk_kernel, dim3(nch, cibs, cobs), dim3(256), 0,
-                         (hipStream_t)stream, a, s, ch);
+      hipLaunchKernelGGL((conv_wgrad_flat_kernel<2, 2>), grid, block, 0, st, a, s, ch);
   }
   const int64_t items = (int64_t)(9 * Cin + 1) * ((Cout + 3) / 4);
   hipLaunchKernelGGL(conv_wgrad_reduce_kernel, dim3((unsigned)((items + 31) / 32), s.K), dim3(256), 0,
-                     (hipStream_t)stream, scratch, Cin, Cout, cibs, cobs, dW, db, group_stride, ch);
+                     (hipStream_t)stream, scratch, Cin, Cout, ci32, co32, dW, db, group_stride, ch);
   return hipGetLastError() == hipSuccess ? DYNB_OK : fail(DYNB_ERR_HIP, "conv_wgrad: launch failed");
 }
 

@@ -508,3 +508,42 @@ def test_bf16_rounding_points_through_two_relu_layers():
     for k in range(len(b)):
         e = worst_pair_relerr(got[k], ref[k])
         assert e < tol, (seed, k, e)
+
+
+@pytest.mark.parametrize("image,channels", [
+    ((9, 8, 3), (20, 32)),        # the narrowest images of the flat weight gradient; one-block sides
+    ((5, 11, 1), (33, 8)),        # 32-channel blocks on one side only; rows that divide no stage
+    ((11, 40, 3), (64, 40)),      # two blocks on both sides, images wider than a 32-pixel stage
+    ((3, 71, 2), (8, 72)),        # ... than a 64-pixel one; a second 64-channel block
+    ((6, 7, 3), (12, 40)),        # too narrow: the per-tap kernel
+])
+def test_flat_conv_weight_gradients(image, channels):
+    # runs of pixels that cross image rows, images and workers; workers that end inside a stage,
+    # an idle one, several row chunks per worker
+    c1, c2 = channels
+    spec = {"dtype": "bf16", "input": image, "classes": 4,
+            "layers": [synth.conv3x3(image[2], c1, 1), synth.conv3x3(c1, c2, 1), synth.gap(),
+                       synth.dense(c2, 4, relu=False)]}
+    params = synth.init_params(spec, "he", 71)
+    b = [1, 0, 7, 2]
+    x, y = synth.make_batch(spec, "normal", sum(b), 72, 0)
+    check_worker_gradients(spec, params, x, y, b, label="flat %s %s" % (image, channels))
+
+
+@pytest.mark.parametrize("image,channels,stride", [
+    ((5, 3, 1), 7, 1),            # fewer pixels than a wave's 64; narrower than a stage
+    ((9, 13, 2), 64, 2),          # strided, two channels, one whole channel block
+    ((16, 21, 3), 72, 1),         # a second, ragged channel block; several row chunks
+    ((8, 8, 4), 16, 1),           # four channels: the general kernels
+])
+def test_stem_convolution(image, channels, stride):
+    # the first convolution on the caller's pixels: ragged pixel counts, borders, idle worker
+    spec = {"dtype": "bf16", "input": image, "classes": 3,
+            "layers": [synth.conv3x3(image[2], channels, stride), synth.gap(),
+                       synth.dense(channels, 3, relu=False)]}
+    params = synth.init_params(spec, "he", 81)
+    rng = np.random.default_rng(4)
+    params = [(W, (rng.standard_normal(bb.shape) * 0.1).astype(np.float32)) for W, bb in params]
+    b = [3, 0, 1, 6]
+    x, y = synth.make_batch(spec, "normal", sum(b), 82, 0)
+    check_worker_gradients(spec, params, x, y, b, label="stem %s %d" % (image, channels))
