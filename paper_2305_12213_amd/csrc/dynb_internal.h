@@ -243,6 +243,16 @@ int launch_conv_wgrad(const void* in, int64_t ldi, int Cin, int H, int W, const 
                       int64_t scratch_floats, float* dW, float* db, int64_t group_stride,
                       const Segs& s, double flops, double bytes, void* stream);
 
+// The first convolution of a model, on images of at most three channels (conv_stem.hip): forward and
+// weight gradient straight from the caller's fp32 pixels [images * H * W][Cin].
+bool conv_stem_applies(int Cin);
+int launch_stem_forward(const float* x, int Cin, int H, int W, int Ho, int Wo, int stride, int64_t pixels,
+                        const void* w, int kf, const float* bias, int N, int relu, void* out,
+                        int64_t ldo, double flops, double bytes, void* stream);
+int launch_stem_wgrad(const float* x, int Cin, int H, int W, int Ho, int Wo, int stride, const void* dy,
+                      int64_t ldd, int Cout, int chunk_rows, float* scratch, int64_t scratch_floats, float* dW,
+                      float* db, int64_t group_stride, const Segs& s, double flops, double bytes, void* stream);
+
 // Batch normalisation over each worker's own rows (bf16; x: T [rows][ldx], y: T [rows][ldy]):
 // writes mean / rstd [k][C] (kept for the backward pass).  `scratch`: row_scratch_floats() floats
 // (the partial results of the row chunks), shared by forward and backward.

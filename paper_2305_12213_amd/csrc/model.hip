@@ -425,6 +425,8 @@ int run_forward_backward(dynb_model* m, const float* x, const int32_t* y, const 
   }
   // (an fp32 batch whose rows already have the padded pitch is read where it is)
   const bool x_as_is = dt == DYNB_F32 && m->in_c == m->ld0 && m->in_h * m->in_w == 1 && !((uintptr_t)x & 15);
+  // (a first convolution of at most three channels reads the fp32 pixels itself)
+  const bool stem = m->layers[0].kind == DYNB_LAYER_CONV3X3 && conv_stem_applies(m->layers[0].n_in);
   const void* const act0 = x_as_is ? (const void*)x : m->act0;
   auto in_act = [&](size_t l) -> const void* { return l == 0 ? act0 : m->layers[l - 1].out; };
 
@@ -473,13 +475,17 @@ int run_forward_backward(dynb_model* m, const float* x, const int32_t* y, const 
     }
     if (!L.has_params) return (int)DYNB_OK;
     if (L.kind == DYNB_LAYER_CONV3X3) {
-      rc = launch_conv_wgrad(in_act(l), L.ld_in, L.n_in, L.h_in, L.w_in, dyv[l], L.ld_out, L.n_out,
-                             L.h_out, L.w_out, L.stride, L.conv_chunk, m->partial, m->partial_floats,
-                             grads + L.w_off, grads + L.b_off, m->P_pad, segs[l],
-                             2.0 * B * L.hw_out * L.wg_rows * L.n_out,
-                             (double)K * L.wg_rows * L.n_out * 4 +
-                                 (double)B * (L.hw_in * L.n_in + L.hw_out * L.n_out) * es,
-                             stream);
+      const double flops = 2.0 * B * L.hw_out * L.wg_rows * L.n_out;
+      const double bytes = (double)K * L.wg_rows * L.n_out * 4 +
+                           (double)B * (L.hw_in * L.n_in + L.hw_out * L.n_out) * es;
+      if (l == 0 && stem)
+        rc = launch_stem_wgrad(x, L.n_in, L.h_in, L.w_in, L.h_out, L.w_out, L.stride, dyv[l], L.ld_out,
+                               L.n_out, L.conv_chunk, m->partial, m->partial_floats, grads + L.w_off,
+                               grads + L.b_off, m->P_pad, segs[l], flops, bytes, stream);
+      else
+        rc = launch_conv_wgrad(in_act(l), L.ld_in, L.n_in, L.h_in, L.w_in, dyv[l], L.ld_out, L.n_out,
+                               L.h_out, L.w_out, L.stride, L.conv_chunk, m->partial, m->partial_floats,
+                               grads + L.w_off, grads + L.b_off, m->P_pad, segs[l], flops, bytes, stream);
       if (rc) return rc;
       if (agg) {
         rc = add_small(L.w_off, (int64_t)L.wg_rows * L.n_out);
@@ -549,7 +555,7 @@ int run_forward_backward(dynb_model* m, const float* x, const int32_t* y, const 
   };
   if (B > 0) {
     // ---- forward ----
-    if (!x_as_is) {
+    if (!x_as_is && !stem) {
       rc = launch_pack_rows(dt, x, B * m->in_h * m->in_w, m->in_c, m->act0, m->ld0, stream);
       if (rc) return rc;
     }
@@ -600,6 +606,14 @@ int run_forward_backward(dynb_model* m, const float* x, const int32_t* y, const 
         g.alg_flops = 2.0 * rows_out * L.n_in * L.n_out;
         g.alg_bytes = ((double)rows_out * (L.n_in + L.n_out) + (double)L.n_in * L.n_out) * es;
       } else {
+        if (l == 0 && stem) {
+          rc = launch_stem_forward(x, L.n_in, L.h_in, L.w_in, L.h_out, L.w_out, L.stride, rows_out, L.Wt, L.kf,
+                                   g.bias, L.n_out, L.relu, L.out, L.ld_out,
+                                   2.0 * rows_out * 9 * L.n_in * L.n_out,
+                                   ((double)B * L.hw_in * L.n_in + (double)rows_out * L.n_out) * es, stream);
+          if (rc) return rc;
+          continue;
+        }
         g.A = in_act(l); g.lda = L.ld_in;
         g.B = L.Wt; g.ldb = L.kf;
         g.K = L.kf;
