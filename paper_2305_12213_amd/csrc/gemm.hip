@@ -84,11 +84,17 @@ struct PatchArea<0> {
 // owns rows [off[g], off[g+1])), and a stage holds 32 rows x BM (BN) features as they lie in
 // memory; MFMA operands are fetched with the LDS transpose read (see conv_wgrad.hip for its
 // lane layout).  No transposed copies of the activations are needed.
-template <int BM, int BN, int WM, int WN, int MODE, bool GATHER, int S, bool AGG = false>
+// PAR (gathered input gradient of a stride-2 convolution): an input pixel (y, x) receives taps of one
+// parity per direction only -- one row tap for even y, two for odd y -- so the pixels of each of the
+// four parity classes (blockIdx.y) form a product of their own, with 1, 2, 2 or 4 of the 9 taps.  Nine
+// taps of which five to eight read zeros cost 51 and 111 us on the 8 x 8 <- 16 x 16 and 16 x 16 <- 32 x
+// 32 layers of the 32-64-128 model at 512 images; by classes PARA and PARB.
+template <int BM, int BN, int WM, int WN, int MODE, bool GATHER, int S, bool AGG = false, bool PAR = false>
 __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmArgs p, Segs segs) {
   constexpr bool RM = MODE == MODE_WGRAD;
   constexpr bool WEAVE = !GATHER;   // copies placed between the MFMAs (see the stage pipeline)
   static_assert(!AGG || MODE == MODE_WGRAD, "aggregation belongs to the weight gradient");
+  static_assert(!PAR || (GATHER && MODE == MODE_DGRAD), "parity classes belong to the gathered input gradient");
   static_assert(!RM || (!GATHER && (BM == 256 || BM == 128) && (BN == 256 || BN == 128)),
                 "weight gradient: plain operands, 128 or 256 features per tile side");
   constexpr int NW = WM * WN;
@@ -115,8 +121,20 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmArgs p, Seg
   const int g_hi = MODE == MODE_WGRAD
                        ? (g_lo + p.groups_per_block < n_groups ? g_lo + p.groups_per_block : n_groups)
                        : 1;
+  // rows and reduction length of this launch, or of the parity class: pixels (2 yy + py, 2 xx + px)
+  const int py = PAR ? blockIdx.y >> 1 : 0, px = PAR ? blockIdx.y & 1 : 0;
+  const int hc = PAR ? (p.row_h - py + 1) >> 1 : 0, wc = PAR ? (p.row_w - px + 1) >> 1 : 0;
+  const int M = PAR ? p.M / (p.row_h * p.row_w) * hc * wc : p.M;
+  const int K = PAR ? (1 + py) * (1 + px) * p.cp : p.K;
+  auto row_of = [&](int i) {          // row of the output tensor
+    if constexpr (!PAR) return i;
+    const int n = i / (hc * wc), rem = i - n * (hc * wc), yy = rem / wc, xx = rem - yy * wc;
+    return (n * p.row_h + 2 * yy + py) * p.row_w + 2 * xx + px;
+  };
   int ti, tj;
-  tile_of_block(blockIdx.x, (p.M + BM - 1) / BM, (p.N + BN - 1) / BN, ti, tj);
+  const int tiles_i = (M + BM - 1) / BM, tiles_j = (p.N + BN - 1) / BN;
+  if (PAR && blockIdx.x >= tiles_i * tiles_j) return;   // (the grid covers the largest class)
+  tile_of_block(blockIdx.x, tiles_i, tiles_j, ti, tj);
   const int i0 = ti * BM, j0 = tj * BN;
   // (the wave index as a scalar: everything derived from it -- LDS block addresses, which wave
   // sums the bias gradient -- then stays in scalar registers and uniform branches; a wave issues
@@ -130,7 +148,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmArgs p, Seg
     return split > 1 ? segs.off[g / split] + (g % split) * p.chunk : segs.off[g];
   };
   auto depth_of = [&](int g) {
-    if (MODE != MODE_WGRAD) return p.K;
+    if (MODE != MODE_WGRAD) return K;
     if (split == 1) return segs.off[g + 1] - segs.off[g];
     const int w = g / split, left = segs.off[w + 1] - segs.off[w] - (g % split) * p.chunk;
     return left < 0 ? 0 : (left < p.chunk ? left : p.chunk);
@@ -178,8 +196,16 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmArgs p, Seg
 #pragma unroll
   for (int u = 0; u < LA; ++u) {
     int i = i0 + (wave + NW * u) * 16 + lrow;
-    i = i < p.M ? i : p.M - 1;
-    if (GATHER) {
+    i = i < M ? i : M - 1;
+    if (PAR) {
+      const int n = i / (hc * wc), rem = i - n * (hc * wc), yy = rem / wc, xx = rem - yy * wc;
+      goff[u] = (uint32_t)(((int64_t)((n * p.src_h + yy) * p.src_w + xx) * p.lda) * 2);
+      gok[u] = 0;
+      for (int t = 0; t < (1 + py) * (1 + px); ++t) {   // tap t reads (yy, xx) moved by 0 or 1
+        const int a = px ? t >> 1 : t, b = px ? t & 1 : 0;
+        if (yy + (py ? 1 - a : 0) < p.src_h && xx + (px ? 1 - b : 0) < p.src_w) gok[u] |= 1u << t;
+      }
+    } else if (GATHER) {
       const int hw = p.row_h * p.row_w;
       const int n = i / hw, rem = i - n * hw;
       gy[u] = rem / p.row_w;
@@ -285,8 +311,22 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmArgs p, Seg
       return;
     }
     const int k0 = c.kt * BK;
-    const uint32_t kbyte = (uint32_t)k0 * 2;
-    if (gfast) {
+    uint32_t kbyte = (uint32_t)k0 * 2;
+    if constexpr (PAR) {
+      // this lane's granule: tap t of the class, channel ch (past the last tap: zeros times the last)
+      const int taps = (1 + py) * (1 + px), k = k0 + lgran * 8;
+      const int t = (k >= p.cp) + (k >= 2 * p.cp) + (k >= 3 * p.cp) + (k >= 4 * p.cp);
+      const int tc = t < taps ? t : taps - 1, ch = k - t * p.cp < p.cp ? k - t * p.cp : 0;
+      const int a = px ? tc >> 1 : tc, b = px ? tc & 1 : 0;
+      const uint32_t dbyte = (uint32_t)((((py ? 1 - a : 0) * p.src_w + (px ? 1 - b : 0)) * (int)p.lda + ch) * 2);
+#pragma unroll
+      for (int u = 0; u < LA; ++u) {
+        const void* src = t < taps && ((gok[u] >> tc) & 1u) ? (const void*)(Ab + (uint32_t)(goff[u] + dbyte)) : p.zeros;
+        async_copy_1k(src, ldsA + (uint32_t)((buf * BM * GPR + (wave + NW * u) * 64) * 16));
+      }
+      // (offB carries the lane's granule already)
+      kbyte = (uint32_t)((((py ? 2 * a : 1) * 3 + (px ? 2 * b : 1)) * p.cp + ch - lgran * 8) * 2);
+    } else if (gfast) {
       // the whole stage lies in tap k0 >> log2(cp): one signed byte offset for every row
       const int tap = k0 >> p.gather_log2cp, kc = k0 & (p.cp - 1);
       const int th = (tap * 11) >> 5, tw = tap - 3 * th;          // tap / 3, tap % 3 (tap <= 9)
@@ -827,7 +867,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmArgs p, Seg
 #pragma unroll
         for (int t = 0; t < 32 / RPI; ++t) {
           int i = i0 + wm * (BM / WM) + a * 32 + rrow + RPI * t;
-          i = i < p.M ? i : p.M - 1;
+          i = row_of(i < M ? i : M - 1);
           if (p.mask) mkv[t] = *(const bf16x8*)((const bf16*)p.mask + (int64_t)i * p.ldmask + jcol);
           if (p.addend) adv[t] = *(const bf16x8*)((const bf16*)p.addend + (int64_t)i * p.ldadd + jcol);
         }
@@ -844,10 +884,11 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmArgs p, Seg
 #pragma unroll
       for (int t = 0; t < 32 / RPI; ++t) {
         const int r = rrow + RPI * t;
-        const int i = i0 + wm * (BM / WM) + a * 32 + r;
+        int i = i0 + wm * (BM / WM) + a * 32 + r;
         const f32x4 lo = *(const f32x4*)&patch[r * EP + rcol];
         const f32x4 hi = *(const f32x4*)&patch[r * EP + rcol + 4];
-        if (i >= p.M || jcol >= p.N) continue;
+        if (i >= M || jcol >= p.N) continue;
+        i = row_of(i);
         float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
         if (MODE == MODE_FWD) {
 #pragma unroll
@@ -968,6 +1009,16 @@ void launch_bf16_gather(GemmArgs a, const Segs& s, hipStream_t st) {
       src_bytes < ((int64_t)1 << 31))
     for (int l = 5; l < 31; ++l)
       if ((1 << l) == a.cp) a.gather_log2cp = l;
+  if (a.conv == 2 && a.stride == 2 && src_bytes < ((int64_t)1 << 31)) {   // (32-bit source offsets)
+    const int64_t most = (int64_t)(a.M / (a.row_h * a.row_w)) * ((a.row_h + 1) / 2) * ((a.row_w + 1) / 2);
+    const int bm = a.N <= 64 ? 256 : 128, bn = a.N <= 64 ? 64 : 128;
+    const dim3 grid((unsigned)(((most + bm - 1) / bm) * ((a.N + bn - 1) / bn)), 4);
+    if (a.N <= 64)
+      hipLaunchKernelGGL((gemm_bf16_kernel<256, 64, 4, 1, MODE_DGRAD, true, 4, false, true>), grid, dim3(256), 0, st, a, s);
+    else
+      hipLaunchKernelGGL((gemm_bf16_kernel<128, 128, 2, 2, MODE_DGRAD, true, 5, false, true>), grid, dim3(256), 0, st, a, s);
+    return;
+  }
   if (a.N <= 64)
     launch_bf16_gather_as<256, 64, 4, 1, 4>(a, s, st);
   else

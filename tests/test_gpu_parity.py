@@ -547,3 +547,19 @@ def test_stem_convolution(image, channels, stride):
     b = [3, 0, 1, 6]
     x, y = synth.make_batch(spec, "normal", sum(b), 82, 0)
     check_worker_gradients(spec, params, x, y, b, label="stem %s %d" % (image, channels))
+
+
+@pytest.mark.parametrize("image,channels", [
+    ((7, 5, 4), (8, 72)),         # odd sides: classes of unequal size; one tile of 64 input channels
+    ((1, 4, 3), (16, 24)),        # no odd rows at all; taps that share a 32-deep stage
+    ((10, 9, 5), (72, 40)),       # more than 64 input channels: 128 x 128 tiles
+])
+def test_strided_input_gradient_by_parity_classes(image, channels):
+    c1, c2 = channels
+    spec = {"dtype": "bf16", "input": image, "classes": 3,
+            "layers": [synth.conv3x3(image[2], c1, 1), synth.conv3x3(c1, c2, 2), synth.gap(),
+                       synth.dense(c2, 3, relu=False)]}
+    params = synth.init_params(spec, "he", 91)
+    b = [2, 0, 9]
+    x, y = synth.make_batch(spec, "normal", sum(b), 92, 0)
+    check_worker_gradients(spec, params, x, y, b, label="strided %s %s" % (image, channels))
