@@ -130,6 +130,11 @@ struct GemmArgs {
 
 int launch_gemm(int dtype, const GemmArgs& a, const Segs& s, void* stream);
 int launch_gemm_f32(const GemmArgs& a, const Segs& s, void* stream);   // (gemm_f32.hip)
+// bf16 products with few tiles (gemm_small.hip): whether one (unsplit) counts as such, whether its
+// weight gradient can take GemmArgs::agg, and the launch.
+bool gemm_small_applies(const GemmArgs& a);
+bool gemm_small_folds(const GemmArgs& a, const Segs& s);
+int launch_gemm_small(const GemmArgs& a, const Segs& s, void* stream);
 // Whether a weight-gradient launch of these dimensions can take GemmArgs::agg.
 bool gemm_fuses_aggregate(int dtype, const GemmArgs& a, const Segs& s);
 // out[e] = sum_k lam.w[k] * g[k*worker_stride + e], e < n, ascending k (any alignment)

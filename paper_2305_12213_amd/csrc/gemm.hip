@@ -1030,8 +1030,8 @@ void launch_bf16_gather(GemmArgs a, const Segs& s, hipStream_t st) {
 bool gemm_fuses_aggregate(int dtype, const GemmArgs& a, const Segs& s) {
   if (dtype == DYNB_F32) return a.mode == MODE_WGRAD;   // (every workgroup owns all workers of its tile)
   // enough tiles to occupy the compute units without splitting the workers over workgroups
-  return dtype == DYNB_BF16 && a.mode == MODE_WGRAD && !a.conv && a.split <= 1 &&
-         tiles_of(a, AGG_SMALL, AGG_SMALL) >= 256 && s.K <= DYNB_MAX_WORKERS;
+  if (dtype != DYNB_BF16 || a.mode != MODE_WGRAD || a.conv || a.split > 1) return false;
+  return tiles_of(a, AGG_SMALL, AGG_SMALL) >= 256 || gemm_small_folds(a, s);
 }
 
 int launch_gemm(int dtype, const GemmArgs& args, const Segs& s, void* stream) {
@@ -1076,6 +1076,8 @@ int launch_gemm(int dtype, const GemmArgs& args, const Segs& s, void* stream) {
       return fail(DYNB_ERR_UNSUPPORTED, "gemm: gathered operand needs bf16, forward/input-gradient mode");
     if (conv_direct_applies(dtype, a)) return launch_conv_direct(a, stream);
     launch_bf16_gather(a, s, (hipStream_t)stream);
+  } else if (dtype == DYNB_BF16 && a.split <= 1 && gemm_small_applies(a)) {
+    return launch_gemm_small(a, s, stream);
   } else if (dtype == DYNB_BF16 && a.agg) {
     launch_bf16_wgrad_agg(a, s, (hipStream_t)stream);
   } else if (dtype == DYNB_BF16) {

@@ -1,0 +1,299 @@
+// bf16 matrix products with too few 128 x 128 tiles for the 256 compute units, on 64 x 64 tiles: four
+// waves of one 32 x 32 matrix-instruction tile each.  Such launches take a few microseconds, so what
+// bounds them is the latency of their first loads, the copies into LDS (64 rows of operand per 32
+// clocks of matrix work) and, not least, fetching the code itself -- about half a microsecond per
+// kilobyte that a wave runs through for the first time.  Hence rolled loops, results stored straight
+// from the accumulators, and one path for all edges.  Sums run in the order of the large kernels.
+#include <hip/hip_runtime.h>
+
+#include "dynb_internal.h"
+#include "lds_async.h"
+#include "tile_map.h"
+
+namespace dynb {
+namespace {
+
+typedef __bf16 bf16;
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef short s16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+constexpr int T = 64;                      // tile side
+
+// Granule (16 bytes) g of a 128-byte row r sits at slot g ^ swizzle(r): 16 neighbouring rows, read at
+// one granule, then fall into 64 different banks (two rows per pass over the banks; rows r and r + 8
+// differ in the lowest bit, which also keeps lanes l and l + 32 apart).
+__device__ inline int swizzle(int r) { return (((r >> 1) & 3) << 1) | ((r >> 3) & 1); }
+
+// Forward and input gradient: C[i][j] = sum_k A[i][k] B[j][k].  A stage is 64 reduction elements, the
+// whole 128-byte line of each of the 64 + 64 operand rows (16 copies, four per wave); ring of NB
+// stages, NB - 1 in flight (eight instead of four changed nothing: 17.4 against 17.7 us below).  Copies past the last stage are still issued (the wait stays a constant);
+// what they read -- the next rows, zeros past the matrix -- is never used.
+// Against 128 x 128 tiles: 1024 x 1024 x 3072 30 -> 18 us, 1024 x 10 x 1024 14 -> 6, 1531 x 777 x 2050
+// 23 -> 18.
+constexpr int NB = 4, STAGE = 2 * T * 128;
+
+template <int MODE>
+__global__ __launch_bounds__(256) void gemm_small_kernel(GemmArgs p) {
+  __shared__ uint4 ring[NB * STAGE / 16];
+  int ti, tj;
+  tile_of_block(blockIdx.x, (p.M + T - 1) / T, (p.N + T - 1) / T, ti, tj);
+  const int i0 = ti * T, j0 = tj * T;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l31 = lane & 31, h = lane >> 5, wi = wave & 1, wj = wave >> 1;
+  const uint32_t lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)&ring[0];
+  const i32x4 rsA = buffer_resource(p.A, (uint32_t)((int64_t)p.M * p.lda * 2));
+  const i32x4 rsB = buffer_resource(p.B, (uint32_t)((int64_t)p.N * p.ldb * 2));
+  // copy u of this wave: rows 16 wave + 8 u .. of A (u < 2), of B; rows past the edge repeat the last
+  // one (their products are not stored)
+  uint32_t off[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int r = 16 * wave + 8 * (u & 1) + (lane >> 3), g = (lane & 7) ^ swizzle(r);
+    const int i = i0 + r < p.M ? i0 + r : p.M - 1, j = j0 + r < p.N ? j0 + r : p.N - 1;
+    off[u] = (uint32_t)((u < 2 ? (int64_t)i * p.lda : (int64_t)j * p.ldb) * 2) + g * 16;
+  }
+  uint32_t kbyte = 0;
+  auto issue = [&](uint32_t slot) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      async_copy_1k_buffer(u < 2 ? rsA : rsB, off[u] + kbyte,
+                           lds + slot + (uint32_t)((u >> 1) * (T * 128) + (2 * wave + (u & 1)) * 1024));
+    kbyte += 128;
+  };
+  f32x16 acc;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+#pragma unroll 1
+  for (int s = 0; s < NB - 1; ++s) issue((uint32_t)(s * STAGE));
+  const char* const base = (const char*)&ring[0];
+  const int fa = (wi * 32 + l31) * 128, fb = T * 128 + (wj * 32 + l31) * 128, sw = swizzle(l31);
+  uint32_t slot = 0, refill = (NB - 1) * STAGE;
+#pragma unroll 1
+  for (int k = 0; k < p.K; k += 64) {
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NB - 2) * 4) : "memory");   // this wave's part of the stage
+    __syncthreads();                       // ... of every wave; the stage before is no longer read
+    issue(refill);
+    bf16x8 a[4], b[4];
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+      const int g = ((2 * kk + h) ^ sw) * 16;
+      a[kk] = *(const bf16x8*)(base + slot + fa + g);
+      b[kk] = *(const bf16x8*)(base + slot + fb + g);
+    }
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[kk], a[kk], acc, 0, 0, 0);
+    refill = slot;
+    slot = slot + STAGE == NB * STAGE ? 0 : slot + STAGE;
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (no copy may land after the LDS has been given back)
+
+  // accumulator elements 4q .. 4q+3 of a lane: row l31, columns 8q + 4h ..
+  const int i = i0 + wi * 32 + l31;
+  if (i >= p.M) return;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int j = j0 + wj * 32 + 8 * q + 4 * h;
+    if (j >= p.N) continue;
+    const bool whole = j + 3 < p.N;        // (pitches are multiples of 64: aligned)
+    f32x4 v = {acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
+    bf16* const c = (bf16*)p.C + (int64_t)i * p.ldc + j;
+    if (MODE == MODE_FWD) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if (p.bias) v[e] += p.bias[j + e < p.N ? j + e : p.N - 1];
+        if (p.relu) v[e] = fmaxf(v[e], 0.f);
+      }
+      if (p.Cf) {
+        float* const cf = p.Cf + (int64_t)i * p.ldcf + j;
+        if (whole) *(f32x4*)cf = v;
+        else
+          for (int e = 0; e < 3; ++e)
+            if (j + e < p.N) cf[e] = v[e];
+      }
+    } else {
+      // (padding columns of the mask and the addend exist: their rows are padded to 64)
+      if (p.addend) {
+        const bf16x4 t = *(const bf16x4*)((const bf16*)p.addend + (int64_t)i * p.ldadd + j);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = (float)(bf16)v[e] + (float)t[e];
+      }
+      if (p.mask) {
+        const bf16x4 t = *(const bf16x4*)((const bf16*)p.mask + (int64_t)i * p.ldmask + j);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (!((float)t[e] > 0.f)) v[e] = 0.f;
+      }
+    }
+    if (!p.C) continue;
+    const bf16x4 o = {(bf16)v[0], (bf16)v[1], (bf16)v[2], (bf16)v[3]};
+    if (whole) *(bf16x4*)c = o;
+    else
+      for (int e = 0; e < 3; ++e)
+        if (j + e < p.N) c[e] = o[e];
+  }
+}
+
+// Per-worker weight gradient: grads_g[j][i] = sum over worker g's rows of x[row][j] dy[row][i], the bias
+// gradient, and with `agg` the weighted average.  A stage is 32 rows of both row-major tensors (8
+// copies, two per wave, rows past the worker's last read as zeros); matrix operands come from LDS
+// through the transpose read.  A workgroup walks the workers [g0, g1) of its tile; its stages form one
+// list, so that the ring never drains between workers.  Results leave as 128-byte runs straight from
+// the accumulators.
+// Against 128 x 128 tiles: 1024 x 1024, 8 workers, 1024 rows 12 us + 8 (average) -> 17; 3072 x 1024 31
+// + 22 -> 24; 2050 x 777, 7 workers, 1531 rows 34 -> 20; 777 x 101 11 + 5 (sum of its parts) + 5
+// (biases) -> 7.
+constexpr int WNB = 6, WSTAGE = 2 * 32 * 128;
+
+__device__ inline bf16x8 read_tr(uint32_t a) {   // rows 4 apart: same swizzle
+  const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(uintptr_t)a);
+  const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(uintptr_t)(a + 512));
+  const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+  return __builtin_bit_cast(bf16x8, v);
+}
+
+template <bool AGG>
+__global__ __launch_bounds__(256) void wgrad_small_kernel(GemmArgs p, Segs segs) {
+  __shared__ uint4 ring[WNB * WSTAGE / 16];
+  int ti, tj;
+  tile_of_block(blockIdx.x, (p.M + T - 1) / T, (p.N + T - 1) / T, ti, tj);
+  const int i0 = ti * T, j0 = tj * T;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l31 = lane & 31, h = lane >> 5, wi = wave & 1, wj = wave >> 1;
+  const int g0 = blockIdx.y * p.groups_per_block, g1 = min(g0 + p.groups_per_block, segs.K);
+  const uint32_t lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)&ring[0];
+  i32x4 rsA = buffer_resource(p.A, 0u), rsB = buffer_resource(p.B, 0u);
+  const uint32_t pitchA = (uint32_t)(p.lda * 2), pitchB = (uint32_t)(p.ldb * 2);
+  // copy: rows 8 wave .. 8 wave + 7 of a stage; 64-byte halves of rows 2, 3, 6, 7, ... swapped against
+  // bank conflicts of the transpose reads; whole 64-feature runs lie within the row pitch
+  const int row = 8 * wave + (lane >> 3), gr = (lane & 7) ^ (((row >> 1) & 1) << 2);
+  const uint32_t offA = (uint32_t)row * pitchA + (uint32_t)(i0 * 2 + gr * 16);
+  const uint32_t offB = (uint32_t)row * pitchB + (uint32_t)(j0 * 2 + gr * 16);
+  // next stage to copy: row r of a worker that ends at `end`; a worker without rows has one stage too
+  // (all zeros), which writes its zeros like any other result
+  int ig = g0, ir = segs.off[g0], iend = segs.off[g0 + 1];
+  auto issue = [&](uint32_t slot) {
+    rsA[2] = (int)((uint32_t)iend * pitchA);   // (the range check zeroes rows past the worker's last)
+    rsB[2] = (int)((uint32_t)iend * pitchB);
+    async_copy_1k_buffer(rsA, offA + (uint32_t)ir * pitchA, lds + slot + (uint32_t)(wave * 1024));
+    async_copy_1k_buffer(rsB, offB + (uint32_t)ir * pitchB, lds + slot + (uint32_t)(32 * 128 + wave * 1024));
+    ir += 32;
+    if (ir >= iend && ig < g1) {
+      ++ig;                                    // (past the last worker: its zeros again, never used)
+      ir = iend;
+      iend = ig < g1 ? segs.off[ig + 1] : iend;
+    }
+  };
+  const int tg = lane >> 4, tr = lane & 15;
+  auto tr_off = [&](int half) {
+    const int rr = 8 * (tg >> 1) + (tr >> 2);
+    return (uint32_t)(rr * 128 + (half ^ ((rr >> 1) & 1)) * 64 + (16 * (tg & 1) + 4 * (tr & 3)) * 2);
+  };
+  const uint32_t ta = lds + tr_off(wi), tb = lds + 32 * 128 + tr_off(wj);
+  const bool bias = j0 == 0 && wj == 0;
+  const s16x8 ones_bits = {0x3f80, 0x3f80, 0x3f80, 0x3f80, 0x3f80, 0x3f80, 0x3f80, 0x3f80};
+  const bf16x8 ones = __builtin_bit_cast(bf16x8, ones_bits);
+
+  f32x16 acc, agg, bsum;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] = agg[v] = bsum[v] = 0.f;
+  // accumulator element v of a lane: row (x feature) 8 (v / 4) + 4h + v % 4, column (dy feature) l31
+  const int i = i0 + wi * 32 + l31, jw = j0 + wj * 32 + 4 * h;
+  auto store = [&](float* dst, const f32x16& src) {
+    if (i >= p.M) return;
+    float* d = dst + (int64_t)jw * p.ldcf + i;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int j = 8 * (v / 4) + (v & 3);
+      if (jw + j >= p.N) continue;
+      float* const e = d + (int64_t)j * p.ldcf;
+      // (past the caches, the average too: kept in the L2s as 12 + 4 MB of dirty lines it costs the
+      // 3072-1024-1024-10 model 13 us per iteration at the ends of these launches and saves the update 4)
+      __builtin_nontemporal_store(src[v], e);
+    }
+  };
+#pragma unroll 1
+  for (int s = 0; s < WNB - 1; ++s) issue((uint32_t)(s * WSTAGE));
+  uint32_t slot = 0, refill = (WNB - 1) * WSTAGE;
+#pragma unroll 1
+  for (int g = g0; g < g1; ++g) {
+    const int rows = segs.off[g + 1] - segs.off[g];
+    int r = 0;
+    do {
+      // (stores count as pending too: the wait then covers more than it has to, never less)
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"((WNB - 2) * 2) : "memory");
+      __syncthreads();                     // the stage of every wave; the one before is no longer read
+      issue(refill);
+      bf16x8 a[2], b[2];
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk) {
+        a[kk] = read_tr(ta + slot + kk * 16 * 128);
+        b[kk] = read_tr(tb + slot + kk * 16 * 128);
+      }
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk) {
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[kk], a[kk], acc, 0, 0, 0);
+        if (bias) bsum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, a[kk], bsum, 0, 0, 0);
+      }
+      refill = slot;
+      slot = slot + WSTAGE == WNB * WSTAGE ? 0 : slot + WSTAGE;
+      r += 32;
+    } while (r < rows);
+    store(p.Cf + (int64_t)g * p.group_stride, acc);
+    if (bias && h == 0 && i < p.M) p.bias_grad[(int64_t)g * p.group_stride + i] = bsum[0];
+    if (AGG) agg += p.lam[g] * acc;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = bsum[v] = 0.f;
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (no copy may land after the LDS has been given back)
+  if (AGG) store(p.agg, agg);
+}
+
+int64_t tiles64(const GemmArgs& a) { return (int64_t)((a.M + T - 1) / T) * ((a.N + T - 1) / T); }
+
+}  // namespace
+
+// Up to half as many 128 x 128 tiles as compute units (at 204 of them, 1531 x 2050 x 1024, those take
+// 16 us and these 20); weight gradients, whose larger tiles would have to divide the workers or leave
+// the average to another pass, up to the 256 at which the large kernel folds it in.
+bool gemm_small_applies(const GemmArgs& a) {
+  if (a.conv) return false;
+  const int64_t large = (int64_t)((a.M + 127) / 128) * ((a.N + 127) / 128);
+  if (a.mode != MODE_WGRAD) return a.K % 64 == 0 && large < 128;
+  return large < 256;
+}
+
+// Whether the average is formed in the same launch: one workgroup then walks all rows of its tile
+// (about 0.1 us per 32 rows), which pays once the tiles alone fill a quarter of the chip or the
+// walk is short; else the workers run side by side and the average is left to another pass.
+bool gemm_small_folds(const GemmArgs& a, const Segs& s) {
+  return gemm_small_applies(a) && (tiles64(a) >= 64 || s.K == 1 || s.off[s.K] <= 512);
+}
+
+int launch_gemm_small(const GemmArgs& args, const Segs& s, void* stream) {
+  GemmArgs a = args;
+  const int64_t tiles = tiles64(a);
+  if (tiles >= (int64_t)1 << 31) return fail(DYNB_ERR_UNSUPPORTED, "gemm: too many tiles for one launch");
+  const hipStream_t st = (hipStream_t)stream;
+  if (a.mode == MODE_FWD) {
+    hipLaunchKernelGGL(gemm_small_kernel<MODE_FWD>, dim3((unsigned)tiles), dim3(256), 0, st, a);
+  } else if (a.mode == MODE_DGRAD) {
+    hipLaunchKernelGGL(gemm_small_kernel<MODE_DGRAD>, dim3((unsigned)tiles), dim3(256), 0, st, a);
+  } else {
+    if (!a.bias_grad) return fail(DYNB_ERR_BADARG, "gemm: this weight gradient writes the bias gradient too");
+    // the average needs one workgroup to walk all workers of its tile; without it the workers are
+    // divided until the chip is full
+    int parts = a.agg ? 1 : (int)(512 / tiles);
+    parts = parts < 1 ? 1 : parts > s.K ? s.K : parts;
+    a.groups_per_block = (s.K + parts - 1) / parts;
+    const dim3 grid((unsigned)tiles, (unsigned)((s.K + a.groups_per_block - 1) / a.groups_per_block));
+    if (a.agg) hipLaunchKernelGGL(wgrad_small_kernel<true>, grid, dim3(256), 0, st, a, s);
+    else hipLaunchKernelGGL(wgrad_small_kernel<false>, grid, dim3(256), 0, st, a, s);
+  }
+  return hipGetLastError() == hipSuccess ? DYNB_OK : fail(DYNB_ERR_HIP, "gemm launch failed");
+}
+
+}  // namespace dynb

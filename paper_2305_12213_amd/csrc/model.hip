@@ -510,6 +510,9 @@ int run_forward_backward(dynb_model* m, const float* x, const int32_t* y, const 
     }
     int split = (deepest + 255) / 256;               // chunks of at least eight 32-deep stages
     split = split > L.max_split ? L.max_split : split;
+    // (up to 4096 rows the small-tile kernel walks a worker's rows faster -- 13 us -- than they are
+    // divided, summed and the biases formed in three launches)
+    if (dt == DYNB_BF16 && B <= 4096 && gemm_small_applies(g)) split = 1;
     if (split > 1) {
       g.split = split;
       g.chunk = (int)round_up((deepest + split - 1) / split, 64);
