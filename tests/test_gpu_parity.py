@@ -563,3 +563,25 @@ def test_strided_input_gradient_by_parity_classes(image, channels):
     b = [2, 0, 9]
     x, y = synth.make_batch(spec, "normal", sum(b), 92, 0)
     check_worker_gradients(spec, params, x, y, b, label="strided %s %s" % (image, channels))
+
+
+@pytest.mark.parametrize("image,channels", [
+    ((3, 1, 4), (8, 16)),         # one pixel wide: both side neighbours outside everywhere
+    ((5, 6, 4), (24, 40)),        # steps that span two taps; one and two 32-channel blocks
+    ((9, 64, 4), (40, 24)),       # the widest images; 64-channel weights, a 32-channel side
+    ((4, 65, 4), (24, 24)),       # ... and too wide for the flat run
+    ((17, 18, 4), (56, 72)),      # eight waves; a second block of output channels; 72: too many
+])
+def test_flat_convolutions(image, channels):
+    # stride 1 forward and input gradient, with a residual branch (addend and mask)
+    c1, c2 = channels
+    spec = {"dtype": "bf16", "input": image, "classes": 4,
+            "layers": [synth.conv3x3(image[2], c1, 1), synth.conv3x3(c1, c2, 1),
+                       synth.conv3x3(c2, c2, 1), synth.conv3x3(c2, c2, 1, relu=False), synth.add(1, True),
+                       synth.gap(), synth.dense(c2, 4, relu=False)]}
+    params = synth.init_params(spec, "he", 95)
+    rng = np.random.default_rng(6)
+    params = [(W, (rng.standard_normal(bb.shape) * 0.1).astype(np.float32)) for W, bb in params]
+    b = [2, 0, 3]
+    x, y = synth.make_batch(spec, "normal", sum(b), 96, 0)
+    check_worker_gradients(spec, params, x, y, b, label="flat conv %s %s" % (image, channels))
