@@ -375,8 +375,8 @@ __global__ __launch_bounds__(256) void conv_wgrad_rows_kernel(ConvWgradArgs p, S
 // and below an image are replaced by zeros while they are copied; a run also crosses image borders
 // sideways, where the pixel at x = 0 (x = W - 1) must not see the left (right) neighbour: these
 // pixels of dy are masked to zero for those taps, in registers.
-// CI / CO = 32-channel blocks of the input / output side (1 or 2: up to 32 or 64 channels): with
-// narrow sides the four waves divide the ten results of a tile -- nine taps and the column sums --
+// CI / CO = 32-channel blocks of the input / output side (1 or 2: up to 32 or 64 channels, not both 2):
+// the four waves divide the ten results of a tile -- nine taps and the column sums --
 // between them instead of padding the channels to 64.
 // A chunk is four to eight stages long, so what bounds a launch is not a rate but the way in and
 // out; the code is kept short for that reason too (a wave that runs through code for the first
@@ -686,10 +686,11 @@ int launch_conv_wgrad(const void* in, int64_t ldi, int Cin, int H, int W, const 
   // Stride 1 on images at least 8 wide (a fragment's eight pixels then hold one border pixel of each
   // kind at most): the flat kernel, whose blocks are only as wide as the channels need.  Whole rows
   // of 32-pixel-wide images with a 64-channel side need neither its masks nor its bookkeeping (3 -> 64
-  // channels on 512 x 32 x 32 pixels: 48 us by rows, 57 flat).
+  // channels on 512 x 32 x 32 pixels: 48 us by rows, 57 flat).  Two sides of more than 32 channels stay
+  // on the per-tap kernel (367 x 28 x 28 pixels, 64 -> 64: 50 us against 54; 24 -> 64: 49 against 36).
   bool by_rows = stride == 1 && W == 32 && Wo == 32 && H == Ho && (Cin > 32 || Cout > 32);
   for (int k = 0; k <= s.K && by_rows; ++k) by_rows = s.off[k] % 32 == 0;
-  const bool flat = stride == 1 && W >= 8 && H == Ho && W == Wo && !by_rows;
+  const bool flat = stride == 1 && W >= 8 && H == Ho && W == Wo && !by_rows && (Cin <= 32 || Cout <= 32);
   const int ci32 = flat && Cin <= 32 ? 1 : 2, co32 = flat && Cout <= 32 ? 1 : 2;
   Timed t(KC_GEMM_WGRAD, stream, flops, bytes);
   if (nch > 0) {
@@ -705,10 +706,8 @@ int launch_conv_wgrad(const void* in, int64_t ldi, int Cin, int H, int W, const 
       hipLaunchKernelGGL((conv_wgrad_flat_kernel<1, 1>), grid, block, 0, st, a, s, ch);
     else if (ci32 == 1)
       hipLaunchKernelGGL((conv_wgrad_flat_kernel<1, 2>), grid, block, 0, st, a, s, ch);
-    else if (co32 == 1)
-      hipLaunchKernelGGL((conv_wgrad_flat_kernel<2, 1>), grid, block, 0, st, a, s, ch);
     else
-      hipLaunchKernelGGL((conv_wgrad_flat_kernel<2, 2>), grid, block, 0, st, a, s, ch);
+      hipLaunchKernelGGL((conv_wgrad_flat_kernel<2, 1>), grid, block, 0, st, a, s, ch);
   }
   const int64_t items = (int64_t)(9 * Cin + 1) * ((Cout + 3) / 4);
   hipLaunchKernelGGL(conv_wgrad_reduce_kernel, dim3((unsigned)((items + 31) / 32), s.K), dim3(256), 0,

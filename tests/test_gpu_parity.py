@@ -513,7 +513,7 @@ def test_bf16_rounding_points_through_two_relu_layers():
 @pytest.mark.parametrize("image,channels", [
     ((9, 8, 3), (20, 32)),        # the narrowest images of the flat weight gradient; one-block sides
     ((5, 11, 1), (33, 8)),        # 32-channel blocks on one side only; rows that divide no stage
-    ((11, 40, 3), (64, 40)),      # two blocks on both sides, images wider than a 32-pixel stage
+    ((11, 40, 3), (64, 24)),      # images wider than a 32-pixel stage
     ((3, 71, 2), (8, 72)),        # ... than a 64-pixel one; a second 64-channel block
     ((6, 7, 3), (12, 40)),        # too narrow: the per-tap kernel
 ])
