@@ -65,6 +65,43 @@ __device__ inline void chunk_span(const Segs& s, const RowChunks& ch, int chunk,
   n = min(ch.rows, s.off[k + 1] - r0);
 }
 
+// Chunk result to memory, in register order: [wave][slot][v/4][lane] x 4 floats.  With two groups of
+// four waves the second hands its sums to the first through `red` (TILE_FLOATS floats of LDS).
+template <int G>
+__device__ inline void store_chunk(f32x16 (&acc)[9], f32x16& colsum, bool sums_columns, int group, int wave,
+                                   int lane, f32x4* red, float* out) {
+  const int at = wave * SLOTS * 256 + lane;      // in quadruples of floats
+  auto quad = [](const f32x16& a, int q) { return f32x4{a[4 * q], a[4 * q + 1], a[4 * q + 2], a[4 * q + 3]}; };
+  if (G == 2) {
+    __syncthreads();                             // the stages are no longer read
+    if (group == 1) {
+#pragma unroll
+      for (int t = 0; t < 9; ++t)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) red[at + (t * 4 + q) * 64] = quad(acc[t], q);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) red[at + (36 + q) * 64] = quad(colsum, q);
+    }
+    __syncthreads();
+    if (group == 1) return;
+  }
+  f32x4* dst = (f32x4*)out;
+#pragma unroll
+  for (int t = 0; t < 9; ++t)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int i = at + (t * 4 + q) * 64;
+      dst[i] = G == 2 ? quad(acc[t], q) + red[i] : quad(acc[t], q);
+    }
+  if (sums_columns) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int i = at + (36 + q) * 64;
+      dst[i] = G == 2 ? quad(colsum, q) + red[i] : quad(colsum, q);
+    }
+  }
+}
+
 struct ConvWgradArgs {
   const bf16* in; int ldi;           // [samples * H * W][ldi]
   const bf16* dy; int ldd;           // [samples * Ho * Wo][ldd]
@@ -75,21 +112,31 @@ struct ConvWgradArgs {
                                      // address would be re-loaded around every copy)
 };
 
-__global__ __launch_bounds__(256) void conv_wgrad_chunk_kernel(ConvWgradArgs p, Segs segs, RowChunks ch) {
-  __shared__ uint4 ring[S * STAGE_BYTES / 16];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+// G = 2: two groups of four waves take one half of a chunk each, with a ring each, and add their sums
+// before they are written.
+template <int G>
+__global__ __launch_bounds__(256 * G) void conv_wgrad_chunk_kernel(ConvWgradArgs p, Segs segs, RowChunks ch) {
+  __shared__ uint4 ring[G == 1 ? S * STAGE_BYTES / 16 : TILE_FLOATS / 4];
+  static_assert(2 * S * STAGE_BYTES <= TILE_FLOATS * 4, "two rings");
+  const int group = G == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
+  const int lane = threadIdx.x & 63, wave = (threadIdx.x >> 6) & 3;
   const int chunk = blockIdx.x, cib = blockIdx.y, cob = blockIdx.z;
   int k, r0, n;
   chunk_span(segs, ch, chunk, k, r0, n);
-  const int n_blocks = (n + 31) / 32;            // 32-pixel blocks
-  const int T = 3 * n_blocks;                    // stages
+  const int n_blocks = ((n + 31) / 32 + G - 1) / G;   // 32-pixel blocks of a group (the last: maybe fewer)
+  r0 += group * n_blocks * 32;
+  n -= group * n_blocks * 32;
+  n = n < 0 ? 0 : n;
+  if (G == 2 && n > n_blocks * 32) n = n_blocks * 32;
+  const int T = 3 * ((n + 31) / 32);             // stages of this group
 
   // ---- global -> LDS: this lane always moves granule (lane & 7) of pixel 8*wave + lane/8 of
   // the block; pixel rows are 128 bytes, and the two 64-byte halves of rows 2,3,6,7,... are
   // swapped so that the transpose reads of 4 neighbouring pixels fall into distinct banks.
   const int prow = 8 * wave + (lane >> 3);
   const int gq = (lane & 7) ^ (((lane >> 4) & 1) << 2);     // logical granule this lane fetches
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)&ring[0];
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)&ring[0] +
+                        (uint32_t)(group * S * STAGE_BYTES);
   // output pixel of this lane in the current block: dense row, and (sample, y, x)
   int row = r0 + prow;
   int img = row / (p.Ho * p.Wo), rem = row - img * (p.Ho * p.Wo);
@@ -174,8 +221,9 @@ __global__ __launch_bounds__(256) void conv_wgrad_chunk_kernel(ConvWgradArgs p, 
 #pragma unroll
     for (int kh = 0; kh < 3; ++kh) {
       const int t = 3 * blk + kh;
-      wait_copies(issued - t - 1);               // stage t of this wave has landed
+      if (G == 1 || t < T) wait_copies(issued - t - 1);   // stage t of this wave has landed
       __syncthreads();                           // ... of all waves; stage t-1 is no longer read
+      if (G == 2 && t >= T) continue;            // (the same for all waves of the group)
       issue_next();                              // into the buffer of stage t-1
       const uint32_t stage = lds0 + (uint32_t)((t % S) * STAGE_BYTES);
       const bf16x8 b0 = frag(stage + 3 * TILE_BYTES, foff_b, 0);
@@ -195,22 +243,8 @@ __global__ __launch_bounds__(256) void conv_wgrad_chunk_kernel(ConvWgradArgs p, 
     }
   }
 
-  // ---- chunk result, in register order: [wave][slot][v/4][lane] x 4 floats ----
-  float* out = p.partial + ((int64_t)(chunk * gridDim.y + cib) * gridDim.z + cob) * TILE_FLOATS;
-#pragma unroll
-  for (int t = 0; t < 9; ++t)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const f32x4 o = {acc[t][4 * q], acc[t][4 * q + 1], acc[t][4 * q + 2], acc[t][4 * q + 3]};
-      *(f32x4*)&out[(((wave * SLOTS + t) * 4 + q) * 64 + lane) * 4] = o;
-    }
-  if (sums_columns) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const f32x4 o = {colsum[4 * q], colsum[4 * q + 1], colsum[4 * q + 2], colsum[4 * q + 3]};
-      *(f32x4*)&out[(((wave * SLOTS + 9) * 4 + q) * 64 + lane) * 4] = o;
-    }
-  }
+  store_chunk<G>(acc, colsum, sums_columns, group, wave, lane, (f32x4*)ring,
+                 p.partial + ((int64_t)(chunk * gridDim.y + cib) * gridDim.z + cob) * TILE_FLOATS);
 }
 
 // The same for stride 1 on images exactly 32 pixels wide, where a 32-pixel block is one image
@@ -231,14 +265,20 @@ __device__ inline void wait_row_copies(int stages) {
   }
 }
 
-__global__ __launch_bounds__(256) void conv_wgrad_rows_kernel(ConvWgradArgs p, Segs segs, RowChunks ch) {
-  __shared__ uint4 ring[S * ROW_STAGE / 16];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+template <int G>
+__global__ __launch_bounds__(256 * G) void conv_wgrad_rows_kernel(ConvWgradArgs p, Segs segs, RowChunks ch) {
+  __shared__ uint4 ring[G * S * ROW_STAGE / 16];
+  static_assert(2 * S * ROW_STAGE == TILE_FLOATS * 4, "a result in the space of two rings");
+  const int group = G == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
+  const int lane = threadIdx.x & 63, wave = (threadIdx.x >> 6) & 3;
   const int chunk = blockIdx.x, cib = blockIdx.y, cob = blockIdx.z;
   int k, r0, n;
   chunk_span(segs, ch, chunk, k, r0, n);         // r0 and n are multiples of 32: whole image rows
-  const int T = n / 32;                          // stages = output rows
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)&ring[0];
+  const int rounds = (n / 32 + G - 1) / G;       // stages = output rows; the second group's share is
+  const int T = group == 0 ? rounds : n / 32 - rounds;   // smaller by one if the rows are odd
+  r0 += group * rounds * 32;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)&ring[0] +
+                        (uint32_t)(group * S * ROW_STAGE);
 
   // ---- global -> LDS.  Copy c = wave + 4u (u < 5) of a stage: c < 15: input row kh = c / 5,
   // pixel slots [8o, 8o+8), o = c % 5 (slot hx holds source pixel x = hx - 1); 15 <= c < 19:
@@ -320,9 +360,10 @@ __global__ __launch_bounds__(256) void conv_wgrad_rows_kernel(ConvWgradArgs p, S
 #pragma unroll
   for (int f = 0; f < S - 1; ++f)
     if (issued < T) { issue(issued); ++issued; }
-  for (int t = 0; t < T; ++t) {
-    wait_row_copies(issued - t - 1);             // stage t of this wave has landed
+  for (int t = 0; t < rounds; ++t) {
+    if (G == 1 || t < T) wait_row_copies(issued - t - 1);   // stage t of this wave has landed
     __syncthreads();                             // ... of all waves; stage t-1 is no longer read
+    if (G == 2 && t >= T) continue;              // (the same for all waves of the group)
     if (issued < T) { issue(issued); ++issued; }
     const uint32_t stage = lds0 + (uint32_t)((t % S) * ROW_STAGE);
     const bf16x8 b0 = frag(stage + 3 * ROW_TILE, foff_b, 0);
@@ -351,21 +392,8 @@ __global__ __launch_bounds__(256) void conv_wgrad_rows_kernel(ConvWgradArgs p, S
     }
   }
 
-  float* out = p.partial + ((int64_t)(chunk * gridDim.y + cib) * gridDim.z + cob) * TILE_FLOATS;
-#pragma unroll
-  for (int t = 0; t < 9; ++t)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const f32x4 o = {acc[t][4 * q], acc[t][4 * q + 1], acc[t][4 * q + 2], acc[t][4 * q + 3]};
-      *(f32x4*)&out[(((wave * SLOTS + t) * 4 + q) * 64 + lane) * 4] = o;
-    }
-  if (sums_columns) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const f32x4 o = {colsum[4 * q], colsum[4 * q + 1], colsum[4 * q + 2], colsum[4 * q + 3]};
-      *(f32x4*)&out[(((wave * SLOTS + 9) * 4 + q) * 64 + lane) * 4] = o;
-    }
-  }
+  store_chunk<G>(acc, colsum, sums_columns, group, wave, lane, (f32x4*)ring,
+                 p.partial + ((int64_t)(chunk * gridDim.y + cib) * gridDim.z + cob) * TILE_FLOATS);
 }
 
 // The same for stride 1 and images at least 8 pixels wide: the pixels of all images are one flat run,
@@ -382,8 +410,8 @@ __global__ __launch_bounds__(256) void conv_wgrad_rows_kernel(ConvWgradArgs p, S
 // out; the code is kept short for that reason too (a wave that runs through code for the first
 // time fetches it at about 2 KB per microsecond: with the taps unrolled in every wave, a copy plan
 // per copy and the waves' sums combined through LDS, 13 KB, the first figure below was 22).
-// 167 x 28 x 28 pixels: 24 -> 24 channels 42 -> FLATA us, 1 -> 24 43 -> FLATB; 512 x 32 x 32: 3 -> 64
-// 48 -> FLATC us.
+// 167 x 28 x 28 pixels, 24 -> 24 channels: per-tap kernel 42 us, here 19, 16 with chunks that all run
+// at a time (514 workgroups -> 457).
 template <int CI, int CO>
 struct Flat {
   static constexpr int KS = 4 / (CI * CO);            // waves that share a 32 x 32 channel tile
@@ -679,8 +707,8 @@ int launch_conv_wgrad(const void* in, int64_t ldi, int Cin, int H, int W, const 
     return fail(DYNB_ERR_UNSUPPORTED, "conv_wgrad: tensor too large for 32-bit pixel indices");
   const void* zeros = device_zero_granule();
   if (!zeros) return fail(DYNB_ERR_HIP, "conv_wgrad: no address for the zero granule");
-  const RowChunks ch = make_row_chunks(s, chunk_rows);
-  const int nch = ch.first[s.K];
+  RowChunks ch = make_row_chunks(s, chunk_rows);
+  int nch = ch.first[s.K];
   if ((int64_t)nch * cibs * cobs * TILE_FLOATS > scratch_floats)
     return fail(DYNB_ERR_BADARG, "conv_wgrad: scratch area too small");
   // Stride 1 on images at least 8 wide (a fragment's eight pixels then hold one border pixel of each
@@ -692,16 +720,38 @@ int launch_conv_wgrad(const void* in, int64_t ldi, int Cin, int H, int W, const 
   for (int k = 0; k <= s.K && by_rows; ++k) by_rows = s.off[k] % 32 == 0;
   const bool flat = stride == 1 && W >= 8 && H == Ho && W == Wo && !by_rows && (Cin <= 32 || Cout <= 32);
   const int ci32 = flat && Cin <= 32 ? 1 : 2, co32 = flat && Cout <= 32 ? 1 : 2;
+  // From about two chunks per compute unit on, two chunks are one workgroup's, whose halves meet in LDS:
+  // half as many results (147 KB each) to write and to add up.  512 x 32 x 32 pixels, 64 -> 64 channels:
+  // 53 + 15.5 us for the product and the sum over chunks -> 51 + 10.3; 512 x 16 x 16, 32 -> 64, stride
+  // 2: 31 + 13 -> 30 + 7.  With fewer chunks each has a compute unit to itself, which is worth more.
+  const bool paired = !flat && (int64_t)nch * cibs * cobs >= 384;
+  // Every worker ends with a chunk of its own, so there may be a few chunks more than workgroups that
+  // run at a time, which would then run alone at the end: chunks up to a quarter longer, if that
+  // makes them fit.
+  const int slots = paired ? 256 : 512, base = paired ? 2 * chunk_rows : chunk_rows;
+  const int64_t per_chunk = (int64_t)cibs * cobs;
+  const int64_t fit = round_up(((int64_t)s.off[s.K] + base - 1) / base * per_chunk, slots) / per_chunk;
+  for (int rows = base; rows <= base + base / 4; rows += 32) {
+    const RowChunks longer = make_row_chunks(s, rows);
+    if (longer.first[s.K] > fit && rows > base) continue;
+    ch = longer;
+    if (longer.first[s.K] <= fit) break;
+  }
+  nch = ch.first[s.K];
   Timed t(KC_GEMM_WGRAD, stream, flops, bytes);
   if (nch > 0) {
     ConvWgradArgs a = {(const bf16*)in, (int)ldi, (const bf16*)dy, (int)ldd, H, W, Ho, Wo, stride,
                        scratch, zeros};
-    const dim3 grid(nch, cibs, cobs), block(256);
+    const dim3 grid(nch, cibs, cobs), block(paired ? 512 : 256);
     const hipStream_t st = (hipStream_t)stream;
-    if (by_rows)
-      hipLaunchKernelGGL(conv_wgrad_rows_kernel, grid, block, 0, st, a, s, ch);
+    if (by_rows && paired)
+      hipLaunchKernelGGL(conv_wgrad_rows_kernel<2>, grid, block, 0, st, a, s, ch);
+    else if (by_rows)
+      hipLaunchKernelGGL(conv_wgrad_rows_kernel<1>, grid, block, 0, st, a, s, ch);
+    else if (paired)
+      hipLaunchKernelGGL(conv_wgrad_chunk_kernel<2>, grid, block, 0, st, a, s, ch);
     else if (!flat)
-      hipLaunchKernelGGL(conv_wgrad_chunk_kernel, grid, block, 0, st, a, s, ch);
+      hipLaunchKernelGGL(conv_wgrad_chunk_kernel<1>, grid, block, 0, st, a, s, ch);
     else if (ci32 == 1 && co32 == 1)
       hipLaunchKernelGGL((conv_wgrad_flat_kernel<1, 1>), grid, block, 0, st, a, s, ch);
     else if (ci32 == 1)

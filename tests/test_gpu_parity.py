@@ -565,6 +565,22 @@ def test_strided_input_gradient_by_parity_classes(image, channels):
     check_worker_gradients(spec, params, x, y, b, label="strided %s %s" % (image, channels))
 
 
+@pytest.mark.parametrize("image,b", [
+    ((1, 32, 3), [1, 3, 8, 15, 16, 17, 0, 35]),   # whole rows; odd ones; a chunk more than full
+    ((3, 5, 3), [1, 2, 3, 4, 5, 17, 18, 36]),     # per tap; a half without pixels, with part of a block
+])
+def test_paired_conv_weight_gradients(image, b):
+    # 8 x 8 channel blocks: enough work items for two chunk halves to meet in one workgroup
+    spec = {"dtype": "bf16", "input": image, "classes": 4,
+            "layers": [synth.conv3x3(3, 512, 1), synth.conv3x3(512, 512, 1), synth.gap(),
+                       synth.dense(512, 4, relu=False)]}
+    params = synth.init_params(spec, "he", 97)
+    rng = np.random.default_rng(7)
+    params = [(W, (rng.standard_normal(bb.shape) * 0.1).astype(np.float32)) for W, bb in params]
+    x, y = synth.make_batch(spec, "normal", sum(b), 98, 0)
+    check_worker_gradients(spec, params, x, y, b, label="paired %s" % (image,))
+
+
 @pytest.mark.parametrize("image,channels", [
     ((3, 1, 4), (8, 16)),         # one pixel wide: both side neighbours outside everywhere
     ((5, 6, 4), (24, 40)),        # steps that span two taps; one and two 32-channel blocks
