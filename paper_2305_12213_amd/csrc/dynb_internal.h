@@ -129,7 +129,10 @@ struct GemmArgs {
 };
 
 int launch_gemm(int dtype, const GemmArgs& a, const Segs& s, void* stream);
-int launch_gemm_f32(const GemmArgs& a, const Segs& s, void* stream);   // (gemm_f32.hip)
+int launch_gemm_f32(const GemmArgs& a, void* stream);   // forward / input gradient (gemm_f32.hip)
+// fp32 weight gradients of up to WGRAD_F32_ITEMS layers (all over the same rows) in one launch
+constexpr int WGRAD_F32_ITEMS = 8;
+int launch_wgrad_f32(const GemmArgs* a, int n, const Segs& s, void* stream);
 // bf16 products with few tiles (gemm_small.hip): whether one (unsplit) counts as such, whether its
 // weight gradient can take GemmArgs::agg, and the launch.
 bool gemm_small_applies(const GemmArgs& a);

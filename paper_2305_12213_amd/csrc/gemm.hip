@@ -1102,7 +1102,7 @@ int launch_gemm(int dtype, const GemmArgs& args, const Segs& s, void* stream) {
       launch_bf16_plain<128, 128, 2, 2, 8>(a, s, st);
     }
   } else {
-    return launch_gemm_f32(a, s, stream);
+    return launch_gemm_f32(a, stream);
   }
   return hipGetLastError() == hipSuccess ? DYNB_OK : fail(DYNB_ERR_HIP, "gemm launch failed");
 }

@@ -159,13 +159,32 @@ __global__ __launch_bounds__(64) void gemm_f32_kernel(GemmArgs p) {
 // the bias gradient.
 // 3072 x 512 weights, 4 workers, 256 rows: 25 us + 5 (bias) + 6 (average) + 10 (transposed
 // copies) -> 25 us; 785 x 301, 7 workers, 785 rows: 28 + 5 + 4 + 12 -> 19 us.
+// One launch serves every layer of a model (a launch is bound by the chain of a wave, hardly by any
+// rate, so the waves of one layer hide those of another; 785-301-97-10: 19 + 17 + 17 us for the three
+// layers one after the other -> 25 together, 3072-512-512-10: 24 + 10 + 9 -> 36).
+struct WgradItem {
+  const void* A; const void* B;            // dy, x
+  int64_t lda, ldb, ldcf;
+  int M, N, first, wide;                   // first: its first workgroup; wide: R = 2
+  float* Cf; float* bias_grad; float* agg; float* bias_agg;
+};
+struct WgradGroup {
+  WgradItem item[WGRAD_F32_ITEMS];
+  int n;
+  int64_t group_stride;
+  const void* zeros;
+  float lam[DYNB_MAX_WORKERS];
+};
+constexpr uint32_t WGRAD_RING = 24 * KB;
+
 template <int R>
-__global__ __launch_bounds__(64) void wgrad_f32_kernel(GemmArgs p, Segs segs) {
+__device__ __forceinline__ void wgrad_f32_tile(const WgradItem& p, const WgradGroup& grp, const Segs& segs,
+                                               uint32_t block, uint4* ring_area) {
   constexpr int NB = R == 1 ? 12 : 6, S = 16 * R, C = 2 * R;    // copies per block: R of dy, R of x
   constexpr uint32_t SLOT = C * KB;
-  __shared__ uint4 ring_area[NB * SLOT / 16];
+  static_assert(NB * SLOT == WGRAD_RING, "ring");
   int ti, tj;
-  tile_of_block(blockIdx.x, (p.M + S - 1) / S, (p.N + S - 1) / S, ti, tj);
+  tile_of_block(block, (p.M + S - 1) / S, (p.N + S - 1) / S, ti, tj);
   const int lane = threadIdx.x, l15 = lane & 15, kg = lane >> 4;
   const int i0 = ti * S, j0 = tj * S;
   const uint32_t lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)&ring_area[0];
@@ -176,7 +195,7 @@ __global__ __launch_bounds__(64) void wgrad_f32_kernel(GemmArgs p, Segs segs) {
   // (the workers' first rows and weights sit in a register, one worker per lane: a scalar load
   // would make every wait for the operand fetches wait for it too)
   const int offv = segs.off[lane], total = segs.off[segs.K];
-  const float lamv = p.lam[lane];
+  const float lamv = grp.lam[lane];
   struct Pos { int g, r, end; };           // worker, first row of the block, end of the worker's rows
   auto enter = [&](Pos& c) {
     const int g = c.g < segs.K ? c.g : segs.K - 1;
@@ -205,7 +224,7 @@ __global__ __launch_bounds__(64) void wgrad_f32_kernel(GemmArgs p, Segs segs) {
   auto issue_one = [&](uint32_t slot, const Pos& q, int c) {
     // (rows past the worker's last, and blocks past the last worker, are zeros)
     const bool ok = q.r + lrow + (16 / R) * (c % R) < q.end;
-    async_copy_1k(ok ? (const void*)src[c] : p.zeros, lds + slot + c * KB);
+    async_copy_1k(ok ? (const void*)src[c] : grp.zeros, lds + slot + c * KB);
   };
   auto advance = [&](Pos& q) {
     const int row = q.r;
@@ -299,7 +318,7 @@ __global__ __launch_bounds__(64) void wgrad_f32_kernel(GemmArgs p, Segs segs) {
     if (!next(cc)) return;
     // ---- end of worker g ----
     const float lam = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(lamv), g));
-    store(p.Cf + (int64_t)g * p.group_stride, acc);
+    store(p.Cf + (int64_t)g * grp.group_stride, acc);
 #pragma unroll
     for (int u = 0; u < R; ++u)
 #pragma unroll
@@ -316,7 +335,7 @@ __global__ __launch_bounds__(64) void wgrad_f32_kernel(GemmArgs p, Segs segs) {
         bagg[w] += lam * v;
         bsum[w] = 0.f;
         const int i = i0 + 16 * w + l15;
-        if (kg == 0 && i < p.M) p.bias_grad[(int64_t)g * p.group_stride + i] = v;
+        if (kg == 0 && i < p.M) p.bias_grad[(int64_t)g * grp.group_stride + i] = v;
       }
     }
   };
@@ -335,30 +354,74 @@ __global__ __launch_bounds__(64) void wgrad_f32_kernel(GemmArgs p, Segs segs) {
   }
 }
 
+__global__ __launch_bounds__(64) void wgrad_f32_kernel(WgradGroup grp, Segs segs) {
+  __shared__ uint4 ring_area[WGRAD_RING / 16];
+  int q = 0;
+  while (q + 1 < grp.n && (int)blockIdx.x >= grp.item[q + 1].first) ++q;
+  const WgradItem& p = grp.item[q];
+  if (p.wide) wgrad_f32_tile<2>(p, grp, segs, blockIdx.x - p.first, ring_area);
+  else wgrad_f32_tile<1>(p, grp, segs, blockIdx.x - p.first, ring_area);
+}
+
 template <int R>
-void launch_as(const GemmArgs& a, const Segs& s, unsigned blocks, hipStream_t st) {
+void launch_as(const GemmArgs& a, unsigned blocks, hipStream_t st) {
   const dim3 grid(blocks), block(64);
   if (a.mode == MODE_FWD)
     hipLaunchKernelGGL((gemm_f32_kernel<MODE_FWD, R>), grid, block, 0, st, a);
-  else if (a.mode == MODE_DGRAD)
-    hipLaunchKernelGGL((gemm_f32_kernel<MODE_DGRAD, R>), grid, block, 0, st, a);
   else
-    hipLaunchKernelGGL((wgrad_f32_kernel<R>), grid, block, 0, st, a, s);
+    hipLaunchKernelGGL((gemm_f32_kernel<MODE_DGRAD, R>), grid, block, 0, st, a);
 }
 
 }  // namespace
 
-int launch_gemm_f32(const GemmArgs& a, const Segs& s, void* stream) {
-  auto blocks = [&](int side) { return (int64_t)((a.M + side - 1) / side) * ((a.N + side - 1) / side); };
-  if (a.mode == MODE_WGRAD ? !a.bias_grad || (a.agg && !a.bias_agg) : a.K % 32 != 0)
-    return fail(DYNB_ERR_BADARG, "gemm: fp32 products take whole 32-deep blocks and write the bias gradient too");
-  // 2 x 2 tiles per wave once that gives each of the chip's 1024 SIMDs a wave: below that the chain
-  // of one wave, four times as long, outweighs the halved copies
-  const bool wide = blocks(32) >= 1024;
-  const int64_t n = blocks(wide ? 32 : 16);
+// 2 x 2 tiles per wave once that gives each of the chip's 1024 SIMDs a wave: below that the chain
+// of one wave, four times as long, outweighs the halved copies
+static int64_t tiles_with(const GemmArgs& a, int side) {
+  return (int64_t)((a.M + side - 1) / side) * ((a.N + side - 1) / side);
+}
+static bool wide_tiles(const GemmArgs& a) { return tiles_with(a, 32) >= 1024; }
+
+int launch_gemm_f32(const GemmArgs& a, void* stream) {
+  if (a.mode == MODE_WGRAD || a.K % 32 != 0)
+    return fail(DYNB_ERR_BADARG, "gemm: fp32 products take whole 32-deep blocks");
+  const bool wide = wide_tiles(a);
+  const int64_t n = tiles_with(a, wide ? 32 : 16);
   if (n >= (int64_t)1 << 31) return fail(DYNB_ERR_UNSUPPORTED, "gemm: too many tiles for one launch");
-  if (wide) launch_as<2>(a, s, (unsigned)n, (hipStream_t)stream);
-  else launch_as<1>(a, s, (unsigned)n, (hipStream_t)stream);
+  if (wide) launch_as<2>(a, (unsigned)n, (hipStream_t)stream);
+  else launch_as<1>(a, (unsigned)n, (hipStream_t)stream);
+  return hipGetLastError() == hipSuccess ? DYNB_OK : fail(DYNB_ERR_HIP, "gemm launch failed");
+}
+
+int launch_wgrad_f32(const GemmArgs* a, int n, const Segs& s, void* stream) {
+  if (n > WGRAD_F32_ITEMS) return fail(DYNB_ERR_BADARG, "gemm: too many weight gradients for one launch");
+  WgradGroup grp = {};
+  grp.zeros = device_zero_granule();
+  if (!grp.zeros) return fail(DYNB_ERR_HIP, "gemm: no address for the zero granule");
+  double flops = 0, bytes = 0;
+  int64_t blocks = 0;
+  for (int q = 0; q < n; ++q) {
+    const GemmArgs& g = a[q];
+    if (g.M <= 0 || g.N <= 0) continue;
+    if (g.mode != MODE_WGRAD || !g.bias_grad || (g.agg && !g.bias_agg) ||
+        (grp.n && g.group_stride != grp.group_stride))
+      return fail(DYNB_ERR_BADARG, "gemm: an fp32 weight gradient writes the bias gradient too");
+    if ((g.lda & 3) || (g.ldb & 3) || (((uintptr_t)g.A | (uintptr_t)g.B) & 15))
+      return fail(DYNB_ERR_BADARG, "gemm: operands must have 16-byte aligned rows");
+    const bool wide = wide_tiles(g);
+    const int64_t tiles = tiles_with(g, wide ? 32 : 16);
+    if (blocks + tiles >= (int64_t)1 << 31)
+      return fail(DYNB_ERR_UNSUPPORTED, "gemm: too many tiles for one launch");
+    grp.item[grp.n++] = {g.A, g.B, g.lda, g.ldb, g.ldcf, g.M, g.N, (int)blocks, wide, g.Cf, g.bias_grad,
+                         g.agg, g.bias_agg};
+    grp.group_stride = g.group_stride;
+    for (int k = 0; k < s.K; ++k) grp.lam[k] = g.lam[k];   // (of the call: the same for every layer)
+    blocks += tiles;
+    flops += g.alg_flops;
+    bytes += g.alg_bytes;
+  }
+  if (!grp.n) return DYNB_OK;
+  Timed t(KC_GEMM_WGRAD, stream, flops, bytes);
+  hipLaunchKernelGGL(wgrad_f32_kernel, dim3((unsigned)blocks), dim3(64), 0, (hipStream_t)stream, grp, s);
   return hipGetLastError() == hipSuccess ? DYNB_OK : fail(DYNB_ERR_HIP, "gemm launch failed");
 }
 

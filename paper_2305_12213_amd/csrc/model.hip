@@ -457,6 +457,13 @@ int run_forward_backward(dynb_model* m, const float* x, const int32_t* y, const 
   // Per-worker weight and bias gradients of layer l (and, with `agg`, their aggregate).  Needs
   // the layer's input and the finished gradient wrt its output.
   std::vector<char> wgrad_done(nL, 0);
+  std::vector<GemmArgs> f32_group;   // fp32 weight gradients not launched yet (dense: all over the samples)
+  auto flush_f32 = [&]() -> int {
+    const int r = f32_group.empty() ? (int)DYNB_OK
+                                    : launch_wgrad_f32(f32_group.data(), (int)f32_group.size(), s1, stream);
+    f32_group.clear();
+    return r;
+  };
   auto weight_gradient = [&](size_t l) -> int {
     wgrad_done[l] = 1;
     Layer& L = m->layers[l];
@@ -531,6 +538,10 @@ int run_forward_backward(dynb_model* m, const float* x, const int32_t* y, const 
     // unsplit: the bias gradient is formed by the same kernel
     const bool bias_inside = split <= 1;
     if (bias_inside) g.bias_grad = grads + L.b_off;
+    if (dt == DYNB_F32) {   // one launch for as many layers as it takes
+      f32_group.push_back(g);
+      return f32_group.size() == WGRAD_F32_ITEMS ? flush_f32() : (int)DYNB_OK;
+    }
     rc = launch_gemm(dt, g, segs[l], stream);
     if (rc) return rc;
     if (split > 1) {
@@ -739,6 +750,8 @@ int run_forward_backward(dynb_model* m, const float* x, const int32_t* y, const 
       rc = weight_gradient(l);
       if (rc) return rc;
     }
+  rc = flush_f32();
+  if (rc) return rc;
   // per-worker losses and zero padding; with an aggregate: the small tensors still on the list
   // and the aggregate's padding [P, P_pad) in the same launch
   return launch_finalize(m->rowloss, m->loss, grads, m->P, m->P_pad, s1, agg ? &lam : nullptr,

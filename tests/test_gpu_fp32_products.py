@@ -22,6 +22,7 @@ pytestmark = pytest.mark.gpu
     ([1024, 1056, 5], [7, 40, 0, 2], 0),     # 2 x 2 tiles per wave, with an edge of one 16-wide tile
     ([1000, 1041, 5], [3, 18], 0),           # ... and one that leaves less than a tile
     ([48, 2], [1] * 64, 0),
+    ([20, 17, 16, 40, 33, 9, 18, 16, 15, 12, 10, 3], [5, 0, 18], 0),   # more layers than one launch takes
 ])
 def test_fp32_products_at_the_edges_of_their_tiles(dims, b, shift):
     import torch
