@@ -137,7 +137,10 @@ int launch_wgrad_f32(const GemmArgs* a, int n, const Segs& s, void* stream);
 // weight gradient can take GemmArgs::agg, and the launch.
 bool gemm_small_applies(const GemmArgs& a);
 bool gemm_small_folds(const GemmArgs& a, const Segs& s);
-int launch_gemm_small(const GemmArgs& a, const Segs& s, void* stream);
+int launch_gemm_small(const GemmArgs& a, void* stream);   // forward / input gradient
+// weight gradients of up to WGRAD_SMALL_ITEMS such layers (all over the same rows) in one launch
+constexpr int WGRAD_SMALL_ITEMS = 8;
+int launch_wgrad_small(const GemmArgs* a, int n, const Segs& s, void* stream);
 // Whether a weight-gradient launch of these dimensions can take GemmArgs::agg.
 bool gemm_fuses_aggregate(int dtype, const GemmArgs& a, const Segs& s);
 // out[e] = sum_k lam.w[k] * g[k*worker_stride + e], e < n, ascending k (any alignment)

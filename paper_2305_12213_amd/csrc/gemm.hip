@@ -1078,7 +1078,7 @@ int launch_gemm(int dtype, const GemmArgs& args, const Segs& s, void* stream) {
     if (conv_flat_applies(dtype, a)) return launch_conv_flat(a, stream);
     launch_bf16_gather(a, s, (hipStream_t)stream);
   } else if (dtype == DYNB_BF16 && a.split <= 1 && gemm_small_applies(a)) {
-    return launch_gemm_small(a, s, stream);
+    return launch_gemm_small(a, stream);
   } else if (dtype == DYNB_BF16 && a.agg) {
     launch_bf16_wgrad_agg(a, s, (hipStream_t)stream);
   } else if (dtype == DYNB_BF16) {

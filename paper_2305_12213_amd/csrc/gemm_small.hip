@@ -155,15 +155,34 @@ __device__ inline bf16x8 read_tr(uint32_t a) {   // rows 4 apart: same swizzle
   return __builtin_bit_cast(bf16x8, v);
 }
 
-template <bool AGG>
-__global__ __launch_bounds__(256) void wgrad_small_kernel(GemmArgs p, Segs segs) {
+// One launch serves several layers: their workgroups fill each other's tails (the three layers of
+// 3072-1024-1024-10, 8 workers, 1024 rows: 4 + 17 + 24 us in turn -> 39; of 1001-2050-777-101: 7 + 20
+// + 27 -> 49).
+struct SmallWgrad {
+  const void* A; const void* B;                  // dy, x
+  int64_t lda, ldb, ldcf;
+  int M, N, first, tiles, groups_per_block;      // first: its first workgroup
+  float* Cf; float* bias_grad; float* agg;
+};
+struct SmallWgrads {
+  SmallWgrad item[WGRAD_SMALL_ITEMS];
+  int n;
+  int64_t group_stride;
+  float lam[DYNB_MAX_WORKERS];
+};
+
+__global__ __launch_bounds__(256) void wgrad_small_kernel(SmallWgrads grp, Segs segs) {
   __shared__ uint4 ring[WNB * WSTAGE / 16];
+  int q = 0;
+  while (q + 1 < grp.n && (int)blockIdx.x >= grp.item[q + 1].first) ++q;
+  const SmallWgrad& p = grp.item[q];
+  const int block = (int)blockIdx.x - p.first, part = block / p.tiles;
   int ti, tj;
-  tile_of_block(blockIdx.x, (p.M + T - 1) / T, (p.N + T - 1) / T, ti, tj);
+  tile_of_block((uint32_t)(block - part * p.tiles), (p.M + T - 1) / T, (p.N + T - 1) / T, ti, tj);
   const int i0 = ti * T, j0 = tj * T;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l31 = lane & 31, h = lane >> 5, wi = wave & 1, wj = wave >> 1;
-  const int g0 = blockIdx.y * p.groups_per_block, g1 = min(g0 + p.groups_per_block, segs.K);
+  const int g0 = part * p.groups_per_block, g1 = min(g0 + p.groups_per_block, segs.K);
   const uint32_t lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)&ring[0];
   i32x4 rsA = buffer_resource(p.A, 0u), rsB = buffer_resource(p.B, 0u);
   const uint32_t pitchA = (uint32_t)(p.lda * 2), pitchB = (uint32_t)(p.ldb * 2);
@@ -242,14 +261,14 @@ __global__ __launch_bounds__(256) void wgrad_small_kernel(GemmArgs p, Segs segs)
       slot = slot + WSTAGE == WNB * WSTAGE ? 0 : slot + WSTAGE;
       r += 32;
     } while (r < rows);
-    store(p.Cf + (int64_t)g * p.group_stride, acc);
-    if (bias && h == 0 && i < p.M) p.bias_grad[(int64_t)g * p.group_stride + i] = bsum[0];
-    if (AGG) agg += p.lam[g] * acc;
+    store(p.Cf + (int64_t)g * grp.group_stride, acc);
+    if (bias && h == 0 && i < p.M) p.bias_grad[(int64_t)g * grp.group_stride + i] = bsum[0];
+    if (p.agg) agg += grp.lam[g] * acc;
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[v] = bsum[v] = 0.f;
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (no copy may land after the LDS has been given back)
-  if (AGG) store(p.agg, agg);
+  if (p.agg) store(p.agg, agg);
 }
 
 int64_t tiles64(const GemmArgs& a) { return (int64_t)((a.M + T - 1) / T) * ((a.N + T - 1) / T); }
@@ -273,8 +292,7 @@ bool gemm_small_folds(const GemmArgs& a, const Segs& s) {
   return gemm_small_applies(a) && (tiles64(a) >= 64 || s.K == 1 || s.off[s.K] <= 512);
 }
 
-int launch_gemm_small(const GemmArgs& args, const Segs& s, void* stream) {
-  GemmArgs a = args;
+int launch_gemm_small(const GemmArgs& a, void* stream) {
   const int64_t tiles = tiles64(a);
   if (tiles >= (int64_t)1 << 31) return fail(DYNB_ERR_UNSUPPORTED, "gemm: too many tiles for one launch");
   const hipStream_t st = (hipStream_t)stream;
@@ -283,16 +301,44 @@ int launch_gemm_small(const GemmArgs& args, const Segs& s, void* stream) {
   } else if (a.mode == MODE_DGRAD) {
     hipLaunchKernelGGL(gemm_small_kernel<MODE_DGRAD>, dim3((unsigned)tiles), dim3(256), 0, st, a);
   } else {
-    if (!a.bias_grad) return fail(DYNB_ERR_BADARG, "gemm: this weight gradient writes the bias gradient too");
+    return fail(DYNB_ERR_BADARG, "gemm: weight gradients have a launch of their own");
+  }
+  return hipGetLastError() == hipSuccess ? DYNB_OK : fail(DYNB_ERR_HIP, "gemm launch failed");
+}
+
+int launch_wgrad_small(const GemmArgs* a, int n, const Segs& s, void* stream) {
+  if (n > WGRAD_SMALL_ITEMS) return fail(DYNB_ERR_BADARG, "gemm: too many weight gradients for one launch");
+  SmallWgrads grp = {};
+  double flops = 0, bytes = 0;
+  int64_t blocks = 0;
+  for (int q = 0; q < n; ++q) {
+    const GemmArgs& g = a[q];
+    if (g.M <= 0 || g.N <= 0) continue;
+    if (!gemm_small_applies(g) || !g.bias_grad || g.split > 1 || (g.agg && !gemm_small_folds(g, s)) ||
+        (grp.n && g.group_stride != grp.group_stride))
+      return fail(DYNB_ERR_BADARG, "gemm: not a weight gradient of few tiles with its bias gradient");
+    if ((g.lda & 7) || (g.ldb & 7) || (((uintptr_t)g.A | (uintptr_t)g.B) & 15))
+      return fail(DYNB_ERR_BADARG, "gemm: operands must have 16-byte aligned rows");
+    if (s.off[s.K] * g.lda * 2 >= (int64_t)1 << 31 || s.off[s.K] * g.ldb * 2 >= (int64_t)1 << 31)
+      return fail(DYNB_ERR_UNSUPPORTED, "gemm: an operand of 2 GiB or more (rows * pitch) is not supported");
     // the average needs one workgroup to walk all workers of its tile; without it the workers are
     // divided until the chip is full
-    int parts = a.agg ? 1 : (int)(512 / tiles);
+    const int64_t tiles = tiles64(g);
+    int parts = g.agg ? 1 : (int)(512 / tiles);
     parts = parts < 1 ? 1 : parts > s.K ? s.K : parts;
-    a.groups_per_block = (s.K + parts - 1) / parts;
-    const dim3 grid((unsigned)tiles, (unsigned)((s.K + a.groups_per_block - 1) / a.groups_per_block));
-    if (a.agg) hipLaunchKernelGGL(wgrad_small_kernel<true>, grid, dim3(256), 0, st, a, s);
-    else hipLaunchKernelGGL(wgrad_small_kernel<false>, grid, dim3(256), 0, st, a, s);
+    const int per = (s.K + parts - 1) / parts;
+    grp.item[grp.n++] = {g.A, g.B, g.lda, g.ldb, g.ldcf, g.M, g.N, (int)blocks, (int)tiles, per, g.Cf,
+                         g.bias_grad, g.agg};
+    grp.group_stride = g.group_stride;
+    if (g.agg)
+      for (int k = 0; k < s.K; ++k) grp.lam[k] = g.lam[k];   // (of the call: the same for every layer)
+    blocks += tiles * ((s.K + per - 1) / per);
+    flops += g.alg_flops;
+    bytes += g.alg_bytes;
   }
+  if (!grp.n) return DYNB_OK;
+  Timed t(KC_GEMM_WGRAD_SMALL, stream, flops, bytes);
+  hipLaunchKernelGGL(wgrad_small_kernel, dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream, grp, s);
   return hipGetLastError() == hipSuccess ? DYNB_OK : fail(DYNB_ERR_HIP, "gemm launch failed");
 }
 

@@ -63,7 +63,7 @@ __global__ __launch_bounds__(256) void pack_rows_vec_kernel(const float* __restr
   }
 }
 
-// rows of at most 8 features (an RGB pixel): one lane per row, one 16-byte store; the columns
+// rows of at most 8 features (a pixel of few channels): one lane per row, one 16-byte store; the columns
 // [D, 8) are written as zero, the rest of the padded row is never touched (it holds zeros)
 __global__ __launch_bounds__(256) void pack_rows_narrow_kernel(const float* __restrict__ x,
                                                                int64_t rows, int D,

@@ -443,7 +443,20 @@ int run_forward_backward(dynb_model* m, const float* x, const int32_t* y, const 
   // aggregates of the small tensors (biases, small weights, padding): one launch for all
   Ranges small;
   small.n = 0;
+  // weight gradients of dense layers that share a launch and are not launched yet: fp32 ones, or bf16
+  // ones of few tiles
+  std::vector<GemmArgs> group;
+  auto flush_group = [&]() -> int {
+    const int n = (int)group.size();
+    const int r = n == 0 ? (int)DYNB_OK
+                  : dt == DYNB_F32 ? launch_wgrad_f32(group.data(), n, s1, stream)
+                                   : launch_wgrad_small(group.data(), n, s1, stream);
+    group.clear();
+    return r;
+  };
   auto flush_small = [&]() {
+    const int g = flush_group();   // (whose results are read here)
+    if (g) return g;
     const int r = small.n ? launch_aggregate_ranges(grads, m->P_pad, lam, small, agg, stream) : DYNB_OK;
     small.n = 0;
     return r;
@@ -457,13 +470,6 @@ int run_forward_backward(dynb_model* m, const float* x, const int32_t* y, const 
   // Per-worker weight and bias gradients of layer l (and, with `agg`, their aggregate).  Needs
   // the layer's input and the finished gradient wrt its output.
   std::vector<char> wgrad_done(nL, 0);
-  std::vector<GemmArgs> f32_group;   // fp32 weight gradients not launched yet (dense: all over the samples)
-  auto flush_f32 = [&]() -> int {
-    const int r = f32_group.empty() ? (int)DYNB_OK
-                                    : launch_wgrad_f32(f32_group.data(), (int)f32_group.size(), s1, stream);
-    f32_group.clear();
-    return r;
-  };
   auto weight_gradient = [&](size_t l) -> int {
     wgrad_done[l] = 1;
     Layer& L = m->layers[l];
@@ -538,11 +544,15 @@ int run_forward_backward(dynb_model* m, const float* x, const int32_t* y, const 
     // unsplit: the bias gradient is formed by the same kernel
     const bool bias_inside = split <= 1;
     if (bias_inside) g.bias_grad = grads + L.b_off;
-    if (dt == DYNB_F32) {   // one launch for as many layers as it takes
-      f32_group.push_back(g);
-      return f32_group.size() == WGRAD_F32_ITEMS ? flush_f32() : (int)DYNB_OK;
+    // one launch for as many layers as it takes
+    const bool grouped = dt == DYNB_F32 || (split <= 1 && gemm_small_applies(g));
+    if (grouped) {
+      static_assert(WGRAD_F32_ITEMS == WGRAD_SMALL_ITEMS, "one limit");
+      group.push_back(g);
+      if (group.size() == WGRAD_F32_ITEMS) rc = flush_group();
+    } else {
+      rc = launch_gemm(dt, g, segs[l], stream);
     }
-    rc = launch_gemm(dt, g, segs[l], stream);
     if (rc) return rc;
     if (split > 1) {
       rc = launch_wgrad_reduce(m->partial, split, g.partial_stride, (int64_t)L.wg_rows * L.n_out,
@@ -556,6 +566,8 @@ int run_forward_backward(dynb_model* m, const float* x, const int32_t* y, const 
     if (agg) {
       const int64_t nw = (int64_t)L.wg_rows * L.n_out;
       if (!fold && nw >= 65536) {
+        if (grouped) rc = flush_group();
+        if (rc) return rc;
         rc = launch_aggregate_range(grads + L.w_off, m->P_pad, lam, nw, agg + L.w_off, stream);
         if (rc) return rc;
       } else if (!fold) {
@@ -750,7 +762,7 @@ int run_forward_backward(dynb_model* m, const float* x, const int32_t* y, const 
       rc = weight_gradient(l);
       if (rc) return rc;
     }
-  rc = flush_f32();
+  rc = flush_group();
   if (rc) return rc;
   // per-worker losses and zero padding; with an aggregate: the small tensors still on the list
   // and the aggregate's padding [P, P_pad) in the same launch

@@ -23,6 +23,8 @@ pytestmark = pytest.mark.gpu
     ([130, 70, 5], [600]),                       # ... one worker: folded
     ([72, 40, 3], [4090, 6]),                    # the last batch that is walked ...
     ([72, 40, 3], [4090, 7]),                    # ... and the first that is divided
+    ([512, 256, 10], [500, 100]),                # average by a pass over the matrix, behind the shared launch
+    ([24, 65, 40, 33, 64, 70, 48, 20, 66, 34, 12, 4], [20, 0, 33]),   # more layers than one launch takes
 ])
 def test_small_products_at_the_edges_of_their_tiles(dims, b):
     spec = synth.mlp_spec(dims, "bf16")
