@@ -2,7 +2,7 @@
 (tile sides, the two tile counts per wave), reductions shorter than the ring of blocks, idle and
 one-row workers, workers that end inside a 16-row block, and inputs that are read in place or, for
 their width or alignment, packed first.  Gradients, biases and their weighted average against the
-float64 checker; 1e-4 is the fp32 bound of the other parity tests."""
+float64 oracle; 1e-4 is the fp32 bound of the other parity tests."""
 import numpy as np
 import pytest
 
@@ -28,7 +28,7 @@ def test_fp32_products_at_the_edges_of_their_tiles(dims, b, shift):
     import torch
     spec = synth.mlp_spec(dims, "f32")
     for L in spec["layers"]:
-        L["relu"] = False                    # (no 0/1 decisions: the checker needs no resolving)
+        L["relu"] = False                    # (no 0/1 decisions: the oracle needs no resolving)
     params = synth.init_params(spec, "he", 7)
     rng = np.random.default_rng(11)
     params = [(W, (rng.standard_normal(bb.shape) * 0.1).astype(np.float32)) for W, bb in params]
