@@ -2,7 +2,7 @@
 reductions shorter and longer than the ring, idle and one-row workers, workers that end inside a
 32-row stage, averages folded in (many tiles, one worker, few rows) and left to another pass, and
 batches on both sides of the row count from which a reduction is divided instead.  Gradients and
-their average against the float64 checker with bf16 rounding emulated; bound of the other parity
+their average against the float64 oracle with bf16 rounding emulated; bound of the other parity
 tests (8e-3; without ReLU, so there are no 0/1 decisions to resolve)."""
 import numpy as np
 import pytest
