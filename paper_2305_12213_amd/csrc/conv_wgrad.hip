@@ -400,9 +400,10 @@ __global__ __launch_bounds__(256 * G) void conv_wgrad_rows_kernel(ConvWgradArgs 
 // and the three horizontal taps of a kernel row read neighbouring pixels of it, so a stage holds PX
 // consecutive output pixels, the three runs of input pixels one image row apart around them (with a
 // pixel more on both sides, used through a pixel offset), and nothing is staged per tap.  Rows above
-// and below an image are replaced by zeros while they are copied; a run also crosses image borders
-// sideways, where the pixel at x = 0 (x = W - 1) must not see the left (right) neighbour: these
-// pixels of dy are masked to zero for those taps, in registers.
+// and below an image are replaced by zeros while they are copied, and so are pixels of other workers
+// (zeros in dy alone do not keep an infinity there out of this worker's sums: 0 x Inf is NaN); a run
+// also crosses image borders sideways, where the pixel at x = 0 (x = W - 1) must not see the left
+// (right) neighbour: for those taps its operand is fetched from a granule of zeros instead.
 // CI / CO = 32-channel blocks of the input / output side (1 or 2: up to 32 or 64 channels, not both 2):
 // the four waves divide the ten results of a tile -- nine taps and the column sums --
 // between them instead of padding the channels to 64.
@@ -436,27 +437,20 @@ __device__ inline void wait_at_most(int n) {
   }
 }
 
-// Fragment with pixel j (0..7) cleared; j outside: as it is.
-__device__ inline bf16x8 without_pixel(const bf16x8& v, int j) {
-  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-  u32x4 w = __builtin_bit_cast(u32x4, v);
-  const uint32_t keep = (j & 1) ? 0x0000ffffu : 0xffff0000u;
-#pragma unroll
-  for (int d = 0; d < 4; ++d) w[d] &= (j >> 1) == d ? keep : 0xffffffffu;
-  return __builtin_bit_cast(bf16x8, w);
-}
-
 template <int CI, int CO>
 __global__ __launch_bounds__(256, 2) void conv_wgrad_flat_kernel(ConvWgradArgs p, Segs segs, RowChunks ch) {
   using F = Flat<CI, CO>;
-  __shared__ uint4 ring[F::RING * F::STAGE / 16];
+  __shared__ uint4 ring[F::RING * F::STAGE / 16 + 1];   // (the last granule: zeros)
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int chunk = blockIdx.x, cib = blockIdx.y, cob = blockIdx.z;
   int k, r0, n;
   chunk_span(segs, ch, chunk, k, r0, n);
   const int T = (n + F::PX - 1) / F::PX;              // stages
-  const int total = segs.off[segs.K];                 // pixels of the batch
+  // the worker's pixels, up to one behind the chunk: what valid taps read
+  const int lo = segs.off[k], hi = min(segs.off[k + 1], r0 + n + 1);
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)&ring[0];
+  const uint32_t lds_zero = lds0 + F::RING * F::STAGE;
+  if (threadIdx.x == 0) ring[F::RING * F::STAGE / 16] = make_uint4(0, 0, 0, 0);
 
   // ---- global -> LDS.  Copy (group q, kh): slots GROUP q .. of input run kh (slot t of a run belongs
   // to output pixel t - 1 of the stage and holds the pixel kh - 1 image rows on).  Waves 0 and 1 copy
@@ -493,7 +487,7 @@ __global__ __launch_bounds__(256, 2) void conv_wgrad_flat_kernel(ConvWgradArgs p
     for (int q = 0; q < 2; ++q) {
       if (q >= groups) break;
       const int at = pix + q * F::GROUP;
-      const bool live = at >= 0 && at < total;
+      const bool live = at >= lo && at < hi;
 #pragma unroll
       for (int kh = 0; kh < 3; ++kh) {
         const bool ok = live && (kh != 0 || y[q] > 0) && (kh != 2 || y[q] < p.H - 1);
@@ -538,8 +532,8 @@ __global__ __launch_bounds__(256, 2) void conv_wgrad_flat_kernel(ConvWgradArgs p
     const int tap = ks + F::KS * i < 9 ? ks + F::KS * i : 0;     // (column sums: fetched, not used)
     foff_a[i] = (tap / 3) * F::IN_TILE + offset(fpix + tap % 3, wci, CI);
   }
-  auto frag = [&](uint32_t a, int row_bytes) {        // pixels 4 apart: same swizzle
-    const s16x4 lo = read_tr(a), hi = read_tr(a + 4 * row_bytes);
+  auto frag = [&](uint32_t a0, uint32_t a1) {
+    const s16x4 lo = read_tr(a0), hi = read_tr(a1);
     const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
     return __builtin_bit_cast(bf16x8, v);
   };
@@ -551,7 +545,7 @@ __global__ __launch_bounds__(256, 2) void conv_wgrad_flat_kernel(ConvWgradArgs p
   for (int i = 0; i < F::ITEMS; ++i)
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[i][v] = 0.f;
-  int lx = (r0 + 8 * (lane >> 5)) % p.W;              // x of this lane's first pixel of a 16-pixel step
+  int lx = (r0 + fpix) % p.W;                         // x of the first pixel this lane reads in a 16-pixel step
   const int lx_step = 16 % p.W;
 
 #pragma unroll 1
@@ -563,18 +557,23 @@ __global__ __launch_bounds__(256, 2) void conv_wgrad_flat_kernel(ConvWgradArgs p
     if (t + 2 < T) issue(nbuf);
 #pragma unroll
     for (int step = 0; step < F::PX / 16; ++step) {
-      const bf16x8 b = frag(buf + step * 16 * F::DY_ROW + foff_b, F::DY_ROW);
-      // the pixels of these eight at x = 0 and x = W - 1 (none: 8 or more)
-      const int j0 = lx == 0 ? 0 : p.W - lx, j1 = p.W - 1 - lx;
+      const uint32_t at_b = buf + step * 16 * F::DY_ROW + foff_b;
+      const bf16x8 b = frag(at_b, at_b + 4 * F::DY_ROW);      // (pixels 4 apart: same swizzle)
+      // whether the lane's two pixels have a left and a right neighbour
+      const int lx4 = lx + 4 >= p.W ? lx + 4 - p.W : lx + 4;
+      const bool l0 = lx != 0, l1 = lx4 != 0, q0 = lx != p.W - 1, q1 = lx4 != p.W - 1;
       bf16x8 a[F::ITEMS];
 #pragma unroll
-      for (int i = 0; i < F::ITEMS; ++i) a[i] = frag(buf + step * 16 * F::IN_ROW + foff_a[i], F::IN_ROW);
+      for (int i = 0; i < F::ITEMS; ++i) {
+        const int kw = (ks + F::KS * i) % 3;
+        const uint32_t at = buf + step * 16 * F::IN_ROW + foff_a[i];
+        const bool ok0 = kw == 0 ? l0 : kw == 2 ? q0 : true, ok1 = kw == 0 ? l1 : kw == 2 ? q1 : true;
+        a[i] = frag(ok0 ? at : lds_zero, ok1 ? at + 4 * F::IN_ROW : lds_zero);
+      }
 #pragma unroll
       for (int i = 0; i < F::ITEMS; ++i) {
-        const int tap = ks + F::KS * i, kw = tap % 3;
-        if (tap >= 9) a[i] = ones;
-        const bf16x8 bm = tap < 9 && kw != 1 ? without_pixel(b, kw == 0 ? j0 : j1) : b;
-        acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bm, a[i], acc[i], 0, 0, 0);
+        if (ks + F::KS * i >= 9) a[i] = ones;
+        acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, a[i], acc[i], 0, 0, 0);
       }
       lx += lx_step;
       if (lx >= p.W) lx -= p.W;

@@ -1,0 +1,62 @@
+"""Infinities and NaN stay where they belong: a worker's gradient depends on its own samples only, and
+a convolution tap on the pixels that it reads only, whatever the pixels beside them hold.  (Kernels
+that take runs of neighbouring pixels see values that no sum of theirs may use; a zero on the other
+side of a product does not keep these out, as 0 x Inf is NaN.)  All comparisons are bit for bit."""
+import numpy as np
+import pytest
+
+from paper_2305_12213_amd import synth
+from gpu_harness import DeviceRun, worker_grads_as_lists
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("image,channels", [
+    ((9, 8, 4), (20, 32)),        # weight gradients on flat runs of pixels: one-block sides
+    ((5, 11, 5), (33, 8)),        # ... 32-channel blocks on one side only
+    ((11, 40, 4), (64, 24)),      # ... images wider than a stage
+    ((3, 71, 4), (8, 72)),
+    ((6, 7, 4), (12, 40)),        # per tap
+    ((4, 32, 4), (40, 40)),       # whole rows of 32 pixels
+    ((8, 9, 3), (16, 16)),        # the first convolution on the caller's pixels
+])
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+def test_a_worker_does_not_see_its_neighbours(image, channels, value):
+    c1, c2 = channels
+    spec = {"dtype": "bf16", "input": image, "classes": 4,
+            "layers": [synth.conv3x3(image[2], c1, 1, relu=False), synth.conv3x3(c1, c2, 1), synth.gap(),
+                       synth.dense(c2, 4, relu=False)]}
+    params = synth.init_params(spec, "he", 21)
+    b = [3, 2, 1]
+    x, y = synth.make_batch(spec, "normal", sum(b), 22, 0)
+    run = DeviceRun(spec, params, sum(b), len(b))
+    clean = run.forward_backward(x, y, b).cpu().numpy()
+    x[3:5] = value
+    g = run.forward_backward(x, y, b).cpu().numpy()
+    assert np.isfinite(clean).all()
+    assert np.array_equal(g[0], clean[0]) and np.array_equal(g[2], clean[2])
+    assert not np.isfinite(g[1]).all()
+
+
+@pytest.mark.parametrize("image,channels", [
+    ((9, 8, 4), 20), ((4, 11, 4), 40), ((3, 40, 36), 24), ((6, 7, 4), 12), ((4, 32, 4), 40),
+])
+def test_a_tap_does_not_see_the_other_side_of_the_image(image, channels):
+    # an infinity in the last column that the ReLU clears: the left taps, which never read that
+    # column, and the other channels keep finite gradients
+    h, w, c = image
+    spec = {"dtype": "bf16", "input": image, "classes": 4,
+            "layers": [synth.conv3x3(c, channels, 1), synth.gap(), synth.dense(channels, 4, relu=False)]}
+    params = synth.init_params(spec, "he", 23)
+    params[0][0][:, :, 0, :] = -np.abs(params[0][0][:, :, 0, :]) - 0.1
+    b = [1, 3]
+    x, y = synth.make_batch(spec, "normal", sum(b), 24, 0)
+    run = DeviceRun(spec, params, sum(b), len(b))
+    got = []
+    for value in (2.0 ** 20, np.inf):
+        x[:, :, w - 1, 0] = value
+        got.append([p[0][0] for p in worker_grads_as_lists(spec, run.forward_backward(x, y, b).cpu().numpy(), run.P)])
+    for finite, inf in zip(*got):
+        assert np.isfinite(finite).all()
+        assert np.array_equal(inf[:, 0], finite[:, 0])
+        assert np.array_equal(inf[:, :, 1:], finite[:, :, 1:])
