@@ -30,13 +30,22 @@ __device__ inline void wait_pending() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
+// Wait until every LDS read issued so far has returned: a slot may then be copied into again.  (A copy's
+// LDS write is not ordered behind reads in flight, and the compiler waits for these only where their
+// values are used.)  The builtin, so that the compiler knows and does not wait for them once more.
+__device__ inline void wait_reads() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0xc07f);      // lgkmcnt(0), the other counters at their limits
+  asm volatile("" ::: "memory");
+}
+
 // Forward and input gradient: C[i][j] = sum_k A[i][k] B[j][k], both operands contiguous in k.  A
 // block is 32 reduction indices, the whole 128-byte line of each operand row (half a line per block
 // fetches every line twice: 19 instead of 11 us at 785 x 301 x 832): two copies of 8 rows per 16 rows.  Granule e
 // (16 bytes) of row r sits at slot e ^ (r / 2 % 8), so that matrix instruction e, which reads index
 // 4e + kg of 16 rows, finds 64 different banks.  A wave issues in order and the next matrix
-// instruction of a chain waits for the last, so copies and fetches are placed one by one between
-// them, in their 32-clock shadows.
+// instruction of a chain waits for the last, so fetches (in a step's first half) and copies (in its
+// second) are placed between them, in their 32-clock shadows.
 // Against 64 x 64 vector-unit tiles: 256 x 512 x 3072 165 -> 28 us (the chain of matrix
 // instructions alone is 11 us, the issue of everything else of a lone wave 12), 785 x 301 x 832
 // 49 -> 11 us.
@@ -91,8 +100,9 @@ __global__ __launch_bounds__(64) void gemm_f32_kernel(GemmArgs p) {
   wait_pending<(NB - 1) * C>();
 #pragma unroll
   for (int e = 0; e < 8; ++e) fetch_one(0, 0, e);
-  // Step: block c's operands are in registers; those of block c + 1 have landed once at most the
-  // NB - 2 blocks behind it are pending; block c's slot, read a step ago, takes block c + NB.
+  // Step: block c's operands are in registers, or on their way there since the first half of the last
+  // step; those of block c + 1 have landed once at most the NB - 2 blocks behind it are pending; block
+  // c's slot, whose reads are waited for before this step's own begin, takes block c + NB.
   // (Two steps unrolled, not the ring: such launches are so short that fetching a long loop body
   // for the first time shows.)
   uint32_t slot = 0;
@@ -107,9 +117,14 @@ __global__ __launch_bounds__(64) void gemm_f32_kernel(GemmArgs p) {
         for (int w = 0; w < R; ++w)
           acc[u][w] = __builtin_amdgcn_mfma_f32_16x16x4f32(f[set][u][e], f[set][R + w][e], acc[u][w], 0, 0, 0);
       __builtin_amdgcn_sched_barrier(0);
-      fetch_one(set ^ 1, next, e);
+      if (e == 0) wait_reads();
+      if (e < 4) {
+        fetch_one(set ^ 1, next, 2 * e);
+        fetch_one(set ^ 1, next, 2 * e + 1);
+      } else {
 #pragma unroll
-      for (int c = e * C / 8; c < (e + 1) * C / 8; ++c) issue_one(slot, c);
+        for (int c = (e - 4) * C / 4; c < (e - 3) * C / 4; ++c) issue_one(slot, c);
+      }
       __builtin_amdgcn_sched_barrier(0);
     }
     advance();
@@ -307,9 +322,14 @@ __device__ __forceinline__ void wgrad_f32_tile(const WgradItem& p, const WgradGr
         for (int w = 0; w < R; ++w) bsum[w] += f[set][w][t];
       }
       __builtin_amdgcn_sched_barrier(0);
-      fetch_one(set ^ 1, ahead, t);
+      if (t == 0) wait_reads();            // (of `slot`, before it is copied into)
+      if (t < 2) {
+        fetch_one(set ^ 1, ahead, 2 * t);
+        fetch_one(set ^ 1, ahead, 2 * t + 1);
+      } else {
 #pragma unroll
-      for (int c = t * C / 4; c < (t + 1) * C / 4; ++c) issue_one(slot, ic, c);
+        for (int c = (t - 2) * C / 2; c < (t - 1) * C / 2; ++c) issue_one(slot, ic, c);
+      }
       __builtin_amdgcn_sched_barrier(0);
     }
     advance(ic);
