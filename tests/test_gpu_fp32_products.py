@@ -9,6 +9,7 @@ import pytest
 from oracle import network as on
 from paper_2305_12213_amd import binding, synth
 from gpu_harness import DeviceRun, worker_grads_as_lists, worst_pair_relerr, worst_relerr
+from test_gpu_parity import check_worker_gradients
 
 pytestmark = pytest.mark.gpu
 
@@ -46,3 +47,85 @@ def test_fp32_products_at_the_edges_of_their_tiles(dims, b, shift):
     # the two-call form gives the same gradients bit for bit
     two = run.forward_backward(xd, y, b).cpu().numpy()
     assert np.array_equal(two, g)
+
+
+def test_two_by_two_tiles_in_forward_and_input_gradient():
+    # 33 x 33 tiles of 32 x 32 in four products, with ragged edges and ReLU masks; reductions of 60
+    # and 5 (two blocks, against a ring of four) and of 1041 and 1030
+    spec = synth.mlp_spec([60, 1041, 1030, 5], "f32")
+    params = synth.init_params(spec, "he", 17)
+    b = [515, 0, 498, 17]
+    x, y = synth.make_batch(spec, "normal", sum(b), 18, 0)
+    check_worker_gradients(spec, params, x, y, b, label="fp32 2 x 2 tiles")
+
+
+# The products as one chain of fused multiply-adds in ascending order of the reduction index, bit for
+# bit.  Operands of at most 13 bits in [1, 2) make every step exact in float64, so rounding its result
+# to float32 is the fused operation.  Each product is read off a gradient that only scales it by a
+# power of two: equal logits of 2^n classes make dz = (2^-n - onehot) / b exact.
+def chain(a, b):
+    acc = np.zeros((a.shape[0], b.shape[1]), np.float32)
+    for k in range(a.shape[1]):
+        acc = (acc.astype(np.float64) + a[:, k:k + 1].astype(np.float64) * b[k].astype(np.float64)).astype(np.float32)
+    return acc
+
+
+def few_bits(rng, *shape):
+    return ((1 + rng.integers(0, 4096, shape) / 4096) * rng.choice([-1.0, 1.0], shape)).astype(np.float32)
+
+
+def dz_of(y, b, classes):
+    dz = np.full((len(y), classes), 1.0 / classes)
+    dz[np.arange(len(y)), y] -= 1.0
+    return (dz / np.repeat(b, b)[:, None]).astype(np.float32)
+
+
+def linear_run(dims, params, x, y, b):
+    spec = synth.mlp_spec(dims, "f32")
+    for L in spec["layers"]:
+        L["relu"] = False
+    run = DeviceRun(spec, params, len(x), len(b))
+    g = run.forward_backward(x, y, b).cpu().numpy()
+    return worker_grads_as_lists(spec, g, run.P)
+
+
+@pytest.mark.parametrize("n,m", [(300, 50), (70, 16370)])     # 2 x 2 tiles from 16353 columns on
+def test_forward_is_one_chain(n, m):
+    rng = np.random.default_rng(31)
+    rows, W = 33, few_bits(rng, n, m)
+    x, y = few_bits(rng, rows, n), rng.integers(0, 2, rows).astype(np.int32)
+    zeros = np.zeros
+    params = [(W, zeros(m, np.float32)), (zeros((m, 2), np.float32), zeros(2, np.float32))]
+    got = linear_run([n, m, 2], params, x, y, [1] * rows)     # one row per worker: dW of layer 2 is h dz
+    want = chain(x, W)
+    for k in range(rows):
+        assert np.array_equal(got[k][1][0][:, 1 - y[k]], 0.5 * want[k]), k
+
+
+@pytest.mark.parametrize("m,classes", [(50, 64), (16370, 32)])
+def test_input_gradient_is_one_chain(m, classes):
+    rng = np.random.default_rng(32)
+    rows, W = 33, few_bits(rng, m, classes)
+    x, y = np.zeros((rows, 1), np.float32), rng.integers(0, classes, rows).astype(np.int32)
+    zeros = np.zeros
+    params = [(zeros((1, m), np.float32), zeros(m, np.float32)), (W, zeros(classes, np.float32))]
+    got = linear_run([1, m, classes], params, x, y, [1] * rows)   # bias gradient of layer 1: dz W'
+    want = chain(dz_of(y, [1] * rows, classes), np.ascontiguousarray(W.T))
+    for k in range(rows):
+        assert np.array_equal(got[k][0][1], want[k]), k
+
+
+@pytest.mark.parametrize("n,classes,b", [
+    (77, 16, [64, 32, 8]),
+    (1000, 1024, [64, 16]),          # 2 x 2 tiles
+    (40, 4, [1024, 512, 2048]),
+])
+def test_weight_gradient_is_one_chain_per_worker(n, classes, b):
+    rng = np.random.default_rng(33)
+    x, y = few_bits(rng, sum(b), n), rng.integers(0, classes, sum(b)).astype(np.int32)
+    params = [(np.zeros((n, classes), np.float32), np.zeros(classes, np.float32))]
+    got = linear_run([n, classes], params, x, y, b)
+    dz, off = dz_of(y, b, classes), 0
+    for k, bk in enumerate(b):
+        assert np.array_equal(got[k][0][0], chain(x[off:off + bk].T, dz[off:off + bk])), k
+        off += bk
