@@ -14,13 +14,13 @@
 // 367 x 28 x 28, 24 -> 64 and 64 -> 24: 41 and 52 -> 32 and 39.
 #include <hip/hip_runtime.h>
 
+#include "device_rows.h"
 #include "dynb_internal.h"
 #include "lds_async.h"
 
 namespace dynb {
 namespace {
 
-typedef __bf16 bf16;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -166,9 +166,11 @@ __global__ __launch_bounds__(NW * 64) void conv_flat_kernel(ConvFlatArgs p) {
     }
   __builtin_amdgcn_wave_barrier();
   constexpr int LPR = 4 * CO, RPI = 64 / LPR;          // lanes per row, rows per instruction
+  const int ch = (lane % LPR) * 8;
+  const uint4 keep = keep8(p.N - j0 - ch);
 #pragma unroll
   for (int t = 0; t < LPR; ++t) {
-    const int r = t * RPI + lane / LPR, ch = (lane % LPR) * 8;
+    const int r = t * RPI + lane / LPR;
     const int64_t i = p0 + wave * 64 + r;
     if (i >= p.total) continue;
     bf16x8 v = *(const bf16x8*)(patch + r * F::OPITCH + ch * 2);
@@ -183,7 +185,7 @@ __global__ __launch_bounds__(NW * 64) void conv_flat_kernel(ConvFlatArgs p) {
       for (int e = 0; e < 8; ++e)
         if (!((float)k[e] > 0.f)) v[e] = (bf16)0.f;
     }
-    *(bf16x8*)(p.out + i * p.ldo + j0 + ch) = v;
+    store8(p.out + i * p.ldo + j0 + ch, __builtin_bit_cast(uint4, v) & keep);
   }
 }
 

@@ -8,13 +8,13 @@
 // -> forward 27, weight gradient 24 + 5 (the 67 MB of the wide tensor take 10 us to write, 14 to read).
 #include <hip/hip_runtime.h>
 
+#include "device_rows.h"
 #include "dynb_internal.h"
 #include "lds_async.h"
 
 namespace dynb {
 namespace {
 
-typedef __bf16 bf16;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
@@ -53,8 +53,8 @@ __device__ inline void fetch_tap(const StemArgs& p, int img, int oy, int ox, int
 // A workgroup takes 256 output pixels x 64 output channels, a wave 64 pixels, of which each lane
 // gathers one: 9 taps x 8 channels in LDS, as the weight copies lie in memory (their padding and the
 // tenth granule are zeros; five matrix-instruction steps, in the order of the general kernel).  The
-// results pass through LDS so that a store writes whole 128-byte rows; padding channels have zero
-// weights and biases and are written as zeros.
+// results pass through LDS so that a store writes whole 128-byte rows; padding channels are written
+// as zeros.
 constexpr int APITCH = 176, OPITCH = 144;  // bytes per pixel: patch, result (odd multiples of 16: no bank conflicts)
 
 template <int CIN>
@@ -128,11 +128,12 @@ __global__ __launch_bounds__(256) void stem_forward_kernel(StemArgs p) {
         *(bf16x4*)(mine + (a * 32 + l31) * OPITCH + (b * 32 + 8 * q + 4 * h) * 2) = o;
       }
   __builtin_amdgcn_wave_barrier();
+  const uint4 keep = keep8(p.N - j0 - (lane & 7) * 8);
 #pragma unroll
   for (int t = 0; t < 8; ++t) {
     const int r = 8 * t + (lane >> 3);
     const uint4 o = *(const uint4*)(mine + r * OPITCH + (lane & 7) * 16);
-    if (pix0 + r < p.pixels) *(uint4*)(p.out + (pix0 + r) * p.ldo + j0 + (lane & 7) * 8) = o;
+    if (pix0 + r < p.pixels) *(uint4*)(p.out + (pix0 + r) * p.ldo + j0 + (lane & 7) * 8) = o & keep;
   }
 }
 

@@ -28,6 +28,16 @@ __device__ inline uint4 pack8(const float (&f)[8]) {
   return make_uint4(pack2(f[0], f[1]), pack2(f[2], f[3]), pack2(f[4], f[5]), pack2(f[6], f[7]));
 }
 
+// Mask of 8 neighbouring channels of which the first `live` exist (any value): padding channels are
+// stored as zeros whatever the data -- a product with zero weights is no zero next to an infinity.
+__device__ inline uint4 keep8(int live) {
+  auto word = [&](int d) { return live > 2 * d + 1 ? 0xffffffffu : live > 2 * d ? 0x0000ffffu : 0u; };
+  return make_uint4(word(0), word(1), word(2), word(3));
+}
+__device__ inline uint4 operator&(const uint4& a, const uint4& b) {
+  return make_uint4(a.x & b.x, a.y & b.y, a.z & b.z, a.w & b.w);
+}
+
 __device__ inline uint4 load8(const bf16* p) { return *reinterpret_cast<const uint4*>(p); }
 __device__ inline void store8(bf16* p, const uint4& q) { *reinterpret_cast<uint4*>(p) = q; }
 

@@ -373,7 +373,8 @@ extern "C" int dynb_model_bind(dynb_model* m, float* params, void* ws, size_t ws
   m->max_batch = max_batch;
   m->max_workers = max_workers;
   // Padding columns (beyond a layer's width) are operands of the GEMMs and are multiplied by
-  // zero weights: they must hold finite values.  Clearing once is enough, no kernel writes them.
+  // zero weights: they must hold finite values.  Clearing once is enough: kernels leave them alone or
+  // write them as zeros.
   if (hipMemsetAsync(ws, 0, need, (hipStream_t)stream) != hipSuccess)
     return fail(DYNB_ERR_HIP, "bind: hipMemsetAsync failed");
   m->bound = true;

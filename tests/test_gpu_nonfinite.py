@@ -60,3 +60,24 @@ def test_a_tap_does_not_see_the_other_side_of_the_image(image, channels):
         assert np.isfinite(finite).all()
         assert np.array_equal(inf[:, 0], finite[:, 0])
         assert np.array_equal(inf[:, :, 1:], finite[:, :, 1:])
+
+
+@pytest.mark.parametrize("image", [(5, 6, 4), (5, 6, 3), (4, 65, 4)])   # flat run, caller's pixels, gathered
+def test_an_overflow_is_not_lost_in_padding_channels(image):
+    # One channel, padded to eight, without ReLU: +Inf, which the positive weights above carry to the
+    # loss.  (A padding channel that is not zero would make it NaN, which the next ReLU turns into 0.)
+    spec = {"dtype": "bf16", "input": image, "classes": 4,
+            "layers": [synth.conv3x3(image[2], 1, 1, relu=False), synth.conv3x3(1, 8, 1), synth.gap(),
+                       synth.dense(8, 4, relu=False)]}
+    params = [(np.abs(W) + 0.1, bb) for W, bb in synth.init_params(spec, "he", 25)]
+    b = [2, 1]
+    x, y = synth.make_batch(spec, "normal", sum(b), 26, 0)
+    run = DeviceRun(spec, params, sum(b), len(b))
+    clean = run.forward_backward(x, y, b).cpu().numpy()
+    x2 = x.copy()
+    x2[0, 2, 3, 0] = np.inf
+    g = run.forward_backward(x2, y, b).cpu().numpy()
+    losses = run.losses(2)
+    assert not np.isfinite(losses[0]) and np.isfinite(losses[1])
+    assert np.array_equal(g[1], clean[1])
+    assert np.array_equal(run.forward_backward(x, y, b).cpu().numpy(), clean)   # nothing stays behind
