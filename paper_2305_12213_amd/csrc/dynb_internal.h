@@ -133,6 +133,15 @@ int launch_gemm_f32(const GemmArgs& a, void* stream);   // forward / input gradi
 // fp32 weight gradients of up to WGRAD_F32_ITEMS layers (all over the same rows) in one launch
 constexpr int WGRAD_F32_ITEMS = 8;
 int launch_wgrad_f32(const GemmArgs* a, int n, const Segs& s, void* stream);
+// whether a wave can walk all workers of its tile and form the average, whether one walks them in any
+// case (the tiles fill the chip), and whether walking them costs less than a pass over their results
+bool wgrad_f32_can_fold(const GemmArgs& a, const Segs& s);
+bool wgrad_f32_walks(const GemmArgs& a, const Segs& s);
+bool wgrad_f32_folds(const GemmArgs& a, const Segs& s);
+// The choice behind it: a walk over all workers of `walk_us`, against a `shares`-th of it and a pass
+// over K results of `weights` floats.
+constexpr int64_t AGGREGATE_ALONE = 65536;   // from so many on, a launch of its own (else part of the last)
+bool fold_pays(double walk_us, int shares, int64_t weights, int K);
 // bf16 products with few tiles (gemm_small.hip): whether one (unsplit) counts as such, whether its
 // weight gradient can take GemmArgs::agg, and the launch.
 bool gemm_small_applies(const GemmArgs& a);

@@ -1027,8 +1027,16 @@ void launch_bf16_gather(GemmArgs a, const Segs& s, hipStream_t st) {
 
 }  // namespace
 
+// The pass over the results costs what reading them takes (5.8 TB/s), or a launch (4 us); below
+// AGGREGATE_ALONE weights it is part of the last launch of the call, and next to free.
+bool fold_pays(double walk_us, int shares, int64_t weights, int K) {
+  const double read_us = 4.0 * K * weights / 5.8e6;
+  const double pass_us = weights < AGGREGATE_ALONE ? 0.5 : read_us > 4.0 ? read_us : 4.0;
+  return walk_us - walk_us / shares <= pass_us;
+}
+
 bool gemm_fuses_aggregate(int dtype, const GemmArgs& a, const Segs& s) {
-  if (dtype == DYNB_F32) return a.mode == MODE_WGRAD;   // (every workgroup owns all workers of its tile)
+  if (dtype == DYNB_F32) return a.mode == MODE_WGRAD && wgrad_f32_can_fold(a, s);
   // enough tiles to occupy the compute units without splitting the workers over workgroups
   if (dtype != DYNB_BF16 || a.mode != MODE_WGRAD || a.conv || a.split > 1) return false;
   return tiles_of(a, AGG_SMALL, AGG_SMALL) >= 256 || gemm_small_folds(a, s);

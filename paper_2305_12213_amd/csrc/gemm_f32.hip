@@ -166,12 +166,11 @@ __global__ __launch_bounds__(64) void gemm_f32_kernel(GemmArgs p) {
 // Per-worker weight gradient, bias gradient and their weighted average in one pass over the
 // row-major tensors: grads_g[j][i] = sum over worker g's rows of x[row][j] dy[row][i].  The
 // reduction runs over rows; a block is 16 rows of 16 R features per operand, copied as it lies in
-// memory (R = 1: one copy of 16 half lines; R = 2: two copies of 8 whole lines, granule g of row r
-// at slot g ^ 4 (r / 2 % 2) against bank conflicts; a row past the worker's last comes from the zero
-// granule), and matrix instruction t reads row 4t + kg: no transposed copies.  A wave walks all
-// workers of its tile in ascending order, blocks in flight across worker boundaries; the lane that
-// stores an element keeps its weighted sum.  The waves of the first tile column sum dy alongside:
-// the bias gradient.
+// memory (R copies; a row past the worker's last comes from the zero granule), and matrix instruction t
+// reads row 4t + kg: no transposed copies.  A wave walks workers of its tile in ascending order, blocks
+// in flight across worker boundaries: all of them where it forms the average too (the lane that stores
+// an element keeps its weighted sum), else a share.  The waves of the first tile column sum dy
+// alongside: the bias gradient.
 // 3072 x 512 weights, 4 workers, 256 rows: 25 us + 5 (bias) + 6 (average) + 10 (transposed
 // copies) -> 25 us; 785 x 301, 7 workers, 785 rows: 28 + 5 + 4 + 12 -> 19 us.
 // One launch serves every layer of a model (a launch is bound by the chain of a wave, hardly by any
@@ -181,6 +180,7 @@ struct WgradItem {
   const void* A; const void* B;            // dy, x
   int64_t lda, ldb, ldcf;
   int M, N, first, wide;                   // first: its first workgroup; wide: R = 2
+  int tiles, per;                          // workgroups tiles * part .. take workers per * part ..
   float* Cf; float* bias_grad; float* agg; float* bias_agg;
 };
 struct WgradGroup {
@@ -190,18 +190,25 @@ struct WgradGroup {
   const void* zeros;
   float lam[DYNB_MAX_WORKERS];
 };
-constexpr uint32_t WGRAD_RING = 24 * KB;
+template <int R> constexpr uint32_t WGRAD_RING = (R == 4 ? 32 : 24) * KB;
+
+// Granule g of a block's row r sits at slot g ^ swizzle(r): the four rows that a matrix instruction
+// reads 16 features of then take all 64 banks.
+template <int R>
+__device__ inline int swizzle(int r) { return R == 1 ? 0 : R == 2 ? 4 * ((r >> 1) & 1) : 4 * (r & 3); }
 
 template <int R>
 __device__ __forceinline__ void wgrad_f32_tile(const WgradItem& p, const WgradGroup& grp, const Segs& segs,
                                                uint32_t block, uint4* ring_area) {
-  constexpr int NB = R == 1 ? 12 : 6, S = 16 * R, C = 2 * R;    // copies per block: R of dy, R of x
+  constexpr int NB = R == 1 ? 12 : R == 2 ? 6 : 4, S = 16 * R, C = 2 * R;   // copies per block: R of dy, R of x
   constexpr uint32_t SLOT = C * KB;
-  static_assert(NB * SLOT == WGRAD_RING, "ring");
+  static_assert(NB * SLOT == WGRAD_RING<R>, "ring");
+  const int part = (int)block / p.tiles;
   int ti, tj;
-  tile_of_block(block, (p.M + S - 1) / S, (p.N + S - 1) / S, ti, tj);
+  tile_of_block((int)block - part * p.tiles, (p.M + S - 1) / S, (p.N + S - 1) / S, ti, tj);
   const int lane = threadIdx.x, l15 = lane & 15, kg = lane >> 4;
   const int i0 = ti * S, j0 = tj * S;
+  const int g0 = part * p.per, g1 = min(g0 + p.per, segs.K);
   const uint32_t lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)&ring_area[0];
   const bool bias = j0 == 0;
 
@@ -213,13 +220,13 @@ __device__ __forceinline__ void wgrad_f32_tile(const WgradItem& p, const WgradGr
   const float lamv = grp.lam[lane];
   struct Pos { int g, r, end; };           // worker, first row of the block, end of the worker's rows
   auto enter = [&](Pos& c) {
-    const int g = c.g < segs.K ? c.g : segs.K - 1;
+    const int g = c.g < g1 ? c.g : g1 - 1;
     c.end = g + 1 < segs.K ? __builtin_amdgcn_readlane(offv, g + 1) : total;
-    c.r = c.g < segs.K ? __builtin_amdgcn_readlane(offv, g) : c.end;
+    c.r = c.g < g1 ? __builtin_amdgcn_readlane(offv, g) : c.end;
   };
   auto next = [&](Pos& c) {                // true: another worker
     c.r += 16;
-    if (c.r < c.end || c.g >= segs.K) return false;
+    if (c.r < c.end || c.g >= g1) return false;
     ++c.g;
     enter(c);
     return true;
@@ -230,9 +237,11 @@ __device__ __forceinline__ void wgrad_f32_tile(const WgradItem& p, const WgradGr
   const int lrow = lane / LPR;
   const char* src[C];
   const int64_t pitch[2] = {p.lda * 4, p.ldb * 4};
+  const int64_t row0 = segs.off[g0];
 #pragma unroll
   for (int c = 0; c < C; ++c) {
-    const int row = lrow + (16 / R) * (c % R), g = R == 1 ? lane & 3 : (lane & 7) ^ (4 * ((row >> 1) & 1));
+    const int64_t row = row0 + lrow + (16 / R) * (c % R);
+    const int r = (int)(row - row0), g = (lane & (LPR - 1)) ^ swizzle<R>(r);
     src[c] = c < R ? (const char*)((const float*)p.A + row * p.lda + i0 + 4 * g)
                    : (const char*)((const float*)p.B + row * p.ldb + j0 + 4 * g);
   }
@@ -253,7 +262,7 @@ __device__ __forceinline__ void wgrad_f32_tile(const WgradItem& p, const WgradGr
   uint32_t at[R];
 #pragma unroll
   for (int u = 0; u < R; ++u)              // (row 4t + kg: its swizzle does not depend on t)
-    at[u] = R == 1 ? 64 * kg + 4 * l15 : 128 * kg + 64 * (u ^ ((kg >> 1) & 1)) + 4 * l15;
+    at[u] = 64 * R * kg + ((64 * u) ^ (16 * swizzle<R>(kg))) + 4 * l15;
   auto fetch_one = [&](int set, uint32_t slot, int t) {
 #pragma unroll
     for (int u = 0; u < R; ++u) {
@@ -262,13 +271,14 @@ __device__ __forceinline__ void wgrad_f32_tile(const WgradItem& p, const WgradGr
       f[set][R + u][t] = *(const float*)(a + R * KB);
     }
   };
-  f32x4 acc[R][R], agg[R][R];              // [x block][dy block]
+  constexpr bool AVERAGE = R != 4;         // (its registers would halve the waves)
+  f32x4 acc[R][R], agg[AVERAGE ? R : 1][R];   // [x block][dy block]
   float bsum[R], bagg[R];
 #pragma unroll
   for (int u = 0; u < R; ++u) {
     bsum[u] = bagg[u] = 0.f;
 #pragma unroll
-    for (int w = 0; w < R; ++w) acc[u][w] = agg[u][w] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int w = 0; w < R; ++w) acc[u][w] = agg[AVERAGE ? u : 0][w] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
   // accumulator element v of a lane: row (x feature) 4 * kg + v, column (dy feature) l15
   auto store = [&](float* out, const f32x4 (&v)[R][R]) {
@@ -286,13 +296,13 @@ __device__ __forceinline__ void wgrad_f32_tile(const WgradItem& p, const WgradGr
       }
   };
 
-  int todo = 0;                            // blocks of all workers
-  for (int k = 0; k < segs.K; ++k) {
+  int todo = 0;                            // blocks of these workers
+  for (int k = g0; k < g1; ++k) {
     const int n = segs.off[k + 1] - segs.off[k];
     todo += n > 0 ? (n + 15) / 16 : 1;
   }
   Pos cc, ic;                              // block being computed, next block to copy
-  cc.g = 0;
+  cc.g = g0;
   enter(cc);
   ic = cc;
 #pragma unroll
@@ -343,7 +353,7 @@ __device__ __forceinline__ void wgrad_f32_tile(const WgradItem& p, const WgradGr
     for (int u = 0; u < R; ++u)
 #pragma unroll
       for (int w = 0; w < R; ++w) {
-        agg[u][w] += lam * acc[u][w];
+        if (AVERAGE) agg[AVERAGE ? u : 0][w] += lam * acc[u][w];
         acc[u][w] = f32x4{0.f, 0.f, 0.f, 0.f};
       }
     if (bias) {
@@ -365,22 +375,32 @@ __device__ __forceinline__ void wgrad_f32_tile(const WgradItem& p, const WgradGr
     step(1);
   }
   wait_pending<0>();                       // (no copy may land after the LDS has been given back)
-  if (!p.agg) return;
-  store(p.agg, agg);
-  if (bias && kg == 0) {
+  if constexpr (AVERAGE) {
+    if (!p.agg) return;
+    store(p.agg, agg);
+    if (bias && kg == 0) {
 #pragma unroll
-    for (int w = 0; w < R; ++w)
-      if (i0 + 16 * w + l15 < p.M) p.bias_agg[i0 + 16 * w + l15] = bagg[w];
+      for (int w = 0; w < R; ++w)
+        if (i0 + 16 * w + l15 < p.M) p.bias_agg[i0 + 16 * w + l15] = bagg[w];
+    }
   }
 }
 
 __global__ __launch_bounds__(64) void wgrad_f32_kernel(WgradGroup grp, Segs segs) {
-  __shared__ uint4 ring_area[WGRAD_RING / 16];
+  __shared__ uint4 ring_area[WGRAD_RING<2> / 16];
   int q = 0;
   while (q + 1 < grp.n && (int)blockIdx.x >= grp.item[q + 1].first) ++q;
   const WgradItem& p = grp.item[q];
   if (p.wide) wgrad_f32_tile<2>(p, grp, segs, blockIdx.x - p.first, ring_area);
   else wgrad_f32_tile<1>(p, grp, segs, blockIdx.x - p.first, ring_area);
+}
+
+// (a kernel of its own: its registers would halve the waves of the other two)
+__global__ __launch_bounds__(64) void wgrad_f32_large_kernel(WgradGroup grp, Segs segs) {
+  __shared__ uint4 ring_area[WGRAD_RING<4> / 16];
+  int q = 0;
+  while (q + 1 < grp.n && (int)blockIdx.x >= grp.item[q + 1].first) ++q;
+  wgrad_f32_tile<4>(grp.item[q], grp, segs, blockIdx.x - grp.item[q].first, ring_area);
 }
 
 template <int R>
@@ -395,53 +415,104 @@ void launch_as(const GemmArgs& a, unsigned blocks, hipStream_t st) {
 }  // namespace
 
 // 2 x 2 tiles per wave once that gives each of the chip's 1024 SIMDs a wave: below that the chain
-// of one wave, four times as long, outweighs the halved copies
+// of one wave, four times as long, outweighs the halved copies.
 static int64_t tiles_with(const GemmArgs& a, int side) {
   return (int64_t)((a.M + side - 1) / side) * ((a.N + side - 1) / side);
 }
-static bool wide_tiles(const GemmArgs& a) { return tiles_with(a, 32) >= 1024; }
+static int tile_side(const GemmArgs& a) { return tiles_with(a, 32) >= 1024 ? 32 : 16; }
+
+// Weight gradients take 4 x 4 where that gives each SIMD a wave with the workers side by side: half the
+// copies again, but a wave too long to walk all workers, so the average is a pass of its own.  Both
+// layers of 1024-1024-1024, 16 workers: 1024 rows 93 us and 27 of pass against 136, 4096 rows 209
+// against 350, 16384 rows 683 against 1223 (64 x 64 vector-unit tiles and transposed copies: 172, 342,
+// 1069 us and the pass); below 1024 rows 2 x 2 with the average inside is ahead (512 rows 105, 112).
+static int wgrad_side(const GemmArgs& a, const Segs& s) {
+  return tiles_with(a, 64) * s.K >= 1024 && s.off[s.K] >= 1024 ? 64 : tile_side(a);
+}
+
+// Workers per wave of a weight gradient that leaves the average to another pass.  Six waves of the
+// smaller tiles fit on a compute unit (64 x 10, 16 workers: 512 rows 22 -> 7 us, 4096 rows 66 -> 11,
+// 16384 rows 217 -> 27 against one wave per tile).  Four of 64 x 64 ones do: the least of (rounds of
+// waves) x (workers each), with the longest walks that give it (3072 x 512, 8 workers, 16384 rows: 695
+// us with 4 workers per wave, 632 with 1).
+static int workers_per_wave(const GemmArgs& a, const Segs& s, int side) {
+  const int64_t tiles = tiles_with(a, side);
+  if (side != 64) {
+    const int64_t shares = 1536 / tiles;
+    return shares < 1 ? s.K : shares > s.K ? 1 : (s.K + (int)shares - 1) / (int)shares;
+  }
+  int best = s.K;
+  int64_t least = INT64_MAX;
+  for (int per = s.K; per >= 1; --per) {
+    const int64_t cost = (tiles * ((s.K + per - 1) / per) + 1023) / 1024 * per;
+    if (cost < least) {
+      least = cost;
+      best = per;
+    }
+  }
+  return best;
+}
+
+bool wgrad_f32_can_fold(const GemmArgs& a, const Segs& s) { return wgrad_side(a, s) != 64; }
+bool wgrad_f32_walks(const GemmArgs& a, const Segs& s) {
+  const int side = wgrad_side(a, s);
+  return side != 64 && workers_per_wave(a, s, side) == s.K;
+}
+// (a wave of 16 x 16 tiles takes 0.06 us per 16 rows and 0.7 us per worker; larger tiles fill the chip)
+bool wgrad_f32_folds(const GemmArgs& a, const Segs& s) {
+  const int per = workers_per_wave(a, s, wgrad_side(a, s));
+  return fold_pays(0.7 * s.K + 0.0036 * s.off[s.K], (s.K + per - 1) / per, (int64_t)a.M * a.N, s.K);
+}
 
 int launch_gemm_f32(const GemmArgs& a, void* stream) {
   if (a.mode == MODE_WGRAD || a.K % 32 != 0)
     return fail(DYNB_ERR_BADARG, "gemm: fp32 products take whole 32-deep blocks");
-  const bool wide = wide_tiles(a);
-  const int64_t n = tiles_with(a, wide ? 32 : 16);
+  const int side = tile_side(a);
+  const int64_t n = tiles_with(a, side);
   if (n >= (int64_t)1 << 31) return fail(DYNB_ERR_UNSUPPORTED, "gemm: too many tiles for one launch");
-  if (wide) launch_as<2>(a, (unsigned)n, (hipStream_t)stream);
+  if (side == 32) launch_as<2>(a, (unsigned)n, (hipStream_t)stream);
   else launch_as<1>(a, (unsigned)n, (hipStream_t)stream);
   return hipGetLastError() == hipSuccess ? DYNB_OK : fail(DYNB_ERR_HIP, "gemm launch failed");
 }
 
 int launch_wgrad_f32(const GemmArgs* a, int n, const Segs& s, void* stream) {
   if (n > WGRAD_F32_ITEMS) return fail(DYNB_ERR_BADARG, "gemm: too many weight gradients for one launch");
-  WgradGroup grp = {};
-  grp.zeros = device_zero_granule();
-  if (!grp.zeros) return fail(DYNB_ERR_HIP, "gemm: no address for the zero granule");
+  const void* const zeros = device_zero_granule();
+  if (!zeros) return fail(DYNB_ERR_HIP, "gemm: no address for the zero granule");
+  WgradGroup group[2] = {};                // the layers of 64 x 64 tiles; the others
+  int64_t blocks[2] = {0, 0};
   double flops = 0, bytes = 0;
-  int64_t blocks = 0;
   for (int q = 0; q < n; ++q) {
     const GemmArgs& g = a[q];
     if (g.M <= 0 || g.N <= 0) continue;
-    if (g.mode != MODE_WGRAD || !g.bias_grad || (g.agg && !g.bias_agg) ||
+    const int side = wgrad_side(g, s), which = side == 64 ? 0 : 1;
+    WgradGroup& grp = group[which];
+    if (g.mode != MODE_WGRAD || !g.bias_grad || (g.agg && (!g.bias_agg || side == 64)) ||
         (grp.n && g.group_stride != grp.group_stride))
       return fail(DYNB_ERR_BADARG, "gemm: an fp32 weight gradient writes the bias gradient too");
     if ((g.lda & 3) || (g.ldb & 3) || (((uintptr_t)g.A | (uintptr_t)g.B) & 15))
       return fail(DYNB_ERR_BADARG, "gemm: operands must have 16-byte aligned rows");
-    const bool wide = wide_tiles(g);
-    const int64_t tiles = tiles_with(g, wide ? 32 : 16);
-    if (blocks + tiles >= (int64_t)1 << 31)
+    const int64_t tiles = tiles_with(g, side);
+    if (blocks[which] + tiles * s.K >= (int64_t)1 << 31)
       return fail(DYNB_ERR_UNSUPPORTED, "gemm: too many tiles for one launch");
-    grp.item[grp.n++] = {g.A, g.B, g.lda, g.ldb, g.ldcf, g.M, g.N, (int)blocks, wide, g.Cf, g.bias_grad,
-                         g.agg, g.bias_agg};
+    const int per = g.agg ? s.K : workers_per_wave(g, s, side);
+    grp.item[grp.n++] = {g.A, g.B, g.lda, g.ldb, g.ldcf, g.M, g.N, (int)blocks[which], side == 32, (int)tiles,
+                         per, g.Cf, g.bias_grad, g.agg, g.bias_agg};
     grp.group_stride = g.group_stride;
-    for (int k = 0; k < s.K; ++k) grp.lam[k] = g.lam[k];   // (of the call: the same for every layer)
-    blocks += tiles;
+    grp.zeros = zeros;
+    if (g.agg)
+      for (int k = 0; k < s.K; ++k) grp.lam[k] = g.lam[k];   // (of the call: the same for every layer)
+    blocks[which] += tiles * ((s.K + per - 1) / per);
     flops += g.alg_flops;
     bytes += g.alg_bytes;
   }
-  if (!grp.n) return DYNB_OK;
+  if (!blocks[0] && !blocks[1]) return DYNB_OK;
   Timed t(KC_GEMM_WGRAD, stream, flops, bytes);
-  hipLaunchKernelGGL(wgrad_f32_kernel, dim3((unsigned)blocks), dim3(64), 0, (hipStream_t)stream, grp, s);
+  const hipStream_t st = (hipStream_t)stream;
+  if (blocks[0])
+    hipLaunchKernelGGL(wgrad_f32_large_kernel, dim3((unsigned)blocks[0]), dim3(64), 0, st, group[0], s);
+  if (blocks[1])
+    hipLaunchKernelGGL(wgrad_f32_kernel, dim3((unsigned)blocks[1]), dim3(64), 0, st, group[1], s);
   return hipGetLastError() == hipSuccess ? DYNB_OK : fail(DYNB_ERR_HIP, "gemm launch failed");
 }
 

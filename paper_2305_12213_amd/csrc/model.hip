@@ -445,16 +445,29 @@ int run_forward_backward(dynb_model* m, const float* x, const int32_t* y, const 
   Ranges small;
   small.n = 0;
   // weight gradients of dense layers that share a launch and are not launched yet: fp32 ones, or bf16
-  // ones of few tiles
-  std::vector<GemmArgs> group;
+  // ones of few tiles; and those of them whose average is a pass behind that launch
+  static_assert(WGRAD_F32_ITEMS == WGRAD_SMALL_ITEMS, "one limit");
+  GemmArgs group[WGRAD_F32_ITEMS];
+  int64_t pass_off[WGRAD_F32_ITEMS], pass_len[WGRAD_F32_ITEMS];
+  int grouped_n = 0, passes = 0;
   auto flush_group = [&]() -> int {
-    const int n = (int)group.size();
-    const int r = n == 0 ? (int)DYNB_OK
-                  : dt == DYNB_F32 ? launch_wgrad_f32(group.data(), n, s1, stream)
-                                   : launch_wgrad_small(group.data(), n, s1, stream);
-    group.clear();
+    int r = grouped_n == 0 ? (int)DYNB_OK
+            : dt == DYNB_F32 ? launch_wgrad_f32(group, grouped_n, s1, stream)
+                             : launch_wgrad_small(group, grouped_n, s1, stream);
+    for (int i = 0; i < passes && !r; ++i)
+      r = launch_aggregate_range(grads + pass_off[i], m->P_pad, lam, pass_len[i], agg + pass_off[i], stream);
+    grouped_n = passes = 0;
     return r;
   };
+  // (one workgroup walks all workers of a tile of some layer in any case: walks of other layers, to form
+  // their averages, run beside it at no cost)
+  bool walked = false;
+  for (const Layer& L : m->layers) {
+    if (!agg || L.kind != DYNB_LAYER_DENSE || dt != DYNB_F32) continue;
+    GemmArgs g = {};
+    g.mode = MODE_WGRAD; g.M = L.n_out; g.N = L.n_in;
+    walked = walked || wgrad_f32_walks(g, s1);
+  }
   auto flush_small = [&]() {
     const int g = flush_group();   // (whose results are read here)
     if (g) return g;
@@ -535,7 +548,8 @@ int run_forward_backward(dynb_model* m, const float* x, const int32_t* y, const 
     }
     // the aggregate of this weight: in the same kernel while the per-worker tiles are in
     // registers where the launch shape allows it, else by a pass over what was written
-    const bool fold = agg && gemm_fuses_aggregate(dt, g, segs[l]);
+    const bool fold = agg && gemm_fuses_aggregate(dt, g, segs[l]) &&
+                      (dt != DYNB_F32 || walked || wgrad_f32_folds(g, s1));
     if (fold) {
       g.alg_bytes += (double)L.wg_rows * L.n_out * 4;   // the aggregated tile is written too
       g.agg = agg + L.w_off;
@@ -548,9 +562,9 @@ int run_forward_backward(dynb_model* m, const float* x, const int32_t* y, const 
     // one launch for as many layers as it takes
     const bool grouped = dt == DYNB_F32 || (split <= 1 && gemm_small_applies(g));
     if (grouped) {
-      static_assert(WGRAD_F32_ITEMS == WGRAD_SMALL_ITEMS, "one limit");
-      group.push_back(g);
-      if (group.size() == WGRAD_F32_ITEMS) rc = flush_group();
+      if (grouped_n == WGRAD_F32_ITEMS) rc = flush_group();
+      if (rc) return rc;
+      group[grouped_n++] = g;
     } else {
       rc = launch_gemm(dt, g, segs[l], stream);
     }
@@ -566,9 +580,10 @@ int run_forward_backward(dynb_model* m, const float* x, const int32_t* y, const 
     }
     if (agg) {
       const int64_t nw = (int64_t)L.wg_rows * L.n_out;
-      if (!fold && nw >= 65536) {
-        if (grouped) rc = flush_group();
-        if (rc) return rc;
+      if (!fold && nw >= AGGREGATE_ALONE && grouped) {
+        pass_off[passes] = L.w_off;
+        pass_len[passes++] = nw;
+      } else if (!fold && nw >= AGGREGATE_ALONE) {
         rc = launch_aggregate_range(grads + L.w_off, m->P_pad, lam, nw, agg + L.w_off, stream);
         if (rc) return rc;
       } else if (!fold) {

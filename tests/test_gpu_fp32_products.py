@@ -1,7 +1,7 @@
 """The fp32 matrix products where their tiling can go wrong: widths and batches around 16 and 32
-(tile sides, the two tile counts per wave), reductions shorter than the ring of blocks, idle and
-one-row workers, workers that end inside a 16-row block, and inputs that are read in place or, for
-their width or alignment, packed first.  Gradients, biases and their weighted average against the
+(tile sides, the tile counts per wave), reductions shorter than the ring of blocks, idle and
+one-row workers, workers walked by one wave and divided over waves, workers that end inside a 16-row
+block, and inputs that are read in place or, for their width or alignment, packed first.  Gradients, biases and their weighted average against the
 float64 oracle; 1e-4 is the fp32 bound of the other parity tests."""
 import numpy as np
 import pytest
@@ -24,6 +24,9 @@ pytestmark = pytest.mark.gpu
     ([1000, 1041, 5], [3, 18], 0),           # ... and one that leaves less than a tile
     ([48, 2], [1] * 64, 0),
     ([20, 17, 16, 40, 33, 9, 18, 16, 15, 12, 10, 3], [5, 0, 18], 0),   # more layers than one launch takes
+    ([70, 20, 5], [900, 0, 300, 1, 17, 64, 30], 0),       # workers side by side, average in the last launch
+    ([300, 320, 5], [300, 0, 300, 1, 17, 64, 30], 0),     # ... two per wave and one left, average by a pass
+    ([130, 1030, 5], [0, 40] + [16, 17, 15] * 20 + [33, 0], 0),   # 64 x 64 tiles, ragged on both sides
 ])
 def test_fp32_products_at_the_edges_of_their_tiles(dims, b, shift):
     import torch
@@ -119,6 +122,7 @@ def test_input_gradient_is_one_chain(m, classes):
     (77, 16, [64, 32, 8]),
     (1000, 1024, [64, 16]),          # 2 x 2 tiles
     (40, 4, [1024, 512, 2048]),
+    (200, 1024, [64] * 14 + [128] + [1]),   # 64 x 64 tiles
 ])
 def test_weight_gradient_is_one_chain_per_worker(n, classes, b):
     rng = np.random.default_rng(33)
