@@ -142,16 +142,19 @@ bool wgrad_f32_folds(const GemmArgs& a, const Segs& s);
 // over K results of `weights` floats.
 constexpr int64_t AGGREGATE_ALONE = 65536;   // from so many on, a launch of its own (else part of the last)
 bool fold_pays(double walk_us, int shares, int64_t weights, int K);
-// bf16 products with few tiles (gemm_small.hip): whether one (unsplit) counts as such, whether its
-// weight gradient can take GemmArgs::agg, and the launch.
+// bf16 products with few tiles (gemm_small.hip): whether one (unsplit) counts as such, and the launch.
 bool gemm_small_applies(const GemmArgs& a);
-bool gemm_small_folds(const GemmArgs& a, const Segs& s);
 int launch_gemm_small(const GemmArgs& a, void* stream);   // forward / input gradient
 // weight gradients of up to WGRAD_SMALL_ITEMS such layers (all over the same rows) in one launch
 constexpr int WGRAD_SMALL_ITEMS = 8;
 int launch_wgrad_small(const GemmArgs* a, int n, const Segs& s, void* stream);
-// Whether a weight-gradient launch of these dimensions can take GemmArgs::agg.
-bool gemm_fuses_aggregate(int dtype, const GemmArgs& a, const Segs& s);
+// whether that is faster than the 128 x 128-tile kernel (and, with `average`, a pass over its results);
+// the other two as for fp32
+bool wgrad_small_pays(const GemmArgs& a, const Segs& s, bool average);
+bool wgrad_small_walks(const GemmArgs& a, const Segs& s);
+bool wgrad_small_folds(const GemmArgs& a, const Segs& s);
+// Whether a bf16 weight-gradient launch of launch_gemm of these dimensions can take GemmArgs::agg.
+bool gemm_fuses_aggregate(int dtype, const GemmArgs& a);
 // out[e] = sum_k lam.w[k] * g[k*worker_stride + e], e < n, ascending k (any alignment)
 int launch_aggregate_range(const float* g, int64_t worker_stride, const Lambdas& lam, int64_t n,
                            float* out, void* stream);

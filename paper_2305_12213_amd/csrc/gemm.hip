@@ -1027,19 +1027,20 @@ void launch_bf16_gather(GemmArgs a, const Segs& s, hipStream_t st) {
 
 }  // namespace
 
-// The pass over the results costs what reading them takes (5.8 TB/s), or a launch (4 us); below
-// AGGREGATE_ALONE weights it is part of the last launch of the call, and next to free.
+// Results are written at 4.4 TB/s at best.  The pass over them costs what reading them takes (5.8 TB/s),
+// or a launch (5 us); below AGGREGATE_ALONE weights it is part of the last launch of the call, and next
+// to free.
 bool fold_pays(double walk_us, int shares, int64_t weights, int K) {
-  const double read_us = 4.0 * K * weights / 5.8e6;
-  const double pass_us = weights < AGGREGATE_ALONE ? 0.5 : read_us > 4.0 ? read_us : 4.0;
-  return walk_us - walk_us / shares <= pass_us;
+  const double read_us = 4.0 * K * weights / 5.8e6, write_us = 4.0 * K * weights / 4.4e6;
+  const double pass_us = weights < AGGREGATE_ALONE ? 0.5 : read_us > 5.0 ? read_us : 5.0;
+  const double share_us = walk_us / shares > write_us ? walk_us / shares : write_us;
+  return walk_us - share_us <= pass_us;
 }
 
-bool gemm_fuses_aggregate(int dtype, const GemmArgs& a, const Segs& s) {
-  if (dtype == DYNB_F32) return a.mode == MODE_WGRAD && wgrad_f32_can_fold(a, s);
+bool gemm_fuses_aggregate(int dtype, const GemmArgs& a) {
   // enough tiles to occupy the compute units without splitting the workers over workgroups
-  if (dtype != DYNB_BF16 || a.mode != MODE_WGRAD || a.conv || a.split > 1) return false;
-  return tiles_of(a, AGG_SMALL, AGG_SMALL) >= 256 || gemm_small_folds(a, s);
+  return dtype == DYNB_BF16 && a.mode == MODE_WGRAD && !a.conv && a.split <= 1 &&
+         tiles_of(a, AGG_SMALL, AGG_SMALL) >= 256;
 }
 
 int launch_gemm(int dtype, const GemmArgs& args, const Segs& s, void* stream) {
@@ -1047,7 +1048,7 @@ int launch_gemm(int dtype, const GemmArgs& args, const Segs& s, void* stream) {
   a.zeros = device_zero_granule();
   if (!a.zeros) return fail(DYNB_ERR_HIP, "gemm: no address for the zero granule");
   if (a.M <= 0 || a.N <= 0) return DYNB_OK;
-  if (a.agg && !gemm_fuses_aggregate(dtype, a, s))
+  if (a.agg && !gemm_fuses_aggregate(dtype, a))
     return fail(DYNB_ERR_UNSUPPORTED, "gemm: this weight gradient cannot fold the aggregation in");
   const int es = dtype == DYNB_BF16 ? 2 : 4;
   const int gran = 16 / es;
@@ -1085,7 +1086,7 @@ int launch_gemm(int dtype, const GemmArgs& args, const Segs& s, void* stream) {
     if (conv_direct_applies(dtype, a)) return launch_conv_direct(a, stream);
     if (conv_flat_applies(dtype, a)) return launch_conv_flat(a, stream);
     launch_bf16_gather(a, s, (hipStream_t)stream);
-  } else if (dtype == DYNB_BF16 && a.split <= 1 && gemm_small_applies(a)) {
+  } else if (dtype == DYNB_BF16 && a.mode != MODE_WGRAD && gemm_small_applies(a)) {
     return launch_gemm_small(a, stream);
   } else if (dtype == DYNB_BF16 && a.agg) {
     launch_bf16_wgrad_agg(a, s, (hipStream_t)stream);

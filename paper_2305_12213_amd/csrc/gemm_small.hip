@@ -275,21 +275,48 @@ int64_t tiles64(const GemmArgs& a) { return (int64_t)((a.M + T - 1) / T) * ((a.N
 
 }  // namespace
 
+static int64_t large_tiles(const GemmArgs& a) { return (int64_t)((a.M + 127) / 128) * ((a.N + 127) / 128); }
+
 // Up to half as many 128 x 128 tiles as compute units (at 204 of them, 1531 x 2050 x 1024, those take
 // 16 us and these 20); weight gradients, whose larger tiles would have to divide the workers or leave
 // the average to another pass, up to the 256 at which the large kernel folds it in.
 bool gemm_small_applies(const GemmArgs& a) {
   if (a.conv) return false;
-  const int64_t large = (int64_t)((a.M + 127) / 128) * ((a.N + 127) / 128);
-  if (a.mode != MODE_WGRAD) return a.K % 64 == 0 && large < 128;
-  return large < 256;
+  if (a.mode != MODE_WGRAD) return a.K % 64 == 0 && large_tiles(a) < 128;
+  return large_tiles(a) < 256;
 }
 
-// Whether the average is formed in the same launch: one workgroup then walks all rows of its tile
-// (about 0.1 us per 32 rows), which pays once the tiles alone fill a quarter of the chip or the
-// walk is short; else the workers run side by side and the average is left to another pass.
-bool gemm_small_folds(const GemmArgs& a, const Segs& s) {
-  return gemm_small_applies(a) && (tiles64(a) >= 64 || s.K == 1 || s.off[s.K] <= 512);
+// Parts that the workers of a tile are divided into where the average is left to another pass: until
+// the chip is full.
+static int worker_parts(const GemmArgs& a, int K) {
+  const int64_t parts = 512 / tiles64(a);
+  return parts < 1 ? 1 : parts > K ? K : (int)parts;
+}
+
+bool wgrad_small_walks(const GemmArgs& a, const Segs& s) { return worker_parts(a, s.K) == 1; }
+
+// Walking all workers takes a workgroup 1 us per worker and 0.18 us per 32 rows.  Folded, and with a pass
+// (kernel times): 64 x 10, 64 workers, 512 rows 71 and 7 + 14 us; 512 x 1024, 16 workers, 4096 rows 44
+// and 19 + 10; 1024 x 1024, 16 workers, 1024 rows 28 and 18 + 15; 784 x 128, 2 workers, 512 rows 11 and
+// 8 + 6.
+bool wgrad_small_folds(const GemmArgs& a, const Segs& s) {
+  return fold_pays(s.K + 0.0055 * s.off[s.K], worker_parts(a, s.K), (int64_t)a.M * a.N, s.K);
+}
+
+// Matrix work is cheaper on 128 x 128 tiles, results are cheaper to leave from 64 x 64 ones, above all
+// where rows of the result are no whole lines.  So the large ones take over with enough of them and
+// enough rows per worker (kernel times on small and large tiles, 16 workers, at 1024, 4096 and 16384
+// rows: 1024 x 1024 18, 29, 75 us and 22, 29, 59; 1024 x 2048 28, 52, 141 and 30, 44, 100; 1500 x 1500
+// 71, 64, 211 and 106, 112, 181; 2048 x 256 12, 18, 39 and 13, 19, 37; 768 x 768, whose 36 large tiles
+// divide the chip badly, 14, 23, 54 and 22, 27, 56) -- later where these would leave the average to a
+// pass and a workgroup of the small ones walks all workers anyway (1024 x 2048, average included: 30,
+// 55, 141 and 57, 71, 127).
+bool wgrad_small_pays(const GemmArgs& a, const Segs& s, bool average) {
+  const int64_t rows = s.off[s.K], large = large_tiles(a);
+  if (large < 64) return large != 32 || s.K < 16 || rows < 16384 || rows < 256 * s.K;
+  if (average && worker_parts(a, s.K) == 1) return rows < 16384 || rows < 512 * s.K;
+  if (a.ldcf % 32) return rows < 8192 || rows * large < (int64_t)131072 * s.K;
+  return rows < (s.K < 4 ? 4096 : 2048) || rows * large < (int64_t)16384 * s.K;
 }
 
 int launch_gemm_small(const GemmArgs& a, void* stream) {
@@ -314,19 +341,16 @@ int launch_wgrad_small(const GemmArgs* a, int n, const Segs& s, void* stream) {
   for (int q = 0; q < n; ++q) {
     const GemmArgs& g = a[q];
     if (g.M <= 0 || g.N <= 0) continue;
-    if (!gemm_small_applies(g) || !g.bias_grad || g.split > 1 || (g.agg && !gemm_small_folds(g, s)) ||
+    if (!gemm_small_applies(g) || !g.bias_grad || g.split > 1 ||
         (grp.n && g.group_stride != grp.group_stride))
       return fail(DYNB_ERR_BADARG, "gemm: not a weight gradient of few tiles with its bias gradient");
     if ((g.lda & 7) || (g.ldb & 7) || (((uintptr_t)g.A | (uintptr_t)g.B) & 15))
       return fail(DYNB_ERR_BADARG, "gemm: operands must have 16-byte aligned rows");
     if (s.off[s.K] * g.lda * 2 >= (int64_t)1 << 31 || s.off[s.K] * g.ldb * 2 >= (int64_t)1 << 31)
       return fail(DYNB_ERR_UNSUPPORTED, "gemm: an operand of 2 GiB or more (rows * pitch) is not supported");
-    // the average needs one workgroup to walk all workers of its tile; without it the workers are
-    // divided until the chip is full
+    // (the average needs one workgroup to walk all workers of its tile)
     const int64_t tiles = tiles64(g);
-    int parts = g.agg ? 1 : (int)(512 / tiles);
-    parts = parts < 1 ? 1 : parts > s.K ? s.K : parts;
-    const int per = (s.K + parts - 1) / parts;
+    const int parts = g.agg ? 1 : worker_parts(g, s.K), per = (s.K + parts - 1) / parts;
     grp.item[grp.n++] = {g.A, g.B, g.lda, g.ldb, g.ldcf, g.M, g.N, (int)blocks, (int)tiles, per, g.Cf,
                          g.bias_grad, g.agg};
     grp.group_stride = g.group_stride;

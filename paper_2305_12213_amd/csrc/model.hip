@@ -463,10 +463,11 @@ int run_forward_backward(dynb_model* m, const float* x, const int32_t* y, const 
   // their averages, run beside it at no cost)
   bool walked = false;
   for (const Layer& L : m->layers) {
-    if (!agg || L.kind != DYNB_LAYER_DENSE || dt != DYNB_F32) continue;
+    if (!agg || L.kind != DYNB_LAYER_DENSE || walked) continue;
     GemmArgs g = {};
-    g.mode = MODE_WGRAD; g.M = L.n_out; g.N = L.n_in;
-    walked = walked || wgrad_f32_walks(g, s1);
+    g.mode = MODE_WGRAD; g.M = L.n_out; g.N = L.n_in; g.ldcf = L.n_out;
+    walked = dt == DYNB_F32 ? wgrad_f32_walks(g, s1)
+                            : gemm_small_applies(g) && wgrad_small_pays(g, s1, true) && wgrad_small_walks(g, s1);
   }
   auto flush_small = [&]() {
     const int g = flush_group();   // (whose results are read here)
@@ -539,17 +540,21 @@ int run_forward_backward(dynb_model* m, const float* x, const int32_t* y, const 
     split = split > L.max_split ? L.max_split : split;
     // (up to 4096 rows the small-tile kernel walks a worker's rows faster -- 13 us -- than they are
     // divided, summed and the biases formed in three launches)
-    if (dt == DYNB_BF16 && B <= 4096 && gemm_small_applies(g)) split = 1;
+    const bool small = dt == DYNB_BF16 && gemm_small_applies(g) && wgrad_small_pays(g, s1, agg != nullptr);
+    if (small && B <= 4096) split = 1;
     if (split > 1) {
       g.split = split;
       g.chunk = (int)round_up((deepest + split - 1) / split, 64);
       g.partial = m->partial;
       g.partial_stride = round_up((int64_t)L.wg_rows * L.n_out, 64);
     }
+    // (one launch for as many layers as it takes)
+    const bool grouped = dt == DYNB_F32 || (split <= 1 && small);
     // the aggregate of this weight: in the same kernel while the per-worker tiles are in
-    // registers where the launch shape allows it, else by a pass over what was written
-    const bool fold = agg && gemm_fuses_aggregate(dt, g, segs[l]) &&
-                      (dt != DYNB_F32 || walked || wgrad_f32_folds(g, s1));
+    // registers where the launch shape allows it and it pays, else by a pass over what was written
+    const bool fold = agg && (!grouped         ? gemm_fuses_aggregate(dt, g)
+                              : dt == DYNB_F32 ? wgrad_f32_can_fold(g, s1) && (walked || wgrad_f32_folds(g, s1))
+                                               : walked || wgrad_small_folds(g, s1));
     if (fold) {
       g.alg_bytes += (double)L.wg_rows * L.n_out * 4;   // the aggregated tile is written too
       g.agg = agg + L.w_off;
@@ -559,8 +564,6 @@ int run_forward_backward(dynb_model* m, const float* x, const int32_t* y, const 
     // unsplit: the bias gradient is formed by the same kernel
     const bool bias_inside = split <= 1;
     if (bias_inside) g.bias_grad = grads + L.b_off;
-    // one launch for as many layers as it takes
-    const bool grouped = dt == DYNB_F32 || (split <= 1 && gemm_small_applies(g));
     if (grouped) {
       if (grouped_n == WGRAD_F32_ITEMS) rc = flush_group();
       if (rc) return rc;
