@@ -421,13 +421,35 @@ static int64_t tiles_with(const GemmArgs& a, int side) {
 }
 static int tile_side(const GemmArgs& a) { return tiles_with(a, 32) >= 1024 ? 32 : 16; }
 
-// Weight gradients take 4 x 4 where that gives each SIMD a wave with the workers side by side: half the
-// copies again, but a wave too long to walk all workers, so the average is a pass of its own.  Both
-// layers of 1024-1024-1024, 16 workers: 1024 rows 93 us and 27 of pass against 136, 4096 rows 209
-// against 350, 16384 rows 683 against 1223 (64 x 64 vector-unit tiles and transposed copies: 172, 342,
-// 1069 us and the pass); below 1024 rows 2 x 2 with the average inside is ahead (512 rows 105, 112).
+// Weight gradients may take 4 x 4, half the copies again, by a wave too long to walk all workers: the
+// average is then a pass of its own.
+static bool large_possible(const GemmArgs& a, const Segs& s) { return tiles_with(a, 64) * s.K >= 256; }
 static int wgrad_side(const GemmArgs& a, const Segs& s) {
-  return tiles_with(a, 64) * s.K >= 1024 && s.off[s.K] >= 1024 ? 64 : tile_side(a);
+  return a.large_tiles && large_possible(a, s) ? 64 : tile_side(a);
+}
+
+// It pays on many rows, where what bounds the smaller tiles is fetching operands: 0.25 us per 16 rows for
+// 1024 tiles of 16 x 16, 0.6 for 32 x 32.  A wave of 64 x 64 takes 1.25 us per 16 rows of its worker, so
+// there have to be workers, or layers in the same launch, enough for 1024 waves; the longest worker
+// counts.  1024-1024-1024, 16 workers, both layers: 1024 rows 93 us and 27 of pass against 136, 16384
+// rows 683 against 1223 (64 x 64 vector-unit tiles and transposed copies: 172 and 1069, and the pass).
+// Iterations of 512-512-512-512, 65536 rows: 8 workers 4.5 ms against 7.7, 4 workers 5.1 against 7.7;
+// of 512-512, 4 workers, 16384 rows: 687 us against 463.
+bool wgrad_f32_large(const GemmArgs* layers, int n, const Segs& s) {
+  const double rows = s.off[s.K];
+  double longest = 0, small_us = 0, large_tiles = 0;
+  for (int k = 0; k < s.K; ++k) {
+    const double b = s.off[k + 1] - s.off[k];
+    longest = b > longest ? b : longest;
+  }
+  for (int q = 0; q < n; ++q) {
+    if (!large_possible(layers[q], s)) continue;
+    const int side = tile_side(layers[q]);
+    small_us += (side == 32 ? 0.6 : 0.25) * tiles_with(layers[q], side) / 1024 * rows / 16;
+    large_tiles += tiles_with(layers[q], 64);
+  }
+  const double work = rows * large_tiles / 1024;
+  return rows >= 1024 && 1.25 * (longest > work ? longest : work) / 16 < small_us;
 }
 
 // Workers per wave of a weight gradient that leaves the average to another pass.  Six waves of the
