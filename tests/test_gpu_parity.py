@@ -601,3 +601,30 @@ def test_flat_convolutions(image, channels):
     b = [2, 0, 3]
     x, y = synth.make_batch(spec, "normal", sum(b), 96, 0)
     check_worker_gradients(spec, params, x, y, b, label="flat conv %s %s" % (image, channels))
+
+
+@pytest.mark.parametrize("image,channels,stride", [
+    ((9, 20), 24, 1),             # against the kernel on flat runs of pixels
+    ((5, 70), 40, 1),             # ... the gathered product, for images too wide for it
+    ((8, 32), 64, 1),             # ... the halo tiles of 32-wide images
+    ((9, 13), 72, 2),             # ... the gathered product, strided
+])
+def test_first_convolution_rounds_like_the_general_kernels(image, channels, stride):
+    # a fourth channel of zeros takes the general kernels: the same sums in the same order, so the
+    # loss and the gradients of the layers above agree bit for bit
+    three = {"dtype": "bf16", "input": image + (3,), "classes": 4,
+             "layers": [synth.conv3x3(3, channels, stride), synth.gap(), synth.dense(channels, 4, relu=False)]}
+    four = dict(three, input=image + (4,), layers=[synth.conv3x3(4, channels, stride)] + three["layers"][1:])
+    params = synth.init_params(three, "he", 51)
+    params[0] = (params[0][0], np.linspace(-0.2, 0.2, channels, dtype=np.float32))
+    wide = [(np.pad(params[0][0], ((0, 0), (0, 0), (0, 1), (0, 0))), params[0][1])] + params[1:]
+    b = [3, 0, 2]
+    x, y = synth.make_batch(three, "normal", sum(b), 52, 0)
+    got = []
+    for spec, p, xs in ((three, params, x), (four, wide, np.pad(x, ((0, 0), (0, 0), (0, 0), (0, 1))))):
+        run = DeviceRun(spec, p, sum(b), len(b))
+        g = worker_grads_as_lists(spec, run.forward_backward(xs, y, b).cpu().numpy(), run.P)
+        got.append((run.losses(len(b)), [k[1] for k in g]))
+    assert list(got[0][0]) == list(got[1][0])
+    for stem, general in zip(got[0][1], got[1][1]):
+        assert np.array_equal(stem[0], general[0]) and np.array_equal(stem[1], general[1])
