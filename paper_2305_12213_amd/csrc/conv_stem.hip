@@ -17,7 +17,6 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
@@ -146,10 +145,6 @@ constexpr int ROWS_P = 144;                // bytes per patch row
 constexpr int DY_STAGE = 64 * 128;
 constexpr int PART = 2 * 16 * 64;          // floats of a chunk result: [channel half][4 quads][lane] x 4
 
-__device__ inline s16x4 read_tr(uint32_t lds_addr) {
-  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(uintptr_t)lds_addr);
-}
-
 template <int CIN>
 __global__ __launch_bounds__(256) void stem_wgrad_kernel(StemArgs p, Segs segs, RowChunks ch) {
   __shared__ __align__(16) uint4 dyring[3 * DY_STAGE / 16];
@@ -226,7 +221,7 @@ __global__ __launch_bounds__(256) void stem_wgrad_kernel(StemArgs p, Segs segs, 
     for (int s = 0; s < 2; ++s) {
       const int step = 2 * s + ks;
       const uint32_t a = buf + foff + (uint32_t)(step * 16 * 128);
-      const s16x4 lo = read_tr(a), hi = read_tr(a + 4 * 128);
+      const s16x4 lo = lds_read_tr(a), hi = lds_read_tr(a + 4 * 128);
       const s16x8 d = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
       const bf16x8 x8 = *(const bf16x8*)&patch[t & 1][l31 * ROWS_P + (step * 16 + 8 * h) * 2];
       acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, d), x8, acc, 0, 0, 0);

@@ -29,7 +29,6 @@ namespace {
 
 typedef __bf16 bf16;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -50,11 +49,6 @@ __device__ inline void wait_copies(int stages) {   // at most `stages` stages of
     case 1: asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PER) : "memory"); break;
     default: asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * PER) : "memory"); break;
   }
-}
-
-__device__ inline s16x4 read_tr(uint32_t lds_addr) {
-  return __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-      (__attribute__((address_space(3))) s16x4*)(uintptr_t)lds_addr);
 }
 
 // worker, first row and row count of a chunk
@@ -187,7 +181,7 @@ __global__ __launch_bounds__(256 * G) void conv_wgrad_chunk_kernel(ConvWgradArgs
   const uint32_t foff_b = (uint32_t)(fpix * 128 + ((wco ^ fswap) * 64)) + fcol;
   auto frag = [&](uint32_t tile, uint32_t foff, int kk) {   // 8 reduction indices of k-step kk
     const uint32_t a = tile + foff + (uint32_t)(kk * 16 * 128);
-    const s16x4 lo = read_tr(a), hi = read_tr(a + 4 * 128);
+    const s16x4 lo = lds_read_tr(a), hi = lds_read_tr(a + 4 * 128);
     const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
     return __builtin_bit_cast(bf16x8, v);
   };
@@ -340,7 +334,7 @@ __global__ __launch_bounds__(256 * G) void conv_wgrad_rows_kernel(ConvWgradArgs 
   const uint32_t foff_b = (uint32_t)(fpix * 128 + ((wco ^ ((r >> 3) & 1)) * 64)) + fcol;
   auto frag = [&](uint32_t tile, uint32_t foff, int kk) {
     const uint32_t a = tile + foff + (uint32_t)(kk * 16 * 128);
-    const s16x4 lo = read_tr(a), hi = read_tr(a + 4 * 128);
+    const s16x4 lo = lds_read_tr(a), hi = lds_read_tr(a + 4 * 128);
     const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
     return __builtin_bit_cast(bf16x8, v);
   };
@@ -533,7 +527,7 @@ __global__ __launch_bounds__(256, 2) void conv_wgrad_flat_kernel(ConvWgradArgs p
     foff_a[i] = (tap / 3) * F::IN_TILE + offset(fpix + tap % 3, wci, CI);
   }
   auto frag = [&](uint32_t a0, uint32_t a1) {
-    const s16x4 lo = read_tr(a0), hi = read_tr(a1);
+    const s16x4 lo = lds_read_tr(a0), hi = lds_read_tr(a1);
     const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
     return __builtin_bit_cast(bf16x8, v);
   };

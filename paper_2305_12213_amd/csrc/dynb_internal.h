@@ -43,7 +43,6 @@ enum KClass {
   KC_GEMM_DGRAD,
   KC_GEMM_WGRAD,
   KC_PACK,
-  KC_TRANSPOSE,
   KC_SOFTMAX,
   KC_BIAS_GRAD,
   KC_FINALIZE,
@@ -54,6 +53,8 @@ enum KClass {
   KC_NORM,
   KC_GEMM_WGRAD_SMALL,   // bf16 weight gradients that run on the 128 x 128-tile kernels
   KC_GEMM_SMALL,         // bf16 forward / input-gradient products on the 128 x 128-tile kernel
+  KC_GEMM_WGRAD_64,      // bf16 weight gradients on the 64 x 64-tile kernel
+  KC_GEMM_64,            // bf16 forward / input-gradient products on the 64 x 64-tile kernel
   KC_COUNT
 };
 

@@ -88,7 +88,7 @@ struct PatchArea<0> {
 // parity per direction only -- one row tap for even y, two for odd y -- so the pixels of each of the
 // four parity classes (blockIdx.y) form a product of their own, with 1, 2, 2 or 4 of the 9 taps.  Nine
 // taps of which five to eight read zeros cost 51 and 111 us on the 8 x 8 <- 16 x 16 and 16 x 16 <- 32 x
-// 32 layers of the 32-64-128 model at 512 images; by classes PARA and PARB.
+// 32 layers of the 32-64-128 model at 512 images; by classes 23 and 49.
 template <int BM, int BN, int WM, int WN, int MODE, bool GATHER, int S, bool AGG = false, bool PAR = false>
 __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmArgs p, Segs segs) {
   constexpr bool RM = MODE == MODE_WGRAD;
@@ -352,11 +352,8 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmArgs p, Seg
           sy = gy[u] * p.stride + kh - 1;
           sx = gx[u] * p.stride + kw - 1;
         } else {
-          // (stride is 1 or 2: a shift instead of a division in the hot loop)
-          const int ty = gy[u] + 1 - kh, tx = gx[u] + 1 - kw, sh = p.stride - 1;
-          sy = ty >> sh;
-          sx = tx >> sh;
-          ok = ok && ty >= 0 && tx >= 0 && (sy << sh) == ty && (sx << sh) == tx;
+          sy = gy[u] + 1 - kh;                     // (stride 1: stride 2 goes by parity classes)
+          sx = gx[u] + 1 - kw;
         }
         ok = ok && sy >= 0 && sy < p.src_h && sx >= 0 && sx < p.src_w;
         const int64_t pix = (int64_t)offA[u] + sy * p.src_w + sx;
@@ -391,12 +388,8 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmArgs p, Seg
     for (int b = 0; b < TN; ++b) trB[b] = tr_off(wn * (BN / WN) + b * 32, BN * 2);
   }
   auto tr_frag = [&](uint32_t addr, int pitch) {
-    typedef short s16x4 __attribute__((ext_vector_type(4)));
     typedef short s16x8 __attribute__((ext_vector_type(8)));
-    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-        (__attribute__((address_space(3))) s16x4*)(uintptr_t)addr);
-    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-        (__attribute__((address_space(3))) s16x4*)(uintptr_t)(addr + 4 * pitch));
+    const s16x4 lo = lds_read_tr(addr), hi = lds_read_tr(addr + 4 * pitch);
     const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
     return __builtin_bit_cast(bf16x8, v);
   };
@@ -1005,11 +998,10 @@ void launch_bf16_gather(GemmArgs a, const Segs& s, hipStream_t st) {
   a.gather_log2cp = -1;
   const int64_t src_bytes = ((int64_t)((a.M + a.row_h * a.row_w - 1) / (a.row_h * a.row_w)) * a.src_h *
                              a.src_w + 1) * a.lda * 2;
-  if (a.cp >= 32 && (a.cp & (a.cp - 1)) == 0 && !(a.conv == 2 && a.stride != 1) &&
-      src_bytes < ((int64_t)1 << 31))
+  if (a.cp >= 32 && (a.cp & (a.cp - 1)) == 0 && src_bytes < ((int64_t)1 << 31))
     for (int l = 5; l < 31; ++l)
       if ((1 << l) == a.cp) a.gather_log2cp = l;
-  if (a.conv == 2 && a.stride == 2 && src_bytes < ((int64_t)1 << 31)) {   // (32-bit source offsets)
+  if (a.conv == 2 && a.stride == 2) {
     const int64_t most = (int64_t)(a.M / (a.row_h * a.row_w)) * ((a.row_h + 1) / 2) * ((a.row_w + 1) / 2);
     const int bm = a.N <= 64 ? 256 : 128, bn = a.N <= 64 ? 64 : 128;
     const dim3 grid((unsigned)(((most + bm - 1) / bm) * ((a.N + bn - 1) / bn)), 4);
@@ -1069,15 +1061,15 @@ int launch_gemm(int dtype, const GemmArgs& args, const Segs& s, void* stream) {
     return fail(DYNB_ERR_UNSUPPORTED, "gemm: an addend belongs to a bf16 input gradient");
   KClass cls = a.mode == MODE_FWD ? KC_GEMM_FWD : a.mode == MODE_DGRAD ? KC_GEMM_DGRAD
                                                                         : KC_GEMM_WGRAD;
-  // (the two tile sizes of the bf16 weight gradient are different kernels with different
-  // bounds: timed apart, so that a class's average launch is one kernel's)
+  // (the tile sizes of the bf16 products are different kernels with different bounds: timed apart, so
+  // that a class's average launch is one kernel's)
   if (a.mode == MODE_WGRAD && dtype == DYNB_BF16 && !a.conv) {
     const bool large = a.agg ? tiles_of(a, AGG_BM, AGG_BN) >= 256
                              : (int64_t)((a.M + 255) / 256) * ((a.N + 255) / 256) >= 192;
     if (!large) cls = KC_GEMM_WGRAD_SMALL;
   } else if (dtype == DYNB_BF16 && !a.conv &&
              (int64_t)((a.M + 255) / 256) * ((a.N + 255) / 256) < 192) {
-    cls = KC_GEMM_SMALL;
+    cls = gemm_small_applies(a) ? KC_GEMM_64 : KC_GEMM_SMALL;
   }
   Timed t(cls, stream, a.alg_flops, a.alg_bytes);
   if (a.conv) {

@@ -16,7 +16,6 @@ namespace {
 typedef __bf16 bf16;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
@@ -30,8 +29,8 @@ __device__ inline int swizzle(int r) { return (((r >> 1) & 3) << 1) | ((r >> 3) 
 
 // Forward and input gradient: C[i][j] = sum_k A[i][k] B[j][k].  A stage is 64 reduction elements, the
 // whole 128-byte line of each of the 64 + 64 operand rows (16 copies, four per wave); ring of NB
-// stages, NB - 1 in flight (eight instead of four changed nothing: 17.4 against 17.7 us below).  Copies past the last stage are still issued (the wait stays a constant);
-// what they read -- the next rows, zeros past the matrix -- is never used.
+// stages, NB - 1 in flight (eight instead of four changed nothing: 17.4 against 17.7 us below).  Copies
+// past the last stage are still issued (the wait stays a constant); what they read -- the next rows, zeros past the matrix -- is never used.
 // Against 128 x 128 tiles: 1024 x 1024 x 3072 30 -> 18 us, 1024 x 10 x 1024 14 -> 6, 1531 x 777 x 2050
 // 23 -> 18.
 constexpr int NB = 4, STAGE = 2 * T * 128;
@@ -149,8 +148,7 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(GemmArgs p) {
 constexpr int WNB = 6, WSTAGE = 2 * 32 * 128;
 
 __device__ inline bf16x8 read_tr(uint32_t a) {   // rows 4 apart: same swizzle
-  const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(uintptr_t)a);
-  const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(uintptr_t)(a + 512));
+  const s16x4 lo = lds_read_tr(a), hi = lds_read_tr(a + 512);
   const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
   return __builtin_bit_cast(bf16x8, v);
 }
@@ -361,7 +359,7 @@ int launch_wgrad_small(const GemmArgs* a, int n, const Segs& s, void* stream) {
     bytes += g.alg_bytes;
   }
   if (!grp.n) return DYNB_OK;
-  Timed t(KC_GEMM_WGRAD_SMALL, stream, flops, bytes);
+  Timed t(KC_GEMM_WGRAD_64, stream, flops, bytes);
   hipLaunchKernelGGL(wgrad_small_kernel, dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream, grp, s);
   return hipGetLastError() == hipSuccess ? DYNB_OK : fail(DYNB_ERR_HIP, "gemm launch failed");
 }

@@ -1,5 +1,5 @@
-// Small kernels around the GEMMs: input packing, softmax cross-entropy with the per-worker 1/b_k, bias gradients, loss reduction and the
-// 16-bit weight copies.
+// Small kernels around the GEMMs: input packing, softmax cross-entropy with the per-worker 1/b_k, bias
+// gradients and loss reduction.
 #include <hip/hip_runtime.h>
 
 #include "device_rows.h"

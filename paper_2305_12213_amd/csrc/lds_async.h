@@ -38,6 +38,13 @@ __device__ inline void async_copy_1k_buffer(i32x4 rsrc, uint32_t voffset, uint32
                : "memory", "m0");
 }
 
+// LDS transpose read: within 16 lanes, lane r supplies the address of 4 neighbouring 16-bit elements of
+// row r / 4, and lane l receives element l of each of the 4 rows.
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+__device__ inline s16x4 lds_read_tr(uint32_t lds_addr) {
+  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(uintptr_t)lds_addr);
+}
+
 // Address, on the current device, of 16 bytes of zeros: what lanes outside an image or a chunk
 // copy instead (a copy cannot be predicated to zero).  Passed to kernels as an argument, which
 // stays in scalar registers; nullptr if the lookup fails.

@@ -27,7 +27,7 @@ struct Layer {
   int64_t ld_in = 0, ld_out = 0;     // channel pitch of input / output rows
   int cin_p = 0, cout_p = 0;         // conv: channels per tap, padded to 8
   int kf = 0, kd = 0;                // conv: reduction length forward / input gradient (x64)
-  int wg_rows = 0;                   // rows of the transposed weight-gradient operand
+  int wg_rows = 0;                   // weights per output feature or channel
   int64_t w_off = 0, b_off = 0;      // offsets into the flat parameter vector
   bool relu = false, has_params = false;
   void* Wn = nullptr;                // B operand of the input-gradient GEMM
