@@ -23,15 +23,15 @@ PEAK = {"mfma_bf16": 2500.0, "fp32": 157.3, "hbm": 8000.0}   # TFLOP/s, TFLOP/s,
 
 # Bytes per launch from rocprofv3 FETCH_SIZE / WRITE_SIZE (scaled by a plain copy of known
 # size; profiles/bench_workload4_rocprofv3.md), valid for workload 4 and only as long as the
-# kernel source they were taken from is unchanged (sha1 of the file, first 12 hex digits).
-# "gemm_wgrad" on workload 4 is the 256 x 128-tile aggregating kernel alone (three launches per
-# step); the output layer's 128 x 128-tile launch is the class "gemm_wgrad_small_tiles".
+# sources of the kernel that they were taken from are unchanged (sha1 over the files, first 12
+# hex digits).  "gemm_wgrad" on workload 4 is the 256 x 128-tile aggregating kernel alone (three
+# launches per step); the output layer's 128 x 128-tile launch is the class "gemm_wgrad_small_tiles".
+CSRC = os.path.join("paper_2305_12213_amd", "csrc")
 MEASURED_TRAFFIC = {
-    "gemm_wgrad": {"bytes_per_launch": 1.5658e9, "source": "paper_2305_12213_amd/csrc/gemm.hip",
-                   "sha1": "f3ee997b0be1"},
+    "gemm_wgrad": {"bytes_per_launch": 1.5791e9, "sources": ("gemm.hip", "tile_map.h", "lds_async.h"),
+                   "sha1": "575d5463baf8"},
     # one launch per step: the four weight matrices with their 16-bit copies, and the biases
-    "sgd_update": {"bytes_per_launch": 8.837e8,
-                   "source": "paper_2305_12213_amd/csrc/kernels_update.hip", "sha1": "2c2b1d0ac685"},
+    "sgd_update": {"bytes_per_launch": 8.837e8, "sources": ("kernels_update.hip",), "sha1": "2c2b1d0ac685"},
 }
 
 
@@ -40,11 +40,14 @@ def measured_traffic(kernel, workload):
     m = MEASURED_TRAFFIC.get(kernel)
     if not m or workload != 4:
         return None
+    sha = hashlib.sha1()
     try:
-        sha = hashlib.sha1(open(os.path.join(ROOT, m["source"]), "rb").read()).hexdigest()[:12]
+        for name in m["sources"]:
+            with open(os.path.join(ROOT, CSRC, name), "rb") as f:
+                sha.update(f.read())
     except OSError:
         return None
-    return m["bytes_per_launch"] if sha == m["sha1"] else None
+    return m["bytes_per_launch"] if sha.hexdigest()[:12] == m["sha1"] else None
 
 
 def main():
