@@ -100,7 +100,6 @@ struct GemmArgs {
   // bias_agg[i] (bf16: left to the pass over the small tensors).
   float* bias_grad;
   float* bias_agg;
-  int large_tiles;                     // WGRAD, fp32: see wgrad_f32_large()
   // Implicit-GEMM gather of operand A for a 3x3 convolution with zero padding 1 (bf16 only).
   // conv == 0: A is a plain matrix.  conv == 1 (forward): row i is output pixel (n, y, x) of a
   // row_h x row_w grid and reduction index k = (kh*3 + kw)*cp + c reads channel c of source
@@ -135,11 +134,8 @@ int launch_gemm_f32(const GemmArgs& a, void* stream);   // forward / input gradi
 // fp32 weight gradients of up to WGRAD_F32_ITEMS layers (all over the same rows) in one launch
 constexpr int WGRAD_F32_ITEMS = 8;
 int launch_wgrad_f32(const GemmArgs* a, int n, const Segs& s, void* stream);
-// whether the weight gradients of a call (M, N of each) had better take large tiles where they can
-bool wgrad_f32_large(const GemmArgs* layers, int n, const Segs& s);
-// whether a wave can walk all workers of its tile and form the average, whether one walks them in any
-// case (the tiles fill the chip), and whether walking them costs less than a pass over their results
-bool wgrad_f32_can_fold(const GemmArgs& a, const Segs& s);
+// whether a wave walks all workers of its tile in any case (the tiles fill the chip), and whether walking
+// them, to form the average, costs less than a pass over their results
 bool wgrad_f32_walks(const GemmArgs& a, const Segs& s);
 bool wgrad_f32_folds(const GemmArgs& a, const Segs& s);
 // The choice behind it: a walk over all workers of `walk_us`, against a `shares`-th of it and a pass

@@ -51,7 +51,10 @@ __device__ inline void wait_reads() {
 // 49 -> 11 us.
 template <int MODE, int R>
 __global__ __launch_bounds__(64) void gemm_f32_kernel(GemmArgs p) {
-  constexpr int NB = R == 1 ? 10 : 4, S = 16 * R;               // S: tile side
+  // (40 KB either way: four waves on a compute unit, one per SIMD.  Four blocks of 2 x 2 tiles left room
+  // for a fifth wave, and launches of many waves went in uneven rounds: 1024 x 1024 x 4096 134 -> 100
+  // us, 2048 x 2048 x 4096 457 -> 354)
+  constexpr int NB = R == 1 ? 10 : 5, S = 16 * R;               // S: tile side
   constexpr int G = 2 * R, C = 2 * G;                           // 16-row groups and copies per block
   constexpr uint32_t SLOT = C * KB;
   __shared__ uint4 ring_area[NB * SLOT / 16];
@@ -190,19 +193,21 @@ struct WgradGroup {
   const void* zeros;
   float lam[DYNB_MAX_WORKERS];
 };
-template <int R> constexpr uint32_t WGRAD_RING = (R == 4 ? 32 : 24) * KB;
+// (20 KB: eight waves on a compute unit, two per SIMD.  24 left room for six, and launches of many waves
+// went in uneven rounds: 1024 x 1024, 4096 rows, one worker 150 -> 95 us)
+constexpr uint32_t WGRAD_RING = 20 * KB;
 
 // Granule g of a block's row r sits at slot g ^ swizzle(r): the four rows that a matrix instruction
 // reads 16 features of then take all 64 banks.
 template <int R>
-__device__ inline int swizzle(int r) { return R == 1 ? 0 : R == 2 ? 4 * ((r >> 1) & 1) : 4 * (r & 3); }
+__device__ inline int swizzle(int r) { return R == 1 ? 0 : 4 * ((r >> 1) & 1); }
 
 template <int R>
 __device__ __forceinline__ void wgrad_f32_tile(const WgradItem& p, const WgradGroup& grp, const Segs& segs,
                                                uint32_t block, uint4* ring_area) {
-  constexpr int NB = R == 1 ? 12 : R == 2 ? 6 : 4, S = 16 * R, C = 2 * R;   // copies per block: R of dy, R of x
+  constexpr int NB = R == 1 ? 10 : 5, S = 16 * R, C = 2 * R;   // copies per block: R of dy, R of x
   constexpr uint32_t SLOT = C * KB;
-  static_assert(NB * SLOT == WGRAD_RING<R>, "ring");
+  static_assert(NB * SLOT == WGRAD_RING, "ring");
   const int part = (int)block / p.tiles;
   int ti, tj;
   tile_of_block((int)block - part * p.tiles, (p.M + S - 1) / S, (p.N + S - 1) / S, ti, tj);
@@ -271,14 +276,13 @@ __device__ __forceinline__ void wgrad_f32_tile(const WgradItem& p, const WgradGr
       f[set][R + u][t] = *(const float*)(a + R * KB);
     }
   };
-  constexpr bool AVERAGE = R != 4;         // (its registers would halve the waves)
-  f32x4 acc[R][R], agg[AVERAGE ? R : 1][R];   // [x block][dy block]
+  f32x4 acc[R][R], agg[R][R];              // [x block][dy block]
   float bsum[R], bagg[R];
 #pragma unroll
   for (int u = 0; u < R; ++u) {
     bsum[u] = bagg[u] = 0.f;
 #pragma unroll
-    for (int w = 0; w < R; ++w) acc[u][w] = agg[AVERAGE ? u : 0][w] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int w = 0; w < R; ++w) acc[u][w] = agg[u][w] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
   // accumulator element v of a lane: row (x feature) 4 * kg + v, column (dy feature) l15
   auto store = [&](float* out, const f32x4 (&v)[R][R]) {
@@ -353,7 +357,7 @@ __device__ __forceinline__ void wgrad_f32_tile(const WgradItem& p, const WgradGr
     for (int u = 0; u < R; ++u)
 #pragma unroll
       for (int w = 0; w < R; ++w) {
-        if (AVERAGE) agg[AVERAGE ? u : 0][w] += lam * acc[u][w];
+        agg[u][w] += lam * acc[u][w];
         acc[u][w] = f32x4{0.f, 0.f, 0.f, 0.f};
       }
     if (bias) {
@@ -375,32 +379,22 @@ __device__ __forceinline__ void wgrad_f32_tile(const WgradItem& p, const WgradGr
     step(1);
   }
   wait_pending<0>();                       // (no copy may land after the LDS has been given back)
-  if constexpr (AVERAGE) {
-    if (!p.agg) return;
-    store(p.agg, agg);
-    if (bias && kg == 0) {
+  if (!p.agg) return;
+  store(p.agg, agg);
+  if (bias && kg == 0) {
 #pragma unroll
-      for (int w = 0; w < R; ++w)
-        if (i0 + 16 * w + l15 < p.M) p.bias_agg[i0 + 16 * w + l15] = bagg[w];
-    }
+    for (int w = 0; w < R; ++w)
+      if (i0 + 16 * w + l15 < p.M) p.bias_agg[i0 + 16 * w + l15] = bagg[w];
   }
 }
 
 __global__ __launch_bounds__(64) void wgrad_f32_kernel(WgradGroup grp, Segs segs) {
-  __shared__ uint4 ring_area[WGRAD_RING<2> / 16];
+  __shared__ uint4 ring_area[WGRAD_RING / 16];
   int q = 0;
   while (q + 1 < grp.n && (int)blockIdx.x >= grp.item[q + 1].first) ++q;
   const WgradItem& p = grp.item[q];
   if (p.wide) wgrad_f32_tile<2>(p, grp, segs, blockIdx.x - p.first, ring_area);
   else wgrad_f32_tile<1>(p, grp, segs, blockIdx.x - p.first, ring_area);
-}
-
-// (a kernel of its own: its registers would halve the waves of the other two)
-__global__ __launch_bounds__(64) void wgrad_f32_large_kernel(WgradGroup grp, Segs segs) {
-  __shared__ uint4 ring_area[WGRAD_RING<4> / 16];
-  int q = 0;
-  while (q + 1 < grp.n && (int)blockIdx.x >= grp.item[q + 1].first) ++q;
-  wgrad_f32_tile<4>(grp.item[q], grp, segs, blockIdx.x - grp.item[q].first, ring_area);
 }
 
 template <int R>
@@ -421,68 +415,26 @@ static int64_t tiles_with(const GemmArgs& a, int side) {
 }
 static int tile_side(const GemmArgs& a) { return tiles_with(a, 32) >= 1024 ? 32 : 16; }
 
-// Weight gradients may take 4 x 4, half the copies again, by a wave too long to walk all workers: the
-// average is then a pass of its own.
-static bool large_possible(const GemmArgs& a, const Segs& s) { return tiles_with(a, 64) * s.K >= 256; }
-static int wgrad_side(const GemmArgs& a, const Segs& s) {
-  return a.large_tiles && large_possible(a, s) ? 64 : tile_side(a);
-}
+// For a weight gradient the workers count too: they are divided over waves (512 x 512, 16 workers, 16384
+// rows 165 -> 136 us; three such layers, 8 workers, 65536 rows, whose operands no longer stay in the
+// caches, forward and backward 6700 -> 3925; with 4 workers and 1024 rows 47 -> 39).
+static int wgrad_side(const GemmArgs& a, const Segs& s) { return tiles_with(a, 32) * s.K >= 1024 ? 32 : 16; }
 
-// It pays on many rows, where what bounds the smaller tiles is fetching operands: 0.25 us per 16 rows for
-// 1024 tiles of 16 x 16, 0.6 for 32 x 32.  A wave of 64 x 64 takes 1.25 us per 16 rows of its worker, so
-// there have to be workers, or layers in the same launch, enough for 1024 waves; the longest worker
-// counts.  1024-1024-1024, 16 workers, both layers: 1024 rows 93 us and 27 of pass against 136, 16384
-// rows 683 against 1223 (64 x 64 vector-unit tiles and transposed copies: 172 and 1069, and the pass).
-// Iterations of 512-512-512-512, 65536 rows: 8 workers 4.5 ms against 7.7, 4 workers 5.1 against 7.7;
-// of 512-512, 4 workers, 16384 rows: 687 us against 463.
-bool wgrad_f32_large(const GemmArgs* layers, int n, const Segs& s) {
-  const double rows = s.off[s.K];
-  double longest = 0, small_us = 0, large_tiles = 0;
-  for (int k = 0; k < s.K; ++k) {
-    const double b = s.off[k + 1] - s.off[k];
-    longest = b > longest ? b : longest;
-  }
-  for (int q = 0; q < n; ++q) {
-    if (!large_possible(layers[q], s)) continue;
-    const int side = tile_side(layers[q]);
-    small_us += (side == 32 ? 0.6 : 0.25) * tiles_with(layers[q], side) / 1024 * rows / 16;
-    large_tiles += tiles_with(layers[q], 64);
-  }
-  const double work = rows * large_tiles / 1024;
-  return rows >= 1024 && 1.25 * (longest > work ? longest : work) / 16 < small_us;
+// Workers per wave of a weight gradient that leaves the average to another pass: eight waves of this ring
+// fit on a compute unit (64 x 10, 16 workers: 512 rows 22 -> 7 us, 4096 rows 66 -> 11, 16384 rows 217 ->
+// 27 against one wave per tile).
+static int workers_per_wave(const GemmArgs& a, int K, int side) {
+  const int64_t shares = 2048 / tiles_with(a, side);
+  return shares < 1 ? K : shares > K ? 1 : (K + (int)shares - 1) / (int)shares;
 }
-
-// Workers per wave of a weight gradient that leaves the average to another pass.  Six waves of the
-// smaller tiles fit on a compute unit (64 x 10, 16 workers: 512 rows 22 -> 7 us, 4096 rows 66 -> 11,
-// 16384 rows 217 -> 27 against one wave per tile).  Four of 64 x 64 ones do: the least of (rounds of
-// waves) x (workers each), with the longest walks that give it (3072 x 512, 8 workers, 16384 rows: 695
-// us with 4 workers per wave, 632 with 1).
-static int workers_per_wave(const GemmArgs& a, const Segs& s, int side) {
-  const int64_t tiles = tiles_with(a, side);
-  if (side != 64) {
-    const int64_t shares = 1536 / tiles;
-    return shares < 1 ? s.K : shares > s.K ? 1 : (s.K + (int)shares - 1) / (int)shares;
-  }
-  int best = s.K;
-  int64_t least = INT64_MAX;
-  for (int per = s.K; per >= 1; --per) {
-    const int64_t cost = (tiles * ((s.K + per - 1) / per) + 1023) / 1024 * per;
-    if (cost < least) {
-      least = cost;
-      best = per;
-    }
-  }
-  return best;
-}
-
-bool wgrad_f32_can_fold(const GemmArgs& a, const Segs& s) { return wgrad_side(a, s) != 64; }
-bool wgrad_f32_walks(const GemmArgs& a, const Segs& s) {
-  const int side = wgrad_side(a, s);
-  return side != 64 && workers_per_wave(a, s, side) == s.K;
-}
-// (a wave of 16 x 16 tiles takes 0.06 us per 16 rows and 0.7 us per worker; larger tiles fill the chip)
+bool wgrad_f32_walks(const GemmArgs& a, const Segs& s) { return workers_per_wave(a, s.K, wgrad_side(a, s)) == s.K; }
+// A wave of 16 x 16 tiles takes 0.06 us per 16 rows and 0.7 us per worker.  Where 2 x 2 tiles of divided
+// workers fill the chip instead, they are faster by 0.05 us per 16 rows and 1024 of the small ones, which
+// is worth a pass of 5 us from 1700 rows on (512 x 512, 8 workers, per layer with its average: 1024 rows
+// folded 16 us, with the pass 20; 576 x 576, 16384 rows, forward and backward: 455 and 378).
 bool wgrad_f32_folds(const GemmArgs& a, const Segs& s) {
-  const int per = workers_per_wave(a, s, wgrad_side(a, s));
+  if (wgrad_side(a, s) != tile_side(a) && tiles_with(a, 16) * s.off[s.K] > 1700 * 1024) return false;
+  const int per = workers_per_wave(a, s.K, tile_side(a));
   return fold_pays(0.7 * s.K + 0.0036 * s.off[s.K], (s.K + per - 1) / per, (int64_t)a.M * a.N, s.K);
 }
 
@@ -499,42 +451,39 @@ int launch_gemm_f32(const GemmArgs& a, void* stream) {
 
 int launch_wgrad_f32(const GemmArgs* a, int n, const Segs& s, void* stream) {
   if (n > WGRAD_F32_ITEMS) return fail(DYNB_ERR_BADARG, "gemm: too many weight gradients for one launch");
-  const void* const zeros = device_zero_granule();
-  if (!zeros) return fail(DYNB_ERR_HIP, "gemm: no address for the zero granule");
-  WgradGroup group[2] = {};                // the layers of 64 x 64 tiles; the others
-  int64_t blocks[2] = {0, 0};
+  WgradGroup grp = {};
+  grp.zeros = device_zero_granule();
+  if (!grp.zeros) return fail(DYNB_ERR_HIP, "gemm: no address for the zero granule");
   double flops = 0, bytes = 0;
+  int64_t blocks = 0, wide = 0;
+  for (int q = 0; q < n; ++q) wide += tiles_with(a[q], 32);
   for (int q = 0; q < n; ++q) {
     const GemmArgs& g = a[q];
     if (g.M <= 0 || g.N <= 0) continue;
-    const int side = wgrad_side(g, s), which = side == 64 ? 0 : 1;
-    WgradGroup& grp = group[which];
-    if (g.mode != MODE_WGRAD || !g.bias_grad || (g.agg && (!g.bias_agg || side == 64)) ||
+    if (g.mode != MODE_WGRAD || !g.bias_grad || (g.agg && !g.bias_agg) ||
         (grp.n && g.group_stride != grp.group_stride))
       return fail(DYNB_ERR_BADARG, "gemm: an fp32 weight gradient writes the bias gradient too");
     if ((g.lda & 3) || (g.ldb & 3) || (((uintptr_t)g.A | (uintptr_t)g.B) & 15))
       return fail(DYNB_ERR_BADARG, "gemm: operands must have 16-byte aligned rows");
+    // (a wave that folds the average in walks all workers: then the tiles alone have to fill the chip,
+    // those of all layers together -- three of 512 x 512, 1024 rows: 43 us, and 53 with 2 x 2 tiles)
+    const int side = g.agg && wide < 1024 ? 16 : wgrad_side(g, s);
     const int64_t tiles = tiles_with(g, side);
-    if (blocks[which] + tiles * s.K >= (int64_t)1 << 31)
+    const int per = g.agg ? s.K : workers_per_wave(g, s.K, side);
+    if (blocks + tiles * ((s.K + per - 1) / per) >= (int64_t)1 << 31)
       return fail(DYNB_ERR_UNSUPPORTED, "gemm: too many tiles for one launch");
-    const int per = g.agg ? s.K : workers_per_wave(g, s, side);
-    grp.item[grp.n++] = {g.A, g.B, g.lda, g.ldb, g.ldcf, g.M, g.N, (int)blocks[which], side == 32, (int)tiles,
+    grp.item[grp.n++] = {g.A, g.B, g.lda, g.ldb, g.ldcf, g.M, g.N, (int)blocks, side == 32, (int)tiles,
                          per, g.Cf, g.bias_grad, g.agg, g.bias_agg};
     grp.group_stride = g.group_stride;
-    grp.zeros = zeros;
     if (g.agg)
       for (int k = 0; k < s.K; ++k) grp.lam[k] = g.lam[k];   // (of the call: the same for every layer)
-    blocks[which] += tiles * ((s.K + per - 1) / per);
+    blocks += tiles * ((s.K + per - 1) / per);
     flops += g.alg_flops;
     bytes += g.alg_bytes;
   }
-  if (!blocks[0] && !blocks[1]) return DYNB_OK;
+  if (!grp.n) return DYNB_OK;
   Timed t(KC_GEMM_WGRAD, stream, flops, bytes);
-  const hipStream_t st = (hipStream_t)stream;
-  if (blocks[0])
-    hipLaunchKernelGGL(wgrad_f32_large_kernel, dim3((unsigned)blocks[0]), dim3(64), 0, st, group[0], s);
-  if (blocks[1])
-    hipLaunchKernelGGL(wgrad_f32_kernel, dim3((unsigned)blocks[1]), dim3(64), 0, st, group[1], s);
+  hipLaunchKernelGGL(wgrad_f32_kernel, dim3((unsigned)blocks), dim3(64), 0, (hipStream_t)stream, grp, s);
   return hipGetLastError() == hipSuccess ? DYNB_OK : fail(DYNB_ERR_HIP, "gemm launch failed");
 }
 

@@ -459,23 +459,15 @@ int run_forward_backward(dynb_model* m, const float* x, const int32_t* y, const 
     grouped_n = passes = 0;
     return r;
   };
-  // What the launches of the call's dense layers have to do with each other: whether they take large
-  // tiles (fp32), and whether one workgroup walks all workers of a tile of some layer in any case (walks
-  // of other layers, to form their averages, then run beside it at no cost).
-  GemmArgs dense[DYNB_MAX_LAYERS];
-  int dense_n = 0;
-  for (const Layer& L : m->layers) {
-    if (L.kind != DYNB_LAYER_DENSE) continue;
-    GemmArgs& g = dense[dense_n++] = {};
-    g.mode = MODE_WGRAD; g.M = L.n_out; g.N = L.n_in; g.ldcf = L.n_out;
-  }
-  const bool large_tiles = dt == DYNB_F32 && wgrad_f32_large(dense, dense_n, s1);
+  // (one workgroup walks all workers of a tile of some layer in any case: walks of other layers, to form
+  // their averages, run beside it at no cost)
   bool walked = false;
-  for (int q = 0; q < dense_n && agg && !walked; ++q) {
-    dense[q].large_tiles = large_tiles;
-    walked = dt == DYNB_F32 ? wgrad_f32_walks(dense[q], s1)
-                            : gemm_small_applies(dense[q]) && wgrad_small_pays(dense[q], s1, true) &&
-                                  wgrad_small_walks(dense[q], s1);
+  for (const Layer& L : m->layers) {
+    if (!agg || L.kind != DYNB_LAYER_DENSE || walked) continue;
+    GemmArgs g = {};
+    g.mode = MODE_WGRAD; g.M = L.n_out; g.N = L.n_in; g.ldcf = L.n_out;
+    walked = dt == DYNB_F32 ? wgrad_f32_walks(g, s1)
+                            : gemm_small_applies(g) && wgrad_small_pays(g, s1, true) && wgrad_small_walks(g, s1);
   }
   auto flush_small = [&]() {
     const int g = flush_group();   // (whose results are read here)
@@ -535,7 +527,6 @@ int run_forward_backward(dynb_model* m, const float* x, const int32_t* y, const 
     g.A = dyv[l]; g.lda = L.ld_out;   // the row-major tensors, reduced over each worker's rows
     g.B = in_act(l); g.ldb = L.ld_in;
     g.M = L.n_out; g.N = L.wg_rows;
-    g.large_tiles = large_tiles;
     g.Cf = grads + L.w_off; g.ldcf = L.n_out;
     g.group_stride = m->P_pad;
     g.alg_flops = 2.0 * B * L.hw_out * L.wg_rows * L.n_out;
@@ -562,7 +553,7 @@ int run_forward_backward(dynb_model* m, const float* x, const int32_t* y, const 
     // the aggregate of this weight: in the same kernel while the per-worker tiles are in
     // registers where the launch shape allows it and it pays, else by a pass over what was written
     const bool fold = agg && (!grouped         ? gemm_fuses_aggregate(dt, g)
-                              : dt == DYNB_F32 ? wgrad_f32_can_fold(g, s1) && (walked || wgrad_f32_folds(g, s1))
+                              : dt == DYNB_F32 ? walked || wgrad_f32_folds(g, s1)
                                                : walked || wgrad_small_folds(g, s1));
     if (fold) {
       g.alg_bytes += (double)L.wg_rows * L.n_out * 4;   // the aggregated tile is written too

@@ -26,7 +26,7 @@ pytestmark = pytest.mark.gpu
     ([20, 17, 16, 40, 33, 9, 18, 16, 15, 12, 10, 3], [5, 0, 18], 0),   # more layers than one launch takes
     ([70, 20, 5], [900, 0, 300, 1, 17, 64, 30], 0),       # workers side by side, average in the last launch
     ([300, 320, 5], [300, 0, 300, 1, 17, 64, 30], 0),     # ... two per wave and one left, average by a pass
-    ([130, 1030, 5], [0, 40] + [16, 17, 15] * 20 + [33, 0], 0),   # 64 x 64 tiles, ragged on both sides
+    ([130, 1030, 5], [0, 40] + [16, 17, 15] * 20 + [33, 0], 0),   # 2 x 2 tiles, six workers per wave, the last with four
 ])
 def test_fp32_products_at_the_edges_of_their_tiles(dims, b, shift):
     import torch
@@ -122,7 +122,7 @@ def test_input_gradient_is_one_chain(m, classes):
     (77, 16, [64, 32, 8]),
     (1000, 1024, [64, 16]),          # 2 x 2 tiles
     (40, 4, [1024, 512, 2048]),
-    (200, 1024, [64] * 14 + [128] + [1]),   # 64 x 64 tiles
+    (200, 1024, [64] * 14 + [128] + [1]),   # 2 x 2 tiles, two workers per wave
 ])
 def test_weight_gradient_is_one_chain_per_worker(n, classes, b):
     rng = np.random.default_rng(33)

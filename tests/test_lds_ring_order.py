@@ -9,7 +9,7 @@ import subprocess
 
 from paper_2305_12213_amd import build
 
-RING = 24     # copies of the smallest ring: so many without a matrix instruction fill it, unread so far
+RING = 20     # copies of the smallest ring: so many without a matrix instruction fill it, unread so far
 
 
 def kernels_of(asm):
@@ -63,7 +63,7 @@ def test_ring_slots_are_copied_into_after_their_reads(tmp_path):
                     os.path.join(build.CSRC, "gemm_f32.hip"), "-o", out], check=True, capture_output=True)
     with open(out) as f:
         kernels = kernels_of(f.read())
-    assert len(kernels) == 6, list(kernels)     # forward, input gradient, weight gradient: two tile counts each
+    assert len(kernels) == 5, list(kernels)     # forward / input gradient, two tile counts; weight gradient
     for name, lines in kernels.items():
         assert any(l.startswith("ds_read") for l in lines) and any(l.startswith("global_load_lds") for l in lines)
         assert not unordered_reads(lines), (name, unordered_reads(lines)[:4])
