@@ -122,7 +122,9 @@ struct GemmArgs {
   int64_t partial_stride;
   // WGRAD, optional: also write agg[j*ldcf + i] = sum_g lam[g] * (tile of worker g), summed in
   // ascending g (fp32) or a fixed, tile-dependent rotation of it (bf16): the weighted aggregation
-  // of Eq. 2 while the per-worker tiles are still in registers.  Only when gemm_fuses_aggregate() says so.
+  // of Eq. 2 while the per-worker tiles are still in registers.  Only
+  // in the kernels that walk all workers of a tile: large bf16 layers when gemm_fuses_aggregate() says so,
+  // grouped launches (fp32, bf16 on 64 x 64 tiles) always can.
   float* agg;
   float lam[DYNB_MAX_WORKERS];
   const void* zeros;   // 16 bytes of zeros in device memory (set by launch_gemm): what copies
