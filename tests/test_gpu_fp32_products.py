@@ -26,6 +26,8 @@ pytestmark = pytest.mark.gpu
     ([20, 17, 16, 40, 33, 9, 18, 16, 15, 12, 10, 3], [5, 0, 18], 0),   # more layers than one launch takes
     ([70, 20, 5], [900, 0, 300, 1, 17, 64, 30], 0),       # workers side by side, average in the last launch
     ([300, 320, 5], [300, 0, 300, 1, 17, 64, 30], 0),     # ... two per wave and one left, average by a pass
+    ([520, 530, 5], [7, 40, 0, 18], 0),      # 2 x 2 tiles, a worker per wave; single ones where the average is folded in
+    ([1024, 1056, 520, 5], [7, 40, 0, 2], 0),             # ... 2 x 2 with it too beside a layer that fills the chip
     ([130, 1030, 5], [0, 40] + [16, 17, 15] * 20 + [33, 0], 0),   # 2 x 2 tiles, six workers per wave, the last with four
 ])
 def test_fp32_products_at_the_edges_of_their_tiles(dims, b, shift):
@@ -54,7 +56,7 @@ def test_fp32_products_at_the_edges_of_their_tiles(dims, b, shift):
 
 def test_two_by_two_tiles_in_forward_and_input_gradient():
     # 33 x 33 tiles of 32 x 32 in four products, with ragged edges and ReLU masks; reductions of 60
-    # and 5 (two blocks, against a ring of four) and of 1041 and 1030
+    # and 5 (two blocks, against a ring of five) and of 1041 and 1030
     spec = synth.mlp_spec([60, 1041, 1030, 5], "f32")
     params = synth.init_params(spec, "he", 17)
     b = [515, 0, 498, 17]
