@@ -41,25 +41,50 @@ __device__ inline uint4 operator&(const uint4& a, const uint4& b) {
 __device__ inline uint4 load8(const bf16* p) { return *reinterpret_cast<const uint4*>(p); }
 __device__ inline void store8(bf16* p, const uint4& q) { *reinterpret_cast<uint4*>(p) = q; }
 
-// Sums a[0..7] (this lane's 8 channels) over the 32 row-lanes of the workgroup, in a fixed
-// order; every thread ends with the totals of its channels.  `red` is workgroup-shared.
+// This lane's granules of the first n >= 1 of 256 rows: rows row-lane + 32 i.  Rows past the last repeat it,
+// so that no branch stands between the loads and all are in flight together; the address is one uniform
+// base and a 32-bit offset (256 rows of a tensor below 2 GiB).
+constexpr int ROWS_IN_FLIGHT = 8;          // per lane
+__device__ inline void load_rows(const bf16* base, int64_t ld, int n, uint4 (&q)[ROWS_IN_FLIGHT]) {
+  const uint32_t pitch = (uint32_t)ld * 2, g = (threadIdx.x & 7) * 16;
+  const int rl = threadIdx.x >> 3;
+#pragma unroll
+  for (int i = 0; i < ROWS_IN_FLIGHT; ++i)
+    q[i] = *(const uint4*)((const char*)base + ((uint32_t)min(rl + 32 * i, n - 1) * pitch + g));
+}
+
+// Sums a[0..7] (this lane's 8 channels) over the 32 row-lanes of the workgroup, in a fixed order; `red` is
+// workgroup-shared.  Each exchange between lanes halves the channels that a lane still carries (7 exchanges
+// instead of the 24 of whole vectors, the same additions), so that a lane ends with one channel of its wave.
+__device__ inline void sum_over_wave_rows(const float (&a)[8], float* red) {
+  const int lane = threadIdx.x & 63;
+  const bool u = lane & 8, v = lane & 16, w = lane & 32;
+  float b[4], c[2];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) b[j] = (u ? a[j + 4] : a[j]) + __shfl_xor(u ? a[j] : a[j + 4], 8);
+#pragma unroll
+  for (int j = 0; j < 2; ++j) c[j] = (v ? b[j + 2] : b[j]) + __shfl_xor(v ? b[j] : b[j + 2], 16);
+  red[(lane & 7) * 8 + (u ? 4 : 0) + (v ? 2 : 0) + (w ? 1 : 0)] = (w ? c[1] : c[0]) + __shfl_xor(w ? c[0] : c[1], 32);
+}
+
+// ... every thread ends with the totals of its channels
 __device__ inline void sum_over_rows(float (&a)[8], float (*red)[64]) {
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    a[j] += __shfl_xor(a[j], 8);
-    a[j] += __shfl_xor(a[j], 16);
-    a[j] += __shfl_xor(a[j], 32);
-  }
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, cg = threadIdx.x & 7;
+  const int cg = threadIdx.x & 7;
   __syncthreads();
-  if (lane < 8) {
-#pragma unroll
-    for (int j = 0; j < 8; ++j) red[wave][lane * 8 + j] = a[j];
-  }
+  sum_over_wave_rows(a, red[threadIdx.x >> 6]);
   __syncthreads();
 #pragma unroll
   for (int j = 0; j < 8; ++j)
     a[j] = ((red[0][cg * 8 + j] + red[1][cg * 8 + j]) + red[2][cg * 8 + j]) + red[3][cg * 8 + j];
+}
+
+// ... the total of channel threadIdx.x, for the first 64 threads
+__device__ inline float channel_sum(const float (&a)[8], float (*red)[64]) {
+  const int c = threadIdx.x & 63;
+  __syncthreads();
+  sum_over_wave_rows(a, red[threadIdx.x >> 6]);
+  __syncthreads();
+  return ((red[0][c] + red[1][c]) + red[2][c]) + red[3][c];
 }
 
 }  // namespace dynb

@@ -95,6 +95,27 @@ def test_batchnorm_on_dense_features_and_plain_residual():
     check(spec, params, x, y, b, "dense bn")
 
 
+@pytest.mark.parametrize("b", [[1, 255, 256, 257, 0, 33],
+                               [2] * 31 + [0, 290] + [3] * 31])
+def test_normalisation_at_the_edges_of_row_chunks(b):
+    # workers of one row, one below / at / one above a chunk of 256 rows, and as many workers as a call
+    # takes; channels that fill one 64-channel block and a part of the next
+    spec = {"dtype": "bf16", "input": (40,), "classes": 6,
+            "layers": [synth.dense(40, 72, relu=False), synth.batchnorm(72, relu=False),
+                       synth.dense(72, 6, relu=False)]}
+    params = perturbed(spec, 36)
+    x, y = synth.make_batch(spec, "normal", sum(b), 36, 0)
+    check(spec, params, x, y, b, "row chunks")
+
+
+def test_pooling_over_more_pixels_than_are_fetched_at_once():
+    spec = {"dtype": "bf16", "input": (17, 17, 3), "classes": 5,
+            "layers": [synth.conv3x3(3, 20, 1, relu=False), synth.gap(), synth.dense(20, 5, relu=False)]}
+    params = perturbed(spec, 37)
+    x, y = synth.make_batch(spec, "uniform", 7, 37, 0)
+    check(spec, params, x, y, [4, 3], "pooling")
+
+
 def test_training_steps_with_momentum_follow_the_checker():
     # a few steps on both sides from the same state (the checker owns the trajectory)
     spec = synth.resnet_block_spec(channels=8, image=(8, 8, 3), classes=5)
