@@ -247,6 +247,9 @@ int launch_gap_backward(const void* dpooled, int64_t ldp, const void* act, int64
 // takes the same description as the gathered-operand GEMM where conv_direct_applies() says so.
 bool conv_direct_applies(int dtype, const GemmArgs& a);
 int launch_conv_direct(const GemmArgs& a, void* stream);
+// The same for 64 reduction channels with the weights resident in LDS (conv_resident.hip).
+bool conv_resident_applies(int dtype, const GemmArgs& a);
+int launch_conv_resident(const GemmArgs& a, void* stream);
 // The same from a flat run of pixels, images of any shape (conv_flat.hip).
 bool conv_flat_applies(int dtype, const GemmArgs& a);
 int launch_conv_flat(const GemmArgs& a, void* stream);

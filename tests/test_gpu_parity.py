@@ -115,9 +115,9 @@ def test_cnn_channel_blocks_and_row_chunks(channels):
 
 @pytest.mark.parametrize("image,channels", [((32, 32, 3), (64, 128, 72)), ((8, 32, 3), (64, 20, 64))])
 def test_cnn_on_32_wide_images(image, channels):
-    # 32-wide images select the halo-tile convolution kernel for forward and input gradient and
-    # the row-staged weight gradient (stride 1; whole 64-channel blocks per tap: 64 and 128
-    # channels; output channel counts that fill a block, leave 8, or are no multiple of 8; an
+    # 32-wide images select the halo-tile convolution kernel for forward and input gradient (from 64
+    # reduction channels on those with resident weights) and the row-staged weight gradient (stride 1;
+    # whole 64-channel blocks per tap: 64 and 128 channels; output channel counts that fill a block, leave 8, or are no multiple of 8; an
     # image one tile high); the stem (3 channels), layers behind a ragged channel count and the
     # strided layer stay on the gathered-operand kernel
     c1, c2, c3 = channels
@@ -601,6 +601,28 @@ def test_flat_convolutions(image, channels):
     b = [2, 0, 3]
     x, y = synth.make_batch(spec, "normal", sum(b), 96, 0)
     check_worker_gradients(spec, params, x, y, b, label="flat conv %s %s" % (image, channels))
+
+
+@pytest.mark.parametrize("image,channels,b", [
+    ((5, 1, 4), 64, [3, 0, 2]),       # one pixel wide; less than a tile
+    ((16, 16, 4), 64, [1, 2]),        # tiles that end with an image
+    ((13, 43, 4), 64, [2, 0, 1]),     # the widest images, rows that do not divide a tile
+    ((9, 44, 4), 64, [2, 1]),         # ... and one pixel too wide
+    ((11, 15, 4), 60, [7, 1]),        # padding channels on both sides
+    ((7, 9, 4), 130, [3, 2]),         # 64 -> 130 channels: three blocks of outputs
+    ((32, 32, 4), 64, [2, 1]),
+])
+def test_convolutions_with_resident_weights(image, channels, b):
+    # 64 reduction channels, stride 1, forward and input gradient, with a residual branch (addend and mask)
+    spec = {"dtype": "bf16", "input": image, "classes": 4,
+            "layers": [synth.conv3x3(image[2], 64, 1), synth.conv3x3(64, channels, 1),
+                       synth.conv3x3(channels, 64, 1), synth.conv3x3(64, 64, 1, relu=False), synth.add(0, True),
+                       synth.conv3x3(64, 64, 1), synth.gap(), synth.dense(64, 4, relu=False)]}
+    params = synth.init_params(spec, "he", 97)
+    rng = np.random.default_rng(7)
+    params = [(W, (rng.standard_normal(bb.shape) * 0.1).astype(np.float32)) for W, bb in params]
+    x, y = synth.make_batch(spec, "normal", sum(b), 98, 0)
+    check_worker_gradients(spec, params, x, y, b, label="resident %s %s" % (image, channels))
 
 
 @pytest.mark.parametrize("image,channels,stride", [
