@@ -96,8 +96,8 @@ struct GemmArgs {
   int64_t group_stride;
   int groups_per_block;                // WGRAD, bf16 kernel: workers streamed by one workgroup
   // WGRAD, unsplit (bf16: optional): also write the bias gradient bias_grad[g*group_stride + i] =
-  // sum over worker g's rows of A[row][i].  fp32 with `agg`: its weighted aggregate too, to
-  // bias_agg[i] (bf16: left to the pass over the small tensors).
+  // sum over worker g's rows of A[row][i].  Grouped launches (fp32, bf16 on 64 x 64 tiles) with `agg`: its
+  // weighted aggregate too, to bias_agg[i] (others: left to the pass over the small tensors).
   float* bias_grad;
   float* bias_agg;
   // Implicit-GEMM gather of operand A for a 3x3 convolution with zero padding 1 (bf16 only).
@@ -131,30 +131,52 @@ struct GemmArgs {
                        // fetch for rows past a worker's last and taps outside an image
 };
 
-int launch_gemm(int dtype, const GemmArgs& a, const Segs& s, void* stream);
-int launch_gemm_f32(const GemmArgs& a, void* stream);   // forward / input gradient (gemm_f32.hip)
-// fp32 weight gradients of up to WGRAD_F32_ITEMS layers (all over the same rows) in one launch
+// Softmax cross-entropy in the launch of the last product (softmax_head.h): dz = (softmax(logits) -
+// onehot(y)) / (rows of the worker), zero in columns [C, ldd), rowloss[row]; the logits are not stored.
+struct HeadArgs {
+  const int32_t* y;
+  void* dz; int64_t ldd;
+  float* rowloss;
+  Segs segs;
+};
+// whether that product's kernel has whole rows at hand
+bool head_applies(int dtype, const GemmArgs& a);
+// (with `head`: a forward product for which head_applies)
+int launch_gemm(int dtype, const GemmArgs& a, const Segs& s, void* stream, const HeadArgs* head = nullptr);
+int launch_gemm_f32(const GemmArgs& a, const HeadArgs* head, void* stream);   // forward / input gradient (gemm_f32.hip)
+bool gemm_f32_head_applies(const GemmArgs& a);
+// What ends an iteration (step_end.h): loss[g] = mean of rowloss over worker g's rows; grads[g][P .. P_pad)
+// = 0; out[P .. P_pad) = 0 if out.
+struct StepEnd {
+  const float* rowloss; float* loss;
+  float* grads; int64_t P, P_pad;
+  float* out;
+};
+// fp32 weight gradients of up to WGRAD_F32_ITEMS layers (all over the same rows) in one launch, which does
+// the step's end too if `end`
 constexpr int WGRAD_F32_ITEMS = 8;
-int launch_wgrad_f32(const GemmArgs* a, int n, const Segs& s, void* stream);
-// whether a wave walks all workers of its tile in any case (the tiles fill the chip), and whether walking
-// them, to form the average, costs less than a pass over their results
+int launch_wgrad_f32(const GemmArgs* a, int n, const Segs& s, const StepEnd* end, void* stream);
+// whether a wave walks all workers of its tile in any case (the tiles fill the chip), and what walking them,
+// to form the average, costs beside divided ones
 bool wgrad_f32_walks(const GemmArgs& a, const Segs& s);
-bool wgrad_f32_folds(const GemmArgs& a, const Segs& s);
-// The choice behind it: a walk over all workers of `walk_us`, against a `shares`-th of it and a pass
-// over K results of `weights` floats.
+double wgrad_f32_fold_us(const GemmArgs& a, const Segs& s);
+// The choice behind it: a walk over all workers of `walk_us` beside a `shares`-th of it (fold_us: the
+// difference), and a pass over K results of `weights` floats.
 constexpr int64_t AGGREGATE_ALONE = 65536;   // from so many on, a launch of its own (else part of the last)
-bool fold_pays(double walk_us, int shares, int64_t weights, int K);
+double fold_us(double walk_us, int shares, int64_t weights, int K);
+double average_pass_us(int64_t weights, int K);
 // bf16 products with few tiles (gemm_small.hip): whether one (unsplit) counts as such, and the launch.
 bool gemm_small_applies(const GemmArgs& a);
-int launch_gemm_small(const GemmArgs& a, void* stream);   // forward / input gradient
-// weight gradients of up to WGRAD_SMALL_ITEMS such layers (all over the same rows) in one launch
+int launch_gemm_small(const GemmArgs& a, const HeadArgs* head, void* stream);   // forward / input gradient
+// weight gradients of up to WGRAD_SMALL_ITEMS such layers (all over the same rows) in one launch, which does
+// the step's end too if `end`
 constexpr int WGRAD_SMALL_ITEMS = 8;
-int launch_wgrad_small(const GemmArgs* a, int n, const Segs& s, void* stream);
+int launch_wgrad_small(const GemmArgs* a, int n, const Segs& s, const StepEnd* end, void* stream);
 // whether that is faster than the 128 x 128-tile kernel (and, with `average`, a pass over its results);
 // the other two as for fp32
 bool wgrad_small_pays(const GemmArgs& a, const Segs& s, bool average);
 bool wgrad_small_walks(const GemmArgs& a, const Segs& s);
-bool wgrad_small_folds(const GemmArgs& a, const Segs& s);
+double wgrad_small_fold_us(const GemmArgs& a, const Segs& s);
 // Whether a bf16 weight-gradient launch of launch_gemm of these dimensions can take GemmArgs::agg.
 bool gemm_fuses_aggregate(int dtype, const GemmArgs& a);
 // out[e] = sum_k lam.w[k] * g[k*worker_stride + e], e < n, ascending k (any alignment)
@@ -178,11 +200,9 @@ int launch_bias_grad_rows(const void* dy, int64_t ld, int N, float* grads, int64
 // Reads `bytes` (a multiple of 16, 16-byte aligned) and discards them: what a launch is about to
 // fetch several times over, brought into the last-level cache by one sequential pass.
 int launch_touch(const void* p, int64_t bytes, void* stream);
-// loss[g] = mean of rowloss over worker g's rows; grads[g][P..P_pad) = 0.  With `out` (and lam,
-// small): also out[range] = sum_k lam_k grads[k][range] for every range of `small`, and
-// out[P..P_pad) = 0, in the same launch.
-int launch_finalize(const float* rowloss, float* loss, float* grads, int64_t P, int64_t P_pad,
-                    const Segs& s, const Lambdas* lam, const Ranges* small, float* out, void* stream);
+// The step's end; with end.out (and lam, small): also out[range] = sum_k lam_k grads[k][range] for every
+// range of `small`, in the same launch.
+int launch_finalize(const StepEnd& end, const Segs& s, const Lambdas* lam, const Ranges* small, void* stream);
 int launch_aggregate(const float* grads, const Lambdas& lam, int64_t n, float* out, void* stream);
 int launch_sgd(float* params, const float* g, int64_t n, float lr, void* stream);
 int launch_momentum(float* params, float* v, const float* g, int64_t n, float lr, float mu,

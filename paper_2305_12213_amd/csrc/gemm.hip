@@ -1019,14 +1019,17 @@ void launch_bf16_gather(GemmArgs a, const Segs& s, hipStream_t st) {
 
 }  // namespace
 
-// Results are written at 4.4 TB/s at best.  The pass over them costs what reading them takes (5.8 TB/s),
-// or a launch (5 us); below AGGREGATE_ALONE weights it is part of the last launch of the call, and next
-// to free.
-bool fold_pays(double walk_us, int shares, int64_t weights, int K) {
-  const double read_us = 4.0 * K * weights / 5.8e6, write_us = 4.0 * K * weights / 4.4e6;
-  const double pass_us = weights < AGGREGATE_ALONE ? 0.5 : read_us > 5.0 ? read_us : 5.0;
-  const double share_us = walk_us / shares > write_us ? walk_us / shares : write_us;
-  return walk_us - share_us <= pass_us;
+// (Results are written at 4.4 TB/s at best.)
+double fold_us(double walk_us, int shares, int64_t weights, int K) {
+  const double write_us = 4.0 * K * weights / 4.4e6;
+  return walk_us - (walk_us / shares > write_us ? walk_us / shares : write_us);
+}
+
+// What reading the results takes (5.8 TB/s), or a launch (5 us); below AGGREGATE_ALONE weights the pass is
+// part of the last launch of the call, and next to free.
+double average_pass_us(int64_t weights, int K) {
+  const double read_us = 4.0 * K * weights / 5.8e6;
+  return weights < AGGREGATE_ALONE ? 0.5 : read_us > 5.0 ? read_us : 5.0;
 }
 
 bool gemm_fuses_aggregate(int dtype, const GemmArgs& a) {
@@ -1035,11 +1038,20 @@ bool gemm_fuses_aggregate(int dtype, const GemmArgs& a) {
          tiles_of(a, AGG_SMALL, AGG_SMALL) >= 256;
 }
 
-int launch_gemm(int dtype, const GemmArgs& args, const Segs& s, void* stream) {
+// (bf16: 64 x 64 tiles; fp32: 16 x 16.  10 classes, product and softmax apart and together: 1024 rows of 1024
+// features, bf16, 6.4 + 4.9 -> 8.4 us; 785 rows of 97, fp32, 3.7 + 4.4 -> 5.6; 64 rows of 128 3.1 + 4.2 -> 4.4;
+// and the pause between two launches.  More classes would need several workgroups' columns.)
+bool head_applies(int dtype, const GemmArgs& a) {
+  if (a.mode != MODE_FWD || a.conv || a.C) return false;
+  return dtype == DYNB_BF16 ? a.N <= 64 && gemm_small_applies(a) : gemm_f32_head_applies(a);
+}
+
+int launch_gemm(int dtype, const GemmArgs& args, const Segs& s, void* stream, const HeadArgs* head) {
   GemmArgs a = args;
   a.zeros = device_zero_granule();
   if (!a.zeros) return fail(DYNB_ERR_HIP, "gemm: no address for the zero granule");
   if (a.M <= 0 || a.N <= 0) return DYNB_OK;
+  if (head && !head_applies(dtype, a)) return fail(DYNB_ERR_BADARG, "gemm: a softmax needs whole rows in one tile");
   if (a.agg && !gemm_fuses_aggregate(dtype, a))
     return fail(DYNB_ERR_UNSUPPORTED, "gemm: this weight gradient cannot fold the aggregation in");
   const int es = dtype == DYNB_BF16 ? 2 : 4;
@@ -1080,7 +1092,7 @@ int launch_gemm(int dtype, const GemmArgs& args, const Segs& s, void* stream) {
     if (conv_flat_applies(dtype, a)) return launch_conv_flat(a, stream);
     launch_bf16_gather(a, s, (hipStream_t)stream);
   } else if (dtype == DYNB_BF16 && a.mode != MODE_WGRAD && gemm_small_applies(a)) {
-    return launch_gemm_small(a, stream);
+    return launch_gemm_small(a, head, stream);
   } else if (dtype == DYNB_BF16 && a.agg) {
     launch_bf16_wgrad_agg(a, s, (hipStream_t)stream);
   } else if (dtype == DYNB_BF16) {
@@ -1104,7 +1116,7 @@ int launch_gemm(int dtype, const GemmArgs& args, const Segs& s, void* stream) {
       launch_bf16_plain<128, 128, 2, 2, 8>(a, s, st);
     }
   } else {
-    return launch_gemm_f32(a, stream);
+    return launch_gemm_f32(a, head, stream);
   }
   return hipGetLastError() == hipSuccess ? DYNB_OK : fail(DYNB_ERR_HIP, "gemm launch failed");
 }

@@ -12,8 +12,12 @@
 // take.  Problems with many tiles give each wave 2 x 2 of them (half the copies per instruction).
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "dynb_internal.h"
 #include "lds_async.h"
+#include "softmax_head.h"
+#include "step_end.h"
 #include "tile_map.h"
 
 namespace dynb {
@@ -49,8 +53,10 @@ __device__ inline void wait_reads() {
 // Against 64 x 64 vector-unit tiles: 256 x 512 x 3072 165 -> 28 us (the chain of matrix
 // instructions alone is 11 us, the issue of everything else of a lone wave 12), 785 x 301 x 832
 // 49 -> 11 us.
-template <int MODE, int R>
-__global__ __launch_bounds__(64) void gemm_f32_kernel(GemmArgs p) {
+// With HeadArgs (forward, at most 16 columns) the tile's rows of logits go through the softmax and the loss in
+// LDS instead of to memory.
+template <int MODE, int R, typename Head>
+__global__ __launch_bounds__(64) void gemm_f32_kernel(GemmArgs p, Head head) {
   // (40 KB either way: four waves on a compute unit, one per SIMD.  Four blocks of 2 x 2 tiles left room
   // for a fifth wave, and launches of many waves went in uneven rounds: 1024 x 1024 x 4096 134 -> 100
   // us, 2048 x 2048 x 4096 457 -> 354)
@@ -94,12 +100,16 @@ __global__ __launch_bounds__(64) void gemm_f32_kernel(GemmArgs p) {
   for (int u = 0; u < R; ++u)
 #pragma unroll
     for (int w = 0; w < R; ++w) acc[u][w] = f32x4{0.f, 0.f, 0.f, 0.f};
+  constexpr bool HEAD = std::is_same_v<Head, HeadArgs>;
+  int label = 0, owned = 1;                // of the row of this lane behind the product: lane / 4
+  if constexpr (HEAD) label = head.y[i0 + (lane >> 2) < p.M ? i0 + (lane >> 2) : p.M - 1];
 #pragma unroll
   for (int s = 0; s < NB; ++s) {
 #pragma unroll
     for (int c = 0; c < C; ++c) issue_one(s * SLOT, c);
     advance();
   }
+  if constexpr (HEAD) owned = rows_of_owner(head.segs, i0 + (lane >> 2));
   wait_pending<(NB - 1) * C>();
 #pragma unroll
   for (int e = 0; e < 8; ++e) fetch_one(0, 0, e);
@@ -142,6 +152,33 @@ __global__ __launch_bounds__(64) void gemm_f32_kernel(GemmArgs p) {
   wait_pending<0>();                       // (no copy may land after the LDS has been given back)
 
   // accumulator element v of a lane: row 4 * kg + v, column l15
+  if constexpr (HEAD) {
+    constexpr int PITCH = 20;
+    float* const logits = (float*)&ring_area[0];
+    wait_reads();                          // (a wave of its own: no barrier)
+    const float bias = p.bias ? p.bias[l15 < p.N ? l15 : p.N - 1] : 0.f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      float v = acc[0][0][e];
+      if (p.bias) v += bias;
+      if (p.relu) v = fmaxf(v, 0.f);
+      logits[(4 * kg + e) * PITCH + l15] = v;
+    }
+    __builtin_amdgcn_wave_barrier();
+    const int r = lane >> 2, c0 = 4 * (lane & 3);
+    const float* const row = logits + r * PITCH;
+    const f32x4 z = *(const f32x4*)(row + c0);
+    float e[4] = {z[0], z[1], z[2], z[3]};
+    const int want = label < 0 ? 0 : label >= p.N ? p.N - 1 : label;   // keeps the read in bounds
+    const float loss = softmax_row(4, e, c0, p.N, want, row[want], owned);
+    if (i0 + r >= p.M) return;
+    float* const dz = (float*)head.dz + (int64_t)(i0 + r) * head.ldd + c0;
+    *(f32x4*)dz = f32x4{e[0], e[1], e[2], e[3]};
+#pragma unroll
+    for (int u = 1; u < 4; ++u) *(f32x4*)(dz + 16 * u) = f32x4{0.f, 0.f, 0.f, 0.f};
+    if ((lane & 3) == 0) head.rowloss[i0 + r] = loss;
+    return;
+  }
 #pragma unroll
   for (int w = 0; w < R; ++w) {
     const int j = j0 + 16 * w + l15;
@@ -192,6 +229,8 @@ struct WgradGroup {
   int64_t group_stride;
   const void* zeros;
   float lam[DYNB_MAX_WORKERS];
+  int ends;                                // the first workgroups, one per worker, do the step's end
+  StepEnd end;
 };
 // (20 KB: eight waves on a compute unit, two per SIMD.  24 left room for six, and launches of many waves
 // went in uneven rounds: 1024 x 1024, 4096 rows, one worker 150 -> 95 us)
@@ -390,20 +429,25 @@ __device__ __forceinline__ void wgrad_f32_tile(const WgradItem& p, const WgradGr
 
 __global__ __launch_bounds__(64) void wgrad_f32_kernel(WgradGroup grp, Segs segs) {
   __shared__ uint4 ring_area[WGRAD_RING / 16];
+  const int block = (int)blockIdx.x - grp.ends;
+  if (block < 0) {
+    end_worker(grp.end, segs, blockIdx.x);
+    return;
+  }
   int q = 0;
-  while (q + 1 < grp.n && (int)blockIdx.x >= grp.item[q + 1].first) ++q;
+  while (q + 1 < grp.n && block >= grp.item[q + 1].first) ++q;
   const WgradItem& p = grp.item[q];
-  if (p.wide) wgrad_f32_tile<2>(p, grp, segs, blockIdx.x - p.first, ring_area);
-  else wgrad_f32_tile<1>(p, grp, segs, blockIdx.x - p.first, ring_area);
+  if (p.wide) wgrad_f32_tile<2>(p, grp, segs, block - p.first, ring_area);
+  else wgrad_f32_tile<1>(p, grp, segs, block - p.first, ring_area);
 }
 
 template <int R>
 void launch_as(const GemmArgs& a, unsigned blocks, hipStream_t st) {
   const dim3 grid(blocks), block(64);
   if (a.mode == MODE_FWD)
-    hipLaunchKernelGGL((gemm_f32_kernel<MODE_FWD, R>), grid, block, 0, st, a);
+    hipLaunchKernelGGL((gemm_f32_kernel<MODE_FWD, R, NoHead>), grid, block, 0, st, a, NoHead());
   else
-    hipLaunchKernelGGL((gemm_f32_kernel<MODE_DGRAD, R>), grid, block, 0, st, a);
+    hipLaunchKernelGGL((gemm_f32_kernel<MODE_DGRAD, R, NoHead>), grid, block, 0, st, a, NoHead());
 }
 
 }  // namespace
@@ -432,24 +476,32 @@ bool wgrad_f32_walks(const GemmArgs& a, const Segs& s) { return workers_per_wave
 // workers fill the chip instead, they are faster by 0.05 us per 16 rows and 1024 of the small ones, which
 // is worth a pass of 5 us from 1700 rows on (512 x 512, 8 workers, per layer with its average: 1024 rows
 // folded 16 us, with the pass 20; 576 x 576, 16384 rows, forward and backward: 455 and 378).
-bool wgrad_f32_folds(const GemmArgs& a, const Segs& s) {
-  if (wgrad_side(a, s) != tile_side(a) && tiles_with(a, 16) * s.off[s.K] > 1700 * 1024) return false;
+double wgrad_f32_fold_us(const GemmArgs& a, const Segs& s) {
+  if (wgrad_side(a, s) != tile_side(a) && tiles_with(a, 16) * s.off[s.K] > 1700 * 1024) return 1e30;
   const int per = workers_per_wave(a, s.K, tile_side(a));
-  return fold_pays(0.7 * s.K + 0.0036 * s.off[s.K], (s.K + per - 1) / per, (int64_t)a.M * a.N, s.K);
+  return fold_us(0.7 * s.K + 0.0036 * s.off[s.K], (s.K + per - 1) / per, (int64_t)a.M * a.N, s.K);
 }
 
-int launch_gemm_f32(const GemmArgs& a, void* stream) {
+// (a tile holds whole rows)
+bool gemm_f32_head_applies(const GemmArgs& a) { return a.mode == MODE_FWD && a.N <= 16 && tile_side(a) == 16; }
+
+int launch_gemm_f32(const GemmArgs& a, const HeadArgs* head, void* stream) {
   if (a.mode == MODE_WGRAD || a.K % 32 != 0)
     return fail(DYNB_ERR_BADARG, "gemm: fp32 products take whole 32-deep blocks");
   const int side = tile_side(a);
   const int64_t n = tiles_with(a, side);
   if (n >= (int64_t)1 << 31) return fail(DYNB_ERR_UNSUPPORTED, "gemm: too many tiles for one launch");
-  if (side == 32) launch_as<2>(a, (unsigned)n, (hipStream_t)stream);
+  if (head) {
+    if (!gemm_f32_head_applies(a) || head->ldd != COL_PAD || ((uintptr_t)head->dz & 15))
+      return fail(DYNB_ERR_BADARG, "gemm: a softmax needs whole rows in one tile");
+    hipLaunchKernelGGL((gemm_f32_kernel<MODE_FWD, 1, HeadArgs>), dim3((unsigned)n), dim3(64), 0, (hipStream_t)stream,
+                       a, *head);
+  } else if (side == 32) launch_as<2>(a, (unsigned)n, (hipStream_t)stream);
   else launch_as<1>(a, (unsigned)n, (hipStream_t)stream);
   return hipGetLastError() == hipSuccess ? DYNB_OK : fail(DYNB_ERR_HIP, "gemm launch failed");
 }
 
-int launch_wgrad_f32(const GemmArgs* a, int n, const Segs& s, void* stream) {
+int launch_wgrad_f32(const GemmArgs* a, int n, const Segs& s, const StepEnd* end, void* stream) {
   if (n > WGRAD_F32_ITEMS) return fail(DYNB_ERR_BADARG, "gemm: too many weight gradients for one launch");
   WgradGroup grp = {};
   grp.zeros = device_zero_granule();
@@ -481,9 +533,13 @@ int launch_wgrad_f32(const GemmArgs* a, int n, const Segs& s, void* stream) {
     flops += g.alg_flops;
     bytes += g.alg_bytes;
   }
-  if (!grp.n) return DYNB_OK;
+  if (end) {
+    grp.ends = s.K;
+    grp.end = *end;
+  }
+  if (!grp.n && !grp.ends) return DYNB_OK;
   Timed t(KC_GEMM_WGRAD, stream, flops, bytes);
-  hipLaunchKernelGGL(wgrad_f32_kernel, dim3((unsigned)blocks), dim3(64), 0, (hipStream_t)stream, grp, s);
+  hipLaunchKernelGGL(wgrad_f32_kernel, dim3((unsigned)(blocks + grp.ends)), dim3(64), 0, (hipStream_t)stream, grp, s);
   return hipGetLastError() == hipSuccess ? DYNB_OK : fail(DYNB_ERR_HIP, "gemm launch failed");
 }
 

@@ -6,8 +6,12 @@
 // from the accumulators, and one path for all edges.  Sums run in the order of the large kernels.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "dynb_internal.h"
 #include "lds_async.h"
+#include "softmax_head.h"
+#include "step_end.h"
 #include "tile_map.h"
 
 namespace dynb {
@@ -36,8 +40,10 @@ __device__ inline int swizzle(int r) { return (((r >> 1) & 3) << 1) | ((r >> 3) 
 // 23 -> 18.
 constexpr int NB = 4, STAGE = 2 * T * 128;
 
-template <int MODE>
-__global__ __launch_bounds__(256) void gemm_small_kernel(GemmArgs p) {
+// With HeadArgs (forward, at most 64 columns) the tile's rows of logits go through the softmax and the loss in
+// LDS instead of to memory.
+template <int MODE, typename Head>
+__global__ __launch_bounds__(256) void gemm_small_kernel(GemmArgs p, Head head) {
   __shared__ uint4 ring[NB * STAGE / 16];
   int ti, tj;
   tile_of_block(blockIdx.x, (p.M + T - 1) / T, (p.N + T - 1) / T, ti, tj);
@@ -67,8 +73,20 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(GemmArgs p) {
   f32x16 acc;
 #pragma unroll
   for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+  constexpr bool HEAD = std::is_same_v<Head, HeadArgs>;
+  __shared__ int label[HEAD ? T : 1], owned[HEAD ? T : 1];     // of the tile's rows
+  int mine = 0;
+  if constexpr (HEAD) {
+    if (threadIdx.x < T) mine = head.y[min(i0 + (int)threadIdx.x, p.M - 1)];
+  }
 #pragma unroll 1
   for (int s = 0; s < NB - 1; ++s) issue((uint32_t)(s * STAGE));
+  if constexpr (HEAD) {
+    if (threadIdx.x < T) {                 // (while the first copies are on their way)
+      owned[threadIdx.x] = rows_of_owner(head.segs, i0 + (int)threadIdx.x);
+      label[threadIdx.x] = mine < 0 ? 0 : mine >= p.N ? p.N - 1 : mine;      // keeps the read in bounds
+    }
+  }
   const char* const base = (const char*)&ring[0];
   const int fa = (wi * 32 + l31) * 128, fb = T * 128 + (wj * 32 + l31) * 128, sw = swizzle(l31);
   uint32_t slot = 0, refill = (NB - 1) * STAGE;
@@ -92,6 +110,40 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(GemmArgs p) {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (no copy may land after the LDS has been given back)
 
   // accumulator elements 4q .. 4q+3 of a lane: row l31, columns 8q + 4h ..
+  if constexpr (HEAD) {
+    constexpr int PITCH = T + 4;
+    float* const logits = (float*)&ring[0];
+    __syncthreads();                       // the last stage is no longer read
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int j = wj * 32 + 8 * q + 4 * h;
+      f32x4 v = {acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if (p.bias) v[e] += p.bias[j + e < p.N ? j + e : p.N - 1];
+        if (p.relu) v[e] = fmaxf(v[e], 0.f);
+      }
+      *(f32x4*)&logits[(wi * 32 + l31) * PITCH + j] = v;
+    }
+    __syncthreads();
+    // a wave's 16 rows on four lanes each, or on 16 in four rounds
+    const int lanes = p.N <= 16 ? 4 : 16, c0 = 4 * (lane & (lanes - 1));
+#pragma unroll 1
+    for (int r = 16 * wave + lane / lanes; r < 16 * (wave + 1); r += 64 / lanes) {
+      const float* const row = logits + r * PITCH;
+      const f32x4 z = *(const f32x4*)(row + c0);
+      float e[4] = {z[0], z[1], z[2], z[3]};
+      const int want = label[r];
+      const float loss = softmax_row(lanes, e, c0, p.N, want, row[want], owned[r]);
+      if (i0 + r >= p.M) continue;
+      bf16* const dz = (bf16*)head.dz + (int64_t)(i0 + r) * head.ldd + c0;
+      const bf16x4 o = {(bf16)e[0], (bf16)e[1], (bf16)e[2], (bf16)e[3]}, none = {(bf16)0.f, (bf16)0.f, (bf16)0.f, (bf16)0.f};
+      *(bf16x4*)dz = o;
+      for (int c = 4 * lanes; c < T; c += 4 * lanes) *(bf16x4*)(dz + c) = none;
+      if (c0 == 0) head.rowloss[i0 + r] = loss;
+    }
+    return;
+  }
   const int i = i0 + wi * 32 + l31;
   if (i >= p.M) return;
 #pragma unroll
@@ -161,21 +213,28 @@ struct SmallWgrad {
   const void* A; const void* B;                  // dy, x
   int64_t lda, ldb, ldcf;
   int M, N, first, tiles, groups_per_block;      // first: its first workgroup
-  float* Cf; float* bias_grad; float* agg;
+  float* Cf; float* bias_grad; float* agg; float* bias_agg;
 };
 struct SmallWgrads {
   SmallWgrad item[WGRAD_SMALL_ITEMS];
   int n;
   int64_t group_stride;
   float lam[DYNB_MAX_WORKERS];
+  int ends;                                      // the first workgroups, one per worker, do the step's end
+  StepEnd end;
 };
 
 __global__ __launch_bounds__(256) void wgrad_small_kernel(SmallWgrads grp, Segs segs) {
   __shared__ uint4 ring[WNB * WSTAGE / 16];
+  if ((int)blockIdx.x < grp.ends) {
+    if (threadIdx.x < 64) end_worker(grp.end, segs, blockIdx.x);
+    return;
+  }
+  const int of_all = (int)blockIdx.x - grp.ends;
   int q = 0;
-  while (q + 1 < grp.n && (int)blockIdx.x >= grp.item[q + 1].first) ++q;
+  while (q + 1 < grp.n && of_all >= grp.item[q + 1].first) ++q;
   const SmallWgrad& p = grp.item[q];
-  const int block = (int)blockIdx.x - p.first, part = block / p.tiles;
+  const int block = of_all - p.first, part = block / p.tiles;
   int ti, tj;
   tile_of_block((uint32_t)(block - part * p.tiles), (p.M + T - 1) / T, (p.N + T - 1) / T, ti, tj);
   const int i0 = ti * T, j0 = tj * T;
@@ -218,6 +277,7 @@ __global__ __launch_bounds__(256) void wgrad_small_kernel(SmallWgrads grp, Segs 
   f32x16 acc, agg, bsum;
 #pragma unroll
   for (int v = 0; v < 16; ++v) acc[v] = agg[v] = bsum[v] = 0.f;
+  float bagg = 0.f;
   // accumulator element v of a lane: row (x feature) 8 (v / 4) + 4h + v % 4, column (dy feature) l31
   const int i = i0 + wi * 32 + l31, jw = j0 + wj * 32 + 4 * h;
   auto store = [&](float* dst, const f32x16& src) {
@@ -262,12 +322,17 @@ __global__ __launch_bounds__(256) void wgrad_small_kernel(SmallWgrads grp, Segs 
     } while (r < rows);
     store(p.Cf + (int64_t)g * grp.group_stride, acc);
     if (bias && h == 0 && i < p.M) p.bias_grad[(int64_t)g * grp.group_stride + i] = bsum[0];
-    if (p.agg) agg += grp.lam[g] * acc;
+    if (p.agg) {
+      agg += grp.lam[g] * acc;
+      bagg += grp.lam[g] * bsum[0];
+    }
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[v] = bsum[v] = 0.f;
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (no copy may land after the LDS has been given back)
-  if (p.agg) store(p.agg, agg);
+  if (!p.agg) return;
+  store(p.agg, agg);
+  if (bias && h == 0 && i < p.M) p.bias_agg[i] = bagg;
 }
 
 int64_t tiles64(const GemmArgs& a) { return (int64_t)((a.M + T - 1) / T) * ((a.N + T - 1) / T); }
@@ -298,8 +363,8 @@ bool wgrad_small_walks(const GemmArgs& a, const Segs& s) { return worker_parts(a
 // (kernel times): 64 x 10, 64 workers, 512 rows 71 and 7 + 14 us; 512 x 1024, 16 workers, 4096 rows 44
 // and 19 + 10; 1024 x 1024, 16 workers, 1024 rows 28 and 18 + 15; 784 x 128, 2 workers, 512 rows 11 and
 // 8 + 6.
-bool wgrad_small_folds(const GemmArgs& a, const Segs& s) {
-  return fold_pays(s.K + 0.0055 * s.off[s.K], worker_parts(a, s.K), (int64_t)a.M * a.N, s.K);
+double wgrad_small_fold_us(const GemmArgs& a, const Segs& s) {
+  return fold_us(s.K + 0.0055 * s.off[s.K], worker_parts(a, s.K), (int64_t)a.M * a.N, s.K);
 }
 
 // Matrix work is cheaper on 128 x 128 tiles, results are cheaper to leave from 64 x 64 ones, above all
@@ -318,21 +383,25 @@ bool wgrad_small_pays(const GemmArgs& a, const Segs& s, bool average) {
   return rows < (s.K < 4 ? 4096 : 2048) || rows * large < (int64_t)16384 * s.K;
 }
 
-int launch_gemm_small(const GemmArgs& a, void* stream) {
+int launch_gemm_small(const GemmArgs& a, const HeadArgs* head, void* stream) {
   const int64_t tiles = tiles64(a);
   if (tiles >= (int64_t)1 << 31) return fail(DYNB_ERR_UNSUPPORTED, "gemm: too many tiles for one launch");
   const hipStream_t st = (hipStream_t)stream;
-  if (a.mode == MODE_FWD) {
-    hipLaunchKernelGGL(gemm_small_kernel<MODE_FWD>, dim3((unsigned)tiles), dim3(256), 0, st, a);
+  if (head) {
+    if (a.mode != MODE_FWD || a.N > T || head->ldd != T || ((uintptr_t)head->dz & 7))
+      return fail(DYNB_ERR_BADARG, "gemm: a softmax needs whole rows in one tile");
+    hipLaunchKernelGGL((gemm_small_kernel<MODE_FWD, HeadArgs>), dim3((unsigned)tiles), dim3(256), 0, st, a, *head);
+  } else if (a.mode == MODE_FWD) {
+    hipLaunchKernelGGL((gemm_small_kernel<MODE_FWD, NoHead>), dim3((unsigned)tiles), dim3(256), 0, st, a, NoHead());
   } else if (a.mode == MODE_DGRAD) {
-    hipLaunchKernelGGL(gemm_small_kernel<MODE_DGRAD>, dim3((unsigned)tiles), dim3(256), 0, st, a);
+    hipLaunchKernelGGL((gemm_small_kernel<MODE_DGRAD, NoHead>), dim3((unsigned)tiles), dim3(256), 0, st, a, NoHead());
   } else {
     return fail(DYNB_ERR_BADARG, "gemm: weight gradients have a launch of their own");
   }
   return hipGetLastError() == hipSuccess ? DYNB_OK : fail(DYNB_ERR_HIP, "gemm launch failed");
 }
 
-int launch_wgrad_small(const GemmArgs* a, int n, const Segs& s, void* stream) {
+int launch_wgrad_small(const GemmArgs* a, int n, const Segs& s, const StepEnd* end, void* stream) {
   if (n > WGRAD_SMALL_ITEMS) return fail(DYNB_ERR_BADARG, "gemm: too many weight gradients for one launch");
   SmallWgrads grp = {};
   double flops = 0, bytes = 0;
@@ -340,7 +409,7 @@ int launch_wgrad_small(const GemmArgs* a, int n, const Segs& s, void* stream) {
   for (int q = 0; q < n; ++q) {
     const GemmArgs& g = a[q];
     if (g.M <= 0 || g.N <= 0) continue;
-    if (!gemm_small_applies(g) || !g.bias_grad || g.split > 1 ||
+    if (!gemm_small_applies(g) || !g.bias_grad || (g.agg && !g.bias_agg) || g.split > 1 ||
         (grp.n && g.group_stride != grp.group_stride))
       return fail(DYNB_ERR_BADARG, "gemm: not a weight gradient of few tiles with its bias gradient");
     if ((g.lda & 7) || (g.ldb & 7) || (((uintptr_t)g.A | (uintptr_t)g.B) & 15))
@@ -351,7 +420,7 @@ int launch_wgrad_small(const GemmArgs* a, int n, const Segs& s, void* stream) {
     const int64_t tiles = tiles64(g);
     const int parts = g.agg ? 1 : worker_parts(g, s.K), per = (s.K + parts - 1) / parts;
     grp.item[grp.n++] = {g.A, g.B, g.lda, g.ldb, g.ldcf, g.M, g.N, (int)blocks, (int)tiles, per, g.Cf,
-                         g.bias_grad, g.agg};
+                         g.bias_grad, g.agg, g.bias_agg};
     grp.group_stride = g.group_stride;
     if (g.agg)
       for (int k = 0; k < s.K; ++k) grp.lam[k] = g.lam[k];   // (of the call: the same for every layer)
@@ -359,9 +428,13 @@ int launch_wgrad_small(const GemmArgs* a, int n, const Segs& s, void* stream) {
     flops += g.alg_flops;
     bytes += g.alg_bytes;
   }
-  if (!grp.n) return DYNB_OK;
+  if (end) {
+    grp.ends = s.K;
+    grp.end = *end;
+  }
+  if (!grp.n && !grp.ends) return DYNB_OK;
   Timed t(KC_GEMM_WGRAD_64, stream, flops, bytes);
-  hipLaunchKernelGGL(wgrad_small_kernel, dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream, grp, s);
+  hipLaunchKernelGGL(wgrad_small_kernel, dim3((unsigned)(blocks + grp.ends)), dim3(256), 0, (hipStream_t)stream, grp, s);
   return hipGetLastError() == hipSuccess ? DYNB_OK : fail(DYNB_ERR_HIP, "gemm launch failed");
 }
 

@@ -4,6 +4,7 @@
 
 #include "device_rows.h"
 #include "dynb_internal.h"
+#include "step_end.h"
 
 namespace dynb {
 namespace {
@@ -155,43 +156,20 @@ __global__ __launch_bounds__(256) void softmax_xent_kernel(const float* __restri
   if (lane == 0) rowloss[row] = logf(sum) - (zr[label] - m);
 }
 
-// ---- per-worker mean loss, zero tail of each worker's gradient vector, and (workgroups behind
-// the first K) the weighted aggregate, Eq. 2, of the small tensors listed in r -- one launch
-// for what used to be two tiny ones at the end of every step ---------------------------------
-__global__ __launch_bounds__(64) void finalize_kernel(const float* __restrict__ rowloss,
-                                                      float* __restrict__ loss,
-                                                      float* __restrict__ grads, int64_t P,
-                                                      int64_t P_pad, Segs s, Lambdas lam, Ranges r,
-                                                      float* __restrict__ out, int range_bx) {
-  const int lane = threadIdx.x;
-  if ((int)blockIdx.x >= s.K) {
-    const int q = blockIdx.x - s.K, ri = q / range_bx, bx = q % range_bx;
-    const int64_t off = r.off[ri], n = r.len[ri];
-    for (int64_t i = (int64_t)bx * 64 + lane; i < n; i += (int64_t)range_bx * 64) {
-      float acc = 0.f;
-      for (int k = 0; k < lam.K; ++k) acc += lam.w[k] * grads[(int64_t)k * P_pad + off + i];
-      out[off + i] = acc;
-    }
+// ---- the step's end (first K workgroups) and, behind them, the weighted aggregate, Eq. 2, of the small
+// tensors listed in r -- one launch for what used to be two tiny ones ---------------------------------
+__global__ __launch_bounds__(64) void finalize_kernel(StepEnd end, Segs s, Lambdas lam, Ranges r, int range_bx) {
+  if ((int)blockIdx.x < s.K) {
+    end_worker(end, s, blockIdx.x);
     return;
   }
-  const int g = blockIdx.x;
-  const int bk = s.off[g + 1] - s.off[g];
-  // eight independent partial sums per lane: the loads of a round are in flight together
-  float part[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  for (int i = lane; i < bk; i += 512) {
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if (i + 64 * u < bk) part[u] += rowloss[s.off[g] + i + 64 * u];
+  const int q = blockIdx.x - s.K, ri = q / range_bx, bx = q % range_bx;
+  const int64_t off = r.off[ri], n = r.len[ri];
+  for (int64_t i = (int64_t)bx * 64 + threadIdx.x; i < n; i += (int64_t)range_bx * 64) {
+    float acc = 0.f;
+    for (int k = 0; k < lam.K; ++k) acc += lam.w[k] * end.grads[(int64_t)k * end.P_pad + off + i];
+    end.out[off + i] = acc;
   }
-  float acc = ((part[0] + part[1]) + (part[2] + part[3])) + ((part[4] + part[5]) + (part[6] + part[7]));
-  acc = wave_sum(acc);
-  if (lane == 0) loss[g] = bk > 0 ? acc / (float)bk : 0.f;
-  if (grads)
-    for (int64_t p = P + lane; p < P_pad; p += 64) grads[(int64_t)g * P_pad + p] = 0.f;
-  // (the aggregate's padding is written here, not summed from the tails above: workgroups of
-  // one launch run in no particular order)
-  if (out && g == 0)
-    for (int64_t p = P + lane; p < P_pad; p += 64) out[p] = 0.f;
 }
 
 // ---- read and discard (see launch_touch) -------------------------------------------------
@@ -312,14 +290,13 @@ int launch_touch(const void* p, int64_t bytes, void* stream) {
   return ok("touch");
 }
 
-int launch_finalize(const float* rowloss, float* loss, float* grads, int64_t P, int64_t P_pad,
-                    const Segs& s, const Lambdas* lam, const Ranges* small, float* out, void* stream) {
+int launch_finalize(const StepEnd& end, const Segs& s, const Lambdas* lam, const Ranges* small, void* stream) {
   Lambdas l;
   l.K = 0;
   Ranges r;
   r.n = 0;
   int64_t longest = 0, total = 0;
-  if (out && lam && small) {
+  if (end.out && lam && small) {
     l = *lam;
     r = *small;
     for (int i = 0; i < r.n; ++i) {
@@ -332,8 +309,7 @@ int launch_finalize(const float* rowloss, float* loss, float* grads, int64_t P, 
   if (bx < 1) bx = 1;
   const int extra = longest > 0 ? (int)bx * r.n : 0;
   Timed t(KC_FINALIZE, stream, 2.0 * l.K * total, 4.0 * (l.K + 1) * total);
-  hipLaunchKernelGGL(finalize_kernel, dim3(s.K + extra), dim3(64), 0, (hipStream_t)stream, rowloss, loss,
-                     grads, P, P_pad, s, l, r, out, (int)bx);
+  hipLaunchKernelGGL(finalize_kernel, dim3(s.K + extra), dim3(64), 0, (hipStream_t)stream, end, s, l, r, (int)bx);
   return ok("finalize");
 }
 
