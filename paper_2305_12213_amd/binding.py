@@ -156,7 +156,8 @@ def _stream(stream):
         return stream
     try:
         import torch
-        if torch.cuda.is_available():
+        # (is_initialized() first: is_available() asks the driver, 2 us on every call)
+        if torch.cuda.is_initialized() or torch.cuda.is_available():
             return torch.cuda.current_stream().cuda_stream
     except ImportError:
         pass
