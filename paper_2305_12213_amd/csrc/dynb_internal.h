@@ -242,6 +242,18 @@ struct CastMats {
 };
 // The copies alone, of the weights as they are.
 int launch_weight_casts(int dtype, const float* params, CastMats& mats, void* stream);
+// The same together with the packed input act T [rows][ld] = x fp32 [rows][D], zeros beyond (rows = 0: none),
+// and zeros in the columns [pad_from, pad_ld) of T tensors [pad_rows][pad_ld].
+constexpr int MAX_PADS = 4 * MAX_CAST_MATS;
+struct Prepare {
+  const float* x; void* act;
+  int rows, D;
+  int64_t ld;
+  int n;
+  void* pad[MAX_PADS];
+  int pad_rows[MAX_PADS], pad_from[MAX_PADS], pad_ld[MAX_PADS];
+};
+int launch_prepare(int dtype, const float* params, CastMats& mats, const Prepare& pr, void* stream);
 // One launch: the optimizer step of every matrix of `mats` fused with the refresh of its two
 // copies, and the element-wise step of every range of `small`; s1/s2 point at the state of
 // parameter 0 (may be null when the rule has no such state)

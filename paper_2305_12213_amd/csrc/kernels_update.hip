@@ -98,28 +98,10 @@ __device__ inline void gradients(const GradSource& src, const int64_t (&o)[U], f
 // back-to-back launches on one stream leave the chip idle for a few microseconds each, which
 // for a four-layer model came to a sixth of the whole update.
 template <typename T, int KIND, bool AGG, int TC>
-__global__ __launch_bounds__(256) void update_cast_kernel(float* __restrict__ params, CastMats mats,
-                                                          Ranges small, int range_blocks,
-                                                          GradSource src, UpdateRule rule,
-                                                          float* __restrict__ s1,
-                                                          float* __restrict__ s2) {
+__device__ __forceinline__ void update_tile(int blk, float* __restrict__ params, const CastMats& mats,
+                                            const GradSource& src, const UpdateRule& rule,
+                                            float* __restrict__ s1, float* __restrict__ s2) {
   constexpr bool HAS_S1 = KIND == DYNB_OPT_MOMENTUM || KIND == DYNB_OPT_ADAM;
-  const int blk = blockIdx.x;
-  if (blk >= mats.first_block[mats.n]) {   // the small tensors, element by element
-    const int rb = blk - mats.first_block[mats.n];
-    for (int q = 0; q < small.n; ++q) {
-      const int64_t off = small.off[q], n = small.len[q];
-      for (int64_t i = (int64_t)rb * 256 + threadIdx.x; i < n; i += (int64_t)range_blocks * 256) {
-        const int64_t o = off + i;
-        float a = HAS_S1 ? s1[o] : 0.f;
-        float b = KIND == DYNB_OPT_ADAM ? s2[o] : 0.f;
-        params[o] = step_one<KIND>(rule, params[o], gradient1<AGG>(src, o), a, b);
-        if (HAS_S1) s1[o] = a;
-        if (KIND == DYNB_OPT_ADAM) s2[o] = b;
-      }
-    }
-    return;
-  }
   int mi = 0;
   while (blk >= mats.first_block[mi + 1]) ++mi;
   const int64_t ldn = mats.ldn[mi], ldt = mats.ldt[mi];
@@ -216,6 +198,74 @@ __global__ __launch_bounds__(256) void update_cast_kernel(float* __restrict__ pa
     } else {
       for (int e = 0; e < G && r0 + rg * G + e < R; ++e)
         Wt[(int64_t)(c0 + c) * ldt + r0 + rg * G + e] = from_float<T>(tile[rg * G + e][c]);
+    }
+  }
+}
+
+template <typename T, int KIND, bool AGG, int TC>
+__global__ __launch_bounds__(256) void update_cast_kernel(float* __restrict__ params, CastMats mats,
+                                                          Ranges small, int range_blocks,
+                                                          GradSource src, UpdateRule rule,
+                                                          float* __restrict__ s1,
+                                                          float* __restrict__ s2) {
+  constexpr bool HAS_S1 = KIND == DYNB_OPT_MOMENTUM || KIND == DYNB_OPT_ADAM;
+  const int blk = blockIdx.x;
+  if (blk >= mats.first_block[mats.n]) {   // the small tensors, element by element
+    const int rb = blk - mats.first_block[mats.n];
+    for (int q = 0; q < small.n; ++q) {
+      const int64_t off = small.off[q], n = small.len[q];
+      for (int64_t i = (int64_t)rb * 256 + threadIdx.x; i < n; i += (int64_t)range_blocks * 256) {
+        const int64_t o = off + i;
+        float a = HAS_S1 ? s1[o] : 0.f;
+        float b = KIND == DYNB_OPT_ADAM ? s2[o] : 0.f;
+        params[o] = step_one<KIND>(rule, params[o], gradient1<AGG>(src, o), a, b);
+        if (HAS_S1) s1[o] = a;
+        if (KIND == DYNB_OPT_ADAM) s2[o] = b;
+      }
+    }
+    return;
+  }
+  update_tile<T, KIND, AGG, TC>(blk, params, mats, src, rule, s1, s2);
+}
+
+// ---- everything a dense model's scratch needs before a pass over it, in one launch ---------------
+// The weight copies, the packed input (padding columns included) and zeros in the padding columns of what
+// later kernels write only in part: workgroups of each kind behind those of the one before.
+template <typename T>
+__global__ __launch_bounds__(256) void prepare_kernel(const float* __restrict__ params, CastMats mats, Prepare pr,
+                                                      int pack_blocks, int pad_blocks) {
+  int blk = blockIdx.x;
+  if (blk < mats.first_block[mats.n]) {
+    const GradSource src = {};
+    const UpdateRule rule = {};
+    update_tile<T, COPY_ONLY, false, 64>(blk, const_cast<float*>(params), mats, src, rule, nullptr, nullptr);
+    return;
+  }
+  blk -= mats.first_block[mats.n];
+  if (blk < pack_blocks) {                 // eight columns of a row per lane
+    typedef T vec8T __attribute__((ext_vector_type(8)));
+    const int gpr = (int)(pr.ld / 8);
+    for (int64_t i = (int64_t)blk * 256 + threadIdx.x; i < (int64_t)pr.rows * gpr; i += (int64_t)pack_blocks * 256) {
+      const int64_t r = i / gpr;
+      const int c = (int)(i - r * gpr) * 8;
+      vec8T v;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float t = pr.x[r * pr.D + (c + e < pr.D ? c + e : 0)];
+        v[e] = c + e < pr.D ? from_float<T>(t) : from_float<T>(0.f);
+      }
+      *(vec8T*)((T*)pr.act + r * pr.ld + c) = v;
+    }
+    return;
+  }
+  blk -= pack_blocks;
+  for (int q = 0; q < pr.n; ++q) {
+    const int ld = pr.pad_ld[q], w = ld - pr.pad_from[q];
+    T* const p = (T*)pr.pad[q] + pr.pad_from[q];
+    const int64_t total = (int64_t)pr.pad_rows[q] * w;
+    for (int64_t i = (int64_t)blk * 256 + threadIdx.x; i < total; i += (int64_t)pad_blocks * 256) {
+      const int64_t r = i / w;
+      p[r * ld + (i - r * w)] = from_float<T>(0.f);
     }
   }
 }
@@ -373,6 +423,30 @@ int launch_weight_casts(int dtype, const float* params, CastMats& mats, void* st
     launch_update_cast_t<float, COPY_ONLY, false>(const_cast<float*>(params), mats, none, 0, src, rule, nullptr,
                                                   nullptr, (hipStream_t)stream);
   return ok("weight_casts");
+}
+
+int launch_prepare(int dtype, const float* params, CastMats& mats, const Prepare& pr, void* stream) {
+  const int es = dtype == DYNB_BF16 ? 2 : 4;
+  double n = 0.0;
+  if (int rc = count_blocks(mats, cast_tile_columns(false), n)) return rc;
+  const int64_t granules = (int64_t)pr.rows * (pr.ld / 8);
+  int64_t pads = 0;
+  for (int q = 0; q < pr.n; ++q) {
+    const int64_t t = (int64_t)pr.pad_rows[q] * (pr.pad_ld[q] - pr.pad_from[q]);
+    pads = t > pads ? t : pads;
+  }
+  const int pack_blocks = (int)(granules / 256 < 2048 ? (granules + 255) / 256 : 2048);
+  const int pad_blocks = (int)(pads / 1024 < 1024 ? (pads + 1023) / 1024 : 1024);
+  const int blocks = mats.first_block[mats.n] + pack_blocks + pad_blocks;
+  if (blocks == 0) return DYNB_OK;
+  Timed t(KC_WEIGHT_CAST, stream, 0, n * (4 + 2 * es) + (double)pr.rows * pr.D * (4 + es));
+  if (dtype == DYNB_BF16)
+    hipLaunchKernelGGL(prepare_kernel<bf16>, dim3(blocks), dim3(256), 0, (hipStream_t)stream, params, mats, pr,
+                       pack_blocks, pad_blocks);
+  else
+    hipLaunchKernelGGL(prepare_kernel<float>, dim3(blocks), dim3(256), 0, (hipStream_t)stream, params, mats, pr,
+                       pack_blocks, pad_blocks);
+  return ok("prepare");
 }
 
 void set_adam(UpdateRule& r, double beta1, double beta2, float eps, int64_t t) {
