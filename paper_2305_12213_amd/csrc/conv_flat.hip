@@ -200,13 +200,15 @@ void launch_as(const ConvFlatArgs& p, hipStream_t st) {
 // (32-pixel-wide images with whole 64-channel blocks stay on the halo-tile kernel, whose operand
 // addresses are constants.  64 to more than 32 channels stay on the gathered-operand GEMM: 64 is a power
 // of two, for which its addressing is cheap, and fills its tile -- 367 x 28 x 28 pixels: forward 51 us on
-// either, input gradient 62 - 70 against 60 - 76; 48 channels 38 and 50 against 28 and 39.  Pitches are
-// multiples of 64 channels, so whole 32-channel blocks exist.)
+// either, input gradient 62 - 70 against 60 - 76; 48 channels 38 and 50 against 28 and 39.  Whole blocks of
+// output channels are stored.)
 bool conv_flat_applies(int dtype, const GemmArgs& a) {
   if (dtype != DYNB_BF16 || !a.conv || a.mode == MODE_WGRAD || a.stride != 1) return false;
   if (a.src_w > MAX_W || a.src_w != a.row_w || a.src_h != a.row_h || a.cp > 64 || (a.cp == 64 && a.N > 32)) return false;
-  if (a.Cf || !a.C || a.M % (a.src_h * a.src_w) || a.lda % 64 || a.ldc % 64 || a.ldb % 64) return false;
-  if ((a.mask && a.ldmask % 64) || (a.addend && a.ldadd % 64)) return false;
+  if (a.Cf || !a.C || a.M % (a.src_h * a.src_w) || a.lda % 32 || a.ldc % 32 || a.ldb % 64) return false;
+  const int64_t block = a.N <= 32 ? 32 : round_up(a.N, 64);   // the output channels that whole blocks cover
+  if (a.ldc < block || (a.mask && (a.ldmask % 32 || a.ldmask < block))) return false;
+  if (a.addend && (a.ldadd % 32 || a.ldadd < block)) return false;
   return a.ldb <= (a.cp <= 32 ? 320 : 576) && a.ldb >= 9 * a.cp && a.lda >= (a.cp <= 32 ? 32 : 64);
 }
 

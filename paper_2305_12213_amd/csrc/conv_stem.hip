@@ -28,7 +28,7 @@ struct StemArgs {
   // forward
   const bf16* w; int kf;             // [N][kf]: w[co][tap * 8 + ci], kf >= 80
   const float* bias; int N, relu;
-  bf16* out; int64_t ldo;            // [pixels][ldo], whole 64-channel blocks
+  bf16* out; int64_t ldo;            // [pixels][ldo], whole 32-channel blocks
   // weight gradient
   const bf16* dy; int64_t ldd;       // [pixels][ldd]
   float* partial;                    // [chunk][64-channel block][PART] chunk results
@@ -132,7 +132,7 @@ __global__ __launch_bounds__(256) void stem_forward_kernel(StemArgs p) {
   for (int t = 0; t < 8; ++t) {
     const int r = 8 * t + (lane >> 3);
     const uint4 o = *(const uint4*)(mine + r * OPITCH + (lane & 7) * 16);
-    if (pix0 + r < p.pixels) *(uint4*)(p.out + (pix0 + r) * p.ldo + j0 + (lane & 7) * 8) = o & keep;
+    if (pix0 + r < p.pixels && j0 + (lane & 7) * 8 < p.ldo) *(uint4*)(p.out + (pix0 + r) * p.ldo + j0 + (lane & 7) * 8) = o & keep;
   }
 }
 
@@ -168,7 +168,7 @@ __global__ __launch_bounds__(256) void stem_wgrad_kernel(StemArgs p, Segs segs, 
   const int dg = (lane & 7) ^ (((dslot >> 1) & 1) << 2);
   const char* dsrc = (const char*)(p.dy + (int64_t)(r0 + dslot) * p.ldd + cob * 64 + dg * 8);
   const int64_t dpix = p.ldd * 2;
-  int dleft = n - dslot;
+  int dleft = cob * 64 + dg * 8 < p.ldd ? n - dslot : 0;   // (a narrow row has no upper half: zeros)
   auto issue = [&](uint32_t base) {
 #pragma unroll
     for (int u = 0; u < 2; ++u)
@@ -289,16 +289,16 @@ bool conv_stem_applies(int Cin) { return Cin <= 3; }
 int launch_stem_forward(const float* x, int Cin, int H, int W, int Ho, int Wo, int stride, int64_t pixels,
                         const void* w, int kf, const float* bias, int N, int relu, void* out,
                         int64_t ldo, double flops, double bytes, void* stream) {
-  if (Cin < 1 || Cin > 3 || kf < 80 || kf % 8 || ldo % 64 || ldo < N || pixels >= (int64_t)1 << 31 ||
+  if (Cin < 1 || Cin > 3 || kf < 80 || kf % 8 || ldo % 32 || ldo < N || pixels >= (int64_t)1 << 31 ||
       (((uintptr_t)w | (uintptr_t)out) & 15))
-    return fail(DYNB_ERR_BADARG, "stem: one to three channels, whole 64-channel blocks");
+    return fail(DYNB_ERR_BADARG, "stem: one to three channels, whole 32-channel blocks");
   if (pixels == 0) return DYNB_OK;
   StemArgs p = {};
   p.x = x; p.H = H; p.W = W; p.Ho = Ho; p.Wo = Wo; p.stride = stride; p.pixels = pixels;
   p.w = (const bf16*)w; p.kf = kf; p.bias = bias; p.N = N; p.relu = relu;
   p.out = (bf16*)out; p.ldo = ldo;
   Timed t(KC_GEMM_FWD, stream, flops, bytes);
-  const dim3 grid((unsigned)((pixels + 255) / 256), (unsigned)(ldo / 64));
+  const dim3 grid((unsigned)((pixels + 255) / 256), (unsigned)((ldo + 63) / 64));
   const hipStream_t st = (hipStream_t)stream;
   if (Cin == 1) hipLaunchKernelGGL(stem_forward_kernel<1>, grid, dim3(256), 0, st, p);
   else if (Cin == 2) hipLaunchKernelGGL(stem_forward_kernel<2>, grid, dim3(256), 0, st, p);
@@ -310,9 +310,9 @@ int launch_stem_wgrad(const float* x, int Cin, int H, int W, int Ho, int Wo, int
                       int64_t ldd, int Cout, int chunk_rows, float* scratch, int64_t scratch_floats, float* dW,
                       float* db, int64_t group_stride, const Segs& s, double flops, double bytes, void* stream) {
   const int cobs = (Cout + 63) / 64;
-  if (Cin < 1 || Cin > 3 || ldd % 64 || ldd < 64 * cobs || chunk_rows < 64 ||
+  if (Cin < 1 || Cin > 3 || ldd % 32 || ldd < Cout || chunk_rows < 64 ||
       (((uintptr_t)dy | (uintptr_t)scratch) & 15))
-    return fail(DYNB_ERR_BADARG, "stem: one to three channels, whole 64-channel blocks, 16-byte aligned");
+    return fail(DYNB_ERR_BADARG, "stem: one to three channels, whole 32-channel blocks, 16-byte aligned");
   const RowChunks ch = make_row_chunks(s, chunk_rows);
   const int nch = ch.first[s.K];
   if ((int64_t)nch * cobs * PART > scratch_floats) return fail(DYNB_ERR_BADARG, "stem: scratch area too small");

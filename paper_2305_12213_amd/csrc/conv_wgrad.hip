@@ -138,6 +138,7 @@ __global__ __launch_bounds__(256 * G) void conv_wgrad_chunk_kernel(ConvWgradArgs
   int left = n - prow;                           // > 0 while this lane's pixel lies in the chunk
   const bf16* in_c = p.in + cib * 64 + gq * 8;
   const bf16* dy_c = p.dy + cob * 64 + gq * 8;
+  const bool in_has = cib * 64 + gq * 8 < p.ldi, dy_has = cob * 64 + gq * 8 < p.ldd;   // (narrow rows: no upper half)
 
   auto issue = [&](int t, int kh) {              // stage t = block t/3, kernel row kh = t%3
     const uint32_t base = lds0 + (uint32_t)((t % S) * STAGE_BYTES + wave * 1024);
@@ -154,11 +155,11 @@ __global__ __launch_bounds__(256 * G) void conv_wgrad_chunk_kernel(ConvWgradArgs
       const int sx = ox * p.stride + kw - 1;
       const int csx = sx < 0 ? 0 : (sx >= p.W ? p.W - 1 : sx);
       const bf16* a = in_c + (int64_t)(line + csx) * p.ldi;
-      const void* src = (row_ok && sx >= 0 && sx < p.W) ? (const void*)a : p.zeros;
+      const void* src = (row_ok && in_has && sx >= 0 && sx < p.W) ? (const void*)a : p.zeros;
       async_copy_1k(src, base + kw * TILE_BYTES);
     }
     const bf16* d = dy_c + (int64_t)(valid ? row : 0) * p.ldd;
-    const void* src = valid ? (const void*)d : p.zeros;
+    const void* src = valid && dy_has ? (const void*)d : p.zeros;
     async_copy_1k(src, base + 3 * TILE_BYTES);
   };
   auto next_block = [&]() {                      // this lane's pixel, 32 pixels on
@@ -293,11 +294,11 @@ __global__ __launch_bounds__(256 * G) void conv_wgrad_rows_kernel(ConvWgradArgs 
     ptr[u] = nullptr;
     if (c < 15) {
       const int x = 8 * (c % 5) + (lane >> 3) - 1;
-      if (x >= 0 && x < 32) {
+      if (x >= 0 && x < 32 && cib * 64 + gq * 8 < p.ldi) {   // (narrow rows have no upper half)
         kind[u] = c / 5;
         ptr[u] = (const char*)(p.in + ((int64_t)(o0 + c / 5 - 1) * 32 + x) * p.ldi + cib * 64 + gq * 8);
       }
-    } else if (c < 19) {
+    } else if (c < 19 && cob * 64 + gq * 8 < p.ldd) {
       kind[u] = 3;
       ptr[u] = (const char*)(p.dy + ((int64_t)o0 * 32 + 8 * (c - 15) + (lane >> 3)) * p.ldd + cob * 64 + gq * 8);
     }
@@ -693,9 +694,9 @@ int launch_conv_wgrad(const void* in, int64_t ldi, int Cin, int H, int W, const 
                       const Segs& s, double flops, double bytes, void* stream) {
   if (Cin <= 0 || Cout <= 0) return DYNB_OK;
   const int cibs = (Cin + 63) / 64, cobs = (Cout + 63) / 64;
-  if (ldi % 64 || ldd % 64 || ldi < 64 * cibs || ldd < 64 * cobs || chunk_rows < 32 || chunk_rows % 32 ||
+  if (ldi % 32 || ldd % 32 || ldi < Cin || ldd < Cout || (Cin > 32 && ldi % 64) || (Cout > 32 && ldd % 64) || chunk_rows < 32 || chunk_rows % 32 ||
       (((uintptr_t)in | (uintptr_t)dy | (uintptr_t)scratch) & 15))
-    return fail(DYNB_ERR_BADARG, "conv_wgrad: pitches must cover whole 64-channel blocks, 16-byte aligned");
+    return fail(DYNB_ERR_BADARG, "conv_wgrad: pitches must cover whole 32-channel blocks, 16-byte aligned");
   if (ldi > INT_MAX || ldd > INT_MAX || (int64_t)s.off[s.K] * stride * stride > INT_MAX / 2)
     return fail(DYNB_ERR_UNSUPPORTED, "conv_wgrad: tensor too large for 32-bit pixel indices");
   const void* zeros = device_zero_granule();

@@ -1,7 +1,7 @@
 // Device helpers for kernels that walk row-major bf16 tensors [rows][ld] with 16-byte
-// accesses: a lane takes 8 neighbouring channels of a row, 8 lanes one 128-byte line, the 256
-// threads of a workgroup 32 rows x 64 channels per pass (channel granule = tid & 7, row-lane =
-// tid >> 3).
+// accesses: a lane takes 8 neighbouring channels of a row, LPR lanes a line of 8 LPR channels (LPR = 8: 128
+// bytes; 4: the 64-byte rows of narrow tensors), the 32 LPR threads of a workgroup 32 rows per pass
+// (channel granule = tid % LPR, row-lane = tid / LPR).
 #ifndef DYNB_DEVICE_ROWS_H
 #define DYNB_DEVICE_ROWS_H
 
@@ -45,44 +45,50 @@ __device__ inline void store8(bf16* p, const uint4& q) { *reinterpret_cast<uint4
 // so that no branch stands between the loads and all are in flight together; the address is one uniform
 // base and a 32-bit offset (256 rows of a tensor below 2 GiB).
 constexpr int ROWS_IN_FLIGHT = 8;          // per lane
+template <int LPR>
 __device__ inline void load_rows(const bf16* base, int64_t ld, int n, uint4 (&q)[ROWS_IN_FLIGHT]) {
-  const uint32_t pitch = (uint32_t)ld * 2, g = (threadIdx.x & 7) * 16;
-  const int rl = threadIdx.x >> 3;
+  const uint32_t pitch = (uint32_t)ld * 2, g = (threadIdx.x % LPR) * 16;
+  const int rl = threadIdx.x / LPR;
 #pragma unroll
   for (int i = 0; i < ROWS_IN_FLIGHT; ++i)
     q[i] = *(const uint4*)((const char*)base + ((uint32_t)min(rl + 32 * i, n - 1) * pitch + g));
 }
 
-// Sums a[0..7] (this lane's 8 channels) over the 32 row-lanes of the workgroup, in a fixed order; `red` is
+// Sums a[0..7] (this lane's 8 channels) over the 32 row-lanes of the workgroup, in a fixed order (the same for
+// every LPR): eight neighbouring row-lanes as a tree, then the four groups of eight in turn; `red` is
 // workgroup-shared.  Each exchange between lanes halves the channels that a lane still carries (7 exchanges
-// instead of the 24 of whole vectors, the same additions), so that a lane ends with one channel of its wave.
-__device__ inline void sum_over_wave_rows(const float (&a)[8], float* red) {
-  const int lane = threadIdx.x & 63;
-  const bool u = lane & 8, v = lane & 16, w = lane & 32;
+// instead of the 24 of whole vectors), so that a lane ends with one channel of its group.
+template <int LPR>
+__device__ inline void sum_over_row_group(const float (&a)[8], float (*red)[8 * LPR]) {
+  const int t = threadIdx.x;
+  const bool u = t & LPR, v = t & (2 * LPR), w = t & (4 * LPR);
   float b[4], c[2];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) b[j] = (u ? a[j + 4] : a[j]) + __shfl_xor(u ? a[j] : a[j + 4], 8);
+  for (int j = 0; j < 4; ++j) b[j] = (u ? a[j + 4] : a[j]) + __shfl_xor(u ? a[j] : a[j + 4], LPR);
 #pragma unroll
-  for (int j = 0; j < 2; ++j) c[j] = (v ? b[j + 2] : b[j]) + __shfl_xor(v ? b[j] : b[j + 2], 16);
-  red[(lane & 7) * 8 + (u ? 4 : 0) + (v ? 2 : 0) + (w ? 1 : 0)] = (w ? c[1] : c[0]) + __shfl_xor(w ? c[0] : c[1], 32);
+  for (int j = 0; j < 2; ++j) c[j] = (v ? b[j + 2] : b[j]) + __shfl_xor(v ? b[j] : b[j + 2], 2 * LPR);
+  red[t / (8 * LPR)][(t % LPR) * 8 + (u ? 4 : 0) + (v ? 2 : 0) + (w ? 1 : 0)] =
+      (w ? c[1] : c[0]) + __shfl_xor(w ? c[0] : c[1], 4 * LPR);
 }
 
 // ... every thread ends with the totals of its channels
-__device__ inline void sum_over_rows(float (&a)[8], float (*red)[64]) {
-  const int cg = threadIdx.x & 7;
+template <int LPR>
+__device__ inline void sum_over_rows(float (&a)[8], float (*red)[8 * LPR]) {
+  const int cg = threadIdx.x % LPR;
   __syncthreads();
-  sum_over_wave_rows(a, red[threadIdx.x >> 6]);
+  sum_over_row_group<LPR>(a, red);
   __syncthreads();
 #pragma unroll
   for (int j = 0; j < 8; ++j)
     a[j] = ((red[0][cg * 8 + j] + red[1][cg * 8 + j]) + red[2][cg * 8 + j]) + red[3][cg * 8 + j];
 }
 
-// ... the total of channel threadIdx.x, for the first 64 threads
-__device__ inline float channel_sum(const float (&a)[8], float (*red)[64]) {
-  const int c = threadIdx.x & 63;
+// ... the total of channel threadIdx.x, for the first 8 LPR threads
+template <int LPR>
+__device__ inline float channel_sum(const float (&a)[8], float (*red)[8 * LPR]) {
+  const int c = threadIdx.x % (8 * LPR);
   __syncthreads();
-  sum_over_wave_rows(a, red[threadIdx.x >> 6]);
+  sum_over_row_group<LPR>(a, red);
   __syncthreads();
   return ((red[0][c] + red[1][c]) + red[2][c]) + red[3][c];
 }

@@ -12,7 +12,8 @@ namespace dynb {
 // Records a thread-local message and returns `code`.
 int fail(int code, const char* fmt, ...);
 
-constexpr int COL_PAD = 64;   // leading dimensions are padded to a multiple of this
+constexpr int COL_PAD = 64;   // leading dimensions are padded to a multiple of this ...
+constexpr int NARROW_PITCH = 32;   // ... except images of at most so many channels, whose rows are this wide
 
 inline int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
 

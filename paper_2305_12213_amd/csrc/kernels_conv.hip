@@ -9,21 +9,23 @@ namespace dynb {
 namespace {
 
 // pooled[n][c] = mean over the HW pixels of act[(n, pixel)][c]   (fp32 sum in a fixed order,
-// bf16 store).  One workgroup per (sample, 64 channels); padding channels are written as zero.
+// bf16 store).  One workgroup per (sample, 8 LPR channels); padding channels are written as zero (those
+// beyond act's pitch hold zeros and keep them).
 // (eight rows of a lane in flight: 512 x 32 x 32 x 64 19 -> 12.8 us, 167 x 28 x 28 x 24 10.8 -> 5.8)
-__global__ __launch_bounds__(256) void gap_forward_kernel(const bf16* __restrict__ act, int64_t lda,
+template <int LPR>
+__global__ __launch_bounds__(32 * LPR) void gap_forward_kernel(const bf16* __restrict__ act, int64_t lda,
                                                           int HW, int C, bf16* __restrict__ pooled,
                                                           int64_t ldp) {
-  __shared__ float red[4][64];
-  const int cg = threadIdx.x & 7, rl = threadIdx.x >> 3;
-  const int n = blockIdx.x, c0 = blockIdx.y * 64 + cg * 8;
-  const bf16* base = act + (int64_t)n * HW * lda + blockIdx.y * 64;
+  __shared__ float red[4][8 * LPR];
+  const int cg = threadIdx.x % LPR, rl = threadIdx.x / LPR;
+  const int n = blockIdx.x, c0 = blockIdx.y * (8 * LPR) + cg * 8;
+  const bf16* base = act + (int64_t)n * HW * lda + blockIdx.y * (8 * LPR);
   float acc[8];
 #pragma unroll
   for (int j = 0; j < 8; ++j) acc[j] = 0.f;
   for (int p0 = 0; p0 < HW; p0 += 32 * ROWS_IN_FLIGHT) {
     uint4 q[ROWS_IN_FLIGHT];
-    load_rows(base + (int64_t)p0 * lda, lda, HW - p0, q);
+    load_rows<LPR>(base + (int64_t)p0 * lda, lda, HW - p0, q);
 #pragma unroll
     for (int i = 0; i < ROWS_IN_FLIGHT; ++i) {
       float v[8];
@@ -32,7 +34,7 @@ __global__ __launch_bounds__(256) void gap_forward_kernel(const bf16* __restrict
       for (int j = 0; j < 8; ++j) acc[j] += p0 + rl + 32 * i < HW ? v[j] : 0.f;
     }
   }
-  sum_over_rows(acc, red);
+  sum_over_rows<LPR>(acc, red);
   if (rl == 0) {
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc[j] = c0 + j < C ? acc[j] / (float)HW : 0.f;
@@ -74,18 +76,24 @@ inline int ok(const char* what) {
 int launch_gap_forward(const void* act, int64_t lda, int HW, int C, int samples, void* pooled,
                        int64_t ldp, void* stream) {
   if (samples == 0) return DYNB_OK;
-  if (lda % 64 || ldp % 64 || lda < ldp) return fail(DYNB_ERR_BADARG, "gap_forward: bad pitches");
+  const bool narrow = lda == NARROW_PITCH;
+  if ((lda % 64 && !narrow) || ldp % 64 || ldp < C || lda < C)
+    return fail(DYNB_ERR_BADARG, "gap_forward: bad pitches");
   Timed t(KC_CONV_AUX, stream, 0, (double)samples * HW * C * 2);
-  dim3 grid(samples, (unsigned)(ldp / 64));
-  hipLaunchKernelGGL(gap_forward_kernel, grid, dim3(256), 0, (hipStream_t)stream, (const bf16*)act,
-                     lda, HW, C, (bf16*)pooled, ldp);
+  const hipStream_t st = (hipStream_t)stream;
+  if (narrow)
+    hipLaunchKernelGGL(gap_forward_kernel<4>, dim3(samples), dim3(128), 0, st, (const bf16*)act, lda, HW, C,
+                       (bf16*)pooled, ldp);
+  else
+    hipLaunchKernelGGL(gap_forward_kernel<8>, dim3(samples, (C + 63) / 64), dim3(256), 0, st, (const bf16*)act, lda,
+                       HW, C, (bf16*)pooled, ldp);
   return ok("gap_forward");
 }
 
 int launch_gap_backward(const void* dpooled, int64_t ldp, const void* act, int64_t lda, int HW,
                         int C, int samples, int relu, void* dact, int64_t ldd, void* stream) {
   if (samples == 0) return DYNB_OK;
-  if (lda % 64 || ldp % 64 || ldd % 64 || ldp < ldd || lda < ldd)
+  if (lda % 8 || ldp % 8 || ldd % 8 || ldp < ldd || lda < ldd)
     return fail(DYNB_ERR_BADARG, "gap_backward: bad pitches");
   const int gpr = (int)(ldd / 8);
   const int64_t total = (int64_t)samples * HW * gpr;

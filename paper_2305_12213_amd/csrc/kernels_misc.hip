@@ -262,7 +262,7 @@ __global__ __launch_bounds__(256) void bias_grad_rows_kernel(const bf16* __restr
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc[j] += v[j];
   }
-  sum_over_rows(acc, red);
+  sum_over_rows<8>(acc, red);
   if (rl == 0) {
 #pragma unroll
     for (int j = 0; j < 8; ++j)

@@ -1,11 +1,13 @@
 // Batch normalisation over each worker's own rows and residual additions (bf16 storage).
 // A "row" is a sample or a pixel; worker k owns rows [off_k, off_{k+1}).  The statistics of a
 // worker never see another worker's rows, so every reduction here runs per (worker, channel).
-// The rows of a worker are cut into chunks of CHUNK_ROWS; one workgroup takes one chunk and 64
-// channels (a lane: 8 channels of a row = one 16-byte access, 8 lanes = the 128 bytes of a row,
+// The rows of a worker are cut into chunks of CHUNK_ROWS; one workgroup takes one chunk and 8 LPR = 64 or 32
+// channels (a lane: 8 channels of a row = one 16-byte access, LPR lanes = the 128 or 64 bytes of a row,
 // 32 rows per pass), writes the chunk's partial result, and a second small kernel merges the
 // chunks of each worker in a fixed order.  All sums are fp32 and deterministic.
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 
 #include "device_rows.h"
 #include "dynb_internal.h"
@@ -32,16 +34,24 @@ __device__ inline void chunk_span(const Segs& s, const Chunks& ch, int chunk, in
   n = min(CHUNK_ROWS, s.off[k + 1] - r0);
 }
 
+// Which of four per-channel arrays this thread fetches (8 LPR threads each; whole waves where that is one).
+template <int LPR>
+__device__ inline int array_of() {
+  const int a = threadIdx.x / (8 * LPR);
+  return LPR == 8 ? __builtin_amdgcn_readfirstlane(a) : a;
+}
+
 // Mean and sum of centred squares of one chunk (its values stay in registers between the two).
-__global__ __launch_bounds__(256) void bn_chunk_stats_kernel(const bf16* __restrict__ x, int64_t ld,
+template <int LPR>
+__global__ __launch_bounds__(32 * LPR) void bn_chunk_stats_kernel(const bf16* __restrict__ x, int64_t ld,
                                                              int C, float* __restrict__ pmean,
                                                              float* __restrict__ pm2, Segs s, Chunks ch) {
-  __shared__ float red[4][64];
-  const int rl = threadIdx.x >> 3, chunk = blockIdx.x, c0 = blockIdx.y * 64;
+  __shared__ float red[4][8 * LPR];
+  const int rl = threadIdx.x / LPR, chunk = blockIdx.x, c0 = blockIdx.y * (8 * LPR);
   int k, r0, n;
   chunk_span(s, ch, chunk, k, r0, n);
   uint4 q[PASSES];
-  load_rows(x + (int64_t)r0 * ld + c0, ld, n, q);
+  load_rows<LPR>(x + (int64_t)r0 * ld + c0, ld, n, q);
   float acc[8], mu[8];
 #pragma unroll
   for (int j = 0; j < 8; ++j) acc[j] = 0.f;
@@ -52,8 +62,8 @@ __global__ __launch_bounds__(256) void bn_chunk_stats_kernel(const bf16* __restr
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc[j] += rl + 32 * i < n ? v[j] : 0.f;
   }
-  sum_over_rows(acc, red);
-  const int l = threadIdx.x & 63;
+  sum_over_rows<LPR>(acc, red);
+  const int l = threadIdx.x % (8 * LPR);
   const float mean = (((red[0][l] + red[1][l]) + red[2][l]) + red[3][l]) / (float)n;
 #pragma unroll
   for (int j = 0; j < 8; ++j) { mu[j] = acc[j] / (float)n; acc[j] = 0.f; }
@@ -66,8 +76,8 @@ __global__ __launch_bounds__(256) void bn_chunk_stats_kernel(const bf16* __restr
       for (int j = 0; j < 8; ++j) { const float d = v[j] - mu[j]; acc[j] += d * d; }
     }
   }
-  const float m2 = channel_sum(acc, red);
-  if (threadIdx.x < 64 && c0 + l < C) {
+  const float m2 = channel_sum<LPR>(acc, red);
+  if (threadIdx.x < 8 * LPR && c0 + l < C) {
     pmean[(int64_t)chunk * C + c0 + l] = mean;
     pm2[(int64_t)chunk * C + c0 + l] = m2;
   }
@@ -144,8 +154,8 @@ __global__ __launch_bounds__(1024) void bn_merge_stats_kernel(const float* __res
 // 524288 rows of 64 channels (67 MB a tensor), against every lane fetching its own 32 coefficients and rows
 // one by one behind a branch: this pass 27 -> 22 us, with the addition 44 -> 33, input gradient 39 -> 32,
 // parameter gradients 31 -> 22 (6.0 - 6.3 TB/s each), statistics 14.3 -> 13.1.
-template <bool SKIP>
-__global__ __launch_bounds__(256) void bn_apply_kernel(const bf16* __restrict__ x, int64_t ldx, int C,
+template <int LPR, bool SKIP>
+__global__ __launch_bounds__(32 * LPR) void bn_apply_kernel(const bf16* __restrict__ x, int64_t ldx, int C,
                                                        const float* __restrict__ gamma,
                                                        const float* __restrict__ beta,
                                                        const float* __restrict__ mean,
@@ -153,18 +163,18 @@ __global__ __launch_bounds__(256) void bn_apply_kernel(const bf16* __restrict__ 
                                                        const bf16* __restrict__ skip, int64_t lds_,
                                                        int relu_sum, bf16* __restrict__ y, int64_t ldy,
                                                        Segs s, Chunks ch) {
-  __shared__ __align__(16) float coef[4][64];              // mean, rstd, gamma, beta
-  const int rl = threadIdx.x >> 3, cg = threadIdx.x & 7, c0 = blockIdx.y * 64;
+  __shared__ __align__(16) float coef[4][8 * LPR];              // mean, rstd, gamma, beta
+  const int rl = threadIdx.x / LPR, cg = threadIdx.x % LPR, c0 = blockIdx.y * (8 * LPR);
   int k, r0, n;
   chunk_span(s, ch, blockIdx.x, k, r0, n);
-  const int what = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), c = c0 + (threadIdx.x & 63);
+  const int what = array_of<LPR>(), c = c0 + threadIdx.x % (8 * LPR);
   const float* const from = what == 0 ? mean + (int64_t)k * C : what == 1 ? rstd + (int64_t)k * C
                             : what == 2 ? gamma : beta;
   const float mine = from[c < C ? c : C - 1];
   uint4 q[PASSES], z[PASSES];
-  load_rows(x + (int64_t)r0 * ldx + c0, ldx, n, q);
-  if (SKIP) load_rows(skip + (int64_t)r0 * lds_ + c0, lds_, n, z);
-  coef[what][threadIdx.x & 63] = c < C ? mine : 0.f;       // (padding channels: all zero, whatever x holds
+  load_rows<LPR>(x + (int64_t)r0 * ldx + c0, ldx, n, q);
+  if (SKIP) load_rows<LPR>(skip + (int64_t)r0 * lds_ + c0, lds_, n, z);
+  coef[what][threadIdx.x % (8 * LPR)] = c < C ? mine : 0.f;       // (padding channels: all zero, whatever x holds
   __syncthreads();                                         // there -- see keep below)
   float mu[8], rs[8], ga[8], be[8];
 #pragma unroll
@@ -203,21 +213,22 @@ __global__ __launch_bounds__(256) void bn_apply_kernel(const bf16* __restrict__ 
 }
 
 // Chunk sums of dy and of dy * xhat (dy already carries this layer's ReLU mask).
-__global__ __launch_bounds__(256) void bn_chunk_param_grad_kernel(
+template <int LPR>
+__global__ __launch_bounds__(32 * LPR) void bn_chunk_param_grad_kernel(
     const bf16* __restrict__ dy, int64_t ldd, const bf16* __restrict__ x, int64_t ldx, int C,
     const float* __restrict__ mean, const float* __restrict__ rstd, float* __restrict__ pdg,
     float* __restrict__ pdb, Segs s, Chunks ch) {
-  __shared__ __align__(16) float coef[2][64];              // mean, rstd
-  __shared__ float red[2][4][64];
-  const int rl = threadIdx.x >> 3, cg = threadIdx.x & 7, chunk = blockIdx.x, c0 = blockIdx.y * 64;
+  __shared__ __align__(16) float coef[2][8 * LPR];              // mean, rstd
+  __shared__ float red[2][4][8 * LPR];
+  const int rl = threadIdx.x / LPR, cg = threadIdx.x % LPR, chunk = blockIdx.x, c0 = blockIdx.y * (8 * LPR);
   int k, r0, n;
   chunk_span(s, ch, chunk, k, r0, n);
-  const int what = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), c = c0 + (threadIdx.x & 63);
+  const int what = array_of<LPR>(), c = c0 + threadIdx.x % (8 * LPR);
   const float mine = (what == 0 ? mean : rstd)[(int64_t)k * C + (c < C ? c : C - 1)];
   uint4 q[PASSES], z[PASSES];
-  load_rows(x + (int64_t)r0 * ldx + c0, ldx, n, q);
-  load_rows(dy + (int64_t)r0 * ldd + c0, ldd, n, z);
-  if (what < 2) coef[what][threadIdx.x & 63] = c < C ? mine : 0.f;
+  load_rows<LPR>(x + (int64_t)r0 * ldx + c0, ldx, n, q);
+  load_rows<LPR>(dy + (int64_t)r0 * ldd + c0, ldd, n, z);
+  if (what < 2) coef[what][threadIdx.x % (8 * LPR)] = c < C ? mine : 0.f;
   __syncthreads();
   float mu[8], rs[8], ag[8], ab[8];
 #pragma unroll
@@ -238,13 +249,12 @@ __global__ __launch_bounds__(256) void bn_chunk_param_grad_kernel(
       }
     }
   }
-  const int wave = threadIdx.x >> 6;
-  sum_over_wave_rows(ag, red[0][wave]);
-  sum_over_wave_rows(ab, red[1][wave]);
+  sum_over_row_group<LPR>(ag, red[0]);
+  sum_over_row_group<LPR>(ab, red[1]);
   __syncthreads();
   if (what < 2 && c < C) {
-    const float(*const t)[64] = red[what];
-    const int l = threadIdx.x & 63;
+    const float(*const t)[8 * LPR] = red[what];
+    const int l = threadIdx.x % (8 * LPR);
     (what == 0 ? pdg : pdb)[(int64_t)chunk * C + c] = ((t[0][l] + t[1][l]) + t[2][l]) + t[3][l];
   }
 }
@@ -270,24 +280,25 @@ __global__ __launch_bounds__(1024) void bn_merge_param_grad_kernel(const float* 
 
 // dx = gamma * rstd * (dy - dbeta/n - xhat * dgamma/n), masked by the producer's ReLU (x > 0);
 // padding channels are written as zero
-__global__ __launch_bounds__(256) void bn_input_grad_kernel(
+template <int LPR>
+__global__ __launch_bounds__(32 * LPR) void bn_input_grad_kernel(
     const bf16* __restrict__ dy, int64_t ldd, const bf16* __restrict__ x, int64_t ldx, int C,
     const float* __restrict__ gamma, const float* __restrict__ mean, const float* __restrict__ rstd,
     const float* __restrict__ dgamma, const float* __restrict__ dbeta, int64_t group_stride,
     int relu_below, bf16* __restrict__ dx, int64_t ldo, Segs s, Chunks ch) {
-  __shared__ __align__(16) float coef[5][64];              // mean, rstd, dgamma / n, dbeta / n, gamma rstd
-  const int rl = threadIdx.x >> 3, cg = threadIdx.x & 7, c0 = blockIdx.y * 64;
+  __shared__ __align__(16) float coef[5][8 * LPR];              // mean, rstd, dgamma / n, dbeta / n, gamma rstd
+  const int rl = threadIdx.x / LPR, cg = threadIdx.x % LPR, c0 = blockIdx.y * (8 * LPR);
   int k, r0, n;
   chunk_span(s, ch, blockIdx.x, k, r0, n);
-  const int what = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63, c = c0 + l;
+  const int what = array_of<LPR>(), l = threadIdx.x % (8 * LPR), c = c0 + l;
   const float* const from = what == 0   ? mean + (int64_t)k * C
                             : what == 1 ? rstd + (int64_t)k * C
                             : what == 2 ? dgamma + (int64_t)k * group_stride
                                         : dbeta + (int64_t)k * group_stride;
   const float mine = from[c < C ? c : C - 1], ga = gamma[c < C ? c : C - 1];
   uint4 q[PASSES], z[PASSES];
-  load_rows(x + (int64_t)r0 * ldx + c0, ldx, n, q);
-  load_rows(dy + (int64_t)r0 * ldd + c0, ldd, n, z);
+  load_rows<LPR>(x + (int64_t)r0 * ldx + c0, ldx, n, q);
+  load_rows<LPR>(dy + (int64_t)r0 * ldd + c0, ldd, n, z);
   const float rows = (float)(s.off[k + 1] - s.off[k]);
   coef[what][l] = c < C ? (what < 2 ? mine : mine / rows) : 0.f;
   if (what == 1) coef[4][l] = c < C ? ga * mine : 0.f;
@@ -391,19 +402,24 @@ int launch_bn_forward(const void* x, int64_t ldx, int C, const float* gamma, con
   const int rows = s.off[s.K];
   if (rows == 0 || C == 0) return DYNB_OK;
   const Chunks ch = make_chunks(s);
-  const int nch = ch.first[s.K], cb = (C + 63) / 64;
+  const int nch = ch.first[s.K];
   float* pmean = scratch;
   float* pm2 = scratch + (int64_t)nch * C;
   // algorithmic bytes: x read and y written once (+ the skip tensor); the statistics pass reads x again
   Timed t(KC_NORM, stream, 0, (double)rows * C * (skip ? 6 : 4));
-  hipLaunchKernelGGL(bn_chunk_stats_kernel, dim3(nch, cb), dim3(256), 0, (hipStream_t)stream,
-                     (const bf16*)x, ldx, C, pmean, pm2, s, ch);
-  hipLaunchKernelGGL(bn_merge_stats_kernel, dim3((C + MERGE_C - 1) / MERGE_C, s.K), dim3(1024), 0, (hipStream_t)stream, pmean,
-                     pm2, C, eps, mean, rstd, s, ch);
-  const auto apply = skip ? bn_apply_kernel<true> : bn_apply_kernel<false>;
-  hipLaunchKernelGGL(apply, dim3(nch, (unsigned)(ldy / 64)), dim3(256), 0, (hipStream_t)stream,
-                     (const bf16*)x, ldx, C, gamma, beta, mean, rstd, relu, (const bf16*)skip, lds_, relu_sum,
-                     (bf16*)y, ldy, s, ch);
+  const hipStream_t st = (hipStream_t)stream;
+  auto launch = [&](auto lpr) {
+    constexpr int LPR = decltype(lpr)::value, COLS = 8 * LPR;
+    hipLaunchKernelGGL(bn_chunk_stats_kernel<LPR>, dim3(nch, (C + COLS - 1) / COLS), dim3(32 * LPR), 0, st,
+                       (const bf16*)x, ldx, C, pmean, pm2, s, ch);
+    hipLaunchKernelGGL(bn_merge_stats_kernel, dim3((C + MERGE_C - 1) / MERGE_C, s.K), dim3(1024), 0, st, pmean,
+                       pm2, C, eps, mean, rstd, s, ch);
+    const auto apply = skip ? bn_apply_kernel<LPR, true> : bn_apply_kernel<LPR, false>;
+    hipLaunchKernelGGL(apply, dim3(nch, (unsigned)(ldy / COLS)), dim3(32 * LPR), 0, st, (const bf16*)x, ldx, C,
+                       gamma, beta, mean, rstd, relu, (const bf16*)skip, lds_, relu_sum, (bf16*)y, ldy, s, ch);
+  };
+  if (ldy == NARROW_PITCH) launch(std::integral_constant<int, 4>());
+  else launch(std::integral_constant<int, 8>());
   return ok("bn_forward");
 }
 
@@ -414,20 +430,26 @@ int launch_bn_backward(const void* dy, int64_t ldd, const void* x, int64_t ldx, 
   const int rows = s.off[s.K];
   if (C == 0) return DYNB_OK;
   const Chunks ch = make_chunks(s);
-  const int nch = ch.first[s.K], cb = (C + 63) / 64;
+  const int nch = ch.first[s.K];
   float* pdg = scratch;
   float* pdb = scratch + (int64_t)nch * C;
   // algorithmic bytes: dy and x read once, dx written once (the kernels read dy and x twice)
   Timed t(KC_NORM, stream, 0, (double)rows * C * (need_dx ? 6 : 4));
-  if (nch > 0)
-    hipLaunchKernelGGL(bn_chunk_param_grad_kernel, dim3(nch, cb), dim3(256), 0, (hipStream_t)stream,
-                       (const bf16*)dy, ldd, (const bf16*)x, ldx, C, mean, rstd, pdg, pdb, s, ch);
-  hipLaunchKernelGGL(bn_merge_param_grad_kernel, dim3((C + MERGE_C - 1) / MERGE_C, s.K), dim3(1024), 0, (hipStream_t)stream, pdg,
-                     pdb, C, dgamma, dbeta, group_stride, ch);
-  if (need_dx && nch > 0)
-    hipLaunchKernelGGL(bn_input_grad_kernel, dim3(nch, (unsigned)(ldo / 64)), dim3(256), 0,
-                       (hipStream_t)stream, (const bf16*)dy, ldd, (const bf16*)x, ldx, C, gamma, mean,
-                       rstd, dgamma, dbeta, group_stride, relu_below, (bf16*)dx, ldo, s, ch);
+  const hipStream_t st = (hipStream_t)stream;
+  auto launch = [&](auto lpr) {
+    constexpr int LPR = decltype(lpr)::value, COLS = 8 * LPR;
+    if (nch > 0)
+      hipLaunchKernelGGL(bn_chunk_param_grad_kernel<LPR>, dim3(nch, (C + COLS - 1) / COLS), dim3(32 * LPR), 0, st,
+                         (const bf16*)dy, ldd, (const bf16*)x, ldx, C, mean, rstd, pdg, pdb, s, ch);
+    hipLaunchKernelGGL(bn_merge_param_grad_kernel, dim3((C + MERGE_C - 1) / MERGE_C, s.K), dim3(1024), 0, st, pdg,
+                       pdb, C, dgamma, dbeta, group_stride, ch);
+    if (need_dx && nch > 0)   // (padding columns that no block covers hold zeros and keep them)
+      hipLaunchKernelGGL(bn_input_grad_kernel<LPR>, dim3(nch, (C + COLS - 1) / COLS), dim3(32 * LPR), 0, st,
+                         (const bf16*)dy, ldd, (const bf16*)x, ldx, C, gamma, mean, rstd, dgamma, dbeta,
+                         group_stride, relu_below, (bf16*)dx, ldo, s, ch);
+  };
+  if (ldd == NARROW_PITCH) launch(std::integral_constant<int, 4>());
+  else launch(std::integral_constant<int, 8>());
   return ok("bn_backward");
 }
 

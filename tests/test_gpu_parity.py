@@ -603,14 +603,36 @@ def test_flat_convolutions(image, channels):
     check_worker_gradients(spec, params, x, y, b, label="flat conv %s %s" % (image, channels))
 
 
+@pytest.mark.parametrize("image,layers", [
+    # rows of at most 32 channels are 64 bytes long unless a dense layer reads them; here each kind of layer
+    # meets a neighbour of the other pitch
+    ((4, 3, 2), lambda: [synth.conv3x3(2, 32, 1), synth.conv3x3(32, 33, 1), synth.conv3x3(33, 31, 2),
+                         synth.conv3x3(31, 12, 2), synth.dense(12, 4, relu=False)]),        # ends in 1 x 1 pixels
+    ((9, 8, 5), lambda: [synth.batchnorm(5, relu=False), synth.conv3x3(5, 40, 2), synth.conv3x3(40, 8, 1),
+                         synth.gap(), synth.dense(8, 4, relu=False)]),                       # the packed input
+    ((16, 32, 3), lambda: [synth.conv3x3(3, 64, 1), synth.conv3x3(64, 24, 1), synth.conv3x3(24, 64, 1),
+                           synth.gap(), synth.dense(64, 4, relu=False)]),                    # rows, halo tiles
+    ((6, 70, 4), lambda: [synth.conv3x3(4, 20, 1), synth.conv3x3(20, 64, 2), synth.conv3x3(64, 32, 1),
+                          synth.gap(), synth.dense(32, 4, relu=False)]),                     # wider than 64 pixels
+])
+def test_narrow_rows_next_to_wide_ones(image, layers):
+    spec = {"dtype": "bf16", "input": image, "classes": 4, "layers": layers()}
+    params = synth.init_params(spec, "he", 93)
+    rng = np.random.default_rng(9)
+    params = [(W, (rng.standard_normal(bb.shape) * 0.1).astype(np.float32)) for W, bb in params]
+    b = [2, 0, 3]
+    x, y = synth.make_batch(spec, "normal", sum(b), 94, 0)
+    check_worker_gradients(spec, params, x, y, b, label="narrow %s" % (image,))
+
+
 @pytest.mark.parametrize("image,channels,b", [
     ((5, 1, 4), 64, [3, 0, 2]),       # one pixel wide; less than a tile
     ((16, 16, 4), 64, [1, 2]),        # tiles that end with an image
-    ((13, 43, 4), 64, [2, 0, 1]),     # the widest images, rows that do not divide a tile
-    ((9, 44, 4), 64, [2, 1]),         # ... and one pixel too wide
-    ((11, 15, 4), 60, [7, 1]),        # padding channels on both sides
+    ((6, 43, 4), 64, [2, 0, 1]),      # the widest images, rows that do not divide a tile
+    ((5, 44, 4), 64, [2, 1]),         # ... and one pixel too wide
+    ((7, 15, 4), 60, [4, 1]),         # padding channels on both sides
     ((7, 9, 4), 130, [3, 2]),         # 64 -> 130 channels: three blocks of outputs
-    ((32, 32, 4), 64, [2, 1]),
+    ((8, 32, 4), 64, [1, 2]),
 ])
 def test_convolutions_with_resident_weights(image, channels, b):
     # 64 reduction channels, stride 1, forward and input gradient, with a residual branch (addend and mask)
