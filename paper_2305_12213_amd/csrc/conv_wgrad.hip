@@ -20,6 +20,7 @@
 
 #include <climits>
 #include <mutex>
+#include <type_traits>
 
 #include "dynb_internal.h"
 #include "lds_async.h"
@@ -242,100 +243,78 @@ __global__ __launch_bounds__(256 * G) void conv_wgrad_chunk_kernel(ConvWgradArgs
                  p.partial + ((int64_t)(chunk * gridDim.y + cib) * gridDim.z + cob) * TILE_FLOATS);
 }
 
-// The same for stride 1 on images exactly 32 pixels wide, where a 32-pixel block is one image
-// row: a stage is one output row, and instead of nine shifted copies it stages the three
-// input rows y-1, y, y+1 once, each with one pixel of (zero) border on both sides, and the three
-// horizontal taps read them at a pixel offset.  5.2 KB per row and stage move into LDS instead
-// of 12 KB, which is what bounds the general kernel.  Stage: 3 x 40 pixel slots (5 KB each),
-// the dy row (4 KB) and 1 KB of padding = 20 copies, 5 per wave; ring of 4 stages.
-constexpr int ROW_TILE = 40 * 128;               // an input row with border, 40 pixel slots
-constexpr int ROW_STAGE = 3 * ROW_TILE + TILE_BYTES + 1024;
-constexpr int ROW_PER = 5;                       // copies per wave and stage
-
-__device__ inline void wait_row_copies(int stages) {
-  switch (stages) {
-    case 0: asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); break;
-    case 1: asm volatile("s_waitcnt vmcnt(%0)" ::"n"(ROW_PER) : "memory"); break;
-    default: asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * ROW_PER) : "memory"); break;
-  }
-}
+// The same for stride 1 on images of 17 to 32 pixels a row: the input rows pass through LDS once.  A stage is
+// one input row and one dy row, 32 pixel slots each (zeros beyond the row) with a zero pixel on both sides of
+// the input, 8 KB, two copies per wave; ring of ROW_RING stages.  Input row q meets dy rows q - 1, q and
+// q + 1 under the kernel rows 2, 1 and 0: the operands of three dy rows stay in registers, so a wave fetches
+// 16 operands per row for its 18 matrix instructions instead of 40 (what bounded the version that staged three
+// input rows per dy row was the LDS: its reads, 20 KB of copies per row, a barrier for half the work).  The two 16-pixel
+// steps of a row are half a stage apart: one is fetched while the other's nine instructions run.
+// Combinations outside the worker's rows or across two images are skipped, not multiplied by zeros.
+// 512 x 32 x 32 pixels, 64 -> 64 channels: 52 -> 45 us, of which some 8 write the results and 20 are matrix
+// instructions; 28 pixels a row took the per-tap kernel: a 64 -> 64 model on 512 x 28 x 28, whole iteration with its
+// other convolutions on resident weights, 364 -> 242.
+constexpr int ROW_RING = 8;
+constexpr int ROW_X = 40 * 128;                  // an input row: eight slots of zeros, 32 pixels; the slots in front of
+                                                 // the next stage's row are those behind this one's
+constexpr int ROW_DY = ROW_RING * ROW_X + 1024;  // the dy rows, 4 KB each
+constexpr int ROW_AREA = ROW_DY + ROW_RING * TILE_BYTES;
 
 template <int G>
-__global__ __launch_bounds__(256 * G) void conv_wgrad_rows_kernel(ConvWgradArgs p, Segs segs, RowChunks ch) {
-  __shared__ uint4 ring[G * S * ROW_STAGE / 16];
-  static_assert(2 * S * ROW_STAGE == TILE_FLOATS * 4, "a result in the space of two rings");
+__global__ __launch_bounds__(256 * G, 2) void conv_wgrad_rows_kernel(ConvWgradArgs p, Segs segs, RowChunks ch) {
+  __shared__ uint4 ring[G == 1 ? ROW_AREA / 16 : TILE_FLOATS / 4];
+  static_assert(2 * ROW_AREA <= TILE_FLOATS * 4, "two rings in the space of a result");
   const int group = G == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
-  const int lane = threadIdx.x & 63, wave = (threadIdx.x >> 6) & 3;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) & 3);
   const int chunk = blockIdx.x, cib = blockIdx.y, cob = blockIdx.z;
   int k, r0, n;
-  chunk_span(segs, ch, chunk, k, r0, n);         // r0 and n are multiples of 32: whole image rows
-  const int rounds = (n / 32 + G - 1) / G;       // stages = output rows; the second group's share is
-  const int T = group == 0 ? rounds : n / 32 - rounds;   // smaller by one if the rows are odd
-  r0 += group * rounds * 32;
+  chunk_span(segs, ch, chunk, k, r0, n);         // whole image rows
+  const int rows = n / p.W, rounds = (rows + G - 1) / G;
+  const int T = group == 0 ? rounds : rows - rounds;   // dy rows of this group (the second's: one less if odd)
+  const int o0 = r0 / p.W + group * rounds;      // first of them (image * H + y)
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)&ring[0] +
-                        (uint32_t)(group * S * ROW_STAGE);
+                        (uint32_t)(group * ROW_AREA);
+  // the zero slots: never copied into
+  for (int e = threadIdx.x & 255; e < (ROW_RING + 1) * 64; e += 256)
+    ring[(group * ROW_AREA + (e >> 6) * ROW_X) / 16 + (e & 63)] = make_uint4(0, 0, 0, 0);
 
-  // ---- global -> LDS.  Copy c = wave + 4u (u < 5) of a stage: c < 15: input row kh = c / 5,
-  // pixel slots [8o, 8o+8), o = c % 5 (slot hx holds source pixel x = hx - 1); 15 <= c < 19:
-  // pixels [8(c-15), +8) of the dy row; c = 19: padding.  This lane moves slot lane/8 of the
-  // eight, granule lane%8; halves of slots 2,3,6,7,... are swapped as in the kernel above.
-  // Rows are contiguous in memory across images, so every copy keeps a running pointer that
-  // moves on by one row per stage; whether a neighbouring row lies inside the image is the same
-  // for the whole wave.  (Cycle counters showed the address arithmetic of this step, done from
-  // scratch with 64-bit products, taking longer than the MFMAs of a stage.)
-  const int gq = (lane & 7) ^ (((lane >> 4) & 1) << 2);
-  const char* ptr[ROW_PER];                      // this lane's source in the stage's row, or nullptr
-  int kind[ROW_PER];                             // 0..2: input row kh, 3: dy, 4: zeros
-  const int o0 = r0 / 32;                        // first output row (image * H + y)
-#pragma unroll
-  for (int u = 0; u < ROW_PER; ++u) {
-    const int c = wave + 4 * u;
-    kind[u] = 4;
-    ptr[u] = nullptr;
-    if (c < 15) {
-      const int x = 8 * (c % 5) + (lane >> 3) - 1;
-      if (x >= 0 && x < 32 && cib * 64 + gq * 8 < p.ldi) {   // (narrow rows have no upper half)
-        kind[u] = c / 5;
-        ptr[u] = (const char*)(p.in + ((int64_t)(o0 + c / 5 - 1) * 32 + x) * p.ldi + cib * 64 + gq * 8);
-      }
-    } else if (c < 19 && cob * 64 + gq * 8 < p.ldd) {
-      kind[u] = 3;
-      ptr[u] = (const char*)(p.dy + ((int64_t)o0 * 32 + 8 * (c - 15) + (lane >> 3)) * p.ldd + cob * 64 + gq * 8);
-    }
-  }
-  const int64_t in_step = (int64_t)32 * p.ldi * 2, dy_step = (int64_t)32 * p.ldd * 2;   // bytes per row
-  int iy = o0 % p.H;                             // image row of the next stage to issue
-  auto issue = [&](int t) {
-    const uint32_t base = lds0 + (uint32_t)((t % S) * ROW_STAGE);
-    const bool above = iy > 0, below = iy < p.H - 1;   // rows y-1 / y+1 exist
-#pragma unroll
-    for (int u = 0; u < ROW_PER; ++u) {
-      const int c = wave + 4 * u;
-      const bool row_ok = kind[u] == 0 ? above : (kind[u] == 2 ? below : true);
-      const void* src = (ptr[u] != nullptr && row_ok) ? (const void*)ptr[u] : p.zeros;
-      const uint32_t dst = c < 15 ? (uint32_t)((c / 5) * ROW_TILE + (c % 5) * 1024)
-                                  : (uint32_t)(3 * ROW_TILE + (c - 15) * 1024);
-      async_copy_1k(src, base + dst);
-      if (ptr[u] != nullptr) ptr[u] += kind[u] == 3 ? dy_step : in_step;
-    }
-    if (++iy == p.H) iy = 0;
+  // ---- global -> LDS: wave w copies pixels 8w .. 8w + 7 of both rows; this lane pixel 8w + lane / 8, granule
+  // lane % 8 with the halves of slots 2, 3, 6, 7, ... swapped as in the kernel above.  Pixels and channels
+  // that do not exist are parked out of the buffer's range (zeros); so is a row in front of the first.
+  const int px = 8 * wave + (lane >> 3), gq = (lane & 7) ^ (((lane >> 4) & 1) << 2);
+  const i32x4 rsx = buffer_resource(p.in, (uint32_t)segs.off[segs.K] * (uint32_t)p.ldi * 2);
+  const i32x4 rsd = buffer_resource(p.dy, (uint32_t)segs.off[segs.K] * (uint32_t)p.ldd * 2);
+  const bool x_has = px < p.W && cib * 64 + gq * 8 < p.ldi, dy_has = px < p.W && cob * 64 + gq * 8 < p.ldd;
+  uint32_t xoff = x_has ? (uint32_t)((((o0 - 1) * p.W + px) * p.ldi + cib * 64 + gq * 8) * 2) : 0x80000000u;
+  uint32_t doff = dy_has ? (uint32_t)(((o0 * p.W + px) * p.ldd + cob * 64 + gq * 8) * 2) : 0x80000000u;
+  const uint32_t xstep = (uint32_t)(p.W * p.ldi * 2), dstep = (uint32_t)(p.W * p.ldd * 2);
+  uint32_t slot = 0;                             // of the next stage to copy
+  auto issue = [&]() {
+    async_copy_1k_buffer(rsx, xoff, lds0 + slot * ROW_X + (uint32_t)(1024 + wave * 1024));
+    async_copy_1k_buffer(rsd, doff, lds0 + ROW_DY + slot * TILE_BYTES + (uint32_t)(wave * 1024));
+    if (x_has) xoff += xstep;
+    if (dy_has) doff += dstep;
+    slot = slot + 1 == ROW_RING ? 0 : slot + 1;
   };
 
-  // ---- LDS -> MFMA operands (see the kernel above); input rows are read at slot x + kw
+  // ---- LDS -> MFMA operands (see the kernel above); pixel x under tap kw lies in slot 7 + x + kw
   const int wci = wave & 1, wco = wave >> 1;
   const int g = lane >> 4, r = lane & 15;
   const uint32_t fcol = (uint32_t)((16 * (g & 1) + 4 * (r & 3)) * 2);
   uint32_t foff_a[3];
 #pragma unroll
   for (int kw = 0; kw < 3; ++kw) {
-    const int hx = 8 * (g >> 1) + (r >> 2) + kw;
-    foff_a[kw] = (uint32_t)(hx * 128 + ((wci ^ ((hx >> 1) & 1)) * 64)) + fcol;
+    const int hx = 7 + 8 * (g >> 1) + (r >> 2) + kw;
+    foff_a[kw] = lds0 + (uint32_t)(hx * 128 + ((wci ^ ((hx >> 1) & 1)) * 64)) + fcol;
   }
   const int fpix = 8 * (g >> 1) + (r >> 2);
-  const uint32_t foff_b = (uint32_t)(fpix * 128 + ((wco ^ ((r >> 3) & 1)) * 64)) + fcol;
-  auto frag = [&](uint32_t tile, uint32_t foff, int kk) {
-    const uint32_t a = tile + foff + (uint32_t)(kk * 16 * 128);
-    const s16x4 lo = lds_read_tr(a), hi = lds_read_tr(a + 4 * 128);
+  const uint32_t foff_b = lds0 + ROW_DY + (uint32_t)(fpix * 128 + ((wco ^ ((r >> 3) & 1)) * 64)) + fcol;
+  // (a row shorter than 32: the slot behind its last dy pixel holds a zero, but under tap 0 it would meet the
+  // last input pixel, and 0 x Inf is NaN: that operand comes from a slot of zeros)
+  const uint32_t left_lo = 16 + fpix == p.W ? lds0 + fcol : foff_a[0] + 16 * 128;
+  const uint32_t left_hi = 20 + fpix == p.W ? lds0 + fcol : foff_a[0] + 20 * 128;
+  auto frag = [&](uint32_t a, uint32_t b) {      // 8 reduction indices
+    const s16x4 lo = lds_read_tr(a), hi = lds_read_tr(b);
     const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
     return __builtin_bit_cast(bf16x8, v);
   };
@@ -351,41 +330,76 @@ __global__ __launch_bounds__(256 * G) void conv_wgrad_rows_kernel(ConvWgradArgs 
   const s16x8 ones_bits = {0x3f80, 0x3f80, 0x3f80, 0x3f80, 0x3f80, 0x3f80, 0x3f80, 0x3f80};
   const bf16x8 ones = __builtin_bit_cast(bf16x8, ones_bits);
 
-  int issued = 0;
+  // Stage t: input row q = o0 - 1 + t, dy row q + 1.  uses: bit kh: dy row q + 1 - kh is this group's and of q's
+  // image; bit 3: dy row q + 1 is this group's.
+  int iy = o0 % p.H;                             // image row of q + 1
+  auto uses_of = [&](int t) {
+    const int above = iy;                        // (> 0: q + 1 and q are of one image)
+    if (++iy == p.H) iy = 0;                     // image row of q + 2; q's row is iy - 2
+    const int q_row = above > 0 ? above - 1 : p.H - 1;
+    int u = 0;
+    if (t < T) u |= 8 | (above > 0 ? 1 : 0);
+    if (t >= 1 && t <= T) u |= 2;
+    if (t >= 2 && t <= T + 1 && q_row > 0) u |= 4;
+    return u;
+  };
+  bf16x8 xa[2][3], d[2][3];                      // [step of the row][kw], [step][dy row % 3]
+  auto multiply = [&](auto step, auto newest, int uses) {
+    constexpr int st = decltype(step)::value, J = decltype(newest)::value;
 #pragma unroll
-  for (int f = 0; f < S - 1; ++f)
-    if (issued < T) { issue(issued); ++issued; }
-  for (int t = 0; t < rounds; ++t) {
-    if (G == 1 || t < T) wait_row_copies(issued - t - 1);   // stage t of this wave has landed
-    __syncthreads();                             // ... of all waves; stage t-1 is no longer read
-    if (G == 2 && t >= T) continue;              // (the same for all waves of the group)
-    if (issued < T) { issue(issued); ++issued; }
-    const uint32_t stage = lds0 + (uint32_t)((t % S) * ROW_STAGE);
-    const bf16x8 b0 = frag(stage + 3 * ROW_TILE, foff_b, 0);
-    const bf16x8 b1 = frag(stage + 3 * ROW_TILE, foff_b, 1);
-    // the operands of tap n+1 are fetched before the MFMAs of tap n (two register sets), so
-    // that the LDS latency hides behind them; the column sums run in every wave (no branch in
-    // the loop), only the waves that own them write them out
-    bf16x8 a0[2], a1[2];
-    a0[0] = frag(stage, foff_a[0], 0);
-    a1[0] = frag(stage, foff_a[0], 1);
+    for (int kh = 0; kh < 3; ++kh) {
+      if (!((uses >> kh) & 1)) continue;
 #pragma unroll
-    for (int tap = 0; tap < 9; ++tap) {
-      if (tap + 1 < 9) {
-        const int nh = (tap + 1) / 3, nw = (tap + 1) - 3 * nh;
-        a0[(tap + 1) & 1] = frag(stage + nh * ROW_TILE, foff_a[nw], 0);
-        a1[(tap + 1) & 1] = frag(stage + nh * ROW_TILE, foff_a[nw], 1);
-      }
-      __builtin_amdgcn_sched_barrier(0);         // (keeps the fetches in front of the MFMAs)
-      if (tap == 4) {
-        colsum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b0, ones, colsum, 0, 0, 0);
-        colsum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b1, ones, colsum, 0, 0, 0);
-      }
-      acc[tap] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b0, a0[tap & 1], acc[tap], 0, 0, 0);
-      acc[tap] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b1, a1[tap & 1], acc[tap], 0, 0, 0);
-      __builtin_amdgcn_sched_barrier(0);
+      for (int kw = 0; kw < 3; ++kw)
+        acc[kh * 3 + kw] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(d[st][(J + 3 - kh) % 3], xa[st][kw],
+                                                                   acc[kh * 3 + kw], 0, 0, 0);
     }
+    if (sums_columns && (uses & 8))
+      colsum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(d[st][J], ones, colsum, 0, 0, 0);
+  };
+  uint32_t at = 0;                               // slot of stage t
+  int last_uses = 0;
+  auto stage = [&](int t, auto newest) {         // newest: t % 3
+    constexpr int J = decltype(newest)::value;
+    using Prev = std::integral_constant<int, (J + 2) % 3>;
+    // this wave's part of stage t has landed, its reads of stage t - 1 have returned (what they fetched is not
+    // used yet, so nothing else waits for them) ...
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * (ROW_RING - 2)) : "memory");
+    __builtin_amdgcn_s_waitcnt(0xc07f);          // lgkmcnt(0), the other counters at their limits
+    __syncthreads();                             // ... and so for every wave
+    issue();                                     // into its place
+    const uint32_t xs = at * ROW_X, ds = at * TILE_BYTES;
+    at = at + 1 == ROW_RING ? 0 : at + 1;
+#pragma unroll
+    for (int kw = 0; kw < 3; ++kw) xa[0][kw] = frag(foff_a[kw] + xs, foff_a[kw] + xs + 4 * 128);
+    d[0][J] = frag(foff_b + ds, foff_b + ds + 4 * 128);
+    __builtin_amdgcn_sched_barrier(0);
+    multiply(std::integral_constant<int, 1>(), Prev(), last_uses);
+    __builtin_amdgcn_sched_barrier(0);
+    xa[1][0] = frag(left_lo + xs, left_hi + xs);
+#pragma unroll
+    for (int kw = 1; kw < 3; ++kw) xa[1][kw] = frag(foff_a[kw] + xs + 16 * 128, foff_a[kw] + xs + 20 * 128);
+    d[1][J] = frag(foff_b + ds + 16 * 128, foff_b + ds + 20 * 128);
+    __builtin_amdgcn_sched_barrier(0);
+    last_uses = uses_of(t);
+    multiply(std::integral_constant<int, 0>(), newest, last_uses);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+#pragma unroll 1
+  for (int t = 0; t < ROW_RING - 1; ++t) issue();
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {                  // (registers that a first multiplication may read)
+    d[0][i] = d[1][i] = ones;
+    xa[0][i] = xa[1][i] = ones;
   }
+  // (one stage more for the second step of the last; stages past the end use nothing)
+#pragma unroll 1
+  for (int t = 0; t < rounds + 3; t += 3) {
+    stage(t, std::integral_constant<int, 0>());
+    stage(t + 1, std::integral_constant<int, 1>());
+    stage(t + 2, std::integral_constant<int, 2>());
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (no copy may land on what follows in this space)
 
   store_chunk<G>(acc, colsum, sums_columns, group, wave, lane, (f32x4*)ring,
                  p.partial + ((int64_t)(chunk * gridDim.y + cib) * gridDim.z + cob) * TILE_FLOATS);
@@ -707,11 +721,13 @@ int launch_conv_wgrad(const void* in, int64_t ldi, int Cin, int H, int W, const 
     return fail(DYNB_ERR_BADARG, "conv_wgrad: scratch area too small");
   // Stride 1 on images at least 8 wide (a fragment's eight pixels then hold one border pixel of each
   // kind at most): the flat kernel, whose blocks are only as wide as the channels need.  Whole rows
-  // of 32-pixel-wide images with a 64-channel side need neither its masks nor its bookkeeping (3 -> 64
-  // channels on 512 x 32 x 32 pixels: 48 us by rows, 57 flat).  Two sides of more than 32 channels stay
-  // on the per-tap kernel (367 x 28 x 28 pixels, 64 -> 64: 50 us against 54; 24 -> 64: 49 against 36).
-  bool by_rows = stride == 1 && W == 32 && Wo == 32 && H == Ho && (Cin > 32 || Cout > 32);
-  for (int k = 0; k <= s.K && by_rows; ++k) by_rows = s.off[k] % 32 == 0;
+  // need neither its masks nor its bookkeeping: of 32 pixels with a 64-channel side (3 -> 64
+  // channels on 512 x 32 x 32 pixels: 48 us by rows, 57 flat), and of more than 16 (below, the second of the
+  // two steps of a row would be empty) with two.  Two sides of more than 32 channels otherwise
+  // stay on the per-tap kernel (367 x 28 x 28 pixels, 64 -> 64: 50 us against 54 flat; 24 -> 64: 49 against 36).
+  bool by_rows = stride == 1 && W > 16 && W <= 32 && Wo == W && H == Ho && (W == 32 ? Cin > 32 || Cout > 32 : Cin > 32 && Cout > 32);
+  by_rows = by_rows && (int64_t)s.off[s.K] * ldi * 2 < (int64_t)1 << 31 && (int64_t)s.off[s.K] * ldd * 2 < (int64_t)1 << 31;
+  for (int k = 0; k <= s.K && by_rows; ++k) by_rows = s.off[k] % W == 0;
   const bool flat = stride == 1 && W >= 8 && H == Ho && W == Wo && !by_rows && (Cin <= 32 || Cout <= 32);
   const int ci32 = flat && Cin <= 32 ? 1 : 2, co32 = flat && Cout <= 32 ? 1 : 2;
   // From about two chunks per compute unit on, two chunks are one workgroup's, whose halves meet in LDS:
@@ -722,10 +738,11 @@ int launch_conv_wgrad(const void* in, int64_t ldi, int Cin, int H, int W, const 
   // Every worker ends with a chunk of its own, so there may be a few chunks more than workgroups that
   // run at a time, which would then run alone at the end: chunks up to a quarter longer, if that
   // makes them fit.
-  const int slots = paired ? 256 : 512, base = paired ? 2 * chunk_rows : chunk_rows;
+  const int slots = paired ? 256 : 512, step = by_rows ? W : 32;
+  const int base = (int)round_up(paired ? 2 * chunk_rows : chunk_rows, step);
   const int64_t per_chunk = (int64_t)cibs * cobs;
   const int64_t fit = round_up(((int64_t)s.off[s.K] + base - 1) / base * per_chunk, slots) / per_chunk;
-  for (int rows = base; rows <= base + base / 4; rows += 32) {
+  for (int rows = base; rows <= base + base / 4; rows += step) {
     const RowChunks longer = make_row_chunks(s, rows);
     if (longer.first[s.K] > fit && rows > base) continue;
     ch = longer;
