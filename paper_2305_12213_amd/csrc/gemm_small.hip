@@ -33,7 +33,10 @@ __device__ inline int swizzle(int r) { return (((r >> 1) & 3) << 1) | ((r >> 3) 
 
 // Forward and input gradient: C[i][j] = sum_k A[i][k] B[j][k].  A stage is 64 reduction elements, the
 // whole 128-byte line of each of the 64 + 64 operand rows (16 copies, four per wave); ring of NB
-// stages, NB - 1 in flight (eight instead of four changed nothing: 17.4 against 17.7 us below).  Copies
+// stages, NB - 1 in flight (eight instead of four changed nothing: 17.4 against 17.7 us below).  A compute unit
+// holds one such workgroup, so what bounds a stage is its serial chain: the next stage's operands are on their
+// way into the other register set while the matrix instructions of this one run (1024 x 1024 x 3072 17 -> 14 us, 1024 x 10 x 1024 with its loss 8.4
+// -> 7.2).  Copies
 // past the last stage are still issued (the wait stays a constant); what they read -- the next rows,
 // zeros past the matrix -- is never used.
 // Against 128 x 128 tiles: 1024 x 1024 x 3072 30 -> 18 us, 1024 x 10 x 1024 14 -> 6, 1531 x 777 x 2050
@@ -79,8 +82,23 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(GemmArgs p, Head head) 
   if constexpr (HEAD) {
     if (threadIdx.x < T) mine = head.y[min(i0 + (int)threadIdx.x, p.M - 1)];
   }
+  // What the epilogue adds to this lane's results (accumulator elements 4q .. 4q+3: row l31, columns 8q + 4h ..)
+  // or masks them with, asked for now: fetched where they are used, every value costs a trip to memory.
+  const int i = i0 + wi * 32 + l31, ic = i < p.M ? i : p.M - 1;
+  float bias[4][4];
+  bf16x4 addend[4], mask[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int j = j0 + wj * 32 + 8 * q + 4 * h, jc = j < p.N ? j : 0;   // (rows are padded to 64: whole quads)
+    if (MODE == MODE_FWD && p.bias) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) bias[q][e] = p.bias[j + e < p.N ? j + e : p.N - 1];
+    }
+    if (MODE == MODE_DGRAD && p.addend) addend[q] = *(const bf16x4*)((const bf16*)p.addend + (int64_t)ic * p.ldadd + jc);
+    if (MODE == MODE_DGRAD && p.mask) mask[q] = *(const bf16x4*)((const bf16*)p.mask + (int64_t)ic * p.ldmask + jc);
+  }
 #pragma unroll 1
-  for (int s = 0; s < NB - 1; ++s) issue((uint32_t)(s * STAGE));
+  for (int s = 0; s < NB; ++s) issue((uint32_t)(s * STAGE));
   if constexpr (HEAD) {
     if (threadIdx.x < T) {                 // (while the first copies are on their way)
       owned[threadIdx.x] = rows_of_owner(head.segs, i0 + (int)threadIdx.x);
@@ -89,27 +107,45 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(GemmArgs p, Head head) 
   }
   const char* const base = (const char*)&ring[0];
   const int fa = (wi * 32 + l31) * 128, fb = T * 128 + (wj * 32 + l31) * 128, sw = swizzle(l31);
-  uint32_t slot = 0, refill = (NB - 1) * STAGE;
-#pragma unroll 1
-  for (int k = 0; k < p.K; k += 64) {
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NB - 2) * 4) : "memory");   // this wave's part of the stage
-    __syncthreads();                       // ... of every wave; the stage before is no longer read
-    issue(refill);
-    bf16x8 a[4], b[4];
+  bf16x8 a[2][4], b[2][4];                 // [register set][step of 16]
+  auto fetch = [&](int set, uint32_t slot) {
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
       const int g = ((2 * kk + h) ^ sw) * 16;
-      a[kk] = *(const bf16x8*)(base + slot + fa + g);
-      b[kk] = *(const bf16x8*)(base + slot + fb + g);
+      a[set][kk] = *(const bf16x8*)(base + slot + fa + g);
+      b[set][kk] = *(const bf16x8*)(base + slot + fb + g);
     }
+  };
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NB - 1) * 4) : "memory");
+  __syncthreads();
+  fetch(0, 0);
+  uint32_t slot = 0;                       // of the stage whose operands are in, or on their way to, `set`
+  auto stage = [&](int set) {
+    // this wave's part of the next stage has landed, its reads of this one have returned (its slot takes the
+    // next copies) ...
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NB - 2) * 4) : "memory");
+    __builtin_amdgcn_s_waitcnt(0xc07f);    // lgkmcnt(0), the other counters at their limits
+    __syncthreads();                       // ... and so for every wave
+    const uint32_t next = slot + STAGE == NB * STAGE ? 0 : slot + STAGE;
+    fetch(set ^ 1, next);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[kk], a[kk], acc, 0, 0, 0);
-    refill = slot;
-    slot = slot + STAGE == NB * STAGE ? 0 : slot + STAGE;
+    for (int kk = 0; kk < 4; ++kk)
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[set][kk], a[set][kk], acc, 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    issue(slot);
+    slot = next;
+  };
+  int k = 0;
+#pragma unroll 1
+  for (; k + 64 < p.K; k += 128) {
+    stage(0);
+    stage(1);
   }
+  if (k < p.K) stage(0);
+  __builtin_amdgcn_s_waitcnt(0xc07f);      // (fetches past the last stage)
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (no copy may land after the LDS has been given back)
 
-  // accumulator elements 4q .. 4q+3 of a lane: row l31, columns 8q + 4h ..
   if constexpr (HEAD) {
     constexpr int PITCH = T + 4;
     float* const logits = (float*)&ring[0];
@@ -120,7 +156,7 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(GemmArgs p, Head head) 
       f32x4 v = {acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        if (p.bias) v[e] += p.bias[j + e < p.N ? j + e : p.N - 1];
+        if (p.bias) v[e] += bias[q][e];
         if (p.relu) v[e] = fmaxf(v[e], 0.f);
       }
       *(f32x4*)&logits[(wi * 32 + l31) * PITCH + j] = v;
@@ -144,7 +180,6 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(GemmArgs p, Head head) 
     }
     return;
   }
-  const int i = i0 + wi * 32 + l31;
   if (i >= p.M) return;
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
@@ -156,7 +191,7 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(GemmArgs p, Head head) 
     if (MODE == MODE_FWD) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        if (p.bias) v[e] += p.bias[j + e < p.N ? j + e : p.N - 1];
+        if (p.bias) v[e] += bias[q][e];
         if (p.relu) v[e] = fmaxf(v[e], 0.f);
       }
       if (p.Cf) {
@@ -167,17 +202,14 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(GemmArgs p, Head head) 
             if (j + e < p.N) cf[e] = v[e];
       }
     } else {
-      // (padding columns of the mask and the addend exist: their rows are padded to 64)
       if (p.addend) {
-        const bf16x4 t = *(const bf16x4*)((const bf16*)p.addend + (int64_t)i * p.ldadd + j);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = (float)(bf16)v[e] + (float)t[e];
+        for (int e = 0; e < 4; ++e) v[e] = (float)(bf16)v[e] + (float)addend[q][e];
       }
       if (p.mask) {
-        const bf16x4 t = *(const bf16x4*)((const bf16*)p.mask + (int64_t)i * p.ldmask + j);
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-          if (!((float)t[e] > 0.f)) v[e] = 0.f;
+          if (!((float)mask[q][e] > 0.f)) v[e] = 0.f;
       }
     }
     if (!p.C) continue;
