@@ -230,7 +230,11 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(GemmArgs p, Head head) 
 // Against 128 x 128 tiles: 1024 x 1024, 8 workers, 1024 rows 12 us + 8 (average) -> 17; 3072 x 1024 31
 // + 22 -> 24; 2050 x 777, 7 workers, 1531 rows 34 -> 20; 777 x 101 11 + 5 (sum of its parts) + 5
 // (biases) -> 7.
-constexpr int WNB = 6, WSTAGE = 2 * 32 * 128;
+// What bounds the stages is the LDS: a wave reads 4 KB through the transpose read for two matrix instructions
+// (without stores and copies the three layers of 3072-1024-1024-10 take 19 us, with all 39).  The two 16-row
+// steps of a stage are half a stage apart -- one is fetched while the other's product runs -- and four
+// workgroups of at most 128 registers a lane share a compute unit instead of three: 41 -> 39 us.
+constexpr int WNB = 5, WSTAGE = 2 * 32 * 128;
 
 __device__ inline bf16x8 read_tr(uint32_t a) {   // rows 4 apart: same swizzle
   const s16x4 lo = lds_read_tr(a), hi = lds_read_tr(a + 512);
@@ -256,7 +260,15 @@ struct SmallWgrads {
   StepEnd end;
 };
 
-__global__ __launch_bounds__(256) void wgrad_small_kernel(SmallWgrads grp, Segs segs) {
+// PAST: results, the averages too, leave past the caches.  Right for rows of whole 128-byte lines with the
+// average formed here: kept in the L2s, as dirty lines they cost the 3072-1024-1024-10 model 13 us per iteration
+// at the ends of launches.  Other results go through the caches: past them, every piece of a line is written on
+// its own, and what the update or a pass reads next is in memory only (2048-256 behind a pass, 32 workers: 606 ->
+// 602 us per iteration; 1001-2050-777-101, 7 workers, with Adam: 192 -> 182 us; 1000-1000-1000-100, 32
+// workers: 185 -> 120; 2000-1500-20, 8 workers: 109 -> 81).  (A kernel of its own each: the compiler makes one
+// plain store of the two in a branch.)
+template <bool PAST>
+__global__ __launch_bounds__(256, 4) void wgrad_small_kernel(SmallWgrads grp, Segs segs) {
   __shared__ uint4 ring[WNB * WSTAGE / 16];
   if ((int)blockIdx.x < grp.ends) {
     if (threadIdx.x < 64) end_worker(grp.end, segs, blockIdx.x);
@@ -307,6 +319,7 @@ __global__ __launch_bounds__(256) void wgrad_small_kernel(SmallWgrads grp, Segs 
   const bf16x8 ones = __builtin_bit_cast(bf16x8, ones_bits);
 
   f32x16 acc, agg, bsum;
+  bf16x8 a[2], b[2];
 #pragma unroll
   for (int v = 0; v < 16; ++v) acc[v] = agg[v] = bsum[v] = 0.f;
   float bagg = 0.f;
@@ -320,9 +333,8 @@ __global__ __launch_bounds__(256) void wgrad_small_kernel(SmallWgrads grp, Segs 
       const int j = 8 * (v / 4) + (v & 3);
       if (jw + j >= p.N) continue;
       float* const e = d + (int64_t)j * p.ldcf;
-      // (past the caches, the average too: kept in the L2s as 12 + 4 MB of dirty lines it costs the
-      // 3072-1024-1024-10 model 13 us per iteration at the ends of these launches and saves the update 4)
-      __builtin_nontemporal_store(src[v], e);
+      if (PAST) __builtin_nontemporal_store(src[v], e);
+      else *e = src[v];
     }
   };
 #pragma unroll 1
@@ -333,25 +345,31 @@ __global__ __launch_bounds__(256) void wgrad_small_kernel(SmallWgrads grp, Segs 
     const int rows = segs.off[g + 1] - segs.off[g];
     int r = 0;
     do {
-      // (stores count as pending too: the wait then covers more than it has to, never less)
+      // (stores count as pending too: the wait then covers more than it has to, never less; the reads of the
+      // stage before have returned too, whose second step is not used yet)
       asm volatile("s_waitcnt vmcnt(%0)" ::"n"((WNB - 2) * 2) : "memory");
+      __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0), the other counters at their limits
       __syncthreads();                     // the stage of every wave; the one before is no longer read
       issue(refill);
-      bf16x8 a[2], b[2];
-#pragma unroll
-      for (int kk = 0; kk < 2; ++kk) {
-        a[kk] = read_tr(ta + slot + kk * 16 * 128);
-        b[kk] = read_tr(tb + slot + kk * 16 * 128);
+      a[0] = read_tr(ta + slot);
+      b[0] = read_tr(tb + slot);
+      __builtin_amdgcn_sched_barrier(0);
+      if (r > 0) {
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[1], a[1], acc, 0, 0, 0);
+        if (bias) bsum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, a[1], bsum, 0, 0, 0);
       }
-#pragma unroll
-      for (int kk = 0; kk < 2; ++kk) {
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[kk], a[kk], acc, 0, 0, 0);
-        if (bias) bsum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, a[kk], bsum, 0, 0, 0);
-      }
+      __builtin_amdgcn_sched_barrier(0);
+      a[1] = read_tr(ta + slot + 16 * 128);
+      b[1] = read_tr(tb + slot + 16 * 128);
+      __builtin_amdgcn_sched_barrier(0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[0], a[0], acc, 0, 0, 0);
+      if (bias) bsum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, a[0], bsum, 0, 0, 0);
       refill = slot;
       slot = slot + WSTAGE == WNB * WSTAGE ? 0 : slot + WSTAGE;
       r += 32;
     } while (r < rows);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[1], a[1], acc, 0, 0, 0);
+    if (bias) bsum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, a[1], bsum, 0, 0, 0);
     store(p.Cf + (int64_t)g * grp.group_stride, acc);
     if (bias && h == 0 && i < p.M) p.bias_grad[(int64_t)g * grp.group_stride + i] = bsum[0];
     if (p.agg) {
@@ -437,10 +455,11 @@ int launch_wgrad_small(const GemmArgs* a, int n, const Segs& s, const StepEnd* e
   if (n > WGRAD_SMALL_ITEMS) return fail(DYNB_ERR_BADARG, "gemm: too many weight gradients for one launch");
   SmallWgrads grp = {};
   double flops = 0, bytes = 0;
-  int64_t blocks = 0;
+  int64_t blocks = 0, past = 0;            // past: weights whose results should leave past the caches, less the others
   for (int q = 0; q < n; ++q) {
     const GemmArgs& g = a[q];
     if (g.M <= 0 || g.N <= 0) continue;
+    past += !g.agg || (g.ldcf & 31) || ((uintptr_t)g.Cf & 127) ? -(int64_t)g.M * g.N : (int64_t)g.M * g.N;
     if (!gemm_small_applies(g) || !g.bias_grad || (g.agg && !g.bias_agg) || g.split > 1 ||
         (grp.n && g.group_stride != grp.group_stride))
       return fail(DYNB_ERR_BADARG, "gemm: not a weight gradient of few tiles with its bias gradient");
@@ -466,7 +485,8 @@ int launch_wgrad_small(const GemmArgs* a, int n, const Segs& s, const StepEnd* e
   }
   if (!grp.n && !grp.ends) return DYNB_OK;
   Timed t(KC_GEMM_WGRAD_64, stream, flops, bytes);
-  hipLaunchKernelGGL(wgrad_small_kernel, dim3((unsigned)(blocks + grp.ends)), dim3(256), 0, (hipStream_t)stream, grp, s);
+  const auto kernel = past > 0 ? wgrad_small_kernel<true> : wgrad_small_kernel<false>;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)(blocks + grp.ends)), dim3(256), 0, (hipStream_t)stream, grp, s);
   return hipGetLastError() == hipSuccess ? DYNB_OK : fail(DYNB_ERR_HIP, "gemm launch failed");
 }
 
