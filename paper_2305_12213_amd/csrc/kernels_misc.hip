@@ -158,18 +158,49 @@ __global__ __launch_bounds__(256) void softmax_xent_kernel(const float* __restri
 
 // ---- the step's end (first K workgroups) and, behind them, the weighted aggregate, Eq. 2, of the small
 // tensors listed in r -- one launch for what used to be two tiny ones ---------------------------------
-__global__ __launch_bounds__(64) void finalize_kernel(StepEnd end, Segs s, Lambdas lam, Ranges r, int range_bx) {
+// A workgroup takes 256 neighbouring elements of a range, a lane four of them; what bounds it is the way to
+// memory and back, so the elements of four workers are in flight at once (one at a time, 49149 elements of 11
+// workers: 11.9 us, 4.6 so).  Ascending k per element.
+constexpr int RANGE_BLOCK = 256;
+struct RangeBlocks {
+  int first[MAX_RANGES + 1];               // first workgroup of every range
+};
+
+__global__ __launch_bounds__(64) void finalize_kernel(StepEnd end, Segs s, Lambdas lam, Ranges r, RangeBlocks rb) {
   if ((int)blockIdx.x < s.K) {
     end_worker(end, s, blockIdx.x);
     return;
   }
-  const int q = blockIdx.x - s.K, ri = q / range_bx, bx = q % range_bx;
-  const int64_t off = r.off[ri], n = r.len[ri];
-  for (int64_t i = (int64_t)bx * 64 + threadIdx.x; i < n; i += (int64_t)range_bx * 64) {
-    float acc = 0.f;
-    for (int k = 0; k < lam.K; ++k) acc += lam.w[k] * end.grads[(int64_t)k * end.P_pad + off + i];
-    end.out[off + i] = acc;
+  const int block = blockIdx.x - s.K;
+  int q = 0;                               // the last range whose first workgroup is not behind this one
+  for (int step = 32; step > 0; step >>= 1)
+    if (q + step < r.n && block >= rb.first[q + step]) q += step;
+  const int64_t e0 = (int64_t)(block - rb.first[q]) * RANGE_BLOCK + threadIdx.x, n = r.len[q], off = r.off[q];
+  const float* src[4];
+  float acc[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {            // (lanes past the end repeat the last element)
+    src[u] = end.grads + off + (e0 + 64 * u < n ? e0 + 64 * u : n - 1);
+    acc[u] = 0.f;
   }
+  int k = 0;
+  for (; k + 4 <= lam.K; k += 4) {
+    float v[4][4];
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[w][u] = src[u][(int64_t)(k + w) * end.P_pad];
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) acc[u] += lam.w[k + w] * v[w][u];
+  }
+  for (; k < lam.K; ++k)
+#pragma unroll
+    for (int u = 0; u < 4; ++u) acc[u] += lam.w[k] * src[u][(int64_t)k * end.P_pad];
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+    if (e0 + 64 * u < n) end.out[off + e0 + 64 * u] = acc[u];
 }
 
 // ---- read and discard (see launch_touch) -------------------------------------------------
@@ -295,21 +326,21 @@ int launch_finalize(const StepEnd& end, const Segs& s, const Lambdas* lam, const
   l.K = 0;
   Ranges r;
   r.n = 0;
-  int64_t longest = 0, total = 0;
+  RangeBlocks rb;
+  int64_t total = 0, blocks = 0;
   if (end.out && lam && small) {
     l = *lam;
     r = *small;
     for (int i = 0; i < r.n; ++i) {
-      longest = r.len[i] > longest ? r.len[i] : longest;
+      rb.first[i] = (int)blocks;
+      blocks += (r.len[i] + RANGE_BLOCK - 1) / RANGE_BLOCK;
       total += r.len[i];
     }
   }
-  int64_t bx = (longest + 63) / 64;
-  if (bx > 256) bx = 256;
-  if (bx < 1) bx = 1;
-  const int extra = longest > 0 ? (int)bx * r.n : 0;
+  for (int i = r.n; i <= MAX_RANGES; ++i) rb.first[i] = (int)blocks;
+  if (blocks >= ((int64_t)1 << 31) - DYNB_MAX_WORKERS) return fail(DYNB_ERR_UNSUPPORTED, "finalize: ranges too long for one launch");
   Timed t(KC_FINALIZE, stream, 2.0 * l.K * total, 4.0 * (l.K + 1) * total);
-  hipLaunchKernelGGL(finalize_kernel, dim3(s.K + extra), dim3(64), 0, (hipStream_t)stream, end, s, l, r, (int)bx);
+  hipLaunchKernelGGL(finalize_kernel, dim3((unsigned)(s.K + blocks)), dim3(64), 0, (hipStream_t)stream, end, s, l, r, rb);
   return ok("finalize");
 }
 
