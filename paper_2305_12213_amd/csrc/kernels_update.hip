@@ -124,15 +124,19 @@ __device__ __forceinline__ void update_tile(int blk, float* __restrict__ params,
   // per lane -> 43 us, what its 210 MB take at the rate of a large copy.)
   const bool vec = (C & 3) == 0 && (off & 3) == 0;
   if (!vec) {
+    // (only the elements that exist: 64 rows of a head of ten classes are one round, not four; more in flight
+    // would cost the aligned path its occupancy)
     constexpr int U = 4;
-    for (int idx = threadIdx.x; idx < 64 * TC; idx += 256 * U) {
+    const int cols = min(TC, C - c0), total = cols * min(64, R - r0);
+    for (int idx = threadIdx.x; idx < total; idx += 256 * U) {
       int64_t o[U];
-      bool live[U];
+      int er[U], ec[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int e = idx + 256 * u, gr = r0 + e / TC, gc = c0 + e % TC;
-        live[u] = gr < R && gc < C;
-        o[u] = live[u] ? off + (int64_t)gr * C + gc : off;   // (a dead lane reads the first element)
+        const int e = idx + 256 * u < total ? idx + 256 * u : idx;   // (a dead lane repeats its first)
+        er[u] = e / cols;
+        ec[u] = e - er[u] * cols;
+        o[u] = off + (int64_t)(r0 + er[u]) * C + c0 + ec[u];
       }
       float g[U], w[U], a[U], b[U];
       if (KIND != COPY_ONLY) gradients<AGG, U>(src, o, g);
@@ -144,15 +148,13 @@ __device__ __forceinline__ void update_tile(int blk, float* __restrict__ params,
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int e = idx + 256 * u, r = e / TC, c = e % TC;
         w[u] = step_one<KIND>(rule, w[u], g[u], a[u], b[u]);
-        if (live[u]) {
-          if (KIND != COPY_ONLY) params[o[u]] = w[u];
-          if (HAS_S1) s1[o[u]] = a[u];
-          if (KIND == DYNB_OPT_ADAM) s2[o[u]] = b[u];
-          Wn[(int64_t)(r0 + r) * ldn + c0 + c] = from_float<T>(w[u]);
-        }
-        tile[r][c] = live[u] ? w[u] : 0.f;
+        if (idx + 256 * u >= total) continue;
+        if (KIND != COPY_ONLY) params[o[u]] = w[u];
+        if (HAS_S1) s1[o[u]] = a[u];
+        if (KIND == DYNB_OPT_ADAM) s2[o[u]] = b[u];
+        Wn[(int64_t)(r0 + er[u]) * ldn + c0 + ec[u]] = from_float<T>(w[u]);
+        tile[er[u]][ec[u]] = w[u];
       }
     }
   } else {
