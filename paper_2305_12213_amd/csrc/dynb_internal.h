@@ -287,6 +287,10 @@ int launch_conv_resident(const GemmArgs& a, void* stream);
 bool conv_flat_applies(int dtype, const GemmArgs& a);
 int launch_conv_flat(const GemmArgs& a, void* stream);
 
+// Input gradient with stride 2, all parity classes of a run of pixels together (conv_strided_grad.hip).
+bool conv_strided_grad_applies(int dtype, const GemmArgs& a);
+int launch_conv_strided_grad(const GemmArgs& a, void* stream);
+
 // The rows of every worker cut into chunks of `rows` rows: first[k] = index of worker k's first
 // chunk, first[K] = number of chunks (chunk c of worker k starts at off[k] + (c - first[k]) * rows).
 struct RowChunks {

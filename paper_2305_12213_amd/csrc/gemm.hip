@@ -1087,6 +1087,7 @@ int launch_gemm(int dtype, const GemmArgs& args, const Segs& s, void* stream, co
   if (a.conv) {
     if (dtype != DYNB_BF16 || a.mode == MODE_WGRAD || (a.cp & 7) || (a.stride != 1 && a.stride != 2))
       return fail(DYNB_ERR_UNSUPPORTED, "gemm: gathered operand needs bf16, forward/input-gradient mode");
+    if (conv_strided_grad_applies(dtype, a)) return launch_conv_strided_grad(a, stream);
     if (conv_resident_applies(dtype, a)) return launch_conv_resident(a, stream);
     if (conv_direct_applies(dtype, a)) return launch_conv_direct(a, stream);
     if (conv_flat_applies(dtype, a)) return launch_conv_flat(a, stream);

@@ -603,6 +603,27 @@ def test_flat_convolutions(image, channels):
     check_worker_gradients(spec, params, x, y, b, label="flat conv %s %s" % (image, channels))
 
 
+@pytest.mark.parametrize("image,channels", [
+    ((1, 1, 4), (8, 8)),          # one pixel: no neighbours
+    ((2, 2, 4), (33, 32)),        # two blocks of input channels, the second almost empty
+    ((9, 35, 4), (32, 33)),       # odd sides, runs over more than one tile; 33 channels in rows for 64
+    ((16, 10, 4), (20, 120)),     # 256-byte rows that are not full
+    ((3, 128, 4), (24, 24)),      # the widest images of the run ...
+    ((3, 130, 4), (24, 24)),      # ... and wider: the gathered product
+    ((5, 6, 4), (16, 136)),       # too many channels for it
+])
+def test_strided_input_gradient_on_runs_of_pixels(image, channels):
+    # with a residual branch into the strided layer's input (addend and mask), idle and one-sample workers
+    c1, c2 = channels
+    spec = {"dtype": "bf16", "input": image, "classes": 3,
+            "layers": [synth.conv3x3(image[2], c1, 1), synth.conv3x3(c1, c1, 1, relu=False), synth.add(0, True),
+                       synth.conv3x3(c1, c2, 2), synth.gap(), synth.dense(c2, 3, relu=False)]}
+    params = synth.init_params(spec, "he", 91)
+    b = [1, 0, 5]
+    x, y = synth.make_batch(spec, "normal", sum(b), 92, 0)
+    check_worker_gradients(spec, params, x, y, b, label="strided run %s %s" % (image, channels))
+
+
 @pytest.mark.parametrize("image,layers", [
     # rows of at most 32 channels are 64 bytes long unless a dense layer reads them; here each kind of layer
     # meets a neighbour of the other pitch
