@@ -146,6 +146,7 @@ bool head_applies(int dtype, const GemmArgs& a);
 int launch_gemm(int dtype, const GemmArgs& a, const Segs& s, void* stream, const HeadArgs* head = nullptr);
 int launch_gemm_f32(const GemmArgs& a, const HeadArgs* head, void* stream);   // forward / input gradient (gemm_f32.hip)
 bool gemm_f32_head_applies(const GemmArgs& a);
+void launch_gemm_f32_head(const GemmArgs& a, const HeadArgs& head, unsigned tiles, void* stream);   // (its 16 x 16 tiles)
 // What ends an iteration (step_end.h): loss[g] = mean of rowloss over worker g's rows; grads[g][P .. P_pad)
 // = 0; out[P .. P_pad) = 0 if out.
 struct StepEnd {
