@@ -49,71 +49,72 @@ __device__ inline void fetch_tap(const StemArgs& p, int img, int oy, int ox, int
   }
 }
 
-// A workgroup takes 256 output pixels x 64 output channels, a wave 64 pixels, of which each lane
-// gathers one: 9 taps x 8 channels in LDS, as the weight copies lie in memory (their padding and the
-// tenth granule are zeros; five matrix-instruction steps, in the order of the general kernel).  The
-// results pass through LDS so that a store writes whole 128-byte rows; padding channels are written
-// as zeros.
-constexpr int APITCH = 176, OPITCH = 144;  // bytes per pixel: patch, result (odd multiples of 16: no bank conflicts)
+// A workgroup takes 256 output pixels x 64 output channels, a wave 64 pixels.  A matrix-instruction step is two
+// taps x 8 channels, as the weight copies lie in memory (their padding and the tenth tap are zeros; five steps,
+// in the order of the general kernel), one tap per lane half: a lane gathers its operand's channels of its own two
+// pixels straight into registers.  The results pass through LDS, 32 pixels at a time, so that a store writes
+// whole rows; padding channels are written as zeros.  Up to 32 channels the upper half is left out.
+// What bounds a launch is the latency of these gathers, so little LDS and many waves: 512 x 32 x 32 x 3 -> 64
+// 24 us (with the patches of all nine taps built in LDS, two workgroups per compute unit: 27), -> 32 18 (23).
+constexpr int WPITCH = 176, OPITCH = 144;  // bytes per weight row, result (odd multiples of 16: no bank conflicts)
 
 template <int CIN>
 __global__ __launch_bounds__(256) void stem_forward_kernel(StemArgs p) {
-  __shared__ __align__(16) char area[4][64 * APITCH];
-  __shared__ __align__(16) char wl[64 * APITCH];
+  __shared__ __align__(16) char area[4][32 * OPITCH];
+  __shared__ __align__(16) char wl[64 * WPITCH];
   __shared__ __align__(16) float bl[64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int l31 = lane & 31, h = lane >> 5;
   const int j0 = blockIdx.y * 64;
-  for (int e = threadIdx.x; e < 64 * 10; e += 256) {       // weights: ten granules per channel
-    const int co = e / 10, g = e - co * 10;
-    uint4 v = make_uint4(0, 0, 0, 0);
-    if (j0 + co < p.N) v = *(const uint4*)(p.w + (int64_t)(j0 + co) * p.kf + g * 8);
-    *(uint4*)&wl[co * APITCH + g * 16] = v;
-  }
-  if (threadIdx.x < 64) bl[threadIdx.x] = j0 + (int)threadIdx.x < p.N ? p.bias[j0 + threadIdx.x] : 0.f;
-
-  char* const mine = area[wave];
+  const bool upper = p.N - j0 > 32;
   const int64_t pix0 = (int64_t)blockIdx.x * 256 + wave * 64;
-  {
-    const int64_t pix = pix0 + lane;
+  float v[2][5][CIN];                                      // [pixel][step]: tap 2 step + h
+#pragma unroll
+  for (int a = 0; a < 2; ++a) {
+    const int64_t pix = pix0 + a * 32 + l31;
     const bool live = pix < p.pixels;
     const int q = live ? (int)pix : 0, row = q / p.Wo, ox = q - row * p.Wo, img = row / p.Ho, oy = row - img * p.Ho;
-    float v[9][CIN];
 #pragma unroll
-    for (int tap = 0; tap < 9; ++tap) fetch_tap<CIN>(p, img, oy, ox, tap, live, v[tap]);
-#pragma unroll
-    for (int tap = 0; tap < 10; ++tap) {
-      bf16x8 o;
-#pragma unroll
-      for (int c = 0; c < 8; ++c) o[c] = tap < 9 && c < CIN ? (bf16)v[tap < 9 ? tap : 8][c < CIN ? c : 0] : (bf16)0.f;
-      *(bf16x8*)(mine + lane * APITCH + tap * 16) = o;
-    }
+    for (int kk = 0; kk < 5; ++kk) fetch_tap<CIN>(p, img, oy, ox, 2 * kk + h, live && 2 * kk + h < 9, v[a][kk]);
   }
-  __syncthreads();                                         // (the weights; the patches are the wave's own)
-  const int l31 = lane & 31, h = lane >> 5;
+  for (int e = threadIdx.x; e < 64 * 10; e += 256) {       // weights: ten granules per channel
+    const int co = e / 10, g = e - co * 10;
+    uint4 w = make_uint4(0, 0, 0, 0);
+    if (j0 + co < p.N) w = *(const uint4*)(p.w + (int64_t)(j0 + co) * p.kf + g * 8);
+    *(uint4*)&wl[co * WPITCH + g * 16] = w;
+  }
+  if (threadIdx.x < 64) bl[threadIdx.x] = j0 + (int)threadIdx.x < p.N ? p.bias[j0 + threadIdx.x] : 0.f;
   f32x16 acc[2][2];                                        // [32 pixels][32 channels]
 #pragma unroll
   for (int a = 0; a < 2; ++a)
 #pragma unroll
     for (int b = 0; b < 2; ++b)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
-#pragma unroll 1
-  for (int kk = 0; kk < 5; ++kk)
+      for (int e = 0; e < 16; ++e) acc[a][b][e] = 0.f;
+  __syncthreads();                                         // (the weights)
 #pragma unroll
-    for (int a = 0; a < 2; ++a) {
-      const bf16x8 fa = *(const bf16x8*)(mine + (a * 32 + l31) * APITCH + (2 * kk + h) * 16);
+  for (int kk = 0; kk < 5; ++kk) {
+    bf16x8 fa[2];
 #pragma unroll
-      for (int b = 0; b < 2; ++b) {
-        const bf16x8 fb = *(const bf16x8*)&wl[(b * 32 + l31) * APITCH + (2 * kk + h) * 16];
-        acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb, fa, acc[a][b], 0, 0, 0);
-      }
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int c = 0; c < 8; ++c) fa[a][c] = c < CIN ? (bf16)v[a][kk][c < CIN ? c : 0] : (bf16)0.f;
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      if (b == 1 && !upper) continue;
+      const bf16x8 fb = *(const bf16x8*)&wl[(b * 32 + l31) * WPITCH + (2 * kk + h) * 16];
+#pragma unroll
+      for (int a = 0; a < 2; ++a) acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb, fa[a], acc[a][b], 0, 0, 0);
     }
-  __builtin_amdgcn_wave_barrier();
+  }
   // accumulator element 4q + e of a lane: channel 8q + 4h + e, pixel l31
+  char* const mine = area[wave];
+  const uint4 keep = keep8(p.N - j0 - (lane & 7) * 8);
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int a = 0; a < 2; ++a) {
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int b = 0; b < 2; ++b) {
+      if (b == 1 && !upper) continue;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const f32x4 bv = *(const f32x4*)&bl[b * 32 + 8 * q + 4 * h];
@@ -124,15 +125,18 @@ __global__ __launch_bounds__(256) void stem_forward_kernel(StemArgs p) {
           if (p.relu) t = fmaxf(t, 0.f);
           o[e] = (bf16)t;
         }
-        *(bf16x4*)(mine + (a * 32 + l31) * OPITCH + (b * 32 + 8 * q + 4 * h) * 2) = o;
+        *(bf16x4*)(mine + l31 * OPITCH + (b * 32 + 8 * q + 4 * h) * 2) = o;
       }
-  __builtin_amdgcn_wave_barrier();
-  const uint4 keep = keep8(p.N - j0 - (lane & 7) * 8);
+    }
+    __builtin_amdgcn_wave_barrier();
 #pragma unroll
-  for (int t = 0; t < 8; ++t) {
-    const int r = 8 * t + (lane >> 3);
-    const uint4 o = *(const uint4*)(mine + r * OPITCH + (lane & 7) * 16);
-    if (pix0 + r < p.pixels && j0 + (lane & 7) * 8 < p.ldo) *(uint4*)(p.out + (pix0 + r) * p.ldo + j0 + (lane & 7) * 8) = o & keep;
+    for (int t = 0; t < 4; ++t) {                          // (channels past N, which nothing has written here: zeros)
+      const int r = 8 * t + (lane >> 3);
+      const int64_t pix = pix0 + a * 32 + r;
+      const uint4 o = *(const uint4*)(mine + r * OPITCH + (lane & 7) * 16);
+      if (pix < p.pixels && j0 + (lane & 7) * 8 < p.ldo) *(uint4*)(p.out + pix * p.ldo + j0 + (lane & 7) * 8) = o & keep;
+    }
+    __builtin_amdgcn_wave_barrier();
   }
 }
 
