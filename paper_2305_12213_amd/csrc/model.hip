@@ -4,7 +4,7 @@
 // Forward and the activation-gradient pass treat the global batch as one matrix (rows are
 // independent and all workers share the weights); only the loss scaling 1/b_k and the
 // weight/bias gradients are per worker.  A "row" is a sample for dense layers and a pixel
-// (sample, y, x) for convolutions (NHWC with the channel pitch padded to 64).
+// (sample, y, x) for convolutions (NHWC, channel pitch a multiple of 64, or 32 for up to 32 channels).
 //
 // The per-worker weight-gradient kernels reduce over the rows of the row-major activations and
 // gradients themselves; there are no transposed copies.
