@@ -90,14 +90,14 @@ __device__ inline void gradients(const GradSource& src, const int64_t (&o)[U], f
 
 // ---- weight matrices: step + both 16-bit copies in one pass ----------------------------------
 // W[r][c] <- step(W[r][c]); Wn[r][c] = T(W), Wt[c][r] = T(W).  (A convolution is nine such matrices,
-// one per tap, whose copies lie side by side in the rows of its two operands.)  A workgroup owns a 64 x TC tile:
+// one per tap, whose copies lie side by side in the rows of its two operands.)  A workgroup owns a TR x TC tile:
 // 16-byte accesses on the fp32 side, the transposed copy goes through an LDS tile so that its
 // stores are 16 bytes per lane and whole 128-byte lines per 8 (bf16) lanes.
 // One launch serves every matrix of `mats` (workgroups mats.first_block[i] ... belong to matrix
 // i) and, with the workgroups behind the last tile, the small tensors of `small` (biases):
 // back-to-back launches on one stream leave the chip idle for a few microseconds each, which
 // for a four-layer model came to a sixth of the whole update.
-template <typename T, int KIND, bool AGG, int TC>
+template <typename T, int KIND, bool AGG, int TC, int TR>
 __device__ __forceinline__ void update_tile(int blk, float* __restrict__ params, const CastMats& mats,
                                             const GradSource& src, const UpdateRule& rule,
                                             float* __restrict__ s1, float* __restrict__ s2) {
@@ -107,7 +107,7 @@ __device__ __forceinline__ void update_tile(int blk, float* __restrict__ params,
   const int64_t ldn = mats.ldn[mi], ldt = mats.ldt[mi];
   const int R = mats.R[mi], C = mats.C[mi];
   const int tiles_x = (C + TC - 1) / TC, local = blk - mats.first_block[mi];
-  const int per_tap = tiles_x * ((R + 63) / 64), tap = local / per_tap, in_tap = local - tap * per_tap;
+  const int per_tap = tiles_x * ((R + TR - 1) / TR), tap = local / per_tap, in_tap = local - tap * per_tap;
   const int tile_x = in_tap % tiles_x, tile_y = in_tap / tiles_x;
   const int64_t off = mats.off[mi] + (int64_t)tap * R * C;
   T* __restrict__ Wn = (T*)mats.Wn[mi] + tap * mats.tap_n[mi];
@@ -116,18 +116,18 @@ __device__ __forceinline__ void update_tile(int blk, float* __restrict__ params,
   typedef T vecT __attribute__((ext_vector_type(G)));
   typedef T vec4T __attribute__((ext_vector_type(4)));
   constexpr int QC = TC / 4;   // 16-byte granules per tile row
-  __shared__ float tile[64][TC + 1];
-  const int r0 = tile_y * 64, c0 = tile_x * TC;
+  __shared__ float tile[TR][TC + 1];
+  const int r0 = tile_y * TR, c0 = tile_x * TC;
   // 16-byte accesses need aligned rows in every array (all start at a multiple of 4 floats);
   // otherwise a lane takes single elements, 64 neighbouring ones of a row per wave, U rows or column
   // halves at once.  (1001 x 2050 and 2050 x 777, 7 workers, Adam: 106 us with four elements in turn
   // per lane -> 43 us, what its 210 MB take at the rate of a large copy.)
   const bool vec = (C & 3) == 0 && (off & 3) == 0;
   if (!vec) {
-    // (only the elements that exist: 64 rows of a head of ten classes are one round, not four; more in flight
+    // (only the elements that exist: rows of a head of ten classes are one round, not several; more in flight
     // would cost the aligned path its occupancy)
     constexpr int U = 4;
-    const int cols = min(TC, C - c0), total = cols * min(64, R - r0);
+    const int cols = min(TC, C - c0), total = cols * min(TR, R - r0);
     for (int idx = threadIdx.x; idx < total; idx += 256 * U) {
       int64_t o[U];
       int er[U], ec[U];
@@ -159,7 +159,7 @@ __device__ __forceinline__ void update_tile(int blk, float* __restrict__ params,
     }
   } else {
 #pragma unroll 2
-    for (int idx = threadIdx.x; idx < 64 * QC; idx += 256) {
+    for (int idx = threadIdx.x; idx < TR * QC; idx += 256) {
       const int r = idx / QC, cq = (idx % QC) * 4;
       const int gr = r0 + r, gc = c0 + cq;
       f4 w = {0.f, 0.f, 0.f, 0.f};
@@ -188,7 +188,7 @@ __device__ __forceinline__ void update_tile(int blk, float* __restrict__ params,
     }
   }
   __syncthreads();
-  constexpr int GR = 64 / G;   // granules of rows per tile column
+  constexpr int GR = TR / G;   // granules of rows per tile column
   for (int idx = threadIdx.x; idx < TC * GR; idx += 256) {
     const int rg = idx % GR, c = idx / GR;
     if (c0 + c >= C) continue;
@@ -204,7 +204,7 @@ __device__ __forceinline__ void update_tile(int blk, float* __restrict__ params,
   }
 }
 
-template <typename T, int KIND, bool AGG, int TC>
+template <typename T, int KIND, bool AGG, int TC, int TR>
 __global__ __launch_bounds__(256) void update_cast_kernel(float* __restrict__ params, CastMats mats,
                                                           Ranges small, int range_blocks,
                                                           GradSource src, UpdateRule rule,
@@ -227,20 +227,20 @@ __global__ __launch_bounds__(256) void update_cast_kernel(float* __restrict__ pa
     }
     return;
   }
-  update_tile<T, KIND, AGG, TC>(blk, params, mats, src, rule, s1, s2);
+  update_tile<T, KIND, AGG, TC, TR>(blk, params, mats, src, rule, s1, s2);
 }
 
 // ---- everything a dense model's scratch needs before a pass over it, in one launch ---------------
 // The weight copies, the packed input (padding columns included) and zeros in the padding columns of what
 // later kernels write only in part: workgroups of each kind behind those of the one before.
-template <typename T>
+template <typename T, int TR>
 __global__ __launch_bounds__(256) void prepare_kernel(const float* __restrict__ params, CastMats mats, Prepare pr,
                                                       int pack_blocks, int pad_blocks) {
   int blk = blockIdx.x;
   if (blk < mats.first_block[mats.n]) {
     const GradSource src = {};
     const UpdateRule rule = {};
-    update_tile<T, COPY_ONLY, false, 64>(blk, const_cast<float*>(params), mats, src, rule, nullptr, nullptr);
+    update_tile<T, COPY_ONLY, false, 64, TR>(blk, const_cast<float*>(params), mats, src, rule, nullptr, nullptr);
     return;
   }
   blk -= mats.first_block[mats.n];
@@ -327,52 +327,67 @@ double flops_per_param(const UpdateRule& rule, const GradSource& src) {
 
 // (wider tiles when K gradient streams are read: 512-byte runs per row and stream)
 constexpr int cast_tile_columns(bool agg) { return agg ? 128 : 64; }
+// A tile of 64 rows is a chain of four to sixteen rounds of loads and stores in one workgroup; with fewer tiles than
+// compute units that chain is the launch, and tiles of 16 rows shorten it: Adam on 785-301-97-10, 79 -> 297 workgroups,
+// 10.6 -> 6.5 us; 32-64-128 convolutions, 39 -> 108, 5.3 -> 4.6.  From there on it is the bytes (3072-512-512-10: 458
+// workgroups 8.1, 1826 8.0), and tall tiles write the transposed copy in whole lines.
+constexpr int SHORT_ROWS = 16, TALL_ROWS = 64, SHORT_BELOW = 256;
+int cast_tile_rows(const CastMats& mats, int tile_columns) {
+  int64_t tall = 0;
+  for (int i = 0; i < mats.n && i < MAX_CAST_MATS; ++i)
+    tall += (int64_t)((mats.C[i] + tile_columns - 1) / tile_columns) * ((mats.R[i] + TALL_ROWS - 1) / TALL_ROWS) * mats.taps[i];
+  return tall < SHORT_BELOW ? SHORT_ROWS : TALL_ROWS;
+}
 
 template <typename T, int KIND, bool AGG>
-void launch_update_cast_t(float* params, const CastMats& mats, const Ranges& small, int range_blocks,
+void launch_update_cast_t(float* params, const CastMats& mats, int rows, const Ranges& small, int range_blocks,
                           const GradSource& src, const UpdateRule& rule, float* s1, float* s2,
                           hipStream_t st) {
   constexpr int TC = cast_tile_columns(AGG);
   const dim3 grid((unsigned)(mats.first_block[mats.n] + range_blocks));
-  hipLaunchKernelGGL((update_cast_kernel<T, KIND, AGG, TC>), grid, dim3(256), 0, st, params, mats, small,
-                     range_blocks, src, rule, s1, s2);
+  if (rows == SHORT_ROWS)
+    hipLaunchKernelGGL((update_cast_kernel<T, KIND, AGG, TC, SHORT_ROWS>), grid, dim3(256), 0, st, params, mats,
+                       small, range_blocks, src, rule, s1, s2);
+  else
+    hipLaunchKernelGGL((update_cast_kernel<T, KIND, AGG, TC, TALL_ROWS>), grid, dim3(256), 0, st, params, mats,
+                       small, range_blocks, src, rule, s1, s2);
 }
 
 template <typename T, int KIND>
-void launch_update_cast_k(float* params, const CastMats& mats, const Ranges& small, int range_blocks,
+void launch_update_cast_k(float* params, const CastMats& mats, int rows, const Ranges& small, int range_blocks,
                           const GradSource& src, const UpdateRule& rule, float* s1, float* s2,
                           hipStream_t st) {
   if (src.lam.K > 0)
-    launch_update_cast_t<T, KIND, true>(params, mats, small, range_blocks, src, rule, s1, s2, st);
+    launch_update_cast_t<T, KIND, true>(params, mats, rows, small, range_blocks, src, rule, s1, s2, st);
   else
-    launch_update_cast_t<T, KIND, false>(params, mats, small, range_blocks, src, rule, s1, s2, st);
+    launch_update_cast_t<T, KIND, false>(params, mats, rows, small, range_blocks, src, rule, s1, s2, st);
 }
 
 template <typename T>
-void launch_update_cast_d(float* params, const CastMats& mats, const Ranges& small, int range_blocks,
+void launch_update_cast_d(float* params, const CastMats& mats, int rows, const Ranges& small, int range_blocks,
                           const GradSource& src, const UpdateRule& rule, float* s1, float* s2,
                           hipStream_t st) {
   switch (rule.kind) {
     case DYNB_OPT_SGD:
-      launch_update_cast_k<T, DYNB_OPT_SGD>(params, mats, small, range_blocks, src, rule, s1, s2, st);
+      launch_update_cast_k<T, DYNB_OPT_SGD>(params, mats, rows, small, range_blocks, src, rule, s1, s2, st);
       break;
     case DYNB_OPT_MOMENTUM:
-      launch_update_cast_k<T, DYNB_OPT_MOMENTUM>(params, mats, small, range_blocks, src, rule, s1, s2, st);
+      launch_update_cast_k<T, DYNB_OPT_MOMENTUM>(params, mats, rows, small, range_blocks, src, rule, s1, s2, st);
       break;
     default:
-      launch_update_cast_k<T, DYNB_OPT_ADAM>(params, mats, small, range_blocks, src, rule, s1, s2, st);
+      launch_update_cast_k<T, DYNB_OPT_ADAM>(params, mats, rows, small, range_blocks, src, rule, s1, s2, st);
   }
 }
 
 // Fills first_block and counts the parameters of `mats`.
-int count_blocks(CastMats& mats, int tile_columns, double& params_counted) {
+int count_blocks(CastMats& mats, int tile_columns, int tile_rows, double& params_counted) {
   if (mats.n < 0 || mats.n > MAX_CAST_MATS) return fail(DYNB_ERR_BADARG, "update_cast: too many tensors for one launch");
   int64_t blocks = 0;
   params_counted = 0.0;
   for (int i = 0; i < mats.n; ++i) {
     if (mats.R[i] <= 0 || mats.C[i] <= 0) return fail(DYNB_ERR_BADARG, "update_cast: empty matrix");
     mats.first_block[i] = (int)blocks;
-    blocks += (int64_t)((mats.C[i] + tile_columns - 1) / tile_columns) * ((mats.R[i] + 63) / 64) * mats.taps[i];
+    blocks += (int64_t)((mats.C[i] + tile_columns - 1) / tile_columns) * ((mats.R[i] + tile_rows - 1) / tile_rows) * mats.taps[i];
     if (blocks >= ((int64_t)1 << 31) - 256)
       return fail(DYNB_ERR_UNSUPPORTED, "update_cast: too many tiles for one launch");
     params_counted += (double)mats.R[i] * mats.C[i] * mats.taps[i];
@@ -391,7 +406,8 @@ int launch_update_cast(int dtype, float* params, CastMats& mats, const Ranges& s
   const int es = dtype == DYNB_BF16 ? 2 : 4;
   double cast_n = 0.0, small_n = 0.0;
   int64_t longest = 0;
-  if (int rc = count_blocks(mats, cast_tile_columns(src.lam.K > 0), cast_n)) return rc;
+  const int columns = cast_tile_columns(src.lam.K > 0), rows = cast_tile_rows(mats, columns);
+  if (int rc = count_blocks(mats, columns, rows, cast_n)) return rc;
   for (int i = 0; i < small.n; ++i) {
     longest = small.len[i] > longest ? small.len[i] : longest;
     small_n += (double)small.len[i];
@@ -402,16 +418,17 @@ int launch_update_cast(int dtype, float* params, CastMats& mats, const Ranges& s
   Timed t(KC_UPDATE, stream, flops_per_param(rule, src) * (cast_n + small_n),
           (bytes_per_param(rule, src) + 2 * es) * cast_n + bytes_per_param(rule, src) * small_n);
   if (dtype == DYNB_BF16)
-    launch_update_cast_d<bf16>(params, mats, small, (int)range_blocks, src, rule, s1, s2, (hipStream_t)stream);
+    launch_update_cast_d<bf16>(params, mats, rows, small, (int)range_blocks, src, rule, s1, s2, (hipStream_t)stream);
   else
-    launch_update_cast_d<float>(params, mats, small, (int)range_blocks, src, rule, s1, s2, (hipStream_t)stream);
+    launch_update_cast_d<float>(params, mats, rows, small, (int)range_blocks, src, rule, s1, s2, (hipStream_t)stream);
   return ok("update_cast");
 }
 
 int launch_weight_casts(int dtype, const float* params, CastMats& mats, void* stream) {
   const int es = dtype == DYNB_BF16 ? 2 : 4;
   double n = 0.0;
-  if (int rc = count_blocks(mats, cast_tile_columns(false), n)) return rc;
+  const int rows = cast_tile_rows(mats, cast_tile_columns(false));
+  if (int rc = count_blocks(mats, cast_tile_columns(false), rows, n)) return rc;
   if (n == 0.0) return DYNB_OK;
   Timed t(KC_WEIGHT_CAST, stream, 0, n * (4 + 2 * es));
   Ranges none;
@@ -419,18 +436,19 @@ int launch_weight_casts(int dtype, const float* params, CastMats& mats, void* st
   const GradSource src = {};
   const UpdateRule rule = {};
   if (dtype == DYNB_BF16)
-    launch_update_cast_t<bf16, COPY_ONLY, false>(const_cast<float*>(params), mats, none, 0, src, rule, nullptr,
-                                                 nullptr, (hipStream_t)stream);
+    launch_update_cast_t<bf16, COPY_ONLY, false>(const_cast<float*>(params), mats, rows, none, 0, src, rule,
+                                                 nullptr, nullptr, (hipStream_t)stream);
   else
-    launch_update_cast_t<float, COPY_ONLY, false>(const_cast<float*>(params), mats, none, 0, src, rule, nullptr,
-                                                  nullptr, (hipStream_t)stream);
+    launch_update_cast_t<float, COPY_ONLY, false>(const_cast<float*>(params), mats, rows, none, 0, src, rule,
+                                                  nullptr, nullptr, (hipStream_t)stream);
   return ok("weight_casts");
 }
 
 int launch_prepare(int dtype, const float* params, CastMats& mats, const Prepare& pr, void* stream) {
   const int es = dtype == DYNB_BF16 ? 2 : 4;
   double n = 0.0;
-  if (int rc = count_blocks(mats, cast_tile_columns(false), n)) return rc;
+  const int rows = cast_tile_rows(mats, cast_tile_columns(false));
+  if (int rc = count_blocks(mats, cast_tile_columns(false), rows, n)) return rc;
   const int64_t granules = (int64_t)pr.rows * (pr.ld / 8);
   int64_t pads = 0;
   for (int q = 0; q < pr.n; ++q) {
@@ -442,12 +460,13 @@ int launch_prepare(int dtype, const float* params, CastMats& mats, const Prepare
   const int blocks = mats.first_block[mats.n] + pack_blocks + pad_blocks;
   if (blocks == 0) return DYNB_OK;
   Timed t(KC_WEIGHT_CAST, stream, 0, n * (4 + 2 * es) + (double)pr.rows * pr.D * (4 + es));
+  const auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, (hipStream_t)stream, params, mats, pr, pack_blocks, pad_blocks);
+  };
   if (dtype == DYNB_BF16)
-    hipLaunchKernelGGL(prepare_kernel<bf16>, dim3(blocks), dim3(256), 0, (hipStream_t)stream, params, mats, pr,
-                       pack_blocks, pad_blocks);
+    launch(rows == SHORT_ROWS ? prepare_kernel<bf16, SHORT_ROWS> : prepare_kernel<bf16, TALL_ROWS>);
   else
-    hipLaunchKernelGGL(prepare_kernel<float>, dim3(blocks), dim3(256), 0, (hipStream_t)stream, params, mats, pr,
-                       pack_blocks, pad_blocks);
+    launch(rows == SHORT_ROWS ? prepare_kernel<float, SHORT_ROWS> : prepare_kernel<float, TALL_ROWS>);
   return ok("prepare");
 }
 

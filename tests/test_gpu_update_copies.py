@@ -25,6 +25,8 @@ SPECS = {
     "conv odd": lambda: conv_spec(9, 13),
     "conv wide": lambda: conv_spec(72, 68),
     "ten layers": lambda: synth.mlp_spec([9] * 11, "bf16"),      # more tensors than one launch takes
+    "many tiles odd": lambda: synth.mlp_spec([2050, 2051, 5], "bf16"),   # (tiles of 64 rows, not of 16)
+    "many tiles aligned": lambda: synth.mlp_spec([2052, 2060, 8], "f32"),
 }
 
 
