@@ -195,13 +195,36 @@ __global__ __launch_bounds__(256, RB == 256 ? 1 : 2) void conv_strided_grad_kern
 
 }  // namespace
 
+// Where it is faster than the gathered-operand product: 11030 calls of 1 to 700 images of 4 x 4 to 64 x 64 pixels,
+// 4 to 512 input channels, 8 to 128 on the side of dy, timed on both (launch and its events, us; the product's
+// time first).  A launch runs in rounds of 512 workgroups (256 with more than 64 channels on the side of dy), and every
+// further 32 input channels copy the same run again; the product's tiles are 64 columns wide, 128 for more than 64.
+//   up to 64 input channels: everywhere (32 x 32 pixels, 512 images, 32 -> 24 channels 47, 24; 64 images, 64 -> 64 16.0,
+//     15.0) but for the smallest launches of few channels (4 x 4, 64 images, 64 -> 8: 11.6, 12.2);
+//   more: where the product's last tile of columns is at most three quarters full (28 x 28, 96 images, 96 -> 40:
+//     22, 17), unless a second round is just begun (16 x 16, 700 images, 72 -> 40, 525 workgroups: 33, 38); otherwise
+//     in one round or in whole ones (9 x 64, 160 images, 128 -> 8, 400 workgroups: 20.0, 19.3; 16 x 16, 256 images,
+//     512 -> 24, 1024: 47, 34; but 700 images, 128 -> 8, 700: 30, 37);
+//   more than 64 channels of dy: up to 32 input channels, above the smallest launches (64 x 64, 64 images, 32 -> 128: 37,
+//     21); more, only in one nearly full round (16 x 16, 512 images, 64 -> 128: 23.0, 22.4; 700 images 33, 37; 13 x 21,
+//     160 images, 256 -> 96: 28, 35).
+static bool faster_than_gathered(int cp, int N, int64_t blocks) {
+  const bool loose = N % 128 >= 1 && N % 128 <= 96;    // (columns of the product's last tile)
+  if (cp > 64) return N <= 32 ? N <= 16 || blocks >= 96 : loose && blocks > 192 && blocks <= 256;
+  if (N <= 64) return N <= 16 || cp >= 48 || blocks >= 96;
+  if (loose) return blocks > 192 && (blocks <= 512 || blocks >= 560);
+  return blocks > 256 && (blocks <= 512 || blocks % 512 == 0 || blocks % 512 >= 496);
+}
+
 bool conv_strided_grad_applies(int dtype, const GemmArgs& a) {
   if (dtype != DYNB_BF16 || a.conv != 2 || a.mode != MODE_DGRAD || a.stride != 2 || a.Cf || !a.C) return false;
   if (a.cp > 128 || a.src_w > MAX_W || a.src_h != (a.row_h + 1) / 2 || a.src_w != (a.row_w + 1) / 2) return false;
   const int64_t block = round_up(a.N, 32);             // the channels that whole blocks cover
   if (a.M % (a.row_h * a.row_w) || a.lda < a.cp || a.lda % 8 || a.ldb < 9 * a.cp || a.ldb % 8) return false;
   if (a.ldc < block || a.ldc % 8 || (a.mask && (a.ldmask < block || a.ldmask % 8))) return false;
-  return !(a.addend && (a.ldadd < block || a.ldadd % 8));
+  if (a.addend && (a.ldadd < block || a.ldadd % 8)) return false;
+  const int64_t cells = (int64_t)(a.M / (a.row_h * a.row_w)) * a.src_h * a.src_w;
+  return faster_than_gathered(a.cp, a.N, (cells + CELLS - 1) / CELLS * (block / 32));
 }
 
 int launch_conv_strided_grad(const GemmArgs& a, void* stream) {

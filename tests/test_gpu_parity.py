@@ -614,6 +614,8 @@ def test_flat_convolutions(image, channels):
 ])
 def test_strided_input_gradient_on_runs_of_pixels(image, channels):
     # with a residual branch into the strided layer's input (addend and mask), idle and one-sample workers
+    # (launches this small mostly stay on the gathered product; those that the kernel on runs of pixels takes are in
+    # test_gpu_strided_rounds.py)
     c1, c2 = channels
     spec = {"dtype": "bf16", "input": image, "classes": 3,
             "layers": [synth.conv3x3(image[2], c1, 1), synth.conv3x3(c1, c1, 1, relu=False), synth.add(0, True),
