@@ -41,16 +41,17 @@ __device__ inline uint4 operator&(const uint4& a, const uint4& b) {
 __device__ inline uint4 load8(const bf16* p) { return *reinterpret_cast<const uint4*>(p); }
 __device__ inline void store8(bf16* p, const uint4& q) { *reinterpret_cast<uint4*>(p) = q; }
 
-// This lane's granules of the first n >= 1 of 256 rows: rows row-lane + 32 i.  Rows past the last repeat it,
+// This lane's granules of the first n >= 1 of 32 F rows: rows row-lane + 32 i.  Rows past the last repeat it,
 // so that no branch stands between the loads and all are in flight together; the address is one uniform
 // base and a 32-bit offset (256 rows of a tensor below 2 GiB).
-constexpr int ROWS_IN_FLIGHT = 8;          // per lane
-template <int LPR>
-__device__ inline void load_rows(const bf16* base, int64_t ld, int n, uint4 (&q)[ROWS_IN_FLIGHT]) {
+constexpr int ROWS_IN_FLIGHT = 8;          // per lane, at most
+template <int LPR, int F>
+__device__ inline void load_rows(const bf16* base, int64_t ld, int n, uint4 (&q)[F]) {
+  static_assert(F <= ROWS_IN_FLIGHT, "32-bit offsets");
   const uint32_t pitch = (uint32_t)ld * 2, g = (threadIdx.x % LPR) * 16;
   const int rl = threadIdx.x / LPR;
 #pragma unroll
-  for (int i = 0; i < ROWS_IN_FLIGHT; ++i)
+  for (int i = 0; i < F; ++i)
     q[i] = *(const uint4*)((const char*)base + ((uint32_t)min(rl + 32 * i, n - 1) * pitch + g));
 }
 

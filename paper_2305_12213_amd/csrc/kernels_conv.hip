@@ -2,6 +2,8 @@
 // global average pooling forward/backward.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "device_rows.h"
 #include "dynb_internal.h"
 
@@ -11,7 +13,9 @@ namespace {
 // pooled[n][c] = mean over the HW pixels of act[(n, pixel)][c]   (fp32 sum in a fixed order,
 // bf16 store).  One workgroup per (sample, 8 LPR channels); padding channels are written as zero (those
 // beyond act's pitch hold zeros and keep them).
-// (eight rows of a lane in flight: 512 x 32 x 32 x 64 19 -> 12.8 us, 167 x 28 x 28 x 24 10.8 -> 5.8)
+// (eight rows of a lane in flight: 512 x 32 x 32 x 64 19 -> 12.8 us, 167 x 28 x 28 x 24 10.8 -> 5.8.  Of the last 128
+// pixels only as many as there are: always eight, a lane's own and seven times the last one, took 2048 x 2 x 2 x 512
+// from 23 us, with one, to 28; now 14.  2048 x 7 x 7 x 128 10.0 -> 6.8.)
 template <int LPR>
 __global__ __launch_bounds__(32 * LPR) void gap_forward_kernel(const bf16* __restrict__ act, int64_t lda,
                                                           int HW, int C, bf16* __restrict__ pooled,
@@ -23,17 +27,23 @@ __global__ __launch_bounds__(32 * LPR) void gap_forward_kernel(const bf16* __res
   float acc[8];
 #pragma unroll
   for (int j = 0; j < 8; ++j) acc[j] = 0.f;
-  for (int p0 = 0; p0 < HW; p0 += 32 * ROWS_IN_FLIGHT) {
-    uint4 q[ROWS_IN_FLIGHT];
+  auto take = [&](auto rows, int p0) {
+    constexpr int F = decltype(rows)::value;
+    uint4 q[F];
     load_rows<LPR>(base + (int64_t)p0 * lda, lda, HW - p0, q);
 #pragma unroll
-    for (int i = 0; i < ROWS_IN_FLIGHT; ++i) {
+    for (int i = 0; i < F; ++i) {
       float v[8];
       unpack8(q[i], v);
 #pragma unroll
       for (int j = 0; j < 8; ++j) acc[j] += p0 + rl + 32 * i < HW ? v[j] : 0.f;
     }
-  }
+  };
+  int p0 = 0;
+  for (; HW - p0 > 16 * ROWS_IN_FLIGHT; p0 += 32 * ROWS_IN_FLIGHT) take(std::integral_constant<int, ROWS_IN_FLIGHT>(), p0);
+  if (HW - p0 > 64) take(std::integral_constant<int, 4>(), p0);
+  else if (HW - p0 > 32) take(std::integral_constant<int, 2>(), p0);
+  else if (HW - p0 > 0) take(std::integral_constant<int, 1>(), p0);
   sum_over_rows<LPR>(acc, red);
   if (rl == 0) {
 #pragma unroll
