@@ -177,6 +177,7 @@ int launch_wgrad_small(const GemmArgs* a, int n, const Segs& s, const StepEnd* e
 // whether that is faster than the 128 x 128-tile kernel (and, with `average`, a pass over its results);
 // the other two as for fp32
 bool wgrad_small_pays(const GemmArgs& a, const Segs& s, bool average);
+bool wgrad_small_past(const GemmArgs* a, int n, int K);   // whether the results of such a launch leave past the caches
 bool wgrad_small_walks(const GemmArgs& a, const Segs& s);
 double wgrad_small_fold_us(const GemmArgs& a, const Segs& s);
 // Whether a bf16 weight-gradient launch of launch_gemm of these dimensions can take GemmArgs::agg.

@@ -260,13 +260,8 @@ struct SmallWgrads {
   StepEnd end;
 };
 
-// PAST: results, the averages too, leave past the caches.  Right for rows of whole 128-byte lines with the
-// average formed here: kept in the L2s, as dirty lines they cost the 3072-1024-1024-10 model 13 us per iteration
-// at the ends of launches.  Other results go through the caches: past them, every piece of a line is written on
-// its own, and what the update or a pass reads next is in memory only (2048-256 behind a pass, 32 workers: 606 ->
-// 602 us per iteration; 1001-2050-777-101, 7 workers, with Adam: 192 -> 182 us; 1000-1000-1000-100, 32
-// workers: 185 -> 120; 2000-1500-20, 8 workers: 109 -> 81).  (A kernel of its own each: the compiler makes one
-// plain store of the two in a branch.)
+// PAST: results, the averages too, leave past the caches (wgrad_small_past below says when).  A kernel of its own
+// each: the compiler makes one plain store of the two in a branch.
 template <bool PAST>
 __global__ __launch_bounds__(256, 4) void wgrad_small_kernel(SmallWgrads grp, Segs segs) {
   __shared__ uint4 ring[WNB * WSTAGE / 16];
@@ -451,15 +446,38 @@ int launch_gemm_small(const GemmArgs& a, const HeadArgs* head, void* stream) {
   return hipGetLastError() == hipSuccess ? DYNB_OK : fail(DYNB_ERR_HIP, "gemm launch failed");
 }
 
+// Whether the results of a launch leave past the caches; where its layers differ, by the more weights.
+// Rows that are not whole 128-byte lines: through them.  Past them, every piece of a line is written on its own, and what
+// the update or a pass reads next is in memory only (1001-2050-777-101, 7 workers, with Adam: 192 -> 182 us; 1000-1000-1000-100,
+// 32 workers: 185 -> 120; 2000-1500-20, 8 workers: 109 -> 81).
+// Whole lines with the average formed here: past them.  Kept in the L2s, as dirty lines they cost the 3072-1024-1024-10
+// model 13 us per iteration at the ends of launches.
+// Other whole lines, by the bytes of the launch's results.  Time through the caches over the time past them, whole
+// iterations of 1814 models of 32 to 4096 features and 2 to 64 workers, geometric means of the launches of each size:
+// below 8 MB 0.99 - 1.00, 8 to 32 MB 1.01 - 1.03 (1.18 at most), 32 to 128 MB 0.99 - 1.03, 128 to 384 MB 0.95 - 0.99,
+// from there on 1.00 - 1.04 (1440-1088-1920-32, 64 workers, 349 -> 410 us).  What the update or a pass reads next is then in
+// a cache; on the other side, dirty lines that fill the L2s (32 MB) have to go before the launches behind can use
+// them, and results that do not fit in the last-level cache (256 MB) displace what these read.
+bool wgrad_small_past(const GemmArgs* a, int n, int K) {
+  double bytes = 0;
+  for (int q = 0; q < n; ++q) bytes += 4.0 * K * a[q].M * a[q].N;
+  const bool sized = (bytes >= 8e6 && bytes < 32e6) || bytes >= 384e6;
+  int64_t past = 0;
+  for (int q = 0; q < n; ++q) {
+    const bool lines = !(a[q].ldcf & 31) && !((uintptr_t)a[q].Cf & 127);
+    past += (lines && (a[q].agg || sized) ? 1 : -1) * (int64_t)a[q].M * a[q].N;
+  }
+  return past > 0;
+}
+
 int launch_wgrad_small(const GemmArgs* a, int n, const Segs& s, const StepEnd* end, void* stream) {
   if (n > WGRAD_SMALL_ITEMS) return fail(DYNB_ERR_BADARG, "gemm: too many weight gradients for one launch");
   SmallWgrads grp = {};
   double flops = 0, bytes = 0;
-  int64_t blocks = 0, past = 0;            // past: weights whose results should leave past the caches, less the others
+  int64_t blocks = 0;
   for (int q = 0; q < n; ++q) {
     const GemmArgs& g = a[q];
     if (g.M <= 0 || g.N <= 0) continue;
-    past += !g.agg || (g.ldcf & 31) || ((uintptr_t)g.Cf & 127) ? -(int64_t)g.M * g.N : (int64_t)g.M * g.N;
     if (!gemm_small_applies(g) || !g.bias_grad || (g.agg && !g.bias_agg) || g.split > 1 ||
         (grp.n && g.group_stride != grp.group_stride))
       return fail(DYNB_ERR_BADARG, "gemm: not a weight gradient of few tiles with its bias gradient");
@@ -485,7 +503,7 @@ int launch_wgrad_small(const GemmArgs* a, int n, const Segs& s, const StepEnd* e
   }
   if (!grp.n && !grp.ends) return DYNB_OK;
   Timed t(KC_GEMM_WGRAD_64, stream, flops, bytes);
-  const auto kernel = past > 0 ? wgrad_small_kernel<true> : wgrad_small_kernel<false>;
+  const auto kernel = wgrad_small_past(a, n, s.K) ? wgrad_small_kernel<true> : wgrad_small_kernel<false>;
   hipLaunchKernelGGL(kernel, dim3((unsigned)(blocks + grp.ends)), dim3(256), 0, (hipStream_t)stream, grp, s);
   return hipGetLastError() == hipSuccess ? DYNB_OK : fail(DYNB_ERR_HIP, "gemm launch failed");
 }

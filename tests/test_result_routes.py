@@ -1,0 +1,64 @@
+"""Rules of launches that were measured on both sides, asked of the library itself through a small program linked against
+it: whether the weight gradients of a launch of 64 x 64 tiles leave past the caches."""
+import os
+import subprocess
+
+import pytest
+
+from paper_2305_12213_amd import build
+
+
+def ask(directory, program, calls):
+    (directory / "main.cpp").write_text(program)
+    if not os.path.exists(build.LIB):
+        build.build_library(verbose=False)
+    subprocess.run(["g++", "-std=c++17", "-I", build.CSRC, str(directory / "main.cpp"), build.LIB, "-o",
+                    str(directory / "main"), "-Wl,--allow-shlib-undefined", "-Wl,-rpath," + os.path.dirname(build.LIB)],
+                   check=True)
+    return subprocess.run([str(directory / "main")], input=calls, check=True, capture_output=True, text=True).stdout.split()
+
+
+# dense layers (inputs, outputs, whether the launch forms the average), workers, whether past the caches was faster
+RESULTS = [
+    ([(960, 160, 0), (160, 192, 0)], 8, False),        # 6 MB
+    ([(672, 160, 0), (160, 1024, 0)], 16, True),       # 17 MB
+    ([(448, 224, 0), (224, 96, 0)], 64, True),         # 31 MB
+    ([(1024, 1024, 0)], 8, False),                     # 34 MB
+    ([(544, 1248, 0), (1248, 256, 0)], 64, False),     # 256 MB
+    ([(1440, 1088, 0), (1088, 1920, 0), (1920, 32, 0)], 64, True),   # 952 MB
+    ([(3072, 1024, 1), (1024, 1024, 1)], 8, True),     # 134 MB, averaged in the launch
+    ([(1024, 500, 0)], 8, False),                      # 16 MB, but rows that are not whole lines
+    ([(1024, 500, 1)], 8, False),
+    ([(1440, 1088, 0), (1088, 1900, 0)], 64, False),   # ... the larger part of a launch
+    ([(3072, 1024, 1), (1024, 10, 1)], 8, True),       # ... the smaller
+]
+
+PROGRAM = """
+#include <cstdio>
+#include "dynb_internal.h"
+int main() {
+  int layers, K;
+  while (std::scanf("%d %d", &layers, &K) == 2) {
+    dynb::GemmArgs a[8] = {};
+    for (int q = 0; q < layers; ++q) {
+      int in, out, folded;
+      if (std::scanf("%d %d %d", &in, &out, &folded) != 3) return 1;
+      a[q].mode = dynb::MODE_WGRAD; a[q].M = out; a[q].N = in; a[q].ldcf = out;
+      a[q].Cf = (float*)(1 << 20);
+      a[q].agg = folded ? a[q].Cf : nullptr;
+    }
+    std::printf("%d\\n", (int)dynb::wgrad_small_past(a, layers, K));
+  }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def results(tmp_path_factory):
+    calls = "".join("%d %d %s\n" % (len(layers), K, " ".join("%d %d %d" % l for l in layers)) for layers, K, _ in RESULTS)
+    return ask(tmp_path_factory.mktemp("results"), PROGRAM, calls)
+
+
+@pytest.mark.parametrize("i", range(len(RESULTS)))
+def test_results_leave_the_faster_way(results, i):
+    assert (results[i] == "1") == RESULTS[i][-1], RESULTS[i]
