@@ -243,6 +243,8 @@ struct CastMats {
   int64_t ldt[MAX_CAST_MATS], tap_t[MAX_CAST_MATS];
   int first_block[MAX_CAST_MATS + 1];   // first workgroup of each matrix (set by the launcher)
 };
+// Rows of a tile of `tile_columns` in such a launch over K workers' gradients (0: over their average).
+int cast_tile_rows(const CastMats& mats, int tile_columns, int K);
 // The copies alone, of the weights as they are.
 int launch_weight_casts(int dtype, const float* params, CastMats& mats, void* stream);
 // The same together with the packed input act T [rows][ld] = x fp32 [rows][D], zeros beyond (rows = 0: none),

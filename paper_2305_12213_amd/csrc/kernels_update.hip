@@ -327,17 +327,7 @@ double flops_per_param(const UpdateRule& rule, const GradSource& src) {
 
 // (wider tiles when K gradient streams are read: 512-byte runs per row and stream)
 constexpr int cast_tile_columns(bool agg) { return agg ? 128 : 64; }
-// A tile of 64 rows is a chain of four to sixteen rounds of loads and stores in one workgroup; with fewer tiles than
-// compute units that chain is the launch, and tiles of 16 rows shorten it: Adam on 785-301-97-10, 79 -> 297 workgroups,
-// 10.6 -> 6.5 us; 32-64-128 convolutions, 39 -> 108, 5.3 -> 4.6.  From there on it is the bytes (3072-512-512-10: 458
-// workgroups 8.1, 1826 8.0), and tall tiles write the transposed copy in whole lines.
-constexpr int SHORT_ROWS = 16, TALL_ROWS = 64, SHORT_BELOW = 256;
-int cast_tile_rows(const CastMats& mats, int tile_columns) {
-  int64_t tall = 0;
-  for (int i = 0; i < mats.n && i < MAX_CAST_MATS; ++i)
-    tall += (int64_t)((mats.C[i] + tile_columns - 1) / tile_columns) * ((mats.R[i] + TALL_ROWS - 1) / TALL_ROWS) * mats.taps[i];
-  return tall < SHORT_BELOW ? SHORT_ROWS : TALL_ROWS;
-}
+constexpr int SHORT_ROWS = 16, TALL_ROWS = 64;
 
 template <typename T, int KIND, bool AGG>
 void launch_update_cast_t(float* params, const CastMats& mats, int rows, const Ranges& small, int range_blocks,
@@ -398,6 +388,23 @@ int count_blocks(CastMats& mats, int tile_columns, int tile_rows, double& params
 
 }  // namespace
 
+// A tile of 64 rows is a chain of four to sixteen rounds of loads and stores in one workgroup; with fewer tiles than
+// compute units that chain is the launch, and tiles of 16 rows shorten it: Adam on 785-301-97-10, 79 -> 297 workgroups,
+// 10.6 -> 6.5 us; 32-64-128 convolutions, 39 -> 108, 5.3 -> 4.6.  From there on it is the bytes (3072-512-512-10: 458
+// workgroups 8.1, 1826 8.0), and tall tiles write the transposed copy in whole lines.
+// With the average folded in, the bytes are those of K gradients.  For convolutions they count before the tiles fill
+// the chip: 568 models, update with tiles of 64 and of 16 rows, below 40 MB of gradients 1.0 : 0.78, 40 to 64 MB
+// 1.0 : 1.07, above 1.0 : 1.2 (320-320 channels, 32 workers, 30 -> 41 us).  Dense layers, 500 models, are faster on
+// short tiles on average at every size measured (up to 200 MB, 1.0 : 0.85 above 64 MB; 0.62 to 1.31 there).
+int cast_tile_rows(const CastMats& mats, int tile_columns, int K) {
+  int64_t tall = 0, weights = 0;
+  for (int i = 0; i < mats.n && i < MAX_CAST_MATS; ++i) {
+    tall += (int64_t)((mats.C[i] + tile_columns - 1) / tile_columns) * ((mats.R[i] + TALL_ROWS - 1) / TALL_ROWS) * mats.taps[i];
+    if (mats.taps[i] > 1) weights += (int64_t)mats.taps[i] * mats.R[i] * mats.C[i];
+  }
+  return tall < 256 && 4 * K * weights < 40000000 ? SHORT_ROWS : TALL_ROWS;
+}
+
 int launch_update_cast(int dtype, float* params, CastMats& mats, const Ranges& small,
                        const GradSource& src, const UpdateRule& rule, float* s1, float* s2,
                        void* stream) {
@@ -406,7 +413,7 @@ int launch_update_cast(int dtype, float* params, CastMats& mats, const Ranges& s
   const int es = dtype == DYNB_BF16 ? 2 : 4;
   double cast_n = 0.0, small_n = 0.0;
   int64_t longest = 0;
-  const int columns = cast_tile_columns(src.lam.K > 0), rows = cast_tile_rows(mats, columns);
+  const int columns = cast_tile_columns(src.lam.K > 0), rows = cast_tile_rows(mats, columns, src.lam.K);
   if (int rc = count_blocks(mats, columns, rows, cast_n)) return rc;
   for (int i = 0; i < small.n; ++i) {
     longest = small.len[i] > longest ? small.len[i] : longest;
@@ -427,7 +434,7 @@ int launch_update_cast(int dtype, float* params, CastMats& mats, const Ranges& s
 int launch_weight_casts(int dtype, const float* params, CastMats& mats, void* stream) {
   const int es = dtype == DYNB_BF16 ? 2 : 4;
   double n = 0.0;
-  const int rows = cast_tile_rows(mats, cast_tile_columns(false));
+  const int rows = cast_tile_rows(mats, cast_tile_columns(false), 0);
   if (int rc = count_blocks(mats, cast_tile_columns(false), rows, n)) return rc;
   if (n == 0.0) return DYNB_OK;
   Timed t(KC_WEIGHT_CAST, stream, 0, n * (4 + 2 * es));
@@ -447,7 +454,7 @@ int launch_weight_casts(int dtype, const float* params, CastMats& mats, void* st
 int launch_prepare(int dtype, const float* params, CastMats& mats, const Prepare& pr, void* stream) {
   const int es = dtype == DYNB_BF16 ? 2 : 4;
   double n = 0.0;
-  const int rows = cast_tile_rows(mats, cast_tile_columns(false));
+  const int rows = cast_tile_rows(mats, cast_tile_columns(false), 0);
   if (int rc = count_blocks(mats, cast_tile_columns(false), rows, n)) return rc;
   const int64_t granules = (int64_t)pr.rows * (pr.ld / 8);
   int64_t pads = 0;

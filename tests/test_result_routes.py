@@ -1,5 +1,6 @@
 """Rules of launches that were measured on both sides, asked of the library itself through a small program linked against
-it: whether the weight gradients of a launch of 64 x 64 tiles leave past the caches."""
+it: whether the weight gradients of a launch of 64 x 64 tiles leave past the caches, and how tall the tiles of an update
+are."""
 import os
 import subprocess
 
@@ -62,3 +63,38 @@ def results(tmp_path_factory):
 @pytest.mark.parametrize("i", range(len(RESULTS)))
 def test_results_leave_the_faster_way(results, i):
     assert (results[i] == "1") == RESULTS[i][-1], RESULTS[i]
+
+
+# layers (rows, columns, taps), workers whose average is folded into the update (0: none), rows of the faster tiles
+TILES = [
+    ([(785, 301, 1), (301, 97, 1), (97, 10, 1)], 0, 16), ([(3072, 512, 1), (512, 512, 1), (512, 10, 1)], 0, 64),
+    ([(320, 320, 9)], 2, 16), ([(256, 256, 9), (256, 256, 9)], 8, 16), ([(256, 256, 9), (256, 256, 9)], 16, 64),
+    ([(320, 320, 9)], 32, 64), ([(128, 128, 9), (128, 128, 9)], 32, 16), ([(256, 256, 9)], 0, 16),
+    ([(1024, 1024, 1), (1024, 10, 1)], 16, 16), ([(1495, 602, 1)], 32, 16), ([(2752, 2048, 1)], 32, 64),
+]
+
+TILE_PROGRAM = """
+#include <cstdio>
+#include "dynb_internal.h"
+int main() {
+  int layers, K;
+  while (std::scanf("%d %d", &layers, &K) == 2) {
+    dynb::CastMats m = {};
+    m.n = layers;
+    for (int q = 0; q < layers; ++q)
+      if (std::scanf("%d %d %d", &m.R[q], &m.C[q], &m.taps[q]) != 3) return 1;
+    std::printf("%d\\n", dynb::cast_tile_rows(m, K > 0 ? 128 : 64, K));
+  }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def tiles(tmp_path_factory):
+    calls = "".join("%d %d %s\n" % (len(layers), K, " ".join("%d %d %d" % l for l in layers)) for layers, K, _ in TILES)
+    return ask(tmp_path_factory.mktemp("tiles"), TILE_PROGRAM, calls)
+
+
+@pytest.mark.parametrize("i", range(len(TILES)))
+def test_updates_take_the_faster_tiles(tiles, i):
+    assert int(tiles[i]) == TILES[i][-1], TILES[i]
