@@ -197,11 +197,11 @@ void launch_as(const ConvFlatArgs& p, hipStream_t st) {
 
 }  // namespace
 
-// (32-pixel-wide images with whole 64-channel blocks stay on the halo-tile kernel, whose operand
-// addresses are constants.  64 to more than 32 channels stay on the gathered-operand GEMM: 64 is a power
-// of two, for which its addressing is cheap, and fills its tile -- 367 x 28 x 28 pixels: forward 51 us on
-// either, input gradient 62 - 70 against 60 - 76; 48 channels 38 and 50 against 28 and 39.  Whole blocks of
-// output channels are stored.)
+// (Asked after the kernels with resident weights, which take 64 to more than 32 channels up to 43 pixels wide, and with
+// halo tiles: 32-pixel-wide images with whole 64-channel blocks, up to 32 outputs here.  Beyond 43 pixels 64 to more than
+// 32 channels stay on the gathered-operand product: 64 is a power of two, for which its addressing is cheap, and
+// fills its tile.  Other numbers of channels are faster here: 367 x 28 x 28 pixels, 48 -> 48 forward and input gradient 49 us
+// each against 59 and 61, 56 -> 56 53 against 64 and 67.  Whole blocks of output channels are stored.)
 bool conv_flat_applies(int dtype, const GemmArgs& a) {
   if (dtype != DYNB_BF16 || !a.conv || a.mode == MODE_WGRAD || a.stride != 1) return false;
   if (a.src_w > MAX_W || a.src_w != a.row_w || a.src_h != a.row_h || a.cp > 64 || (a.cp == 64 && a.N > 32)) return false;

@@ -6,14 +6,13 @@
 // falls outside the image reads a pixel of zeros).  Its eight waves are two groups of four, one wave of
 // each on every SIMD, that take turns: while one group computes a tile -- nine taps read at pixel offsets
 // from the halo run in LDS, no barrier in between -- the other writes its last tile out and fetches the
-// halo of its next one.  What bounds a launch is then the memory traffic, with the 4608 clocks of matrix
-// instructions of a tile beside it; the halo-tile kernel that streams the weights for every tile copies 116
+// halo of its next one.  The halo-tile kernel that streams the weights for every tile copies 116
 // KB into LDS per tile instead of 41 and overlaps the phases of two workgroups only by chance.
 // Sums run in the order of the other kernels: taps ascending, 16 channels at a time.
-// 512 x 32 x 32 pixels, 64 -> 64 channels: forward 49.5 -> 39.5 us, input gradient with a mask 57 -> 44, with
-// mask and addend 66 -> 55 (201 and 268 MB: 4.5 and 4.9 TB/s).  Without the halo copies it takes as long, with
-// a ninth of the matrix steps 31 us: a wave reads one operand from LDS per matrix instruction, 128 bytes per
-// clock and compute unit, which is what the LDS delivers.
+// 512 x 32 x 32 pixels, 64 -> 64 channels, as they run in a residual model: forward 41 us, input gradient with a mask
+// 48 - 50, with mask and addend 61 - 63 (201 and 268 MB: 4.1 and 4.3 TB/s), 48 on average; the halo-tile kernel 58.
+// Without the halo copies the forward takes as long, with a ninth of the matrix steps 31 us: a wave reads one operand
+// from LDS per matrix instruction, 128 bytes per clock and compute unit, which is what the LDS delivers.
 #include <hip/hip_runtime.h>
 
 #include "device_rows.h"
@@ -248,7 +247,9 @@ __global__ __launch_bounds__(512) void conv_resident_kernel(ConvResidentArgs p) 
     } else if (n > 0) {
       results();
       // (the copies overwrite the patch: its reads have returned; stores go behind the copies, so that
-      // waiting for these does not wait for them)
+      // waiting for these does not wait for them.  The compiler moves the arithmetic on mask and addend behind the
+      // copies and waits for both there, that is, for the copies too; with the builtin wait in front of the copies
+      // nothing waits between these and the stores, and 500 models took the same time.)
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
       if (n + 1 < nt) issue_halo(t0 + n + 1);
       asm volatile("" ::: "memory");
@@ -264,7 +265,9 @@ __global__ __launch_bounds__(512) void conv_resident_kernel(ConvResidentArgs p) 
 // (Every case of 64 reduction channels that fits: against the gathered-operand product and the halo-tile
 // kernel, per iteration of a 4 -> 64 -> 64 -> 64 -> 64 model, 28 x 28 pixels: 2 samples 203 -> 152 us, 64
 // samples 259 -> 206, 256 samples 478 -> 371; 32 x 32: 141 -> 127, 207 -> 195, 409 -> 367; 64 -> 200 channels on
-// 20 x 33: 138 -> 127, 205 -> 189, 497 -> 454.  Up to 32 outputs the other two waste less.)
+// 20 x 33: 138 -> 127, 205 -> 189, 497 -> 454.  Up to 32 outputs the other two waste less.  Weights and halo are laid out
+// for exactly 64 channels.  33 to 56 would have to be padded to 64 and stay on the flat run, where they take longer than 64
+// do here: 367 x 28 x 28 pixels, 48 -> 48 49 us, 64 -> 48 here 26.)
 bool conv_resident_applies(int dtype, const GemmArgs& a) {
   if (dtype != DYNB_BF16 || !a.conv || a.mode == MODE_WGRAD || a.stride != 1) return false;
   if (a.src_w > MAX_W || a.src_w != a.row_w || a.src_h != a.row_h || a.cp != 64 || a.N <= 32) return false;

@@ -5,7 +5,7 @@
 // gradient wrt it.  The general kernels pad the input to 64 channels (a packed copy of which 16 of 128
 // bytes are used, and 64 x 64 products of which 3 x 64 count).
 // 512 x 32 x 32 x 3 -> 64 channels, per iteration: packing 17 us, forward 57, weight gradient 54 + 7
-// -> forward 27, weight gradient 24 + 5 (the 67 MB of the wide tensor take 10 us to write, 14 to read).
+// -> forward 24, weight gradient 24 + 5 (the 67 MB of the wide tensor take 10 us to write, 14 to read).
 #include <hip/hip_runtime.h>
 
 #include "device_rows.h"

@@ -42,9 +42,9 @@ __device__ inline void wait_reads() {
 // 4e + kg of 16 rows, finds 64 different banks.  A wave issues in order and the next matrix
 // instruction of a chain waits for the last, so fetches (in a step's first half) and copies (in its
 // second) are placed between them, in their 32-clock shadows.
-// Against 64 x 64 vector-unit tiles: 256 x 512 x 3072 165 -> 28 us (the chain of matrix
-// instructions alone is 11 us, the issue of everything else of a lone wave 12), 785 x 301 x 832
-// 49 -> 11 us.
+// Against 64 x 64 vector-unit tiles: 256 x 512 x 3072 165 -> 25 us, 785 x 301 x 832 49 -> 9.5.  What bounds it is one
+// wave's chain, whatever the number of tiles: 16 x 16 x 3072, a single wave, takes 24.8 us, and from 768 to 12288
+// reduction indices every further matrix instruction 28.5 ns, half of it its own 33 clocks, half what is issued with it.
 // With HeadArgs (forward, at most 16 columns) the tile's rows of logits go through the softmax and the loss in
 // LDS instead of to memory.
 template <int MODE, int R, typename Head>

@@ -33,14 +33,13 @@ __device__ inline int swizzle(int r) { return (((r >> 1) & 3) << 1) | ((r >> 3) 
 
 // Forward and input gradient: C[i][j] = sum_k A[i][k] B[j][k].  A stage is 64 reduction elements, the
 // whole 128-byte line of each of the 64 + 64 operand rows (16 copies, four per wave); ring of NB
-// stages, NB - 1 in flight (eight instead of four changed nothing: 17.4 against 17.7 us below).  A compute unit
+// stages, all issued ahead of the loop (eight instead of four changed nothing).  A compute unit
 // holds one such workgroup, so what bounds a stage is its serial chain: the next stage's operands are on their
 // way into the other register set while the matrix instructions of this one run (1024 x 1024 x 3072 17 -> 14 us, 1024 x 10 x 1024 with its loss 8.4
 // -> 7.2).  Copies
 // past the last stage are still issued (the wait stays a constant); what they read -- the next rows,
 // zeros past the matrix -- is never used.
-// Against 128 x 128 tiles: 1024 x 1024 x 3072 30 -> 18 us, 1024 x 10 x 1024 14 -> 6, 1531 x 777 x 2050
-// 23 -> 18.
+// On 128 x 128 tiles: 1024 x 1024 x 3072 30 us, 1024 x 10 x 1024 14 (without its loss).
 constexpr int NB = 4, STAGE = 2 * T * 128;
 
 // With HeadArgs (forward, at most 64 columns) the tile's rows of logits go through the softmax and the loss in

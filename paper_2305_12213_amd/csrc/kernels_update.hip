@@ -119,8 +119,8 @@ __device__ __forceinline__ void update_tile(int blk, float* __restrict__ params,
   __shared__ float tile[TR][TC + 1];
   const int r0 = tile_y * TR, c0 = tile_x * TC;
   // 16-byte accesses need aligned rows in every array (all start at a multiple of 4 floats);
-  // otherwise a lane takes single elements, 64 neighbouring ones of a row per wave, U rows or column
-  // halves at once.  (1001 x 2050 and 2050 x 777, 7 workers, Adam: 106 us with four elements in turn
+  // otherwise a lane takes single elements, U of the tile's elements row after row, 256 apart, at once.
+  // (1001 x 2050 and 2050 x 777, 7 workers, Adam: 106 us with four elements in turn
   // per lane -> 43 us, what its 210 MB take at the rate of a large copy.)
   const bool vec = (C & 3) == 0 && (off & 3) == 0;
   if (!vec) {
