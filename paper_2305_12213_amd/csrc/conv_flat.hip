@@ -57,7 +57,7 @@ struct FlatConv {
 // Granule g of halo row r sits at slot g ^ swz(r): 16 neighbouring rows at one granule take all 64 banks.
 template <int CI>
 __device__ inline int swz(int r) {
-  return CI == 2 ? (((r >> 1) & 3) << 1) | ((r >> 3) & 1) : (((r >> 2) & 1) << 1) | ((r >> 3) & 1);
+  return CI == 2 ? swizzle128(r) : (((r >> 2) & 1) << 1) | ((r >> 3) & 1);
 }
 
 template <int CI, int CO, int NW>

@@ -54,10 +54,6 @@ struct ConvResidentArgs {
   const bf16* addend; int64_t ldadd; // input gradient: added after rounding (optional)
 };
 
-// Granule g (16 bytes) of a 128-byte row r sits at slot g ^ swz(r): 16 neighbouring rows at one granule take
-// all 64 banks.
-__device__ inline int swz(int r) { return (((r >> 1) & 3) << 1) | ((r >> 3) & 1); }
-
 template <bool MASK, bool ADD>
 __global__ __launch_bounds__(512) void conv_resident_kernel(ConvResidentArgs p) {
   __shared__ __align__(128) char area[AREA];
@@ -73,7 +69,7 @@ __global__ __launch_bounds__(512) void conv_resident_kernel(ConvResidentArgs p) 
 #pragma unroll 1
   for (int c = wave8; c < 72; c += 8) {
     const int r = (c & 7) * 8 + (lane >> 3);
-    async_copy_1k_buffer(rsw, (uint32_t)(j0 + r) * p.w_pitch + (uint32_t)((c >> 3) * 128 + ((lane & 7) ^ swz(r)) * 16),
+    async_copy_1k_buffer(rsw, (uint32_t)(j0 + r) * p.w_pitch + (uint32_t)((c >> 3) * 128 + ((lane & 7) ^ swizzle128(r)) * 16),
                          lds + 2 * HALO + (uint32_t)(c * 1024));
   }
   if (threadIdx.x < 8) *(uint4*)&area[ZEROS + threadIdx.x * 16] = make_uint4(0, 0, 0, 0);
@@ -101,7 +97,7 @@ __global__ __launch_bounds__(512) void conv_resident_kernel(ConvResidentArgs p) 
   uint4 mk[MASK ? 8 : 1], ad[ADD ? 8 : 1];
   uint32_t wat[4];                         // this lane's 16 bytes of weight row l31 in matrix step kk of a tap
 #pragma unroll
-  for (int kk = 0; kk < 4; ++kk) wat[kk] = (uint32_t)(2 * HALO + l31 * 128 + (((2 * kk + h) ^ swz(l31)) * 16));
+  for (int kk = 0; kk < 4; ++kk) wat[kk] = (uint32_t)(2 * HALO + l31 * 128 + (((2 * kk + h) ^ swizzle128(l31)) * 16));
   const int erow = lane >> 3, ecol = (lane & 7) * 8;       // results: this lane's row (of 8) and channels
   auto compute = [&](int tile) {
     const int p0 = tile * TILE + wave * 64;
@@ -141,7 +137,7 @@ __global__ __launch_bounds__(512) void conv_resident_kernel(ConvResidentArgs p) 
 #pragma unroll
       for (int a = 0; a < 2; ++a) {
         const int r = row[a] + shift;
-        at[a] = ((in[a] >> e) & 1u) ? (uint32_t)(group * HALO + r * 128 + ((h ^ swz(r)) * 16)) : (uint32_t)ZEROS;
+        at[a] = ((in[a] >> e) & 1u) ? (uint32_t)(group * HALO + r * 128 + ((h ^ swizzle128(r)) * 16)) : (uint32_t)ZEROS;
       }
     };
     auto fetch = [&](int set, int x, int s) {
@@ -212,12 +208,7 @@ __global__ __launch_bounds__(512) void conv_resident_kernel(ConvResidentArgs p) 
         res[t] = pack8(v);
       }
       if constexpr (MASK) {
-        float k[8];
-        unpack8(mk[t], k);
-        uint4 m;
-        auto word = [&](int d) { return (k[2 * d] > 0.f ? 0x0000ffffu : 0u) | (k[2 * d + 1] > 0.f ? 0xffff0000u : 0u); };
-        m.x = word(0); m.y = word(1); m.z = word(2); m.w = word(3);
-        res[t] = res[t] & m;
+        res[t] = res[t] & positive8(mk[t]);
       }
       res[t] = res[t] & keep;
     }

@@ -55,7 +55,7 @@ struct StridedGrad {
 // Granule g of row r sits at slot g ^ swz(r): 16 neighbouring rows at one granule take all 64 banks.
 template <int RB>
 __device__ inline int swz(int r) {
-  return RB == 256 ? r & 15 : RB == 128 ? (((r >> 1) & 3) << 1) | ((r >> 3) & 1) : (((r >> 2) & 1) << 1) | ((r >> 3) & 1);
+  return RB == 256 ? r & 15 : RB == 128 ? swizzle128(r) : (((r >> 2) & 1) << 1) | ((r >> 3) & 1);
 }
 
 template <int RB>
@@ -181,10 +181,7 @@ __global__ __launch_bounds__(256, RB == 256 ? 1 : 2) void conv_strided_grad_kern
         v = pack8(f);
       }
       if (p.mask) {
-        float k[8];
-        unpack8(mk[t], k);
-        auto word = [&](int d) { return (k[2 * d] > 0.f ? 0x0000ffffu : 0u) | (k[2 * d + 1] > 0.f ? 0xffff0000u : 0u); };
-        v = v & make_uint4(word(0), word(1), word(2), word(3));
+        v = v & positive8(mk[t]);
       }
       if (py == 0 ? pixel[t] >= 0 : (odd_row >> t) & 1u)
         store8(p.out + (int64_t)(pixel[t] + py * p.W) * p.ldo + j0 + ch, v & keep);

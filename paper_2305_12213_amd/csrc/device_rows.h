@@ -34,12 +34,24 @@ __device__ inline uint4 keep8(int live) {
   auto word = [&](int d) { return live > 2 * d + 1 ? 0xffffffffu : live > 2 * d ? 0x0000ffffu : 0u; };
   return make_uint4(word(0), word(1), word(2), word(3));
 }
+// Mask of those of 8 values that are > 0 (a ReLU's gradient passes where its output is).
+__device__ inline uint4 positive8(const uint4& q) {
+  float k[8];
+  unpack8(q, k);
+  auto word = [&](int d) { return (k[2 * d] > 0.f ? 0x0000ffffu : 0u) | (k[2 * d + 1] > 0.f ? 0xffff0000u : 0u); };
+  return make_uint4(word(0), word(1), word(2), word(3));
+}
 __device__ inline uint4 operator&(const uint4& a, const uint4& b) {
   return make_uint4(a.x & b.x, a.y & b.y, a.z & b.z, a.w & b.w);
 }
 
 __device__ inline uint4 load8(const bf16* p) { return *reinterpret_cast<const uint4*>(p); }
 __device__ inline void store8(bf16* p, const uint4& q) { *reinterpret_cast<uint4*>(p) = q; }
+
+// Granule (16 bytes) g of a 128-byte row r in LDS sits at slot g ^ swizzle128(r): 16 neighbouring rows, read at
+// one granule, then fall into 64 different banks (two rows per pass over the banks; rows r and r + 8
+// differ in the lowest bit, which also keeps lanes l and l + 32 apart).
+__device__ inline int swizzle128(int r) { return (((r >> 1) & 3) << 1) | ((r >> 3) & 1); }
 
 // This lane's granules of the first n >= 1 of 32 F rows: rows row-lane + 32 i.  Rows past the last repeat it,
 // so that no branch stands between the loads and all are in flight together; the address is one uniform

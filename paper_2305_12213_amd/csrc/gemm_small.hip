@@ -8,6 +8,7 @@
 
 #include <type_traits>
 
+#include "device_rows.h"
 #include "dynb_internal.h"
 #include "lds_async.h"
 #include "softmax_head.h"
@@ -17,7 +18,6 @@
 namespace dynb {
 namespace {
 
-typedef __bf16 bf16;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
@@ -25,11 +25,6 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int T = 64;                      // tile side
-
-// Granule (16 bytes) g of a 128-byte row r sits at slot g ^ swizzle(r): 16 neighbouring rows, read at
-// one granule, then fall into 64 different banks (two rows per pass over the banks; rows r and r + 8
-// differ in the lowest bit, which also keeps lanes l and l + 32 apart).
-__device__ inline int swizzle(int r) { return (((r >> 1) & 3) << 1) | ((r >> 3) & 1); }
 
 // Forward and input gradient: C[i][j] = sum_k A[i][k] B[j][k].  A stage is 64 reduction elements, the
 // whole 128-byte line of each of the 64 + 64 operand rows (16 copies, four per wave); ring of NB
@@ -60,7 +55,7 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(GemmArgs p, Head head) 
   uint32_t off[4];
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
-    const int r = 16 * wave + 8 * (u & 1) + (lane >> 3), g = (lane & 7) ^ swizzle(r);
+    const int r = 16 * wave + 8 * (u & 1) + (lane >> 3), g = (lane & 7) ^ swizzle128(r);
     const int i = i0 + r < p.M ? i0 + r : p.M - 1, j = j0 + r < p.N ? j0 + r : p.N - 1;
     off[u] = (uint32_t)((u < 2 ? (int64_t)i * p.lda : (int64_t)j * p.ldb) * 2) + g * 16;
   }
@@ -105,7 +100,7 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(GemmArgs p, Head head) 
     }
   }
   const char* const base = (const char*)&ring[0];
-  const int fa = (wi * 32 + l31) * 128, fb = T * 128 + (wj * 32 + l31) * 128, sw = swizzle(l31);
+  const int fa = (wi * 32 + l31) * 128, fb = T * 128 + (wj * 32 + l31) * 128, sw = swizzle128(l31);
   bf16x8 a[2][4], b[2][4];                 // [register set][step of 16]
   auto fetch = [&](int set, uint32_t slot) {
 #pragma unroll
