@@ -392,17 +392,24 @@ int count_blocks(CastMats& mats, int tile_columns, int tile_rows, double& params
 // compute units that chain is the launch, and tiles of 16 rows shorten it: Adam on 785-301-97-10, 79 -> 297 workgroups,
 // 10.6 -> 6.5 us; 32-64-128 convolutions, 39 -> 108, 5.3 -> 4.6.  From there on it is the bytes (3072-512-512-10: 458
 // workgroups 8.1, 1826 8.0), and tall tiles write the transposed copy in whole lines.
-// With the average folded in, the bytes are those of K gradients.  For convolutions they count before the tiles fill
-// the chip: 568 models, update with tiles of 64 and of 16 rows, below 40 MB of gradients 1.0 : 0.78, 40 to 64 MB
-// 1.0 : 1.07, above 1.0 : 1.2 (320-320 channels, 32 workers, 30 -> 41 us).  Dense layers, 500 models, are faster on
-// short tiles on average at every size measured (up to 200 MB, 1.0 : 0.85 above 64 MB; 0.62 to 1.31 there).
+// With the average of K workers folded in, a workgroup walks K gradients, and four times as many of them cost more
+// than shorter chains save once K, the matrices and the tiles or bytes are not few.  Time of the launch, between the
+// others of an iteration, on short tiles over tall ones, dense models (2000, 2 to 64 workers): below 8 workers 0.58 (1.02 at
+// most); one or two layers 0.60 to 0.77, at any size; from three layers and 8 workers on, below 64 tiles 0.6 to 0.98, 128 to
+// 256 1.0 to 1.4 from 16 workers on; more than 100 MB of gradients 1.06 to 1.3; six layers or more 0.95 to 1.05 (the
+// biases of every layer are chains of their own beside the tiles).  Convolutions (568 models): below 40 MB 0.78, 40 to 64
+// MB 1.07, above 1.2 (320-320 channels, 32 workers, 30 -> 41 us).
 int cast_tile_rows(const CastMats& mats, int tile_columns, int K) {
   int64_t tall = 0, weights = 0;
+  bool conv = false;
   for (int i = 0; i < mats.n && i < MAX_CAST_MATS; ++i) {
     tall += (int64_t)((mats.C[i] + tile_columns - 1) / tile_columns) * ((mats.R[i] + TALL_ROWS - 1) / TALL_ROWS) * mats.taps[i];
-    if (mats.taps[i] > 1) weights += (int64_t)mats.taps[i] * mats.R[i] * mats.C[i];
+    weights += (int64_t)mats.taps[i] * mats.R[i] * mats.C[i];
+    conv = conv || mats.taps[i] > 1;
   }
-  return tall < 256 && 4 * K * weights < 40000000 ? SHORT_ROWS : TALL_ROWS;
+  const bool few = K < 8 || (mats.n <= 2 && !conv) ||
+                   (tall < 128 && 4 * K * weights < 48000000 && mats.n <= (K < 16 ? 6 : 5));
+  return tall < 256 && few ? SHORT_ROWS : TALL_ROWS;
 }
 
 int launch_update_cast(int dtype, float* params, CastMats& mats, const Ranges& small,

@@ -66,11 +66,19 @@ def test_results_leave_the_faster_way(results, i):
 
 
 # layers (rows, columns, taps), workers whose average is folded into the update (0: none), rows of the faster tiles
+CHAIN = [(33, 44, 1), (44, 253, 1), (253, 173, 1), (173, 26, 1), (26, 152, 1), (152, 143, 1), (143, 300, 1)]
 TILES = [
     ([(785, 301, 1), (301, 97, 1), (97, 10, 1)], 0, 16), ([(3072, 512, 1), (512, 512, 1), (512, 10, 1)], 0, 64),
-    ([(320, 320, 9)], 2, 16), ([(256, 256, 9), (256, 256, 9)], 8, 16), ([(256, 256, 9), (256, 256, 9)], 16, 64),
-    ([(320, 320, 9)], 32, 64), ([(128, 128, 9), (128, 128, 9)], 32, 16), ([(256, 256, 9)], 0, 16),
-    ([(1024, 1024, 1), (1024, 10, 1)], 16, 16), ([(1495, 602, 1)], 32, 16), ([(2752, 2048, 1)], 32, 64),
+    ([(256, 256, 9)], 0, 16),
+    ([(320, 320, 9)], 2, 16), ([(1495, 1200, 1)], 7, 16),                              # few workers
+    ([(416, 1000, 1)], 64, 16), ([(586, 471, 1), (471, 10, 1)], 64, 16),               # one or two layers
+    ([(682, 203, 1), (203, 788, 1)], 64, 16), ([(1344, 1000, 1)], 16, 16),
+    ([(919, 836, 1), (836, 300, 1), (300, 10, 1)], 16, 64),                            # more: 128 tiles and more
+    ([(600, 700, 1), (700, 300, 1), (300, 10, 1)], 16, 16),
+    ([(600, 700, 1), (700, 300, 1), (300, 10, 1)], 32, 64),                            # 81 MB of gradients
+    ([(256, 256, 9), (256, 256, 9)], 8, 64), ([(128, 128, 9), (128, 128, 9)], 32, 16),
+    ([(192, 192, 9)], 32, 16), ([(256, 256, 9)], 32, 64),                              # 42 and 75 MB, convolutions
+    (CHAIN[:5], 32, 16), (CHAIN[:6], 32, 64), (CHAIN[:6], 8, 16), (CHAIN, 8, 64),
 ]
 
 TILE_PROGRAM = """
