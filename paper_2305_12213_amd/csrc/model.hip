@@ -471,31 +471,48 @@ int run_forward_backward(dynb_model* m, const float* x, const int32_t* y, const 
     grouped_n = passes = 0;
     return r;
   };
-  // Layers of the grouped launch whose average is formed in it.  A workgroup that walks all workers of a tile
-  // takes as long whatever its layer: where one of some layer does so in any case, the walks of all others run
-  // beside it at no cost; where a layer's average is worth one, those of smaller layers do.  And where all
+  // Layers of a grouped launch whose average is formed in it.  A workgroup that walks all workers of a tile
+  // takes as long whatever its layer: where one of some layer does so in any case, the walks of all others of its launch
+  // run beside it at no cost; where a layer's average is worth one, those of smaller layers do.  And where all
   // layers' walks cost less than the call's last launch, which then has nothing left to do, all walk (4 us; that
   // launch takes 3 to 6, and 1.4 pass in front of it).  785-301-97-10, 7 workers: 72.5 -> 69.8 us per iteration.
-  bool walked = false, all = true;
-  int64_t folded = 0;            // weights of the largest layer whose average is worth walking for
-  double most_us = 0.0;
-  for (const Layer& L : m->layers) {
-    if (!agg) break;
-    GemmArgs g = {};
-    g.mode = MODE_WGRAD; g.M = L.n_out; g.N = L.n_in; g.ldcf = L.n_out;
-    const bool mine = L.kind == DYNB_LAYER_DENSE &&
-                      (dt == DYNB_F32 || (gemm_small_applies(g) && wgrad_small_pays(g, s1, true)));
-    if (!mine) {
-      all = all && !L.has_params && L.kind != DYNB_LAYER_BN;
-      continue;
+  // (Per launch: a ninth layer, alone in a second one, walks beside nothing.  767-932-9-14-557-55-46-45-8-17, 32 workers,
+  // decided for all layers together: weight gradients 61 -> 90 us.)
+  std::vector<char> folds(nL, 0);
+  if (agg) {
+    size_t launch[WGRAD_F32_ITEMS];
+    int n = 0;
+    bool only = true, walked = false;   // only: no parameters outside the grouped launches
+    int64_t folded = 0;                 // weights of the largest layer whose average is worth walking for
+    double most_us = 0.0, total_us = 0.0;
+    auto decide = [&]() {
+      for (int i = 0; i < n; ++i) {
+        const Layer& L = m->layers[launch[i]];
+        folds[launch[i]] = walked || (int64_t)L.n_in * L.n_out <= folded;
+      }
+      total_us += most_us;
+      n = 0; walked = false; folded = 0; most_us = 0.0;
+    };
+    for (size_t i = 0; i < nL; ++i) {
+      const size_t l = dt == DYNB_F32 ? i : nL - 1 - i;   // (as the layers join the launches)
+      const Layer& L = m->layers[l];
+      GemmArgs g = {};
+      g.mode = MODE_WGRAD; g.M = L.n_out; g.N = L.n_in; g.ldcf = L.n_out;
+      if (L.kind != DYNB_LAYER_DENSE || (dt != DYNB_F32 && !(gemm_small_applies(g) && wgrad_small_pays(g, s1, true)))) {
+        only = only && !L.has_params && L.kind != DYNB_LAYER_BN;
+        continue;
+      }
+      if (n == WGRAD_F32_ITEMS) decide();
+      launch[n++] = l;
+      const int64_t nw = (int64_t)L.n_in * L.n_out;
+      const double us = dt == DYNB_F32 ? wgrad_f32_fold_us(g, s1) : wgrad_small_fold_us(g, s1);
+      walked = walked || (dt == DYNB_F32 ? wgrad_f32_walks(g, s1) : wgrad_small_walks(g, s1));
+      if (us <= average_pass_us(nw, K) && nw > folded) folded = nw;
+      most_us = us > most_us ? us : most_us;
     }
-    const int64_t nw = (int64_t)L.n_in * L.n_out;
-    const double us = dt == DYNB_F32 ? wgrad_f32_fold_us(g, s1) : wgrad_small_fold_us(g, s1);
-    walked = walked || (dt == DYNB_F32 ? wgrad_f32_walks(g, s1) : wgrad_small_walks(g, s1));
-    if (us <= average_pass_us(nw, K) && nw > folded) folded = nw;
-    most_us = us > most_us ? us : most_us;
+    decide();
+    if (only && total_us <= 4.0) folds.assign(nL, 1);
   }
-  walked = walked || (all && most_us <= 4.0);
   auto flush_small = [&]() {
     const int g = flush_group();   // (whose results are read here)
     if (g) return g;
@@ -579,7 +596,7 @@ int run_forward_backward(dynb_model* m, const float* x, const int32_t* y, const 
     const bool grouped = dt == DYNB_F32 || (split <= 1 && small);
     // the aggregate of this weight: in the same kernel while the per-worker tiles are in
     // registers where the launch shape allows it and it pays, else by a pass over what was written
-    const bool fold = agg && (grouped ? walked || (int64_t)L.wg_rows * L.n_out <= folded : gemm_fuses_aggregate(dt, g));
+    const bool fold = agg && (grouped ? (bool)folds[l] : gemm_fuses_aggregate(dt, g));
     if (fold) {
       g.alg_bytes += (double)L.wg_rows * L.n_out * 4;   // the aggregated tile is written too
       g.agg = agg + L.w_off;
