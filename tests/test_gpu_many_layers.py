@@ -1,5 +1,6 @@
 """Dense models of more layers than one launch takes: which weight gradients form their average is decided launch by
-launch, the aggregate is the weighted sum of the workers' gradients either way."""
+launch, the aggregate is the weighted sum of the workers' gradients either way; and the static call of as many layers as
+its preparation takes in one launch, all of their tensors padded."""
 import numpy as np
 import pytest
 
@@ -35,3 +36,31 @@ def test_aggregate_of_more_layers_than_a_launch_takes(dims, dtype, K, B, finaliz
     assert not got[run.P:].any()
     if finalizes is not None:
         assert (launches > 0) == finalizes
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("dims,b", [
+    ([10, 7, 5, 8, 17], [6, 0, 5, 4]),
+    ([33, 65, 1, 70, 9, 130, 66, 3, 5], [40, 1, 37]),       # eight layers, four padded tensors each
+    ([1, 1], [3]),
+    ([64, 64, 64], [7, 2]),                                 # nothing to pad but the batch
+])
+def test_static_call_pads_every_tensor(dims, b, dtype):
+    import torch
+    # scratch full of another model's finite and infinite values
+    other = binding.Model(synth.mlp_spec([200, 130, 90], dtype))
+    n = other.padded_params()
+    p = torch.full((n,), 3e38, device="cuda")
+    binding.forward_backward_static(other, p, torch.full((64, 200), 3e38, device="cuda"),
+                                    torch.zeros(64, dtype=torch.int32, device="cuda"), [64],
+                                    torch.empty(1, n, device="cuda"))
+    spec = synth.mlp_spec(dims, dtype)
+    params = synth.init_params(spec, "he", 7)
+    x, y = synth.make_batch(spec, "normal", sum(b), 8, 0)
+    run = DeviceRun(spec, params, sum(b), len(b))
+    want = run.forward_backward(x, y, b).clone()
+    got = torch.full_like(want, float("nan"))
+    binding.forward_backward_static(run.model, run.params, torch.from_numpy(np.ascontiguousarray(x, np.float32)).cuda(),
+                                    torch.from_numpy(np.ascontiguousarray(y, np.int32)).cuda(), b, got)
+    torch.cuda.synchronize()
+    assert torch.equal(got[:, :run.P], want[:, :run.P])
