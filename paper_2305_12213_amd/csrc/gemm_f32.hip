@@ -34,6 +34,13 @@ namespace {
 // One launch serves every layer of a model (a launch is bound by the chain of a wave, hardly by any
 // rate, so the waves of one layer hide those of another; 785-301-97-10: 19 + 17 + 17 us for the three
 // layers one after the other -> 25 together, 3072-512-512-10: 24 + 10 + 9 -> 36).
+// What stretches that chain is not the memory (rings twice as deep: the same) but what a wave that has its SIMD
+// for itself issues between the matrix instructions: a vector instruction as in gemm_f32_product.h, and a taken
+// branch some 60 clocks.  So a step has one vector instruction and no branch that is taken: operands are buffers
+// that end with the worker's rows, so that no lane compares and selects; the tiles that sum the bias
+// gradient are a variant of their own; and what ends a worker stands behind the loop over its blocks, once.  134
+// tiles, 785 rows of one worker: 380 -> 250 clocks per 16 rows.  785-301-97-10, 7 workers, all layers: 24.6 -> 18 us;
+// 3072-512-512-10, 4 workers (2 x 2 tiles, 30 MB of results): 28.7 -> 21.5.
 struct WgradItem {
   const void* A; const void* B;            // dy, x
   int64_t lda, ldb, ldcf;
@@ -59,65 +66,64 @@ constexpr uint32_t WGRAD_RING = 20 * KB;
 template <int R>
 __device__ inline int swizzle(int r) { return R == 1 ? 0 : 4 * ((r >> 1) & 1); }
 
-template <int R>
-__device__ __forceinline__ void wgrad_f32_tile(const WgradItem& p, const WgradGroup& grp, const Segs& segs,
-                                               uint32_t block, uint4* ring_area) {
+template <int R, bool BIAS>
+__device__ __forceinline__ void wgrad_f32_tile(const WgradItem& item, const WgradGroup& grp, const Segs& segs,
+                                               int part, int ti, int tj, uint4* ring_area) {
   constexpr int NB = R == 1 ? 10 : 5, S = 16 * R, C = 2 * R;   // copies per block: R of dy, R of x
   constexpr uint32_t SLOT = C * KB;
   static_assert(NB * SLOT == WGRAD_RING, "ring");
-  const int part = (int)block / p.tiles;
-  int ti, tj;
-  tile_of_block((int)block - part * p.tiles, (p.M + S - 1) / S, (p.N + S - 1) / S, ti, tj);
+  const WgradItem p = item;
   const int lane = threadIdx.x, l15 = lane & 15, kg = lane >> 4;
   const int i0 = ti * S, j0 = tj * S;
   const int g0 = part * p.per, g1 = min(g0 + p.per, segs.K);
   const uint32_t lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)&ring_area[0];
-  const bool bias = j0 == 0;
 
-  // position in the list of (worker, block); every worker has at least one block, so that an idle
-  // worker's zeros are written like any other result
-  // (the workers' first rows and weights sit in a register, one worker per lane: a scalar load
-  // would make every wait for the operand fetches wait for it too)
-  const int offv = segs.off[lane], total = segs.off[segs.K];
+  // Every worker has at least one block, so that an idle worker's zeros are written like any other result.
+  // (The workers' row counts and weights sit in a register, one worker per lane: a scalar load
+  // would make every wait for the operand fetches wait for it too.)
+  const int rowsv = segs.off[lane + 1] - segs.off[lane];
   const float lamv = grp.lam[lane];
-  struct Pos { int g, r, end; };           // worker, first row of the block, end of the worker's rows
-  auto enter = [&](Pos& c) {
-    const int g = c.g < g1 ? c.g : g1 - 1;
-    c.end = g + 1 < segs.K ? __builtin_amdgcn_readlane(offv, g + 1) : total;
-    c.r = c.g < g1 ? __builtin_amdgcn_readlane(offv, g) : c.end;
-  };
-  auto next = [&](Pos& c) {                // true: another worker
-    c.r += 16;
-    if (c.r < c.end || c.g >= g1) return false;
-    ++c.g;
-    enter(c);
-    return true;
-  };
-  // copy c < R: rows (16 / R) c .. of dy, else of x.  This lane's row of a copy and its 16 bytes of
-  // the next block (16 R features from a multiple of 16 R on lie within the row pitch)
+  auto rows_of = [&](int g) { return __builtin_amdgcn_readlane(rowsv, g); };
+  // copy c < R: rows (16 / R) c .. of dy, else of x.  This lane's 16 bytes of a block, from the block's first
+  // row (16 R features from a multiple of 16 R on lie within the row pitch).  Each operand is a buffer that begins
+  // there and ends with the worker's rows, or the block: what lies behind reads as zeros.
   constexpr int LPR = 4 * R;               // lanes per row
   const int lrow = lane / LPR;
-  const char* src[C];
-  const int64_t pitch[2] = {p.lda * 4, p.ldb * 4};
-  const int64_t row0 = segs.off[g0];
+  const uint32_t pitch[2] = {(uint32_t)p.lda * 4, (uint32_t)p.ldb * 4};   // (16 rows below 2^31 bytes: see launch_wgrad_f32())
+  uint64_t base[2] = {(uint64_t)(uintptr_t)((const float*)p.A + segs.off[g0] * p.lda + i0),
+                      (uint64_t)(uintptr_t)((const float*)p.B + segs.off[g0] * p.ldb + j0)};
+  uint32_t off[C];
 #pragma unroll
   for (int c = 0; c < C; ++c) {
-    const int64_t row = row0 + lrow + (16 / R) * (c % R);
-    const int r = (int)(row - row0), g = (lane & (LPR - 1)) ^ swizzle<R>(r);
-    src[c] = c < R ? (const char*)((const float*)p.A + row * p.lda + i0 + 4 * g)
-                   : (const char*)((const float*)p.B + row * p.ldb + j0 + 4 * g);
+    const int row = lrow + (16 / R) * (c % R), g = (lane & (LPR - 1)) ^ swizzle<R>(row);
+    off[c] = row * pitch[c / R] + 16 * g;
   }
-  auto issue_one = [&](uint32_t slot, const Pos& q, int c) {
-    // (rows past the worker's last, and blocks past the last worker, are zeros)
-    const bool ok = q.r + lrow + (16 / R) * (c % R) < q.end;
-    async_copy_1k(ok ? (const void*)src[c] : grp.zeros, lds + slot + c * KB);
-  };
-  auto advance = [&](Pos& q) {
-    const int row = q.r;
-    next(q);
-    const int rows = q.r - row;            // 16, or what the worker had left
+  // Copies the next block; rows past the worker's last, and blocks past the last worker, are zeros.
+  int copied = g0, to_copy = segs.off[g0 + 1] - segs.off[g0];   // worker, its rows from this block on
+  const int first_rows = to_copy;
+  auto issue = [&](uint32_t slot) {
+    const uint32_t rows = to_copy < 16 ? to_copy : 16;
 #pragma unroll
-    for (int c = 0; c < C; ++c) src[c] += rows * pitch[c / R];
+    for (int o = 0; o < 2; ++o) {
+      const i32x4 r = {(int)(uint32_t)base[o], (int)(uint32_t)(base[o] >> 32), (int)(rows * pitch[o]), BUFFER_32BIT};
+#pragma unroll
+      for (int c = 0; c < R; ++c) async_copy_1k_buffer(r, off[o * R + c], lds + slot + (o * R + c) * KB);
+      base[o] += rows * pitch[o];
+    }
+    to_copy -= 16;
+    if (__builtin_expect(to_copy <= 0, 0)) to_copy = ++copied < g1 ? rows_of(copied) : 0;
+  };
+  // (the first block by address, with the zero granule behind the rows)
+  auto issue_first = [&]() {
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+      async_copy_1k(lrow + (16 / R) * (c % R) < to_copy ? (const void*)(uintptr_t)(base[c / R] + off[c]) : grp.zeros,
+                    lds + c * KB);
+    const uint32_t rows = to_copy < 16 ? to_copy : 16;
+    base[0] += rows * pitch[0];
+    base[1] += rows * pitch[1];
+    to_copy -= 16;
+    if (to_copy <= 0) to_copy = ++copied < g1 ? rows_of(copied) : 0;
   };
   float f[2][C][4];                        // [register set][16 features of dy / x][matrix instruction]
   const char* const ring = (const char*)&ring_area[0];
@@ -142,36 +148,24 @@ __device__ __forceinline__ void wgrad_f32_tile(const WgradItem& p, const WgradGr
     for (int w = 0; w < R; ++w) acc[u][w] = agg[u][w] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
   // accumulator element v of a lane: row (x feature) 4 * kg + v, column (dy feature) l15
+  const bool in_row = i0 + l15 < p.M, in_row2 = i0 + 16 + l15 < p.M;
   auto store = [&](float* out, const f32x4 (&v)[R][R]) {
 #pragma unroll
     for (int u = 0; u < R; ++u)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const int j = j0 + 16 * u + 4 * kg + e;
-        if (j >= p.N) continue;
-#pragma unroll
-        for (int w = 0; w < R; ++w) {
-          const int i = i0 + 16 * w + l15;
-          if (i < p.M) out[(int64_t)j * p.ldcf + i] = v[u][w][e];
+        const int j = 16 * u + 4 * kg + e;
+        const uint32_t o = (uint32_t)j * (uint32_t)p.ldcf + l15;
+        if (j0 + j < p.N) {
+          if (in_row) out[o] = v[u][0][e];
+          if (R > 1 && in_row2) out[o + 16] = v[u][R - 1][e];
         }
       }
   };
 
-  int todo = 0;                            // blocks of these workers
-  for (int k = g0; k < g1; ++k) {
-    const int n = segs.off[k + 1] - segs.off[k];
-    todo += n > 0 ? (n + 15) / 16 : 1;
-  }
-  Pos cc, ic;                              // block being computed, next block to copy
-  cc.g = g0;
-  enter(cc);
-  ic = cc;
-#pragma unroll
-  for (int s = 0; s < NB; ++s) {
-#pragma unroll
-    for (int c = 0; c < C; ++c) issue_one(s * SLOT, ic, c);
-    advance(ic);
-  }
+  issue_first();
+#pragma unroll 1
+  for (uint32_t s = SLOT; s < NB * SLOT; s += SLOT) issue(s);
   wait_pending<(NB - 1) * C>();
 #pragma unroll
   for (int t = 0; t < 4; ++t) fetch_one(0, 0, t);
@@ -188,28 +182,45 @@ __device__ __forceinline__ void wgrad_f32_tile(const WgradItem& p, const WgradGr
 #pragma unroll
         for (int u = 0; u < R; ++u)
           acc[u][w] = __builtin_amdgcn_mfma_f32_16x16x4f32(f[set][R + u][t], f[set][w][t], acc[u][w], 0, 0, 0);
-      if (bias) {
-#pragma unroll
-        for (int w = 0; w < R; ++w) bsum[w] += f[set][w][t];
-      }
       __builtin_amdgcn_sched_barrier(0);
       if (t == 0) wait_reads();            // (of `slot`, before it is copied into)
       if (t < 2) {
         fetch_one(set ^ 1, ahead, 2 * t);
         fetch_one(set ^ 1, ahead, 2 * t + 1);
-      } else {
-#pragma unroll
-        for (int c = (t - 2) * C / 2; c < (t - 1) * C / 2; ++c) issue_one(slot, ic, c);
+      } else if (t == 2) {
+        issue(slot);
       }
       __builtin_amdgcn_sched_barrier(0);
     }
-    advance(ic);
+    if (BIAS) {
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int w = 0; w < R; ++w) bsum[w] += f[set][w][t];
+    }
     slot = ahead;
-    const int g = cc.g;
-    if (!next(cc)) return;
+  };
+  int g = g0, left = first_rows;
+  float* out = p.Cf + (int64_t)g0 * grp.group_stride + (int64_t)j0 * p.ldcf + i0;
+#pragma unroll 1
+  for (;;) {
+#pragma unroll 1
+    for (;;) {
+      step(0);
+      left -= 16;
+      if (left <= 0) {                     // (an odd number of blocks: the next one's operands into the first set)
+        wait_reads();
+#pragma unroll
+        for (int t = 0; t < 4; ++t) fetch_one(0, slot, t);
+        break;
+      }
+      step(1);
+      left -= 16;
+      if (left <= 0) break;
+    }
     // ---- end of worker g ----
     const float lam = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(lamv), g));
-    store(p.Cf + (int64_t)g * grp.group_stride, acc);
+    store(out, acc);
 #pragma unroll
     for (int u = 0; u < R; ++u)
 #pragma unroll
@@ -217,7 +228,7 @@ __device__ __forceinline__ void wgrad_f32_tile(const WgradItem& p, const WgradGr
         agg[u][w] += lam * acc[u][w];
         acc[u][w] = f32x4{0.f, 0.f, 0.f, 0.f};
       }
-    if (bias) {
+    if (BIAS) {
 #pragma unroll
       for (int w = 0; w < R; ++w) {
         float v = bsum[w];
@@ -229,16 +240,14 @@ __device__ __forceinline__ void wgrad_f32_tile(const WgradItem& p, const WgradGr
         if (kg == 0 && i < p.M) p.bias_grad[(int64_t)g * grp.group_stride + i] = v;
       }
     }
-  };
-#pragma unroll 1
-  for (int n = 0; n < todo; n += 2) {
-    step(0);
-    step(1);
+    if (++g >= g1) break;
+    left = rows_of(g);
+    out += grp.group_stride;
   }
   wait_pending<0>();                       // (no copy may land after the LDS has been given back)
   if (!p.agg) return;
-  store(p.agg, agg);
-  if (bias && kg == 0) {
+  store(p.agg + (int64_t)j0 * p.ldcf + i0, agg);
+  if (BIAS && kg == 0) {
 #pragma unroll
     for (int w = 0; w < R; ++w)
       if (i0 + 16 * w + l15 < p.M) p.bias_agg[i0 + 16 * w + l15] = bagg[w];
@@ -255,8 +264,13 @@ __global__ __launch_bounds__(64) void wgrad_f32_kernel(WgradGroup grp, Segs segs
   int q = 0;
   while (q + 1 < grp.n && block >= grp.item[q + 1].first) ++q;
   const WgradItem& p = grp.item[q];
-  if (p.wide) wgrad_f32_tile<2>(p, grp, segs, block - p.first, ring_area);
-  else wgrad_f32_tile<1>(p, grp, segs, block - p.first, ring_area);
+  const int S = p.wide ? 32 : 16, part = (block - p.first) / p.tiles;
+  int ti, tj;
+  tile_of_block(block - p.first - part * p.tiles, (p.M + S - 1) / S, (p.N + S - 1) / S, ti, tj);
+  if (p.wide && tj == 0) wgrad_f32_tile<2, true>(p, grp, segs, part, ti, tj, ring_area);
+  else if (p.wide) wgrad_f32_tile<2, false>(p, grp, segs, part, ti, tj, ring_area);
+  else if (tj == 0) wgrad_f32_tile<1, true>(p, grp, segs, part, ti, tj, ring_area);
+  else wgrad_f32_tile<1, false>(p, grp, segs, part, ti, tj, ring_area);
 }
 
 template <int R>
@@ -300,13 +314,19 @@ double wgrad_f32_fold_us(const GemmArgs& a, const Segs& s) {
   return fold_us(0.7 * s.K + 0.0036 * s.off[s.K], (s.K + per - 1) / per, (int64_t)a.M * a.N, s.K);
 }
 
+// Single tiles keep the byte offset of a lane from their first row in 32 bits.
+static int product_side(const GemmArgs& a) {
+  const int64_t pitch = a.lda > a.ldb ? a.lda : a.ldb;
+  return 16 * 4 * pitch < (int64_t)1 << 32 ? tile_side(a) : 32;
+}
+
 // (a tile holds whole rows)
-bool gemm_f32_head_applies(const GemmArgs& a) { return a.mode == MODE_FWD && a.N <= 16 && tile_side(a) == 16; }
+bool gemm_f32_head_applies(const GemmArgs& a) { return a.mode == MODE_FWD && a.N <= 16 && product_side(a) == 16; }
 
 int launch_gemm_f32(const GemmArgs& a, const HeadArgs* head, void* stream) {
-  if (a.mode == MODE_WGRAD || a.K % 32 != 0)
-    return fail(DYNB_ERR_BADARG, "gemm: fp32 products take whole 32-deep blocks");
-  const int side = tile_side(a);
+  if (a.mode == MODE_WGRAD || a.K % 64 != 0)
+    return fail(DYNB_ERR_BADARG, "gemm: fp32 products take whole pairs of 32-deep blocks");
+  const int side = product_side(a);
   const int64_t n = tiles_with(a, side);
   if (n >= (int64_t)1 << 31) return fail(DYNB_ERR_UNSUPPORTED, "gemm: too many tiles for one launch");
   if (head) {
@@ -337,6 +357,9 @@ int launch_wgrad_f32(const GemmArgs* a, int n, const Segs& s, const StepEnd* end
     // (a wave that folds the average in walks all workers: then the tiles alone have to fill the chip,
     // those of all layers together -- three of 512 x 512, 1024 rows: 43 us, and 53 with 2 x 2 tiles)
     const int side = g.agg && wide < 1024 ? 16 : wgrad_side(g, s);
+    // (offsets within a block, and within a tile of the result, are 32-bit)
+    if (16 * 4 * (g.lda > g.ldb ? g.lda : g.ldb) >= (int64_t)1 << 31 || 32 * 4 * g.ldcf >= (int64_t)1 << 31)
+      return fail(DYNB_ERR_UNSUPPORTED, "gemm: rows too long for a weight gradient");
     const int64_t tiles = tiles_with(g, side);
     const int per = g.agg ? s.K : workers_per_wave(g, s.K, side);
     if (blocks + tiles * ((s.K + per - 1) / per) >= (int64_t)1 << 31)

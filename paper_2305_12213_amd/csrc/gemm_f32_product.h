@@ -39,12 +39,17 @@ __device__ inline void wait_reads() {
 // block is 32 reduction indices, the whole 128-byte line of each operand row (half a line per block
 // fetches every line twice: 19 instead of 11 us at 785 x 301 x 832): two copies of 8 rows per 16 rows.  Granule e
 // (16 bytes) of row r sits at slot e ^ (r / 2 % 8), so that matrix instruction e, which reads index
-// 4e + kg of 16 rows, finds 64 different banks.  A wave issues in order and the next matrix
-// instruction of a chain waits for the last, so fetches (in a step's first half) and copies (in its
-// second) are placed between them, in their 32-clock shadows.
-// Against 64 x 64 vector-unit tiles: 256 x 512 x 3072 165 -> 25 us, 785 x 301 x 832 49 -> 9.5.  What bounds it is one
-// wave's chain, whatever the number of tiles: 16 x 16 x 3072, a single wave, takes 24.8 us, and from 768 to 12288
-// reduction indices every further matrix instruction 28.5 ns, half of it its own 33 clocks, half what is issued with it.
+// 4e + kg of 16 rows, finds 64 different banks.
+// What bounds it is one wave's chain, whatever the number of tiles: each matrix instruction adds to the last one's
+// result, 33 clocks apart.  Scalar instructions, two LDS reads or two copies between two of them are free; one vector
+// instruction in between costs 16 clocks, every further one 4 (the result is no longer handed on inside the matrix
+// pipe), and more reads or copies cost as much.  So the loop of single tiles has no vector
+// instruction at all: the ring is unrolled, its slots are constants in the reads, and the copies' addresses are a
+// fixed offset per lane and a scalar base that moves on.  A step of 8 matrix instructions: 548 -> 285 clocks;
+// 256 x 512 x 3072 27.4 -> 17 us, 785 x 301 x 832 (where four waves of a compute unit ask for
+// more copies than it takes, 23 clocks each) 13.1 -> 8.3.  (The four chains of 2 x 2 tiles have vector
+// instructions between them for nothing; there, two steps in a rolled loop.)
+// Against 64 x 64 vector-unit tiles: 256 x 512 x 3072 165 us, 785 x 301 x 832 49.
 // With HeadArgs (forward, at most 16 columns) the tile's rows of logits go through the softmax and the loss in
 // LDS instead of to memory.
 template <int MODE, int R, typename Head>
@@ -62,21 +67,33 @@ __global__ __launch_bounds__(64) void gemm_f32_kernel(GemmArgs p, Head head) {
   const int i0 = ti * S, j0 = tj * S;
   const uint32_t lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)&ring_area[0];
   // copy 2g + h: rows 8h .. 8h+7 of group g (g < R: A rows, else B rows); this lane's 16 bytes of
-  // the next block (rows past the edge repeat the last one; their products are not stored)
+  // the next block, from the tile's first row of the operand (rows past the edge repeat the last one;
+  // their products are not stored)
+  const char* base[2] = {(const char*)((const float*)p.A + (int64_t)i0 * p.lda),
+                         (const char*)((const float*)p.B + (int64_t)j0 * p.ldb)};
   const char* src[C];
+  uint32_t off[C];
 #pragma unroll
   for (int c = 0; c < C; ++c) {
     const int g = c >> 1, r = 8 * (c & 1) + (lane >> 3), e = (lane & 7) ^ ((r >> 1) & 7);
-    const int i = i0 + 16 * g + r, j = j0 + 16 * (g - R) + r;
-    src[c] = g < R ? (const char*)((const float*)p.A + (int64_t)(i < p.M ? i : p.M - 1) * p.lda + 4 * e)
-                   : (const char*)((const float*)p.B + (int64_t)(j < p.N ? j : p.N - 1) * p.ldb + 4 * e);
+    const int i = 16 * g + r, j = 16 * (g - R) + r;
+    const int64_t o = g < R ? (i0 + i < p.M ? i : p.M - 1 - i0) * p.lda : (j0 + j < p.N ? j : p.N - 1 - j0) * p.ldb;
+    src[c] = base[c / (2 * R)] + (o + 4 * e) * 4;
+    off[c] = (uint32_t)(o + 4 * e) * 4;    // (single tiles: fits, see product_side())
   }
   const int blocks = p.K / 32;
   uint32_t ahead = 0;                      // byte offset the next block is copied from; past the end
                                            // the last block is copied again, never used
-  auto issue_one = [&](uint32_t slot, int c) { async_copy_1k(src[c] + ahead, lds + slot + c * KB); };
+  auto issue_one = [&](uint32_t slot, int c) {
+    if constexpr (R == 1) async_copy_1k_from(base[c / 2], off[c], lds + slot + c * KB);
+    else async_copy_1k(src[c] + ahead, lds + slot + c * KB);
+  };
   int issued = 0;
-  auto advance = [&]() { if (++issued < blocks) ahead += 128; };
+  auto advance = [&]() {
+    const uint32_t by = ++issued < blocks ? 128 : 0;
+    if constexpr (R == 1) { base[0] += by; base[1] += by; }
+    else ahead += by;
+  };
   uint32_t at[8];                          // this lane's element of granule e of a row group
 #pragma unroll
   for (int e = 0; e < 8; ++e) at[e] = (uint32_t)(l15 * 128 + ((e ^ ((l15 >> 1) & 7)) * 16) + 4 * kg);
@@ -108,11 +125,7 @@ __global__ __launch_bounds__(64) void gemm_f32_kernel(GemmArgs p, Head head) {
   // Step: block c's operands are in registers, or on their way there since the first half of the last
   // step; those of block c + 1 have landed once at most the NB - 2 blocks behind it are pending; block
   // c's slot, whose reads are waited for before this step's own begin, takes block c + NB.
-  // (Two steps unrolled, not the ring: such launches are so short that fetching a long loop body
-  // for the first time shows.)
-  uint32_t slot = 0;
-  auto step = [&](int set) {
-    const uint32_t next = slot + SLOT == NB * SLOT ? 0 : slot + SLOT;
+  auto step = [&](int set, uint32_t slot, uint32_t next) {
     wait_pending<(NB - 2) * C>();
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
@@ -126,21 +139,42 @@ __global__ __launch_bounds__(64) void gemm_f32_kernel(GemmArgs p, Head head) {
       if (e < 4) {
         fetch_one(set ^ 1, next, 2 * e);
         fetch_one(set ^ 1, next, 2 * e + 1);
-      } else {
+      } else if (R > 1 || e < 6) {
+        constexpr int PER = R == 1 ? 2 : C / 4;
 #pragma unroll
-        for (int c = (e - 4) * C / 4; c < (e - 3) * C / 4; ++c) issue_one(slot, c);
+        for (int c = (e - 4) * PER; c < (e - 3) * PER; ++c) issue_one(slot, c);
       }
       __builtin_amdgcn_sched_barrier(0);
     }
     advance();
-    slot = next;
   };
+  if constexpr (R == 1) {
+    static_assert(NB % 2 == 0, "register sets");
 #pragma unroll 1
-  for (int c = 0; c + 1 < blocks; c += 2) {
-    step(0);
-    step(1);
+    for (int c = 0; c < blocks;) {         // (an even number, see launch_gemm_f32())
+#pragma unroll
+      for (int s = 0; s < NB; s += 2) {
+        step(0, s * SLOT, (s + 1) * SLOT);
+        step(1, (s + 1) * SLOT, (s + 2) % NB * SLOT);
+        c += 2;
+        if (c >= blocks) break;
+      }
+    }
+  } else {
+    // (two steps unrolled, not the ring: such launches are so short that fetching a long loop body
+    // for the first time shows)
+    uint32_t slot = 0;
+    auto rolled = [&](int set) {
+      const uint32_t next = slot + SLOT == NB * SLOT ? 0 : slot + SLOT;
+      step(set, slot, next);
+      slot = next;
+    };
+#pragma unroll 1
+    for (int c = 0; c < blocks; c += 2) {
+      rolled(0);
+      rolled(1);
+    }
   }
-  if (blocks & 1) step(0);
   wait_pending<0>();                       // (no copy may land after the LDS has been given back)
 
   // accumulator element v of a lane: row 4 * kg + v, column l15
