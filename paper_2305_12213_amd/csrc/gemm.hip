@@ -9,17 +9,14 @@
 #include <type_traits>
 
 #include "dynb_internal.h"
+#include "gemm_epilogue.h"
 #include "lds_async.h"
 #include "tile_map.h"
 
 namespace dynb {
 namespace {
 
-typedef __bf16 bf16;
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // ------------------------------------------------------------------------------------
 // bf16 MFMA kernel
@@ -62,8 +59,7 @@ __device__ inline void wait_copies(int stages) {
   }
 }
 
-// LDS patch area of the weight-gradient epilogue; other modes declare nothing (the 256 x 256
-// forward kernel uses all 160 KB for its stage ring).
+// LDS patch area of the weight-gradient epilogue; other modes declare nothing.
 template <int N>
 struct PatchArea {
   static __device__ float* get() {
@@ -92,7 +88,8 @@ struct PatchArea<0> {
 template <int BM, int BN, int WM, int WN, int MODE, bool GATHER, int S, bool AGG = false, bool PAR = false>
 __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmArgs p, Segs segs) {
   constexpr bool RM = MODE == MODE_WGRAD;
-  constexpr bool WEAVE = !GATHER;   // copies placed between the MFMAs (see the stage pipeline)
+  constexpr bool WEAVE = RM;        // copies placed between the MFMAs (see the stage pipeline)
+  static_assert(RM || GATHER, "products of plain operands: gemm_lines.hip");
   static_assert(!AGG || MODE == MODE_WGRAD, "aggregation belongs to the weight gradient");
   static_assert(!PAR || (GATHER && MODE == MODE_DGRAD), "parity classes belong to the gathered input gradient");
   static_assert(!RM || (!GATHER && (BM == 256 || BM == 128) && (BN == 256 || BN == 128)),
@@ -220,8 +217,6 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmArgs p, Seg
         const int sy = fwd ? py + dy_ : py - dy_, sx = fwd ? px + dx_ : px - dx_;
         if (sy >= 0 && sy < p.src_h && sx >= 0 && sx < p.src_w) gok[u] |= 1u << tap;
       }
-    } else {
-      offA[u] = (uint32_t)(((int64_t)i * p.lda + lgran * 8) * 2);
     }
   }
 #pragma unroll
@@ -262,50 +257,33 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmArgs p, Seg
   // for every outstanding LDS fragment fetch (they share a counter) -- twice per stage.
   uint32_t pitchA = (uint32_t)(p.lda * 2), pitchB = (uint32_t)(p.ldb * 2);
   asm volatile("" : "+s"(pitchA), "+s"(pitchB));
-  // Buffer resources of the two operands (plain and row-major operands; the gathered operand
-  // keeps 64-bit addresses).  Plain operands: the whole matrix.  Row-major: the size is set per
-  // copy to the end of the worker's rows.
+  // Buffer resources of the two operands of a weight gradient; the size is set per copy to the end of the
+  // worker's rows.  (The gathered operand keeps 64-bit addresses.)
   i32x4 rsA = {0, 0, 0, 0}, rsB = {0, 0, 0, 0};
-  if constexpr (!GATHER) {
-    rsA = buffer_resource(p.A, RM ? 0u : (uint32_t)((int64_t)p.M * p.lda * 2));
-    rsB = buffer_resource(p.B, RM ? 0u : (uint32_t)((int64_t)p.N * p.ldb * 2));
+  if constexpr (RM) {
+    rsA = buffer_resource(p.A, 0u);
+    rsB = buffer_resource(p.B, 0u);
   }
-  // One copy of a stage (plain or row-major operands): idx < LA is copy idx of the A operand,
+  // One copy of a weight gradient's stage: idx < LA is copy idx of the A operand,
   // else copy idx - LA of the B operand.  The hot loop places these between the MFMAs.
   auto copy_one = [&](int buf, const StageCursor& c, int idx) {
     const int k0 = c.kt * BK;
     const bool isA = idx < LA;
     const int u = isA ? idx : idx - LA;
-    const void* src;
-    if constexpr (RM) {
-      // through a buffer resource that ends with the worker's last row: lanes on rows past it
-      // (the last, partly filled stage; every lane once the workgroup is past its last stage)
-      // and lanes past the row pitch read zeros by the hardware's range check
-      const uint32_t pitch = isA ? pitchA : pitchB;
-      i32x4 rs = isA ? rsA : rsB;
-      rs[2] = (int)((uint32_t)(c.col0 + c.depth) * pitch);
-      const uint32_t dst = isA ? ldsA + (uint32_t)((buf * BM * GPR + (wave + NW * u) * 64) * 16)
-                               : ldsB + (uint32_t)((buf * BN * GPR + (wave + NW * u) * 64) * 16);
-      async_copy_1k_buffer(rs, (isA ? roA[u] : roB[u]) + (uint32_t)(c.col0 + k0) * pitch, dst);
-      return;
-    } else if constexpr (!GATHER) {
-      // (a workgroup past its last stage keeps copying, see the stage loop: whatever such a
-      // copy reads -- the rows again from their start, zeros past the matrix -- is never used)
-      const uint32_t dst = isA ? ldsA + (uint32_t)((buf * BM * GPR + (wave + NW * u) * 64) * 16)
-                               : ldsB + (uint32_t)((buf * BN * GPR + (wave + NW * u) * 64) * 16);
-      async_copy_1k_buffer(isA ? rsA : rsB, (isA ? offA[u] : offB[u]) + (uint32_t)k0 * 2, dst);
-      return;
-    } else {
-      src = (const void*)((isA ? Ab + offA[u] : Bb + offB[u]) + (uint32_t)k0 * 2);
-    }
+    // through a buffer resource that ends with the worker's last row: lanes on rows past it
+    // (the last, partly filled stage; every lane once the workgroup is past its last stage)
+    // and lanes past the row pitch read zeros by the hardware's range check
+    const uint32_t pitch = isA ? pitchA : pitchB;
+    i32x4 rs = isA ? rsA : rsB;
+    rs[2] = (int)((uint32_t)(c.col0 + c.depth) * pitch);
     const uint32_t dst = isA ? ldsA + (uint32_t)((buf * BM * GPR + (wave + NW * u) * 64) * 16)
                              : ldsB + (uint32_t)((buf * BN * GPR + (wave + NW * u) * 64) * 16);
-    async_copy_1k(src, dst);
+    async_copy_1k_buffer(rs, (isA ? roA[RM ? u : 0] : roB[RM ? u : 0]) + (uint32_t)(c.col0 + k0) * pitch, dst);
   };
 
   // All copies of a stage at once (the prologue; every stage of the gathered-operand kernels).
   auto issue = [&](int buf, const StageCursor& c) {
-    if constexpr (!GATHER) {
+    if constexpr (RM) {
 #pragma unroll
       for (int idx = 0; idx < LA + LB; ++idx) copy_one(buf, c, idx);
       return;
@@ -685,9 +663,6 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmArgs p, Seg
     lfrag(sA[0], sB[0], 0, 0);
   }
   int buf = 0;
-  bool pend = false;            // second half of the previous refill still to be issued
-  int pbuf = 0;                 // ... into this buffer,
-  StageCursor pc = ic;          // ... of this stage
   while (cc.g < g_hi) {
     const int g = cc.g, nst = cc.nst;
     StageCursor ng;                // first stage of the next worker that has rows
@@ -703,42 +678,29 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmArgs p, Seg
         // behind a block of MFMAs would leave the matrix pipe idle for as long as they take to
         // issue, and the copies of all four waves would reach the memory pipeline in one burst.
         // They are placed *between* the MFMAs instead (32 clocks each).  First k-step: the
-        // fragments of the second k-step, then the second half of the copies that refill the
-        // buffer released by the previous stage.  Second k-step (behind the barrier that
+        // fragments of the second k-step.  Second k-step (behind the barrier that
         // releases this stage's buffer): the fragments of the next stage's first k-step (of a
-        // buffer nobody reads when this is the last stage), then the first half of the copies
-        // that refill this buffer.  While a stage is still to be issued, S - 1 stages are in
-        // flight beyond this one and the wait is a constant; the last S - 1 stages count down.
-        // (weight gradient: all copies of a refill in the second k-step -- the state that
+        // buffer nobody reads when this is the last stage), then the copies
+        // that refill this buffer; S - 1 stages are in flight beyond this one and the wait is a constant.
+        // (Halves of a refill in both k-steps: the state that
         // carries a half-issued refill into the next iteration costs more scalar instructions
-        // per stage than spreading three copies gains)
-        constexpr int NM = TM * TN, NF = TM + TN, NC = LA + LB, NC1 = RM ? NC : NC / 2;
-        constexpr int NI0 = NF + (NC - NC1), NI1 = NF + NC1;
+        // per stage than spreading three copies gains.)
+        constexpr int NM = TM * TN, NF = TM + TN, NC = LA + LB, NI1 = NF + NC;
 #pragma unroll
         for (int i = 0; i < NM; ++i) {
           mma_one(0, i);
           __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-          for (int it = i * NI0 / NM; it < (i + 1) * NI0 / NM; ++it) {
-            if (it < NF) {
-              frag_one(sA[buf], sB[buf], 1, 1, it);
-            } else if (pend) {
-              copy_one(pbuf, pc, NC1 + it - NF);
-            }
-          }
+          for (int it = i * NF / NM; it < (i + 1) * NF / NM; ++it) frag_one(sA[buf], sB[buf], 1, 1, it);
           __builtin_amdgcn_sched_barrier(0);
         }
         mma_sums(0);
         __builtin_amdgcn_sched_barrier(0);
-        // (past its last stage a workgroup keeps issuing copies -- weight gradient: a stage of
-        // depth 0, all zeros; otherwise the rows from their start again -- so that the number in
+        // (past its last stage a workgroup keeps issuing copies -- a stage of
+        // depth 0, all zeros -- so that the number in
         // flight, and with it this wait, is the same constant in every iteration and no branch
         // asks whether stages are left)
-        const bool issuing = true;   // (this path: plain and row-major operands)
-        if (issuing)
-          asm volatile("s_waitcnt vmcnt(%0)" ::"n"((S - 2) * NC) : "memory");
-        else
-          wait_copies<NC>(ahead > 0 ? ahead - 1 : 0);
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"((S - 2) * NC) : "memory");
         __syncthreads();
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -749,7 +711,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmArgs p, Seg
           for (int it = i * NI1 / NM; it < (i + 1) * NI1 / NM; ++it) {
             if (it < NF) {
               frag_one(sA[nbuf], sB[nbuf], 0, 0, it);
-            } else if (issuing) {
+            } else {
               copy_one(buf, ic, it - NF);
             }
           }
@@ -757,15 +719,8 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmArgs p, Seg
         }
         mma_sums(1);
         __builtin_amdgcn_sched_barrier(0);
-        pend = issuing;
-        pbuf = buf;
-        pc = ic;
-        if (issuing) {             // (one stage issued, one consumed: `ahead` stays S - 1)
-          ++ic.kt;
-          settle(ic);
-        } else {
-          --ahead;
-        }
+        ++ic.kt;                   // (one stage issued, one consumed)
+        settle(ic);
         buf = nbuf;
         continue;
       }
@@ -820,115 +775,10 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmArgs p, Seg
   if constexpr (AGG) store_tile(p.agg, agg);
 
   if constexpr (MODE != MODE_WGRAD) {
-    // Epilogue.  The stage ring is free now (every wave is past the last barrier and its last
-    // fragment fetch), so each wave passes its 128-column strip, 32 rows at a time, through a
-    // private fp32 patch in LDS: the accumulator layout (4 consecutive columns per lane, 32
-    // rows per instruction) becomes 8 consecutive columns per lane, 4 rows per instruction,
-    // and bias/ReLU/mask, the bf16 conversion and the global accesses run on whole 128-byte
-    // lines.
-    constexpr int CW = BN / WN;              // columns of a wave's strip
-    constexpr int EP = CW + 4;               // patch row pitch in floats
-    static_assert(CW == 128 || CW == 64, "strip width");
-    static_assert((size_t)NW * 32 * EP * 4 <= sizeof(sA), "patch must fit in the A ring");
-    float* patch = (float*)&sA[0][0] + wave * 32 * EP;
-    constexpr int LPR = CW / 8;              // lanes per row in the read-back phase
-    constexpr int RPI = 64 / LPR;            // rows per read-back instruction
-    const int rrow = lane / LPR, rcol = (lane % LPR) * 8;
-    const int jcol = j0 + wn * CW + rcol;    // first of the lane's 8 columns
-    const bool col_ok = jcol + 7 < p.N;
-    const bool bias_vec = (((uintptr_t)p.bias) & 15) == 0;   // a layer's bias may start anywhere
-    float bv[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    if (MODE == MODE_FWD && p.bias) {
-      if (col_ok && bias_vec) {
-        const float4 t0 = *(const float4*)&p.bias[jcol], t1 = *(const float4*)&p.bias[jcol + 4];
-        bv[0] = t0.x; bv[1] = t0.y; bv[2] = t0.z; bv[3] = t0.w;
-        bv[4] = t1.x; bv[5] = t1.y; bv[6] = t1.z; bv[7] = t1.w;
-      } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-          if (jcol + e < p.N) bv[e] = p.bias[jcol + e];
-      }
-    }
-#pragma unroll
-    for (int a = 0; a < TM; ++a) {
-      // input gradient: the mask and addend rows of this 32-row block are asked for now, all of
-      // them at once (rows past the matrix clamped), and travel while the accumulators pass
-      // through the patch -- fetched row by row where they are used, every row costs a trip to
-      // memory of its own
-      bf16x8 mkv[32 / RPI], adv[32 / RPI];
-      if (MODE == MODE_DGRAD && col_ok) {
-#pragma unroll
-        for (int t = 0; t < 32 / RPI; ++t) {
-          int i = i0 + wm * (BM / WM) + a * 32 + rrow + RPI * t;
-          i = row_of(i < M ? i : M - 1);
-          if (p.mask) mkv[t] = *(const bf16x8*)((const bf16*)p.mask + (int64_t)i * p.ldmask + jcol);
-          if (p.addend) adv[t] = *(const bf16x8*)((const bf16*)p.addend + (int64_t)i * p.ldadd + jcol);
-        }
-      }
-#pragma unroll
-      for (int b = 0; b < TN; ++b)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const f32x4 o = {acc[a][b][4 * q], acc[a][b][4 * q + 1], acc[a][b][4 * q + 2],
-                           acc[a][b][4 * q + 3]};
-          *(f32x4*)&patch[l31 * EP + b * 32 + 8 * q + hi4] = o;
-        }
-      __builtin_amdgcn_wave_barrier();
-#pragma unroll
-      for (int t = 0; t < 32 / RPI; ++t) {
-        const int r = rrow + RPI * t;
-        int i = i0 + wm * (BM / WM) + a * 32 + r;
-        const f32x4 lo = *(const f32x4*)&patch[r * EP + rcol];
-        const f32x4 hi = *(const f32x4*)&patch[r * EP + rcol + 4];
-        if (i >= M || jcol >= p.N) continue;
-        i = row_of(i);
-        float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-        if (MODE == MODE_FWD) {
-#pragma unroll
-          for (int e = 0; e < 8; ++e) v[e] += bv[e];
-          if (p.relu) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] = fmaxf(v[e], 0.f);
-          }
-        }
-        if (col_ok) {
-          if (MODE == MODE_DGRAD && p.addend) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] = (float)(bf16)v[e] + (float)adv[t][e];
-          }
-          if (MODE == MODE_DGRAD && p.mask) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-              if (!((float)mkv[t][e] > 0.f)) v[e] = 0.f;
-          }
-          if (MODE == MODE_FWD && p.Cf) {
-            float* dst = p.Cf + (int64_t)i * p.ldcf + jcol;
-            *(float4*)dst = make_float4(v[0], v[1], v[2], v[3]);
-            *(float4*)(dst + 4) = make_float4(v[4], v[5], v[6], v[7]);
-          }
-          if (p.C) {
-            const bf16x8 o = {(bf16)v[0], (bf16)v[1], (bf16)v[2], (bf16)v[3],
-                              (bf16)v[4], (bf16)v[5], (bf16)v[6], (bf16)v[7]};
-            *(bf16x8*)((bf16*)p.C + (int64_t)i * p.ldc + jcol) = o;
-          }
-        } else {
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const int j = jcol + e;
-            if (j >= p.N) continue;
-            float w = v[e];
-            if (MODE == MODE_DGRAD && p.addend)
-              w = (float)(bf16)w + (float)((const bf16*)p.addend)[(int64_t)i * p.ldadd + j];
-            if (MODE == MODE_DGRAD && p.mask &&
-                !((float)((const bf16*)p.mask)[(int64_t)i * p.ldmask + j] > 0.f))
-              w = 0.f;
-            if (MODE == MODE_FWD && p.Cf) p.Cf[(int64_t)i * p.ldcf + j] = w;
-            if (p.C) ((bf16*)p.C)[(int64_t)i * p.ldc + j] = (bf16)w;
-          }
-        }
-      }
-      __builtin_amdgcn_wave_barrier();
-    }
+    // (the stage ring is free now: every wave is past the last barrier and its last fragment fetch)
+    static_assert((size_t)NW * 32 * (BN / WN + 4) * 4 <= sizeof(sA), "patch must fit in the A ring");
+    store_product<MODE, TM, TN>(p, M, acc, (float*)&sA[0][0] + wave * 32 * (BN / WN + 4), i0 + wm * (BM / WM),
+                                j0 + wn * (BN / WN), row_of);
   }
 }
 
@@ -945,18 +795,6 @@ void launch_bf16_wgrad(GemmArgs a, const Segs& s, hipStream_t st) {
   const int gy = (n_groups + a.groups_per_block - 1) / a.groups_per_block;
   hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, WM, WN, MODE_WGRAD, false, S>), dim3(tiles, gy, 1),
                      dim3(WM * WN * 64), 0, st, a, s);
-}
-
-// forward / input gradient
-template <int BM, int BN, int WM, int WN, int S>
-void launch_bf16_plain(GemmArgs a, const Segs& s, hipStream_t st) {
-  const int tiles = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
-  a.groups_per_block = 1;
-  dim3 grid(tiles, 1, 1), block(WM * WN * 64);
-  if (a.mode == MODE_FWD)
-    hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, WM, WN, MODE_FWD, false, S>), grid, block, 0, st, a, s);
-  else
-    hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, WM, WN, MODE_DGRAD, false, S>), grid, block, 0, st, a, s);
 }
 
 // Weight gradient with the weighted aggregation folded in: 256 x 128 tiles leave room for a
@@ -1098,12 +936,8 @@ int launch_gemm(int dtype, const GemmArgs& args, const Segs& s, void* stream, co
     launch_bf16_wgrad_agg(a, s, (hipStream_t)stream);
   } else if (dtype == DYNB_BF16) {
     // large tiles have the best LDS-traffic-to-MFMA ratio; small problems need more, smaller
-    // tiles to occupy 256 compute units.  Forward / input gradient on 256 x 256 tiles run EIGHT
-    // waves (wave tile 128 x 64, at most 256 registers each): two waves per SIMD, so that one
-    // can issue MFMAs while the other waits for a copy instruction to be accepted (input
-    // gradient 112 -> 102 us, forward 126 -> 124 us per 4096^3 launch against four waves of
-    // 128 x 128).  The weight gradient keeps four waves: its 256 accumulators per lane leave no
-    // room for a second wave on a SIMD.
+    // tiles to occupy 256 compute units.  The weight gradient keeps four waves: its 256 accumulators per lane
+    // leave no room for a second wave on a SIMD.
     const int64_t big = (int64_t)((a.M + 255) / 256) * ((a.N + 255) / 256);
     const hipStream_t st = (hipStream_t)stream;
     if (a.mode == MODE_WGRAD) {
@@ -1111,10 +945,8 @@ int launch_gemm(int dtype, const GemmArgs& args, const Segs& s, void* stream, co
         launch_bf16_wgrad<256, 256, 2, 2, 4>(a, s, st);   // 128 + 18 KB of LDS
       else
         launch_bf16_wgrad<128, 128, 2, 2, 8>(a, s, st);
-    } else if (big >= 192) {
-      launch_bf16_plain<256, 256, 2, 4, 5>(a, s, st);     // all 160 KB of LDS
     } else {
-      launch_bf16_plain<128, 128, 2, 2, 8>(a, s, st);
+      return launch_gemm_lines(a, big >= 192, stream);
     }
   } else {
     return launch_gemm_f32(a, head, stream);
