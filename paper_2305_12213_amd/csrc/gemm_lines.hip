@@ -67,8 +67,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_lines_kernel(GemmArgs p) {
 #pragma unroll
     for (int o = 0; o < 2; ++o) {
       from[o] += 128;
-      // (saturating; in assembly, as the compiler takes a vector instruction for it and with it vector registers)
-      asm("s_sub_u32 %0, %0, 0x80\n\ts_cselect_b32 %0, 0, %0" : "+s"(left[o]) : : "scc");
+      left[o] = less_128(left[o]);
     }
   };
   f32x16 acc[TM][TN];

@@ -31,7 +31,11 @@ constexpr int T = 64;                      // tile side
 // stages, all issued ahead of the loop (eight instead of four changed nothing).  A compute unit
 // holds one such workgroup, so what bounds a stage is its serial chain: the next stage's operands are on their
 // way into the other register set while the matrix instructions of this one run (1024 x 1024 x 3072 17 -> 14 us, 1024 x 10 x 1024 with its loss 8.4
-// -> 7.2).  Copies
+// -> 7.2), and so are the copies, of which a compute unit takes one per 23 clocks: behind the four matrix instructions
+// a wave waited for them with nothing left to do.  Addresses are formed behind the last matrix instruction, as a
+// vector instruction between two of a chain costs 16 clocks (both: 1024 x 1024 x 1024 7.0 -> 6.7 us, iterations of 600
+// models of 4 to 4096 features 1 % faster on average; with the ring unrolled and no address to form, larger models gained
+// half a percent more and the smallest lost it to the longer code).  Copies
 // past the last stage are still issued (the wait stays a constant); what they read -- the next rows,
 // zeros past the matrix -- is never used.
 // On 128 x 128 tiles: 1024 x 1024 x 3072 30 us, 1024 x 10 x 1024 14 (without its loss).
@@ -48,8 +52,9 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(GemmArgs p, Head head) 
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l31 = lane & 31, h = lane >> 5, wi = wave & 1, wj = wave >> 1;
   const uint32_t lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)&ring[0];
-  const i32x4 rsA = buffer_resource(p.A, (uint32_t)((int64_t)p.M * p.lda * 2));
-  const i32x4 rsB = buffer_resource(p.B, (uint32_t)((int64_t)p.N * p.ldb * 2));
+  // the operands as buffers that begin at the stage's first column and end with the matrix
+  uint64_t from[2] = {(uint64_t)(uintptr_t)p.A, (uint64_t)(uintptr_t)p.B};
+  uint32_t left[2] = {(uint32_t)((int64_t)p.M * p.lda * 2), (uint32_t)((int64_t)p.N * p.ldb * 2)};
   // copy u of this wave: rows 16 wave + 8 u .. of A (u < 2), of B; rows past the edge repeat the last
   // one (their products are not stored)
   uint32_t off[4];
@@ -59,13 +64,16 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(GemmArgs p, Head head) 
     const int i = i0 + r < p.M ? i0 + r : p.M - 1, j = j0 + r < p.N ? j0 + r : p.N - 1;
     off[u] = (uint32_t)((u < 2 ? (int64_t)i * p.lda : (int64_t)j * p.ldb) * 2) + g * 16;
   }
-  uint32_t kbyte = 0;
-  auto issue = [&](uint32_t slot) {
+  auto copy_one = [&](uint32_t slot, int u) {
+    const i32x4 r = {(int)(uint32_t)from[u >> 1], (int)(uint32_t)(from[u >> 1] >> 32), (int)left[u >> 1], BUFFER_32BIT};
+    async_copy_1k_buffer(r, off[u], lds + slot + (uint32_t)((u >> 1) * (T * 128) + (2 * wave + (u & 1)) * 1024));
+  };
+  auto next_stage = [&]() {
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
-      async_copy_1k_buffer(u < 2 ? rsA : rsB, off[u] + kbyte,
-                           lds + slot + (uint32_t)((u >> 1) * (T * 128) + (2 * wave + (u & 1)) * 1024));
-    kbyte += 128;
+    for (int o = 0; o < 2; ++o) {
+      from[o] += 128;
+      left[o] = less_128(left[o]);
+    }
   };
   f32x16 acc;
 #pragma unroll
@@ -92,43 +100,58 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(GemmArgs p, Head head) 
     if (MODE == MODE_DGRAD && p.mask) mask[q] = *(const bf16x4*)((const bf16*)p.mask + (int64_t)ic * p.ldmask + jc);
   }
 #pragma unroll 1
-  for (int s = 0; s < NB; ++s) issue((uint32_t)(s * STAGE));
+  for (int s = 0; s < NB; ++s) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) copy_one((uint32_t)(s * STAGE), u);
+    next_stage();
+  }
   if constexpr (HEAD) {
     if (threadIdx.x < T) {                 // (while the first copies are on their way)
       owned[threadIdx.x] = rows_of_owner(head.segs, i0 + (int)threadIdx.x);
       label[threadIdx.x] = mine < 0 ? 0 : mine >= p.N ? p.N - 1 : mine;      // keeps the read in bounds
     }
   }
-  const char* const base = (const char*)&ring[0];
-  const int fa = (wi * 32 + l31) * 128, fb = T * 128 + (wj * 32 + l31) * 128, sw = swizzle128(l31);
+  const int fa = (wi * 32 + l31) * 128, fb = (T + wj * 32 + l31) * 128, sw = swizzle128(l31);
   bf16x8 a[2][4], b[2][4];                 // [register set][step of 16]
-  auto fetch = [&](int set, uint32_t slot) {
+  const char *pa[4], *pb[4];               // this lane's operands of the stage that is fetched next
+  auto point = [&](uint32_t slot) {
+    const char* const base = (const char*)&ring[0] + slot;
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
       const int g = ((2 * kk + h) ^ sw) * 16;
-      a[set][kk] = *(const bf16x8*)(base + slot + fa + g);
-      b[set][kk] = *(const bf16x8*)(base + slot + fb + g);
+      pa[kk] = base + fa + g;
+      pb[kk] = base + fb + g;
     }
+  };
+  auto fetch_one = [&](int set, int kk) {
+    a[set][kk] = *(const bf16x8*)pa[kk];
+    b[set][kk] = *(const bf16x8*)pb[kk];
   };
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NB - 1) * 4) : "memory");
   __syncthreads();
-  fetch(0, 0);
+  point(0);
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) fetch_one(0, kk);
   uint32_t slot = 0;                       // of the stage whose operands are in, or on their way to, `set`
+  point(STAGE);
   auto stage = [&](int set) {
     // this wave's part of the next stage has landed, its reads of this one have returned (its slot takes the
     // next copies) ...
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NB - 2) * 4) : "memory");
     __builtin_amdgcn_s_waitcnt(0xc07f);    // lgkmcnt(0), the other counters at their limits
     __syncthreads();                       // ... and so for every wave
-    const uint32_t next = slot + STAGE == NB * STAGE ? 0 : slot + STAGE;
-    fetch(set ^ 1, next);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk)
+    for (int kk = 0; kk < 4; ++kk) {
       acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[set][kk], a[set][kk], acc, 0, 0, 0);
-    __builtin_amdgcn_sched_barrier(0);
-    issue(slot);
-    slot = next;
+      __builtin_amdgcn_sched_barrier(0);
+      fetch_one(set ^ 1, kk);
+      copy_one(slot, kk);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    next_stage();
+    slot = slot + STAGE == NB * STAGE ? 0 : slot + STAGE;
+    point(slot + STAGE == NB * STAGE ? 0 : slot + STAGE);
   };
   int k = 0;
 #pragma unroll 1

@@ -46,6 +46,13 @@ __device__ inline void async_copy_1k_buffer(i32x4 rsrc, uint32_t voffset, uint32
                : "memory", "m0");
 }
 
+// n - 128, or 0: the bytes left of a buffer whose base moves on by a line.  (Assembly: the compiler takes a
+// vector instruction for a saturating difference, and a resource has to stay in scalar registers.)
+__device__ inline uint32_t less_128(uint32_t n) {
+  asm("s_sub_u32 %0, %0, 0x80\n\ts_cselect_b32 %0, 0, %0" : "+s"(n) : : "scc");
+  return n;
+}
+
 // LDS transpose read: within 16 lanes, lane r supplies the address of 4 neighbouring 16-bit elements of
 // row r / 4, and lane l receives element l of each of the 4 rows.
 typedef short s16x4 __attribute__((ext_vector_type(4)));
