@@ -312,10 +312,16 @@ RowChunks make_row_chunks(const Segs& s, int rows);
 // conv_wgrad_scratch_floats() floats.
 int conv_wgrad_chunk_rows(int64_t max_rows);
 int64_t conv_wgrad_scratch_floats(int64_t max_rows, int max_workers, int Cin, int Cout);
-int launch_conv_wgrad(const void* in, int64_t ldi, int Cin, int H, int W, const void* dy, int64_t ldd,
+// n layers of one geometry (and chunk_rows) at a time.
+constexpr int CONV_WGRAD_ITEMS = 8;
+struct ConvWgradLayer {
+  const void* in; const void* dy;
+  float* dW; float* db;
+};
+int launch_conv_wgrad(const ConvWgradLayer* layers, int n, int64_t ldi, int Cin, int H, int W, int64_t ldd,
                       int Cout, int Ho, int Wo, int stride, int chunk_rows, float* scratch,
-                      int64_t scratch_floats, float* dW, float* db, int64_t group_stride,
-                      const Segs& s, double flops, double bytes, void* stream);
+                      int64_t scratch_floats, int64_t group_stride, const Segs& s, double flops, double bytes,
+                      void* stream);
 
 // The first convolution of a model, on images of at most three channels (conv_stem.hip): forward and
 // weight gradient straight from the caller's fp32 pixels [images * H * W][Cin].

@@ -550,21 +550,39 @@ int run_forward_backward(dynb_model* m, const float* x, const int32_t* y, const 
       const double flops = 2.0 * B * L.hw_out * L.wg_rows * L.n_out;
       const double bytes = (double)K * L.wg_rows * L.n_out * 4 +
                            (double)B * (L.hw_in * L.n_in + L.hw_out * L.n_out) * es;
-      if (l == 0 && stem)
+      if (l == 0 && stem) {
         rc = launch_stem_wgrad(x, L.n_in, L.h_in, L.w_in, L.h_out, L.w_out, L.stride, dyv[l], L.ld_out,
                                L.n_out, L.conv_chunk, m->partial, m->partial_floats, grads + L.w_off,
                                grads + L.b_off, m->P_pad, segs[l], flops, bytes, stream);
-      else
-        rc = launch_conv_wgrad(in_act(l), L.ld_in, L.n_in, L.h_in, L.w_in, dyv[l], L.ld_out, L.n_out,
-                               L.h_out, L.w_out, L.stride, L.conv_chunk, m->partial, m->partial_floats,
-                               grads + L.w_off, grads + L.b_off, m->P_pad, segs[l], flops, bytes, stream);
-      if (rc) return rc;
-      if (agg) {
-        rc = add_small(L.w_off, (int64_t)L.wg_rows * L.n_out);
-        if (!rc) rc = add_small(L.b_off, L.n_out);
         if (rc) return rc;
+        if (agg) {
+          rc = add_small(L.w_off, (int64_t)L.wg_rows * L.n_out);
+          if (!rc) rc = add_small(L.b_off, L.n_out);
+        }
+        return rc;
       }
-      return (int)DYNB_OK;
+      // with it, the layers above it of the same geometry (all gradients wrt outputs are there by now): the six layers
+      // of a residual model of three blocks in one launch and one sum over its chunks
+      ConvWgradLayer same[CONV_WGRAD_ITEMS];
+      size_t which[CONV_WGRAD_ITEMS];
+      int n = 0;
+      for (size_t j = l; j < nL && n < CONV_WGRAD_ITEMS; ++j) {
+        const Layer& M = m->layers[j];
+        if (M.kind != DYNB_LAYER_CONV3X3 || (j != l && wgrad_done[j]) || M.n_in != L.n_in || M.n_out != L.n_out ||
+            M.h_in != L.h_in || M.w_in != L.w_in || M.stride != L.stride || M.ld_in != L.ld_in)
+          continue;
+        wgrad_done[j] = 1;
+        which[n] = j;
+        same[n++] = {in_act(j), dyv[j], grads + M.w_off, grads + M.b_off};
+      }
+      rc = launch_conv_wgrad(same, n, L.ld_in, L.n_in, L.h_in, L.w_in, L.ld_out, L.n_out, L.h_out, L.w_out, L.stride,
+                             L.conv_chunk, m->partial, m->partial_floats, m->P_pad, segs[l], n * flops, n * bytes, stream);
+      for (int i = 0; i < n && !rc && agg; ++i) {
+        const Layer& M = m->layers[which[i]];
+        rc = add_small(M.w_off, (int64_t)M.wg_rows * M.n_out);
+        if (!rc) rc = add_small(M.b_off, M.n_out);
+      }
+      return rc;
     }
     GemmArgs g = {};
     g.mode = MODE_WGRAD;
