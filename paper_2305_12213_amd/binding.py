@@ -156,8 +156,11 @@ def _stream(stream):
         return stream
     try:
         import torch
-        # (is_initialized() first: is_available() asks the driver, 2 us on every call)
-        if torch.cuda.is_initialized() or torch.cuda.is_available():
+        # (is_initialized() first: is_available() asks the driver, 2 us on every call.  The raw value, without
+        # the stream object around it, 2.9 -> 0.4 us a call: the smallest iteration is two of them, and 20 us)
+        if torch.cuda.is_initialized():
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        if torch.cuda.is_available():
             return torch.cuda.current_stream().cuda_stream
     except ImportError:
         pass
