@@ -170,8 +170,8 @@ double average_pass_us(int64_t weights, int K);
 // bf16 products with few tiles (gemm_small.hip): whether one (unsplit) counts as such, and the launch.
 bool gemm_small_applies(const GemmArgs& a);
 int launch_gemm_small(const GemmArgs& a, const HeadArgs* head, void* stream);   // forward / input gradient
-// forward / input gradient of dense bf16 layers on 256 x 256 (large) or 128 x 128 tiles (gemm_lines.hip)
-int launch_gemm_lines(const GemmArgs& a, bool large, void* stream);
+// forward / input gradient of dense bf16 layers on larger tiles (gemm_lines.hip)
+int launch_gemm_lines(const GemmArgs& a, void* stream);
 // weight gradients of up to WGRAD_SMALL_ITEMS such layers (all over the same rows) in one launch, which does
 // the step's end too if `end`
 constexpr int WGRAD_SMALL_ITEMS = 8;

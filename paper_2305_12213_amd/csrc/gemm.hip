@@ -946,7 +946,7 @@ int launch_gemm(int dtype, const GemmArgs& args, const Segs& s, void* stream, co
       else
         launch_bf16_wgrad<128, 128, 2, 2, 8>(a, s, st);
     } else {
-      return launch_gemm_lines(a, big >= 192, stream);
+      return launch_gemm_lines(a, stream);
     }
   } else {
     return launch_gemm_f32(a, head, stream);

@@ -18,7 +18,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // (row l % 32, column 8 (v / 4) + 4 (l / 32) + v % 4).  Row i of the product is row row_of(i) of the output.
 // The strip passes, 32 rows at a time, through a
 // private fp32 patch of 32 x (32 TN + 4) floats in LDS: the accumulator layout (4 consecutive columns per lane, 32
-// rows per instruction) becomes 8 consecutive columns per lane, 4 or 8 rows per instruction,
+// rows per instruction) becomes 8 consecutive columns per lane, 4 to 16 rows per instruction,
 // and bias/ReLU/mask, the bf16 conversion and the global accesses run on whole 128-byte
 // lines.
 template <int MODE, int TM, int TN, typename RowOf>
@@ -27,7 +27,7 @@ __device__ __forceinline__ void store_product(const GemmArgs& p, int M, const f3
   const int lane = threadIdx.x & 63, hi4 = 4 * (lane >> 5), l31 = lane & 31;
   constexpr int CW = 32 * TN;              // columns of the strip
   constexpr int EP = CW + 4;               // patch row pitch in floats
-  static_assert(CW == 128 || CW == 64, "strip width");
+  static_assert(CW == 128 || CW == 64 || CW == 32, "strip width");
   constexpr int LPR = CW / 8;              // lanes per row in the read-back phase
   constexpr int RPI = 64 / LPR;            // rows per read-back instruction
   const int rrow = lane / LPR, rcol = (lane % LPR) * 8;

@@ -10,7 +10,9 @@
 // fetch (in front of its last step) releases its buffer, and the copies of stage t + NB follow at once: on 256 x 256
 // tiles, whose ring holds only two stages, half of them in that step and half in the next, so that they have two steps
 // to land (spread evenly, the last ones arrive late: 4096^3 107 and 122 us); on 128 x 128 tiles, with four stages, evenly.
-// Eight waves, two per SIMD: one issues matrix instructions while the other waits for a copy to be accepted.
+// 128 x 64 tiles, four waves, where those of 128 x 128 are fewer than half the compute units and 64 x 64 ones more than
+// one each (552 clocks of copies per stage and compute unit instead of twice 370; see gemm_small_applies()).
+// Eight waves on the larger tiles, two per SIMD: one issues matrix instructions while the other waits for a copy to be accepted.
 // The loop of 4096^3 takes 158 thousand clocks, of which 131 are matrix work; what is left is power -- such launches in a
 // row run at 1.7 GHz instead of 2.4, and a loop with fewer clocks (147 thousand, other places for the copies) at 1.5.
 //
@@ -154,11 +156,13 @@ void launch_as(const GemmArgs& a, hipStream_t st) {
 
 }  // namespace
 
-int launch_gemm_lines(const GemmArgs& a, bool large, void* stream) {
+int launch_gemm_lines(const GemmArgs& a, void* stream) {
   if (a.mode == MODE_WGRAD || a.conv || a.K % 64 != 0)
     return fail(DYNB_ERR_BADARG, "gemm: products of dense layers take whole 64-deep stages");
-  if (large) launch_as<256, 256, 2, 4, 2, 4>(a, (hipStream_t)stream);
-  else launch_as<128, 128, 4, 2, 4, 2>(a, (hipStream_t)stream);
+  auto tiles = [&](int m, int n) { return (int64_t)((a.M + m - 1) / m) * ((a.N + n - 1) / n); };
+  if (tiles(256, 256) >= 192) launch_as<256, 256, 2, 4, 2, 4>(a, (hipStream_t)stream);
+  else if (tiles(128, 128) >= 128) launch_as<128, 128, 4, 2, 4, 2>(a, (hipStream_t)stream);
+  else launch_as<128, 64, 2, 2, 4, 2>(a, (hipStream_t)stream);
   return hipGetLastError() == hipSuccess ? DYNB_OK : fail(DYNB_ERR_HIP, "gemm launch failed");
 }
 

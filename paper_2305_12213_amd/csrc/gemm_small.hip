@@ -404,11 +404,13 @@ int64_t tiles64(const GemmArgs& a) { return (int64_t)((a.M + T - 1) / T) * ((a.N
 static int64_t large_tiles(const GemmArgs& a) { return (int64_t)((a.M + 127) / 128) * ((a.N + 127) / 128); }
 
 // Up to half as many 128 x 128 tiles as compute units (at 204 of them, 1531 x 2050 x 1024, those take
-// 16 us and these 20); weight gradients, whose larger tiles would have to divide the workers or leave
-// the average to another pass, up to the 256 at which the large kernel folds it in.
+// 12 us and these 20), and where that is more than one of these tiles per compute unit, up to 1024 reduction elements:
+// from there on 128 x 64 tiles make up for their longer way in and out with fewer copies (1531 x 777 x 2112 16.3 ->
+// 13.6 us; 1531 x 777 x 128 5.6 -> 5.8; 1244 x 1519 x 128 some 2 us more).  Weight gradients, whose larger tiles would have
+// to divide the workers or leave the average to another pass, up to the 256 at which the large kernel folds it in.
 bool gemm_small_applies(const GemmArgs& a) {
   if (a.conv) return false;
-  if (a.mode != MODE_WGRAD) return a.K % 64 == 0 && large_tiles(a) < 128;
+  if (a.mode != MODE_WGRAD) return a.K % 64 == 0 && large_tiles(a) < 128 && (tiles64(a) <= 256 || a.K < 1024);
   return large_tiles(a) < 256;
 }
 

@@ -1,5 +1,5 @@
 """The bf16 products on large tiles at the edges of their tiles, ring and dispatch: rows and columns around multiples
-of 128 and 256, one stage and more stages than the ring holds, odd numbers of them, with and without a ReLU mask.
+of 64, 128 and 256, one stage and more stages than the ring holds, odd numbers of them, with and without a ReLU mask.
 They are held bit for bit against the same rows in pieces small enough for the 64 x 64 tiles, whose sums run
 in the same order: a row's results depend on nothing but the row.  (The 64 x 64 tiles are compared with
 the float64 oracle in test_gpu_small_products.py.)"""
@@ -21,6 +21,8 @@ pytestmark = pytest.mark.gpu
     (64, 3585, 65, 3329),        # 14 x 15 tiles of 256: one and two stages
     (190, 3328, 130, 3584),      # whole tiles, three stages each
     (450, 4095, 64, 3073),       # 13 x 16: eight and one
+    (1030, 1100, 1025, 1025),    # 9 x 18 tiles of 128 x 64: seventeen stages each
+    (1024, 1089, 10, 1024),      # 8 x 18: sixteen, and 64 x 64 tiles back
 ])
 def test_rows_of_large_products_equal_rows_of_small_ones(n_in, width, classes, rows):
     spec = synth.mlp_spec([n_in, width, classes], "bf16")
