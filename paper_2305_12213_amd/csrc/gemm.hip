@@ -1,7 +1,8 @@
-// Ragged / grouped GEMMs  C'[i][j] = sum_k A[i][k] * B[j][k]  (both operands k-contiguous).
+// Ragged / grouped GEMMs  C'[i][j] = sum_k A[i][k] * B[j][k]: weight gradients of dense layers (both operands row-major),
+// convolutions as products of a gathered operand, and the choice among all products.
 //   bf16: MFMA 32x32x16 with fp32 accumulators, tiles staged through LDS in 16-byte
 //         granules with an XOR swizzle, software-pipelined global loads.
-// (fp32 products: gemm_f32.hip.)
+// (fp32 products: gemm_f32.hip; forward products and input gradients of dense layers: gemm_lines.hip, gemm_small.hip.)
 // Batch sizes are run-time data: rows, columns and reduction depth are predicated, nothing
 // is compiled per size.
 #include <hip/hip_runtime.h>
@@ -24,7 +25,7 @@ typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 constexpr int BK = 32;          // reduction elements per stage (two MFMA k-steps)
 constexpr int GPR = BK / 8;     // 16-byte granules per tile row
 
-// Staged operand tiles (forward / input gradient): rows of 64 bytes = four 16-byte granules;
+// Staged operand tiles (gathered forward / input gradient): rows of 64 bytes = four 16-byte granules;
 // logical granule g of row r sits at physical granule g ^ swizzle_of_row(r).  The LDS has 64
 // banks of 4 bytes, so a 16-byte fragment read serves 16 lanes per clock and four consecutive
 // rows fill the 256 bytes of one pass over the banks: rows r, r+4, r+8, r+12 need four different

@@ -12,6 +12,9 @@
 // take.  Problems with many tiles give each wave 2 x 2 of them (half the copies per instruction).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <type_traits>
+
 #include "dynb_internal.h"
 #include "gemm_f32_product.h"
 #include "lds_async.h"
@@ -41,10 +44,11 @@ namespace {
 // gradient are a variant of their own; and what ends a worker stands behind the loop over its blocks, once.  134
 // tiles, 785 rows of one worker: 380 -> 250 clocks per 16 rows.  785-301-97-10, 7 workers, all layers: 24.6 -> 18 us;
 // 3072-512-512-10, 4 workers (2 x 2 tiles, 30 MB of results): 28.7 -> 21.5.
+enum { TILE_1, TILE_2, TILE_1_LONG };
 struct WgradItem {
   const void* A; const void* B;            // dy, x
   int64_t lda, ldb, ldcf;
-  int M, N, first, wide;                   // first: its first workgroup; wide: R = 2
+  int M, N, first, kind;                   // first: its first workgroup; kind: TILE_1 ..
   int tiles, per;                          // workgroups tiles * part .. take workers per * part ..
   float* Cf; float* bias_grad; float* agg; float* bias_agg;
 };
@@ -66,11 +70,14 @@ constexpr uint32_t WGRAD_RING = 20 * KB;
 template <int R>
 __device__ inline int swizzle(int r) { return R == 1 ? 0 : 4 * ((r >> 1) & 1); }
 
-template <int R, bool BIAS>
+// LONG: rows whose offsets within a block or a tile do not fit 32 bits.  Blocks are then copied by address, like the
+// first one of every wave.
+template <int R, bool BIAS, bool LONG = false>
 __device__ __forceinline__ void wgrad_f32_tile(const WgradItem& item, const WgradGroup& grp, const Segs& segs,
                                                int part, int ti, int tj, uint4* ring_area) {
   constexpr int NB = R == 1 ? 10 : 5, S = 16 * R, C = 2 * R;   // copies per block: R of dy, R of x
   constexpr uint32_t SLOT = C * KB;
+  using Offset = std::conditional_t<LONG, uint64_t, uint32_t>;
   static_assert(NB * SLOT == WGRAD_RING, "ring");
   const WgradItem p = item;
   const int lane = threadIdx.x, l15 = lane & 15, kg = lane >> 4;
@@ -89,10 +96,10 @@ __device__ __forceinline__ void wgrad_f32_tile(const WgradItem& item, const Wgra
   // there and ends with the worker's rows, or the block: what lies behind reads as zeros.
   constexpr int LPR = 4 * R;               // lanes per row
   const int lrow = lane / LPR;
-  const uint32_t pitch[2] = {(uint32_t)p.lda * 4, (uint32_t)p.ldb * 4};   // (16 rows below 2^31 bytes: see launch_wgrad_f32())
+  const Offset pitch[2] = {(Offset)p.lda * 4, (Offset)p.ldb * 4};   // (16 rows below 2^31 bytes: see launch_wgrad_f32())
   uint64_t base[2] = {(uint64_t)(uintptr_t)((const float*)p.A + segs.off[g0] * p.lda + i0),
                       (uint64_t)(uintptr_t)((const float*)p.B + segs.off[g0] * p.ldb + j0)};
-  uint32_t off[C];
+  Offset off[C];
 #pragma unroll
   for (int c = 0; c < C; ++c) {
     const int row = lrow + (16 / R) * (c % R), g = (lane & (LPR - 1)) ^ swizzle<R>(row);
@@ -101,30 +108,27 @@ __device__ __forceinline__ void wgrad_f32_tile(const WgradItem& item, const Wgra
   // Copies the next block; rows past the worker's last, and blocks past the last worker, are zeros.
   int copied = g0, to_copy = segs.off[g0 + 1] - segs.off[g0];   // worker, its rows from this block on
   const int first_rows = to_copy;
-  auto issue = [&](uint32_t slot) {
+  auto issue = [&](uint32_t slot, auto by_address) {
     const uint32_t rows = to_copy < 16 ? to_copy : 16;
 #pragma unroll
     for (int o = 0; o < 2; ++o) {
-      const i32x4 r = {(int)(uint32_t)base[o], (int)(uint32_t)(base[o] >> 32), (int)(rows * pitch[o]), BUFFER_32BIT};
 #pragma unroll
-      for (int c = 0; c < R; ++c) async_copy_1k_buffer(r, off[o * R + c], lds + slot + (o * R + c) * KB);
+      for (int c = 0; c < R; ++c) {
+        const uint32_t to = lds + slot + (o * R + c) * KB;
+        if constexpr (by_address) {
+          const bool in = lrow + (16 / R) * c < (int)rows;
+          async_copy_1k(in ? (const void*)(uintptr_t)(base[o] + off[o * R + c]) : grp.zeros, to);
+        } else {
+          const i32x4 r = {(int)(uint32_t)base[o], (int)(uint32_t)(base[o] >> 32), (int)(rows * pitch[o]), BUFFER_32BIT};
+          async_copy_1k_buffer(r, off[o * R + c], to);
+        }
+      }
       base[o] += rows * pitch[o];
     }
     to_copy -= 16;
     if (__builtin_expect(to_copy <= 0, 0)) to_copy = ++copied < g1 ? rows_of(copied) : 0;
   };
-  // (the first block by address, with the zero granule behind the rows)
-  auto issue_first = [&]() {
-#pragma unroll
-    for (int c = 0; c < C; ++c)
-      async_copy_1k(lrow + (16 / R) * (c % R) < to_copy ? (const void*)(uintptr_t)(base[c / R] + off[c]) : grp.zeros,
-                    lds + c * KB);
-    const uint32_t rows = to_copy < 16 ? to_copy : 16;
-    base[0] += rows * pitch[0];
-    base[1] += rows * pitch[1];
-    to_copy -= 16;
-    if (to_copy <= 0) to_copy = ++copied < g1 ? rows_of(copied) : 0;
-  };
+  constexpr std::bool_constant<LONG> other_blocks = {};
   float f[2][C][4];                        // [register set][16 features of dy / x][matrix instruction]
   const char* const ring = (const char*)&ring_area[0];
   uint32_t at[R];
@@ -155,7 +159,7 @@ __device__ __forceinline__ void wgrad_f32_tile(const WgradItem& item, const Wgra
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int j = 16 * u + 4 * kg + e;
-        const uint32_t o = (uint32_t)j * (uint32_t)p.ldcf + l15;
+        const Offset o = (Offset)j * (Offset)p.ldcf + l15;
         if (j0 + j < p.N) {
           if (in_row) out[o] = v[u][0][e];
           if (R > 1 && in_row2) out[o + 16] = v[u][R - 1][e];
@@ -163,9 +167,9 @@ __device__ __forceinline__ void wgrad_f32_tile(const WgradItem& item, const Wgra
       }
   };
 
-  issue_first();
+  issue(0, std::true_type());
 #pragma unroll 1
-  for (uint32_t s = SLOT; s < NB * SLOT; s += SLOT) issue(s);
+  for (uint32_t s = SLOT; s < NB * SLOT; s += SLOT) issue(s, other_blocks);
   wait_pending<(NB - 1) * C>();
 #pragma unroll
   for (int t = 0; t < 4; ++t) fetch_one(0, 0, t);
@@ -188,7 +192,7 @@ __device__ __forceinline__ void wgrad_f32_tile(const WgradItem& item, const Wgra
         fetch_one(set ^ 1, ahead, 2 * t);
         fetch_one(set ^ 1, ahead, 2 * t + 1);
       } else if (t == 2) {
-        issue(slot);
+        issue(slot, other_blocks);
       }
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -264,13 +268,15 @@ __global__ __launch_bounds__(64) void wgrad_f32_kernel(WgradGroup grp, Segs segs
   int q = 0;
   while (q + 1 < grp.n && block >= grp.item[q + 1].first) ++q;
   const WgradItem& p = grp.item[q];
-  const int S = p.wide ? 32 : 16, part = (block - p.first) / p.tiles;
+  const int S = p.kind == TILE_2 ? 32 : 16, part = (block - p.first) / p.tiles;
   int ti, tj;
   tile_of_block(block - p.first - part * p.tiles, (p.M + S - 1) / S, (p.N + S - 1) / S, ti, tj);
-  if (p.wide && tj == 0) wgrad_f32_tile<2, true>(p, grp, segs, part, ti, tj, ring_area);
-  else if (p.wide) wgrad_f32_tile<2, false>(p, grp, segs, part, ti, tj, ring_area);
-  else if (tj == 0) wgrad_f32_tile<1, true>(p, grp, segs, part, ti, tj, ring_area);
-  else wgrad_f32_tile<1, false>(p, grp, segs, part, ti, tj, ring_area);
+  if (p.kind == TILE_2 && tj == 0) wgrad_f32_tile<2, true>(p, grp, segs, part, ti, tj, ring_area);
+  else if (p.kind == TILE_2) wgrad_f32_tile<2, false>(p, grp, segs, part, ti, tj, ring_area);
+  else if (p.kind == TILE_1 && tj == 0) wgrad_f32_tile<1, true>(p, grp, segs, part, ti, tj, ring_area);
+  else if (p.kind == TILE_1) wgrad_f32_tile<1, false>(p, grp, segs, part, ti, tj, ring_area);
+  else if (tj == 0) wgrad_f32_tile<1, true, true>(p, grp, segs, part, ti, tj, ring_area);
+  else wgrad_f32_tile<1, false, true>(p, grp, segs, part, ti, tj, ring_area);
 }
 
 template <int R>
@@ -304,7 +310,8 @@ static int workers_per_wave(const GemmArgs& a, int K, int side) {
   return shares < 1 ? K : shares > K ? 1 : (K + (int)shares - 1) / (int)shares;
 }
 bool wgrad_f32_walks(const GemmArgs& a, const Segs& s) { return workers_per_wave(a, s.K, wgrad_side(a, s)) == s.K; }
-// A wave of 16 x 16 tiles takes 0.06 us per 16 rows and 0.7 us per worker.  Where 2 x 2 tiles of divided
+// The rule counts 0.06 us per 16 rows and 0.7 us per worker of a wave of 16 x 16 tiles, fitted over whole iterations
+// (a wave that has its SIMD for itself takes 0.11 and 0.55).  Where 2 x 2 tiles of divided
 // workers fill the chip instead, they are faster by 0.05 us per 16 rows and 1024 of the small ones, which
 // is worth a pass of 5 us from 1700 rows on (512 x 512, 8 workers, per layer with its average: 1024 rows
 // folded 16 us, with the pass 20; 576 x 576, 16384 rows, forward and backward: 455 and 378).
@@ -338,6 +345,12 @@ int launch_gemm_f32(const GemmArgs& a, const HeadArgs* head, void* stream) {
   return hipGetLastError() == hipSuccess ? DYNB_OK : fail(DYNB_ERR_HIP, "gemm launch failed");
 }
 
+// Offsets within a block of 16 rows, and within the 32 rows of a tile of the result, are 32-bit in the tiles that copy
+// through buffers.
+static bool wgrad_rows_long(const GemmArgs& g) {
+  return 16 * 4 * std::max(g.lda, g.ldb) >= (int64_t)1 << 31 || 32 * 4 * g.ldcf >= (int64_t)1 << 31;
+}
+
 int launch_wgrad_f32(const GemmArgs* a, int n, const Segs& s, const StepEnd* end, void* stream) {
   if (n > WGRAD_F32_ITEMS) return fail(DYNB_ERR_BADARG, "gemm: too many weight gradients for one launch");
   WgradGroup grp = {};
@@ -356,15 +369,14 @@ int launch_wgrad_f32(const GemmArgs* a, int n, const Segs& s, const StepEnd* end
       return fail(DYNB_ERR_BADARG, "gemm: operands must have 16-byte aligned rows");
     // (a wave that folds the average in walks all workers: then the tiles alone have to fill the chip,
     // those of all layers together -- three of 512 x 512, 1024 rows: 43 us, and 53 with 2 x 2 tiles)
-    const int side = g.agg && wide < 1024 ? 16 : wgrad_side(g, s);
-    // (offsets within a block, and within a tile of the result, are 32-bit)
-    if (16 * 4 * (g.lda > g.ldb ? g.lda : g.ldb) >= (int64_t)1 << 31 || 32 * 4 * g.ldcf >= (int64_t)1 << 31)
-      return fail(DYNB_ERR_UNSUPPORTED, "gemm: rows too long for a weight gradient");
+    const bool long_rows = wgrad_rows_long(g);
+    const int side = long_rows || (g.agg && wide < 1024) ? 16 : wgrad_side(g, s);
     const int64_t tiles = tiles_with(g, side);
     const int per = g.agg ? s.K : workers_per_wave(g, s.K, side);
     if (blocks + tiles * ((s.K + per - 1) / per) >= (int64_t)1 << 31)
       return fail(DYNB_ERR_UNSUPPORTED, "gemm: too many tiles for one launch");
-    grp.item[grp.n++] = {g.A, g.B, g.lda, g.ldb, g.ldcf, g.M, g.N, (int)blocks, side == 32, (int)tiles,
+    grp.item[grp.n++] = {g.A, g.B, g.lda, g.ldb, g.ldcf, g.M, g.N, (int)blocks,
+                         long_rows ? TILE_1_LONG : side == 32 ? TILE_2 : TILE_1, (int)tiles,
                          per, g.Cf, g.bias_grad, g.agg, g.bias_agg};
     grp.group_stride = g.group_stride;
     if (g.agg)

@@ -135,3 +135,32 @@ def test_weight_gradient_is_one_chain_per_worker(n, classes, b):
     for k, bk in enumerate(b):
         assert np.array_equal(got[k][0][0], chain(x[off:off + bk].T, dz[off:off + bk])), k
         off += bk
+
+
+def test_weight_gradient_of_rows_beyond_32_bit_offsets():
+    # 2^24 outputs: 32 rows of the gradient are 2 GiB.  Equal logits and small whole inputs make every column without a
+    # label exact, in any order; a label's is a chain of at most 32 additions of partial sums below 8.
+    import torch
+    bound = 32 * 8 * 2.0 ** -24
+    n, m, b = 17, 1 << 24, [32, 0, 2]
+    rng = np.random.default_rng(34)
+    x, y = rng.integers(-8, 9, (sum(b), n)).astype(np.float32), rng.integers(0, m, sum(b)).astype(np.int32)
+    y[:3] = [0, m - 1, 17]
+    spec = synth.mlp_spec([n, m], "f32")
+    run = DeviceRun(spec, [(np.zeros((n, m), np.float32), np.zeros(m, np.float32))], sum(b), len(b))
+    g = run.forward_backward_aggregate(x, y, b)
+    mean, off = torch.zeros(n + 1, m, dtype=torch.float64, device="cuda"), 0
+    for k, bk in enumerate(b):
+        got = g[k, :n * m + m].view(n + 1, m)                    # (the biases follow the weights)
+        xk = torch.from_numpy(np.hstack([x[off:off + bk], np.ones((bk, 1), np.float32)])).cuda().double()
+        labels = torch.from_numpy(y[off:off + bk].astype(np.int64)).cuda()
+        want = (xk.sum(0) / (m * max(bk, 1)))[:, None].repeat(1, m)
+        plain = torch.ones(m, dtype=torch.bool, device="cuda")
+        plain[labels] = False
+        want.index_add_(1, labels, -xk.t().contiguous() / max(bk, 1))
+        assert bool((got.double() == want)[:, plain].all()), k
+        assert float((got.double() - want).abs().max()) <= bound, k
+        mean += want * (bk / sum(b))
+        off += bk
+    out = run.out[:n * m + m].view(n + 1, m).double()
+    assert float((out - mean).abs().max()) <= 2 * bound      # (three more, of the workers' shares)
