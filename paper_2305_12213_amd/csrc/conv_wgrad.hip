@@ -18,6 +18,7 @@
 // "tap" whose input operand is all ones.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <climits>
 #include <mutex>
 #include <type_traits>
@@ -651,8 +652,8 @@ __global__ __launch_bounds__(256, 2) void conv_wgrad_flat_kernel(Args p, Segs se
 // 16 bytes of it, all or a quarter: G groups of PER threads add chunks g, g + G, ... (four independent partial sums, so
 // that the loads overlap) and meet in LDS, through which the tile also turns: accumulator element v of lane l belongs to
 // output channel 8*(v/4) + 4*(l/32) + v%4 and input channel l%32, and leaves as rows of 128 or 32 bytes.  Whole tiles and
-// one group where a worker is a few chunks (what counts then are the bytes in flight); 16 groups where a worker is many
-// and there are few tiles.
+// one group where no worker is many chunks (what counts then are the bytes in flight); 16 groups where one is very many
+// and there are few tiles: see conv_wgrad_plan().
 // (With 32 quadruples of neighbouring input channels per workgroup, every 16 bytes of a result went to a line of their
 // own, and seven of eight threads had nothing to add where a worker is one chunk: 256 -> 256 channels, 15 workers
 // of 128 pixels, 85 -> 19 us; 64 -> 64, 8 workers, six layers 25 -> 17; 64 -> 128, 4 workers 10.4 -> 8.7.)
@@ -759,6 +760,72 @@ int64_t conv_wgrad_scratch_floats(int64_t max_rows, int max_workers, int Cin, in
   return chunks * ((Cin + 63) / 64) * ((Cout + 63) / 64) * TILE_FLOATS;
 }
 
+ConvWgradPlan conv_wgrad_plan(int n, int64_t ldi, int Cin, int H, int W, int64_t ldd, int Cout, int Ho, int Wo, int stride,
+                              int chunk_rows, int64_t scratch_floats, const Segs& s) {
+  ConvWgradPlan p;
+  const int cibs = (Cin + 63) / 64, cobs = (Cout + 63) / 64;
+  // Stride 1 on images at least 8 wide (a fragment's eight pixels then hold one border pixel of each
+  // kind at most): the flat kernel, whose blocks are only as wide as the channels need.  Whole rows
+  // need neither its masks nor its bookkeeping: of 32 pixels with a 64-channel side (3 -> 64
+  // channels on 512 x 32 x 32 pixels: 48 us by rows, 57 flat), and of more than 16 (below, the second of the
+  // two steps of a row would be empty) with two.  Two sides of more than 32 channels otherwise
+  // stay on the per-tap kernel (367 x 28 x 28 pixels, 64 -> 64: 50 us against 54 flat; 24 -> 64: 49 against 36).
+  bool by_rows = stride == 1 && W > 16 && W <= 32 && Wo == W && H == Ho && (W == 32 ? Cin > 32 || Cout > 32 : Cin > 32 && Cout > 32);
+  by_rows = by_rows && (int64_t)s.off[s.K] * ldi * 2 < (int64_t)1 << 31 && (int64_t)s.off[s.K] * ldd * 2 < (int64_t)1 << 31;
+  for (int k = 0; k <= s.K && by_rows; ++k) by_rows = s.off[k] % W == 0;
+  const bool flat = stride == 1 && W >= 8 && H == Ho && W == Wo && !by_rows && (Cin <= 32 || Cout <= 32);
+  p.kernel = by_rows ? CONV_WGRAD_ROWS : flat ? CONV_WGRAD_FLAT : CONV_WGRAD_TAPS;
+  p.ci32 = flat && Cin <= 32 ? 1 : 2;
+  p.co32 = flat && Cout <= 32 ? 1 : 2;
+  p.ch = make_row_chunks(s, chunk_rows);
+  const int own_chunks = p.ch.first[s.K];
+  const int64_t per_chunk = (int64_t)cibs * cobs, tile_floats = flat ? (int64_t)p.ci32 * p.co32 * SLOTS * 1024 : TILE_FLOATS;
+  // From about two chunks per compute unit on, two chunks are one workgroup's, whose halves meet in LDS:
+  // half as many results (147 KB each) to write and to add up.  512 x 32 x 32 pixels, 64 -> 64 channels:
+  // 53 + 15.5 us for the product and the sum over chunks -> 51 + 10.3; 512 x 16 x 16, 32 -> 64, stride
+  // 2: 31 + 13 -> 30 + 7.  With fewer chunks each has a compute unit to itself, which is worth more.
+  p.paired = !flat && n * own_chunks * per_chunk >= 384;
+  // Layers of one geometry share a launch, and divide between them the workgroups that one of them would fill the
+  // chip with: as many times longer chunks, so that fewer results are written and added up, and one way in and out
+  // instead of one each.  (Scratch for the results of one layer at its own chunks is enough for all.)  64 -> 64 on 512 x
+  // 32 x 32, six layers: 6 x (45 + 10) -> 221 + 18 us; 24 -> 24 on 167 x 28 x 28, four: 4 x (16 + 5.5) -> 34 + 6; iterations
+  // of 500 residual models of 4 to 300 channels take 0.91 of the time on average, none more than 1.03.
+  // Every worker ends with a chunk of its own, so there may be a few chunks more than workgroups that
+  // run at a time, which would then run alone at the end: chunks up to a quarter longer (of several layers, whose last
+  // chunks are as many times more, up to a half), if that makes them fit.
+  const int slots = p.paired ? 256 : 512, step = by_rows ? W : 32;
+  const int64_t own = p.paired ? 2 * chunk_rows : chunk_rows;
+  int64_t shared = n * (int64_t)s.off[s.K] * per_chunk / slots;
+  shared = shared < own ? own : shared > own * n ? own * n : shared;
+  const int base = (int)round_up(shared, step);
+  const int64_t all = ((int64_t)s.off[s.K] + base - 1) / base * per_chunk * n;
+  const int64_t fit = (n > 1 && all <= slots + slots / 8 ? slots : round_up(all, slots)) / per_chunk;
+  for (int rows = base; rows <= base + base / (n > 1 ? 2 : 4); rows += step) {
+    const RowChunks longer = make_row_chunks(s, rows);
+    if ((int64_t)n * longer.first[s.K] > fit && rows > base) continue;
+    p.ch = longer;
+    if ((int64_t)n * longer.first[s.K] <= fit) break;
+  }
+  const int nch = p.ch.first[s.K];
+  p.layers = n;
+  if (n > 1 && n * nch * per_chunk * tile_floats > scratch_floats)   // (many workers, each with a last chunk per layer)
+    return conv_wgrad_plan(n / 2, ldi, Cin, H, W, ldd, Cout, Ho, Wo, stride, chunk_rows, scratch_floats, s);
+  // The sum over chunks lasts as long as that of the worker with the most of them: one group adds 4 chunks in the
+  // time of a read (0.22 us), four groups 16.  Four groups are four times the workgroups, though, 0.003 us per tile and
+  // worker, and no faster where one worker's tiles alone keep the memory busy.  With 1, 4 and 16 groups, us:
+  // 24 channels, 64 workers, one of them with 32 chunks and the others with one each 4.3, 4.9, 10; 64 of one 6.0, 4.9, 10;
+  // 190 of one 13.1, 5.4, 10; 64 channels, 8 workers with 8 each 3.6, 4.5, 7.6; with 24 each 5.6, 5.2, 10.6; 4 workers, 190
+  // of one 20, 7.4, 5.4; 256 channels, 8 workers, 48 of one 23, 33, 68; 128 of one 61, 69, 111.
+  // (Over 436 such sums the form taken is 0.5 % from the fastest on average and 15 % at most; decided by the mean over
+  // the workers, 7 % and a factor of 2.4.  3-24-24 channels on 16 x 16, 700 images of 64 workers, 637 of one: 134 -> 123 us
+  // per iteration.)
+  int most = 0;
+  for (int k = 0; k < s.K; ++k) most = std::max(most, p.ch.first[k + 1] - p.ch.first[k]);
+  const int64_t tiles = (int64_t)(9 * ((Cin + 31) / 32) + 1) * ((Cout + 31) / 32) * p.layers;
+  p.sum_groups = tiles >= 256 || most <= 4 || most <= tiles * s.K / 16 ? 1 : most > 128 && tiles * s.K < 512 ? 16 : 4;
+  return p;
+}
+
 int launch_conv_wgrad(const ConvWgradLayer* layers, int n, int64_t ldi, int Cin, int H, int W, int64_t ldd,
                       int Cout, int Ho, int Wo, int stride, int chunk_rows, float* scratch,
                       int64_t scratch_floats, int64_t group_stride, const Segs& s, double flops, double bytes,
@@ -775,50 +842,11 @@ int launch_conv_wgrad(const ConvWgradLayer* layers, int n, int64_t ldi, int Cin,
     return fail(DYNB_ERR_UNSUPPORTED, "conv_wgrad: tensor too large for 32-bit pixel indices");
   const void* zeros = device_zero_granule();
   if (!zeros) return fail(DYNB_ERR_HIP, "conv_wgrad: no address for the zero granule");
-  RowChunks ch = make_row_chunks(s, chunk_rows);
-  int nch = ch.first[s.K];
-  if ((int64_t)nch * cibs * cobs * TILE_FLOATS > scratch_floats)
+  if ((int64_t)make_row_chunks(s, chunk_rows).first[s.K] * cibs * cobs * TILE_FLOATS > scratch_floats)
     return fail(DYNB_ERR_BADARG, "conv_wgrad: scratch area too small");
-  // Stride 1 on images at least 8 wide (a fragment's eight pixels then hold one border pixel of each
-  // kind at most): the flat kernel, whose blocks are only as wide as the channels need.  Whole rows
-  // need neither its masks nor its bookkeeping: of 32 pixels with a 64-channel side (3 -> 64
-  // channels on 512 x 32 x 32 pixels: 48 us by rows, 57 flat), and of more than 16 (below, the second of the
-  // two steps of a row would be empty) with two.  Two sides of more than 32 channels otherwise
-  // stay on the per-tap kernel (367 x 28 x 28 pixels, 64 -> 64: 50 us against 54 flat; 24 -> 64: 49 against 36).
-  bool by_rows = stride == 1 && W > 16 && W <= 32 && Wo == W && H == Ho && (W == 32 ? Cin > 32 || Cout > 32 : Cin > 32 && Cout > 32);
-  by_rows = by_rows && (int64_t)s.off[s.K] * ldi * 2 < (int64_t)1 << 31 && (int64_t)s.off[s.K] * ldd * 2 < (int64_t)1 << 31;
-  for (int k = 0; k <= s.K && by_rows; ++k) by_rows = s.off[k] % W == 0;
-  const bool flat = stride == 1 && W >= 8 && H == Ho && W == Wo && !by_rows && (Cin <= 32 || Cout <= 32);
-  const int ci32 = flat && Cin <= 32 ? 1 : 2, co32 = flat && Cout <= 32 ? 1 : 2;
-  const int64_t per_chunk = (int64_t)cibs * cobs, tile_floats = flat ? (int64_t)ci32 * co32 * SLOTS * 1024 : TILE_FLOATS;
-  // From about two chunks per compute unit on, two chunks are one workgroup's, whose halves meet in LDS:
-  // half as many results (147 KB each) to write and to add up.  512 x 32 x 32 pixels, 64 -> 64 channels:
-  // 53 + 15.5 us for the product and the sum over chunks -> 51 + 10.3; 512 x 16 x 16, 32 -> 64, stride
-  // 2: 31 + 13 -> 30 + 7.  With fewer chunks each has a compute unit to itself, which is worth more.
-  const bool paired = !flat && n * nch * per_chunk >= 384;
-  // Layers of one geometry share a launch, and divide between them the workgroups that one of them would fill the
-  // chip with: as many times longer chunks, so that fewer results are written and added up, and one way in and out
-  // instead of one each.  (Scratch for the results of one layer at its own chunks is enough for all.)  64 -> 64 on 512 x
-  // 32 x 32, six layers: 6 x (45 + 10) -> 221 + 18 us; 24 -> 24 on 167 x 28 x 28, four: 4 x (16 + 5.5) -> 34 + 6; iterations
-  // of 500 residual models of 4 to 300 channels take 0.91 of the time on average, none more than 1.03.
-  // Every worker ends with a chunk of its own, so there may be a few chunks more than workgroups that
-  // run at a time, which would then run alone at the end: chunks up to a quarter longer (of several layers, whose last
-  // chunks are as many times more, up to a half), if that makes them fit.
-  const int slots = paired ? 256 : 512, step = by_rows ? W : 32;
-  const int64_t own = paired ? 2 * chunk_rows : chunk_rows;
-  int64_t shared = n * (int64_t)s.off[s.K] * per_chunk / slots;
-  shared = shared < own ? own : shared > own * n ? own * n : shared;
-  const int base = (int)round_up(shared, step);
-  const int64_t all = ((int64_t)s.off[s.K] + base - 1) / base * per_chunk * n;
-  const int64_t fit = (n > 1 && all <= slots + slots / 8 ? slots : round_up(all, slots)) / per_chunk;
-  for (int rows = base; rows <= base + base / (n > 1 ? 2 : 4); rows += step) {
-    const RowChunks longer = make_row_chunks(s, rows);
-    if ((int64_t)n * longer.first[s.K] > fit && rows > base) continue;
-    ch = longer;
-    if ((int64_t)n * longer.first[s.K] <= fit) break;
-  }
-  nch = ch.first[s.K];
-  if (n > 1 && n * nch * per_chunk * tile_floats > scratch_floats) {   // (many workers, each with a last chunk per layer)
+  const ConvWgradPlan plan =
+      conv_wgrad_plan(n, ldi, Cin, H, W, ldd, Cout, Ho, Wo, stride, chunk_rows, scratch_floats, s);
+  if (plan.layers < n) {
     for (int half = 0; half < 2; ++half) {
       const int from = half * (n / 2), count = half ? n - n / 2 : n / 2;
       const int rc = launch_conv_wgrad(layers + from, count, ldi, Cin, H, W, ldd, Cout, Ho, Wo, stride, chunk_rows, scratch,
@@ -827,6 +855,9 @@ int launch_conv_wgrad(const ConvWgradLayer* layers, int n, int64_t ldi, int Cin,
     }
     return DYNB_OK;
   }
+  const RowChunks& ch = plan.ch;
+  const int nch = ch.first[s.K], ci32 = plan.ci32, co32 = plan.co32;
+  const bool paired = plan.paired;
   Timed t(KC_GEMM_WGRAD, stream, flops, bytes);
   ConvWgradGroup a = {};
   MoreResults more = {};
@@ -846,14 +877,14 @@ int launch_conv_wgrad(const ConvWgradLayer* layers, int n, int64_t ldi, int Cin,
   auto launch = [&](auto args) {
     using Args = decltype(args);
     const dim3 grid(nch, cibs, cobs * n), block(paired ? 512 : 256);
-    if (by_rows) {
+    if (plan.kernel == CONV_WGRAD_ROWS) {
       if constexpr (std::is_same_v<Args, ConvWgradGroup>)
         hipLaunchKernelGGL(paired ? conv_wgrad_layers_rows_kernel<2> : conv_wgrad_layers_rows_kernel<1>, grid, block, 0, st, args, s, ch);
       else
         hipLaunchKernelGGL(paired ? conv_wgrad_rows_kernel<2> : conv_wgrad_rows_kernel<1>, grid, block, 0, st, args, s, ch);
     } else if (paired)
       hipLaunchKernelGGL((conv_wgrad_chunk_kernel<2, Args>), grid, block, 0, st, args, s, ch);
-    else if (!flat)
+    else if (plan.kernel == CONV_WGRAD_TAPS)
       hipLaunchKernelGGL((conv_wgrad_chunk_kernel<1, Args>), grid, block, 0, st, args, s, ch);
     else if (ci32 == 1 && co32 == 1)
       hipLaunchKernelGGL((conv_wgrad_flat_kernel<1, 1, Args>), grid, block, 0, st, args, s, ch);
@@ -874,8 +905,8 @@ int launch_conv_wgrad(const ConvWgradLayer* layers, int n, int64_t ldi, int Cin,
       hipLaunchKernelGGL((conv_wgrad_reduce_kernel<G, PER, More>), dim3(tile_slots * (256 / PER), s.K, n), dim3(G * PER), 0, st,
                          scratch, Cin, Cout, ci32, co32, layers[0].dW, layers[0].db, group_stride, ch, behind);
     };
-    if (nch <= 4 * s.K) as(std::integral_constant<int, 1>(), std::integral_constant<int, 256>());
-    else if (nch <= 32 * s.K || (int64_t)tile_slots * s.K * n >= 128) as(std::integral_constant<int, 4>(), std::integral_constant<int, 64>());
+    if (plan.sum_groups == 1) as(std::integral_constant<int, 1>(), std::integral_constant<int, 256>());
+    else if (plan.sum_groups == 4) as(std::integral_constant<int, 4>(), std::integral_constant<int, 64>());
     else as(std::integral_constant<int, 16>(), std::integral_constant<int, 64>());
   };
   if (n == 1) reduce(NoMore());

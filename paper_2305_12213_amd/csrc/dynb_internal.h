@@ -318,6 +318,18 @@ struct ConvWgradLayer {
   const void* in; const void* dy;
   float* dW; float* db;
 };
+// How the first of them are worked on together.
+enum { CONV_WGRAD_TAPS, CONV_WGRAD_ROWS, CONV_WGRAD_FLAT };
+struct ConvWgradPlan {
+  int kernel;          // CONV_WGRAD_TAPS ..
+  int ci32, co32;      // 32-channel tiles on either side of a channel block
+  bool paired;         // two groups of waves, which halve a chunk
+  int layers;          // so many in one launch
+  RowChunks ch;
+  int sum_groups;      // groups of threads that divide a worker's chunks in the sum: 1, 4 or 16
+};
+ConvWgradPlan conv_wgrad_plan(int n, int64_t ldi, int Cin, int H, int W, int64_t ldd, int Cout, int Ho, int Wo, int stride,
+                              int chunk_rows, int64_t scratch_floats, const Segs& s);
 int launch_conv_wgrad(const ConvWgradLayer* layers, int n, int64_t ldi, int Cin, int H, int W, int64_t ldd,
                       int Cout, int Ho, int Wo, int stride, int chunk_rows, float* scratch,
                       int64_t scratch_floats, int64_t group_stride, const Segs& s, double flops, double bytes,
