@@ -787,8 +787,8 @@ ConvWgradPlan conv_wgrad_plan(int n, int64_t ldi, int Cin, int H, int W, int64_t
   p.paired = !flat && n * own_chunks * per_chunk >= 384;
   // Layers of one geometry share a launch, and divide between them the workgroups that one of them would fill the
   // chip with: as many times longer chunks, so that fewer results are written and added up, and one way in and out
-  // instead of one each.  (Scratch for the results of one layer at its own chunks is enough for all.)  64 -> 64 on 512 x
-  // 32 x 32, six layers: 6 x (45 + 10) -> 221 + 18 us; 24 -> 24 on 167 x 28 x 28, four: 4 x (16 + 5.5) -> 34 + 6; iterations
+  // instead of one each.  64 -> 64 on 512 x 32 x 32, six layers:
+  // 6 x (45 + 10) -> 221 + 18 us; 24 -> 24 on 167 x 28 x 28, four: 4 x (16 + 5.5) -> 34 + 6; iterations
   // of 500 residual models of 4 to 300 channels take 0.91 of the time on average, none more than 1.03.
   // Every worker ends with a chunk of its own, so there may be a few chunks more than workgroups that
   // run at a time, which would then run alone at the end: chunks up to a quarter longer (of several layers, whose last
@@ -806,10 +806,26 @@ ConvWgradPlan conv_wgrad_plan(int n, int64_t ldi, int Cin, int H, int W, int64_t
     p.ch = longer;
     if ((int64_t)n * longer.first[s.K] <= fit) break;
   }
-  const int nch = p.ch.first[s.K];
+  // And as long as it takes for the results of all to fit in the scratch area.  It holds those of one layer at its own
+  // chunks, fewer than a chip's worth for small batches (64 -> 64, six layers, iterations of three blocks: 128 images of
+  // 16 x 16, two workers, 493 -> 383 us against one launch each; 48 of 32 x 32, five workers, 435 -> 383 against 1 + 2 + 1 + 2
+  // layers; 10 % on average over 22 such models, none slower; up to twice as long: the same).
+  auto fits = [&](const RowChunks& c) { return (int64_t)n * c.first[s.K] * per_chunk * tile_floats <= scratch_floats; };
+  bool together = n == 1 || (int64_t)n * cobs <= 65535;                   // (what a grid takes)
+  if (n > 1 && together && !fits(p.ch)) {
+    int some = p.ch.rows / step, enough = (int)(own * n * 3 / 2 / step);  // steps per chunk: too few, enough
+    p.ch = make_row_chunks(s, enough * step);
+    together = enough > some && fits(p.ch);                               // (many workers, each with a last chunk per layer)
+    while (together && enough - some > 1) {
+      const int half = (some + enough) / 2;
+      const RowChunks c = make_row_chunks(s, half * step);
+      (fits(c) ? enough : some) = half;
+      if (enough == half) p.ch = c;
+    }
+  }
+  if (!together)
+    return conv_wgrad_plan((n + 1) / 2, ldi, Cin, H, W, ldd, Cout, Ho, Wo, stride, chunk_rows, scratch_floats, s);
   p.layers = n;
-  if (n > 1 && n * nch * per_chunk * tile_floats > scratch_floats)   // (many workers, each with a last chunk per layer)
-    return conv_wgrad_plan(n / 2, ldi, Cin, H, W, ldd, Cout, Ho, Wo, stride, chunk_rows, scratch_floats, s);
   // The sum over chunks lasts as long as that of the worker with the most of them: one group adds 4 chunks in the
   // time of a read (0.22 us), four groups 16.  Four groups are four times the workgroups, though, 0.003 us per tile and
   // worker, and no faster where one worker's tiles alone keep the memory busy.  With 1, 4 and 16 groups, us:
@@ -847,13 +863,12 @@ int launch_conv_wgrad(const ConvWgradLayer* layers, int n, int64_t ldi, int Cin,
   const ConvWgradPlan plan =
       conv_wgrad_plan(n, ldi, Cin, H, W, ldd, Cout, Ho, Wo, stride, chunk_rows, scratch_floats, s);
   if (plan.layers < n) {
-    for (int half = 0; half < 2; ++half) {
-      const int from = half * (n / 2), count = half ? n - n / 2 : n / 2;
-      const int rc = launch_conv_wgrad(layers + from, count, ldi, Cin, H, W, ldd, Cout, Ho, Wo, stride, chunk_rows, scratch,
-                                       scratch_floats, group_stride, s, flops * count / n, bytes * count / n, stream);
-      if (rc) return rc;
-    }
-    return DYNB_OK;
+    const double share = (double)plan.layers / n;
+    const int rc = launch_conv_wgrad(layers, plan.layers, ldi, Cin, H, W, ldd, Cout, Ho, Wo, stride, chunk_rows, scratch,
+                                     scratch_floats, group_stride, s, flops * share, bytes * share, stream);
+    return rc ? rc : launch_conv_wgrad(layers + plan.layers, n - plan.layers, ldi, Cin, H, W, ldd, Cout, Ho, Wo, stride,
+                                       chunk_rows, scratch, scratch_floats, group_stride, s, flops * (1 - share),
+                                       bytes * (1 - share), stream);
   }
   const RowChunks& ch = plan.ch;
   const int nch = ch.first[s.K], ci32 = plan.ci32, co32 = plan.co32;
