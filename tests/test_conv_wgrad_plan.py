@@ -5,6 +5,7 @@ import random
 
 import pytest
 
+from test_gpu_layers_of_one_geometry import CALLS
 from test_result_routes import ask
 
 TAPS, ROWS, FLAT = range(3)
@@ -97,3 +98,29 @@ def test_plans_fit_in_the_scratch_area(tmp_path):
         assert fits and 1 <= layers <= call[0] and groups in (1, 4, 16) and rows > 0, call
         assert rows % (call[1][1] if kernel == ROWS else 32) == 0, call
         assert not paired or kernel != FLAT, call
+
+
+def launches(directory, image, channels, b, most):
+    """(kernel, paired, layers, sum_groups) of every launch that takes more than one layer of such a model."""
+    widths = [image[2], *channels]
+    # (the last layer divides its reduction where it has few tiles: at most 64 results of each worker)
+    dense = -(-widths[-1] * 7 // 64) * 64 * 64 * len(b)
+    todo = {}
+    for i, o in zip(widths, widths[1:]):
+        todo[i, o] = todo.get((i, o), 0) + 1
+    got = []
+    for shape, n in todo.items():
+        while n > 0:
+            p = plans(directory, [(min(n, 8), image[:2], shape, most, b, dense)])[0]
+            got.append(p[:4])
+            n -= p[2]
+    return got
+
+
+def test_the_calls_run_on_the_device_reach_every_form(tmp_path):
+    by_call = [launches(tmp_path, *call) for call in CALLS]
+    several = [p for got in by_call for p in got if p[2] > 1]
+    assert {p[:2] for p in several} == {(FLAT, 0), (ROWS, 0), (ROWS, 1), (TAPS, 0), (TAPS, 1)}
+    assert {p[3] for p in several} == {1, 4, 16}
+    assert [p[2] for p in by_call[0] if p[2] > 1] == [8, 2]
+    assert [p[2] for p in by_call[11] if p[2] > 1] == [4, 4] and all(p[2] == 1 for p in by_call[12])
