@@ -116,7 +116,9 @@ def test_ring_slots_are_copied_into_after_their_reads(source, n, tmp_path):
 
 @pytest.mark.parametrize("source,which,n", [
     ("gemm_small.hip", "", 5),    # forward, with the loss, input gradient; weight gradients, past the caches or not
+    ("gemm_lines.hip", "", 6),    # forward and input gradient, three shapes of tiles
     ("conv_wgrad.hip", "conv_wgrad_rows", 2),     # one or two groups of waves
+    ("conv_wgrad.hip", "conv_wgrad_layers_rows", 2),      # ... for layers that share a launch
     ("conv_resident.hip", "", 4),                 # with and without mask and addend
 ])
 def test_shared_rings_are_read_before_their_barriers(source, which, n, tmp_path):
@@ -134,5 +136,6 @@ def test_a_removed_wait_is_found(tmp_path):
         return [l for l in lines if not (l.startswith("s_waitcnt") and "lgkmcnt" in l)]
     for lines in compiled("gemm_f32_head.hip", tmp_path).values():
         assert unordered_reads(without_waits(lines))
-    for lines in compiled("gemm_small.hip", tmp_path).values():
-        assert reads_in_flight_at_barriers(without_waits(lines))
+    for source in ("gemm_small.hip", "gemm_lines.hip"):
+        for lines in compiled(source, tmp_path).values():
+            assert reads_in_flight_at_barriers(without_waits(lines))
