@@ -159,7 +159,10 @@ def _stream(stream):
         # (is_initialized() first: is_available() asks the driver, 2 us on every call.  The raw value, without
         # the stream object around it, 2.9 -> 0.4 us a call: the smallest iteration is two of them, and 20 us)
         if torch.cuda.is_initialized():
-            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+            try:
+                return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+            except AttributeError:      # (torch does not promise these names)
+                return torch.cuda.current_stream().cuda_stream
         if torch.cuda.is_available():
             return torch.cuda.current_stream().cuda_stream
     except ImportError:
