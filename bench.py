@@ -241,6 +241,7 @@ def main():
     frac = {}
     for name, peak_key, field in (("gemm_wgrad", "hbm", "gbps"), ("gemm_wgrad_small_tiles", "hbm", "gbps"),
                                   ("gemm_wgrad_64_tiles", "hbm", "gbps"), ("gemm_64_tiles", "mfma_bf16", "tflops"),
+                                  ("gemm_128x64_tiles", "mfma_bf16", "tflops"),
                                   ("sgd_update", "hbm", "gbps"),
                                   ("gemm_fwd", "mfma_bf16" if bf else "fp32", "tflops"),
                                   ("gemm_dgrad", "mfma_bf16" if bf else "fp32", "tflops"),

@@ -53,9 +53,10 @@ enum KClass {
   KC_CONV_AUX,
   KC_NORM,
   KC_GEMM_WGRAD_SMALL,   // bf16 weight gradients that run on the 128 x 128-tile kernels
-  KC_GEMM_SMALL,         // bf16 forward / input-gradient products on the 128 x 128-tile kernel
+  KC_GEMM_SMALL,         // bf16 forward / input-gradient products on 128 x 128 tiles
   KC_GEMM_WGRAD_64,      // bf16 weight gradients on the 64 x 64-tile kernel
   KC_GEMM_64,            // bf16 forward / input-gradient products on the 64 x 64-tile kernel
+  KC_GEMM_128X64,        // ... on 128 x 64 tiles
   KC_COUNT
 };
 
@@ -142,6 +143,8 @@ struct HeadArgs {
 };
 // whether that product's kernel has whole rows at hand
 bool head_applies(int dtype, const GemmArgs& a);
+// the class that such a launch is timed in
+KClass gemm_class(int dtype, const GemmArgs& a);
 // (with `head`: a forward product for which head_applies)
 int launch_gemm(int dtype, const GemmArgs& a, const Segs& s, void* stream, const HeadArgs* head = nullptr);
 int launch_gemm_f32(const GemmArgs& a, const HeadArgs* head, void* stream);   // forward / input gradient (gemm_f32.hip)
@@ -171,6 +174,8 @@ double average_pass_us(int64_t weights, int K);
 bool gemm_small_applies(const GemmArgs& a);
 int launch_gemm_small(const GemmArgs& a, const HeadArgs* head, void* stream);   // forward / input gradient
 // forward / input gradient of dense bf16 layers on larger tiles (gemm_lines.hip)
+enum { LINES_256, LINES_128, LINES_128X64 };
+int gemm_lines_tiles(const GemmArgs& a);
 int launch_gemm_lines(const GemmArgs& a, void* stream);
 // weight gradients of up to WGRAD_SMALL_ITEMS such layers (all over the same rows) in one launch, which does
 // the step's end too if `end`

@@ -878,6 +878,20 @@ bool head_applies(int dtype, const GemmArgs& a) {
   return dtype == DYNB_BF16 ? a.N <= 64 && gemm_small_applies(a) : gemm_f32_head_applies(a);
 }
 
+// The tile sizes of the bf16 products are different kernels with different bounds: timed apart, so
+// that a class's average launch is one kernel's.
+KClass gemm_class(int dtype, const GemmArgs& a) {
+  const KClass plain = a.mode == MODE_FWD ? KC_GEMM_FWD : a.mode == MODE_DGRAD ? KC_GEMM_DGRAD : KC_GEMM_WGRAD;
+  if (dtype != DYNB_BF16 || a.conv) return plain;
+  if (a.mode == MODE_WGRAD) {
+    const bool large = a.agg ? tiles_of(a, AGG_BM, AGG_BN) >= 256 : tiles_of(a, 256, 256) >= 192;
+    return large ? plain : KC_GEMM_WGRAD_SMALL;
+  }
+  if (gemm_small_applies(a)) return KC_GEMM_64;
+  const int tiles = gemm_lines_tiles(a);
+  return tiles == LINES_256 ? plain : tiles == LINES_128 ? KC_GEMM_SMALL : KC_GEMM_128X64;
+}
+
 int launch_gemm(int dtype, const GemmArgs& args, const Segs& s, void* stream, const HeadArgs* head) {
   GemmArgs a = args;
   a.zeros = device_zero_granule();
@@ -903,19 +917,7 @@ int launch_gemm(int dtype, const GemmArgs& args, const Segs& s, void* stream, co
     return fail(DYNB_ERR_UNSUPPORTED, "gemm: the bias gradient rides along with an unsplit weight gradient only");
   if (a.addend && (dtype != DYNB_BF16 || a.mode != MODE_DGRAD))
     return fail(DYNB_ERR_UNSUPPORTED, "gemm: an addend belongs to a bf16 input gradient");
-  KClass cls = a.mode == MODE_FWD ? KC_GEMM_FWD : a.mode == MODE_DGRAD ? KC_GEMM_DGRAD
-                                                                        : KC_GEMM_WGRAD;
-  // (the tile sizes of the bf16 products are different kernels with different bounds: timed apart, so
-  // that a class's average launch is one kernel's)
-  if (a.mode == MODE_WGRAD && dtype == DYNB_BF16 && !a.conv) {
-    const bool large = a.agg ? tiles_of(a, AGG_BM, AGG_BN) >= 256
-                             : (int64_t)((a.M + 255) / 256) * ((a.N + 255) / 256) >= 192;
-    if (!large) cls = KC_GEMM_WGRAD_SMALL;
-  } else if (dtype == DYNB_BF16 && !a.conv &&
-             (int64_t)((a.M + 255) / 256) * ((a.N + 255) / 256) < 192) {
-    cls = gemm_small_applies(a) ? KC_GEMM_64 : KC_GEMM_SMALL;
-  }
-  Timed t(cls, stream, a.alg_flops, a.alg_bytes);
+  Timed t(gemm_class(dtype, a), stream, a.alg_flops, a.alg_bytes);
   if (a.conv) {
     if (dtype != DYNB_BF16 || a.mode == MODE_WGRAD || (a.cp & 7) || (a.stride != 1 && a.stride != 2))
       return fail(DYNB_ERR_UNSUPPORTED, "gemm: gathered operand needs bf16, forward/input-gradient mode");
@@ -932,10 +934,9 @@ int launch_gemm(int dtype, const GemmArgs& args, const Segs& s, void* stream, co
     // large tiles have the best LDS-traffic-to-MFMA ratio; small problems need more, smaller
     // tiles to occupy 256 compute units.  The weight gradient keeps four waves: its 256 accumulators per lane
     // leave no room for a second wave on a SIMD.
-    const int64_t big = (int64_t)((a.M + 255) / 256) * ((a.N + 255) / 256);
     const hipStream_t st = (hipStream_t)stream;
     if (a.mode == MODE_WGRAD) {
-      if (big >= 192)
+      if (tiles_of(a, 256, 256) >= 192)
         launch_bf16_wgrad<256, 256, 2, 2, 4>(a, s, st);   // 128 + 18 KB of LDS
       else
         launch_bf16_wgrad<128, 128, 2, 2, 8>(a, s, st);

@@ -156,13 +156,19 @@ void launch_as(const GemmArgs& a, hipStream_t st) {
 
 }  // namespace
 
+int gemm_lines_tiles(const GemmArgs& a) {
+  auto tiles = [&](int m, int n) { return (int64_t)((a.M + m - 1) / m) * ((a.N + n - 1) / n); };
+  return tiles(256, 256) >= 192 ? LINES_256 : tiles(128, 128) >= 128 ? LINES_128 : LINES_128X64;
+}
+
 int launch_gemm_lines(const GemmArgs& a, void* stream) {
   if (a.mode == MODE_WGRAD || a.conv || a.K % 64 != 0)
     return fail(DYNB_ERR_BADARG, "gemm: products of dense layers take whole 64-deep stages");
-  auto tiles = [&](int m, int n) { return (int64_t)((a.M + m - 1) / m) * ((a.N + n - 1) / n); };
-  if (tiles(256, 256) >= 192) launch_as<256, 256, 2, 4, 2, 4>(a, (hipStream_t)stream);
-  else if (tiles(128, 128) >= 128) launch_as<128, 128, 4, 2, 4, 2>(a, (hipStream_t)stream);
-  else launch_as<128, 64, 2, 2, 4, 2>(a, (hipStream_t)stream);
+  switch (gemm_lines_tiles(a)) {
+    case LINES_256: launch_as<256, 256, 2, 4, 2, 4>(a, (hipStream_t)stream); break;
+    case LINES_128: launch_as<128, 128, 4, 2, 4, 2>(a, (hipStream_t)stream); break;
+    default: launch_as<128, 64, 2, 2, 4, 2>(a, (hipStream_t)stream);
+  }
   return hipGetLastError() == hipSuccess ? DYNB_OK : fail(DYNB_ERR_HIP, "gemm launch failed");
 }
 

@@ -49,7 +49,7 @@ const char* kNames[KC_COUNT] = {"gemm_fwd",  "gemm_dgrad", "gemm_wgrad", "pack_i
                                 "softmax_xent", "bias_grad", "finalize",
                                 "weighted_aggregate", "sgd_update", "weight_cast", "conv_aux", "norm_add",
                                 "gemm_wgrad_small_tiles", "gemm_small_tiles",
-                                "gemm_wgrad_64_tiles", "gemm_64_tiles"};
+                                "gemm_wgrad_64_tiles", "gemm_64_tiles", "gemm_128x64_tiles"};
 }  // namespace
 
 // The bracket holds its two events itself and hands them to the pending list only when both
