@@ -298,23 +298,26 @@ static int64_t tiles_with(const GemmArgs& a, int side) {
 static int tile_side(const GemmArgs& a) { return tiles_with(a, 32) >= 1024 ? 32 : 16; }
 
 // For a weight gradient the workers count too: they are divided over waves (512 x 512, 16 workers, 16384
-// rows 165 -> 136 us; three such layers, 8 workers, 65536 rows, whose operands no longer stay in the
-// caches, forward and backward 6700 -> 3925; with 4 workers and 1024 rows 47 -> 39).
+// rows: 186 us in single tiles, 80 in 2 x 2; three such layers, 8 workers, 65536 rows, whose operands no longer stay in the
+// caches, forward and backward 7060 and 3430; 4 workers and 1024 rows, at the line, 15 and 16.  The line is older than the
+// chain without vector instructions: two layers of 256 x 256, 8 workers, 1024 rows, on its other side, 14 and 10.5).
 static int wgrad_side(const GemmArgs& a, const Segs& s) { return tiles_with(a, 32) * s.K >= 1024 ? 32 : 16; }
 
 // Workers per wave of a weight gradient that leaves the average to another pass: eight waves of this ring
-// fit on a compute unit (64 x 10, 16 workers: 512 rows 22 -> 7 us, 4096 rows 66 -> 11, 16384 rows 217 ->
-// 27 against one wave per tile).
+// fit on a compute unit (64 x 10, 16 workers: 512 rows 14.5 -> 7 us, 4096 rows 43 -> 8.3, 16384 rows 139 ->
+// 14.5 against one wave per tile; 512 x 512, 8 workers, 1024 rows 32 -> 13).
 static int workers_per_wave(const GemmArgs& a, int K, int side) {
   const int64_t shares = 2048 / tiles_with(a, side);
   return shares < 1 ? K : shares > K ? 1 : (K + (int)shares - 1) / (int)shares;
 }
 bool wgrad_f32_walks(const GemmArgs& a, const Segs& s) { return workers_per_wave(a, s.K, wgrad_side(a, s)) == s.K; }
 // The rule counts 0.06 us per 16 rows and 0.7 us per worker of a wave of 16 x 16 tiles, fitted over whole iterations
-// (a wave that has its SIMD for itself takes 0.11 and 0.55).  Where 2 x 2 tiles of divided
-// workers fill the chip instead, they are faster by 0.05 us per 16 rows and 1024 of the small ones, which
-// is worth a pass of 5 us from 1700 rows on (512 x 512, 8 workers, per layer with its average: 1024 rows
-// folded 16 us, with the pass 20; 576 x 576, 16384 rows, forward and backward: 455 and 378).
+// before the chain lost its vector instructions (now a wave that has its SIMD for itself takes 0.11 and 0.55).  Where 2 x 2
+// tiles of divided workers fill the chip instead, they are worth a pass of 5 us from 1700 rows times 1024 small tiles on.
+// Weight gradients folded, and without the pass; in brackets with it, per iteration: 512 x 512, 8 workers, 1024 rows 20 and
+// 14.5 us (33.2, 34.0), 1536 26 and 16 (44.9, 41.8), 4096 50 and 26 (87, 69); 576 x 576, 1024 rows 21.5 and 17.2 (40.3, 42.3),
+// 16384 rows 234 and 146 (390, 318); 785-301-97-10, 7 workers 18.6 and 15 (47.9, 52.4).  Of 21 models the rule
+// takes the faster side of 20; two layers of 256 x 256, 8 workers, 1024 rows would be faster folded (35 us, 41).
 double wgrad_f32_fold_us(const GemmArgs& a, const Segs& s) {
   if (wgrad_side(a, s) != tile_side(a) && tiles_with(a, 16) * s.off[s.K] > 1700 * 1024) return 1e30;
   const int per = workers_per_wave(a, s.K, tile_side(a));
@@ -368,7 +371,7 @@ int launch_wgrad_f32(const GemmArgs* a, int n, const Segs& s, const StepEnd* end
     if ((g.lda & 3) || (g.ldb & 3) || (((uintptr_t)g.A | (uintptr_t)g.B) & 15))
       return fail(DYNB_ERR_BADARG, "gemm: operands must have 16-byte aligned rows");
     // (a wave that folds the average in walks all workers: then the tiles alone have to fill the chip,
-    // those of all layers together -- three of 512 x 512, 1024 rows: 43 us, and 53 with 2 x 2 tiles)
+    // those of all layers together -- three of 512 x 512, 8 workers, 1024 rows: 35 us, and 41 with 2 x 2 tiles)
     const bool long_rows = wgrad_rows_long(g);
     const int side = long_rows || (g.agg && wide < 1024) ? 16 : wgrad_side(g, s);
     const int64_t tiles = tiles_with(g, side);
