@@ -28,8 +28,8 @@ PEAK = {"mfma_bf16": 2500.0, "fp32": 157.3, "hbm": 8000.0}   # TFLOP/s, TFLOP/s,
 # launches per step); the output layer's 128 x 128-tile launch is the class "gemm_wgrad_small_tiles".
 CSRC = os.path.join("paper_2305_12213_amd", "csrc")
 MEASURED_TRAFFIC = {
-    "gemm_wgrad": {"bytes_per_launch": 1.5779e9, "sources": ("gemm.hip", "gemm_epilogue.h", "tile_map.h", "lds_async.h"),
-                   "sha1": "211793f26f99"},
+    "gemm_wgrad": {"bytes_per_launch": 1.5635e9, "sources": ("gemm.hip", "gemm_epilogue.h", "tile_map.h", "lds_async.h"),
+                   "sha1": "9107c3ad366f"},
     # one launch per step: the four weight matrices with their 16-bit copies, and the biases
     "sgd_update": {"bytes_per_launch": 8.837e8, "sources": ("kernels_update.hip",), "sha1": "e18fcd127ceb"},
 }

@@ -13,8 +13,9 @@
 // 128 x 64 tiles, four waves, where those of 128 x 128 are fewer than half the compute units and 64 x 64 ones more than
 // one each (552 clocks of copies per stage and compute unit instead of twice 370; see gemm_small_applies()).
 // Eight waves on the larger tiles, two per SIMD: one issues matrix instructions while the other waits for a copy to be accepted.
-// The loop of 4096^3 takes 158 thousand clocks, of which 131 are matrix work; what is left is power -- such launches in a
-// row run at 1.7 GHz instead of 2.4, and a loop with fewer clocks (147 thousand, other places for the copies) at 1.5.
+// Inside the iterations of a 4096-wide model the loop of 4096^3 takes 181 to 201 thousand clocks, of which 131 are matrix work, at
+// 1.7 to 1.9 GHz instead of the rated 2.4: 101 - 106 us.  The clock is no constant: in one iteration right after the first ones it
+// was 1.2 GHz, and the loop took 158 to 164 thousand clocks and 134 us -- waits for memory get shorter in clocks as these get longer.
 //
 // Against 32-deep stages in a ring of 160 KB (launches in a row, us): 4096 x 4096 x 4096 forward 122 -> 107, input
 // gradient 127 -> 112; 4096 x 4096 x 1024 39 -> 37 and 44 -> 42; 2048^3 25 -> 20 and 26 -> 20; 4096 x 1000 x 4096 41 -> 34;
